@@ -10,6 +10,7 @@
 #include "nps.h"
 #include "nps_internal.hpp"
 #include "nps_kernels.hpp"
+#include "nps_setup_kernels.hpp"
 #include "nps_march_kernels.hpp"
 #include "nps_train_kernels.hpp"
 #include "nps_lanczos_kernels.hpp"
@@ -145,6 +146,7 @@ struct Layout {
     size_t gmode[2];                   // level 1 on matrix cores: per-group modes [down, up]
     size_t izero[2];                   // and per-item zero flags [down, up]
     size_t live, items;                // 7-point work items: fluid flags, the list of those with fluid
+    size_t cls, tot;                   // set-up: boundary class sums, totals per pyramid block
     size_t total;
 };
 
@@ -182,7 +184,13 @@ Layout make_layout(nps_dims d, int levels, int precision, int n_ortho, bool solv
         L.izero[0] = put((size_t)march_columns(level_grid(d, 1)).count());
         L.izero[1] = put((size_t)march_columns(level_grid(d, 1)).count());
     }
-    L.dhat = put(s * n);
+    // Set-up tables.  A network evaluation writes its output to the caller's
+    // buffer, so there they share the bytes of the solve's d^.
+    L.dhat = off;
+    L.cls = put(sizeof(ClassSums));
+    L.tot = put(sizeof(uint2) * (size_t)pyramid_blocks(level_grid(d, 1)));
+    if (!solve) off = std::max(off, L.dhat + align256(s * n));
+    else L.dhat = put(s * n);
     if (solve) {
         for (int i = 0; i <= n_ortho; ++i) {
             L.dring[i] = put(s * n);
@@ -474,47 +482,94 @@ T* mptr(void* ws, size_t off) {
 
 uint32_t full_count(int l) { return 1u << (3 * (l - 1)); }
 
-// Image pyramid as counts, Aff scalars, and the stored kernels of small levels.
+// Rows of 16 labels can be read as one aligned word each.
+bool wide_labels(const uint8_t* labels, Grid g) {
+    return g.nx % 16 == 0 && reinterpret_cast<uintptr_t>(labels) % 16 == 0;
+}
+
+// Image pyramid as counts, Aff scalars, modes, and the stored kernels.  The
+// state and the cleared class sums are already in the workspace.
 template <class T>
 int run_setup(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan& plan, const Layout& lay,
               void* ws, hipStream_t s, bool bf16w = false) {
     const int L = net->levels;
-    State* st = mptr<State>(ws, lay.state);
-    double* partials = mptr<double>(ws, lay.partials);
-    for (int l = 2; l <= L; ++l) {
-        const Grid gin = level_grid(d, l - 1), gout = level_grid(d, l);
-        uint32_t* out = mptr<uint32_t>(ws, lay.counts[l]);
-        const int grid = elem_grid(ncells(gout));
-        if (l == 2)
-            NPS_TRY(launch("setup_pool_counts", (double)ncells(gout), s, [&] {
-                k_pool_counts<true><<<grid, kBlock, 0, s>>>(labels, gin, out, gout);
-            }));
-        else
-            NPS_TRY(launch("setup_pool_counts", (double)ncells(gout), s, [&] {
-                k_pool_counts<false><<<grid, kBlock, 0, s>>>(cptr<uint32_t>(ws, lay.counts[l - 1]), gin, out, gout);
-            }));
-    }
+    const Grid g1 = level_grid(d, 1);
     auto img = [&](int l) -> const void* {
         return l == 1 ? static_cast<const void*>(labels) : static_cast<const void*>(cptr<uint32_t>(ws, lay.counts[l]));
     };
-    for (int l = 1; l < L; ++l) {
+    ClassSums* cls = mptr<ClassSums>(ws, lay.cls);
+    uint2* tot = mptr<uint2>(ws, lay.tot);
+    const int pyr = pyramid_blocks(g1);
+    PyramidOut po{};
+    for (int l = 2; l <= L; ++l) po.cnt[l] = mptr<uint32_t>(ws, lay.counts[l]);
+    NPS_TRY(launch("setup_pyramid", (double)ncells(g1), s, [&] {
+        k_pyramid<<<pyr, kPyrThreads, 0, s>>>(labels, g1, L, po, cls, tot, wide_labels(labels, g1) ? 1 : 0);
+    }));
+    FinishArgs fa{};
+    fa.g = g1;
+    fa.L = L;
+    fa.pyr = pyr;
+    fa.cls = cls;
+    fa.tot = tot;
+    fa.aff = aff_block(net, 1, 0);
+    for (int i = 0; i < 2 * (L - 1); ++i) fa.aff_b[i] = net->aff_b[i];
+    fa.st = mptr<State>(ws, lay.state);
+    int blocks = 1;
+    for (int l = 1; l <= L; ++l) {
+        if (plan.km[l] != kStored) continue;
         const Grid g = level_grid(d, l);
-        const double inv_full = std::ldexp(1.0, -3 * (l - 1));
-        const int grid = red_elem_grid(ncells(g));
-        if (l == 1)
-            NPS_TRY(launch("setup_aff", (double)ncells(g), s, [&] {
-                k_aff<true><<<grid, kBlock, 0, s>>>(img(l), g, inv_full, aff_block(net, l, 0), aff_block(net, l, 1), partials);
+        const size_t n = ncells(g);
+        // levels whose counts are exact in bf16, above 4096 cells: matrix cores, with
+        // the pieces of the solve's FP32 mode or the bf16 leg's single piece (below,
+        // a launch has too few 16-cell groups to be faster than one thread per tap)
+        const bool mfma = sizeof(T) == 4 && n > 4096 && l <= kMfmaMaxLevel;
+        for (int which = 0; which < (l < L ? 2 : 1); ++which) {
+            T* out = mptr<T>(ws, which == 0 ? lay.k1[l] : lay.k2[l]);
+            const int blk = which == 0 ? block_down(l) : block_up(net, l);
+            const CConvW<double>* w = bf16w ? cconv_block_bf16<double>(net, blk) : cconv_block<double>(net, blk);
+            const MfmaW* wm = mfma_block(net, blk);
+            const int mg = elem_grid(((size_t)g.nz * g.ny * ((g.nx + 15) / 16)) * 64);
+            if (n <= (size_t)kStoreMaxCells) {   // beside the other small levels
+                KgenSeg& sg = fa.seg[fa.nseg++];
+                sg.img = img(l);
+                sg.g = g;
+                sg.w = w;
+                sg.wm = wm;
+                sg.out = out;
+                sg.l1 = l == 1;
+                sg.kind = mfma ? kGenMfma : n > 4096 ? kGenTap9 : kGenTap;
+                const int nb = ((int)n + kBlock - 1) / kBlock;
+                sg.blocks = mfma ? mg : (sg.kind == kGenTap9 ? kTaps / 9 : kTaps) * nb;
+                blocks += sg.blocks;
+                continue;
+            }
+            if constexpr (std::is_same_v<T, float>) {
+                if (mfma) {
+                    auto mf = [&](auto km, auto l1) {
+                        constexpr int KM = decltype(km)::value;
+                        constexpr bool L1 = decltype(l1)::value;
+                        return launch("setup_kgen", (double)n, s, [&] {
+                            k_kgen_store_mfma<KM, L1><<<mg, kBlock, 0, s>>>(img(l), g, wm, out);
+                        });
+                    };
+                    using x3 = std::integral_constant<int, kMfmaBf16x3>;
+                    using b1 = std::integral_constant<int, kMfmaBf16>;
+                    if (bf16w) NPS_TRY(l == 1 ? mf(b1{}, std::true_type{}) : mf(b1{}, std::false_type{}));
+                    else NPS_TRY(l == 1 ? mf(x3{}, std::true_type{}) : mf(x3{}, std::false_type{}));
+                    continue;
+                }
+            }
+            const int grid = elem_grid(n);
+            NPS_TRY(launch("setup_kgen", (double)n, s, [&] {
+                if (l == 1) k_kgen_store<T, true><<<grid, kBlock, 0, s>>>(img(l), g, w, out);
+                else k_kgen_store<T, false><<<grid, kBlock, 0, s>>>(img(l), g, w, out);
             }));
-        else
-            NPS_TRY(launch("setup_aff", (double)ncells(g), s, [&] {
-                k_aff<false><<<grid, kBlock, 0, s>>>(img(l), g, inv_full, aff_block(net, l, 0), aff_block(net, l, 1), partials);
-            }));
-        const double b1 = net->aff_b[2 * (l - 1)], b2 = net->aff_b[2 * (l - 1) + 1];
-        NPS_TRY(launch("control", 0, s, [&] {
-            k_control<kStageAff><<<1, kCtlBlock, 0, s>>>(st, partials, grid, l - 1, 0, 0, 0, b1, b2, 27.0 * (double)ncells(g),
-                                                           nullptr);
-        }));
+        }
     }
+    NPS_TRY(launch("setup_finish", (double)ncells(g1), s, [&] {
+        if (bf16w) k_setup_finish<T, kMfmaBf16><<<blocks, kBlock, 0, s>>>(fa);
+        else k_setup_finish<T, kMfmaBf16x3><<<blocks, kBlock, 0, s>>>(fa);
+    }));
     if (is_mfma(plan.km[1])) {
         const Grid g = level_grid(d, 1);
         const size_t threads = group_mode_bytes(g) * 16;
@@ -534,6 +589,7 @@ int run_setup(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
         const int grid = tile_grid(g);
         int8_t* md = mptr<int8_t>(ws, lay.wmode[l][0]);
         if (l == 1 && is_mfma(plan.km[1])) continue;   // the marching kernels use the group modes
+        if (l > 1 && plan.km[l] == kStored) continue;   // a stored kernel takes no shortcut
         if (l == 1)
             NPS_TRY(launch("setup_wave_modes", (double)ncells(g), s, [&] {
                 k_wave_modes<true><<<grid, kBlock, 0, s>>>(img(l), g, 1u, md, mptr<int8_t>(ws, lay.wmode[l][1]));
@@ -542,51 +598,6 @@ int run_setup(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
             NPS_TRY(launch("setup_wave_modes", (double)ncells(g), s, [&] {
                 k_wave_modes<false><<<grid, kBlock, 0, s>>>(img(l), g, full_count(l), md, nullptr);
             }));
-    }
-    for (int l = 1; l <= L; ++l) {
-        if (plan.km[l] != kStored) continue;
-        const Grid g = level_grid(d, l);
-        // one thread per (tap, cell) on levels the solve stores; one per cell
-        // (its window read once for all taps) on larger ones (training)
-        const bool per_cell = ncells(g) > (size_t)kStoreMaxCells;
-        const int grid = elem_grid((per_cell ? 1 : (size_t)kTaps) * ncells(g));
-        for (int which = 0; which < (l < L ? 2 : 1); ++which) {
-            T* out = mptr<T>(ws, which == 0 ? lay.k1[l] : lay.k2[l]);
-            const int blk = which == 0 ? block_down(l) : block_up(net, l);
-            const CConvW<double>* w = bf16w ? cconv_block_bf16<double>(net, blk) : cconv_block<double>(net, blk);
-            auto go = [&](auto l1, auto tg) {
-                constexpr bool L1 = decltype(l1)::value;
-                constexpr int TG = decltype(tg)::value;
-                return launch("setup_kgen", (double)ncells(g), s, [&] {
-                    k_kgen_store<T, L1, TG><<<grid, kBlock, 0, s>>>(img(l), g, w, out);
-                });
-            };
-            using one = std::integral_constant<int, 1>;
-            using all = std::integral_constant<int, kTaps>;
-            if constexpr (std::is_same_v<T, float>) {
-                // levels above 4096 cells whose counts are exact in bf16: matrix
-                // cores, the pieces of the solve's FP32 mode or the bf16 leg's
-                // single piece
-                if (ncells(g) > 4096 && l <= kMfmaMaxLevel) {
-                    const MfmaW* wm = mfma_block(net, blk);
-                    const int mg = elem_grid(((size_t)g.nz * g.ny * ((g.nx + 15) / 16)) * 64);
-                    auto mf = [&](auto km, auto l1) {
-                        constexpr int KM = decltype(km)::value;
-                        constexpr bool L1 = decltype(l1)::value;
-                        return launch("setup_kgen", (double)ncells(g), s, [&] {
-                            k_kgen_store_mfma<KM, L1><<<mg, kBlock, 0, s>>>(img(l), g, wm, out);
-                        });
-                    };
-                    using x3 = std::integral_constant<int, kMfmaBf16x3>;
-                    using b1 = std::integral_constant<int, kMfmaBf16>;
-                    if (bf16w) NPS_TRY(l == 1 ? mf(b1{}, std::true_type{}) : mf(b1{}, std::false_type{}));
-                    else NPS_TRY(l == 1 ? mf(x3{}, std::true_type{}) : mf(x3{}, std::false_type{}));
-                    continue;
-                }
-            }
-            if (l == 1) NPS_TRY(per_cell ? go(std::true_type{}, all{}) : go(std::true_type{}, one{}));
-            else NPS_TRY(per_cell ? go(std::false_type{}, all{}) : go(std::false_type{}, one{}));
-        }
     }
     return NPS_OK;
 }
@@ -890,7 +901,8 @@ struct Solver {
     HostFlags* hf_d = nullptr;    // device address of hf
     virtual ~Solver() {}
     virtual int enqueue_validate() = 0;            // scan, then copy the state to hs
-    virtual int enqueue_setup() = 0;               // pyramid, Aff, stored kernels
+    virtual int enqueue_setup() = 0;               // pyramid, Aff, stored kernels (needs no verdict)
+    virtual void begin() = 0;                      // after the verdict, before the first body
     virtual int enqueue_body(int k) = 0;           // iteration k (see below)
     virtual int enqueue_finalize(double* x_out) = 0;   // x_out, then copy the state to hs
 };
@@ -926,23 +938,12 @@ int fill_info(const State* hs, nps_info* info) {
 template <class T, class X>
 struct SolverT : Solver {
     int enqueue_validate() override {
-        const size_t n = ncells(level_grid(d, 1));
         State* st = mptr<State>(ws, lay.state);
         double* partials = mptr<double>(ws, lay.partials);
-        X* x = mptr<X>(ws, lay.x[0]);
-        const int max_iter = std::max(o.max_iter, 0);
-        NPS_TRY(launch("state_init", 0, s, [&] {
-            k_state_init<<<1, 64, 0, s>>>(st, max_iter, o.fixed_iters ? 1 : 0, o.n_ortho, o.method, o.symmetric);
-        }));
-        const int sgrid = red_elem_grid(n);
-        NPS_TRY(launch("setup_scan", (double)n, s, [&] { k_scan<X><<<sgrid, kBlock, 0, s>>>(labels, b, n, x, partials); }));
-        NPS_TRY(launch("control", 0, s, [&] {
-            k_control<kStageScan><<<1, kCtlBlock, 0, s>>>(st, partials, sgrid, 0, 0, 0, 0, o.tol, 0.0, 0.0, nullptr);
-        }));
+        const Grid g = level_grid(d, 1);
+        const int nitems = columns_of(g).count(), vgrid = red_blocks(nitems);
         // the 7-point kernels' live items; the others get zeros in the vectors
         // those kernels write (and read back) there
-        const Grid g = level_grid(d, 1);
-        const int nitems = columns_of(g).count();
         ZeroBufs zb{};
         auto zero = [&](void* p, int bytes) {
             zb.p[zb.n] = p;
@@ -956,19 +957,24 @@ struct SolverT : Solver {
             zero(mptr<T>(ws, lay.adring[i]), (int)sizeof(T));
         }
         uint8_t* live = mptr<uint8_t>(ws, lay.live);
-        NPS_TRY(launch("setup_items", (double)n, s, [&] { k_item_live<<<nitems, kBlock, 0, s>>>(labels, g, live, zb); }));
-        NPS_TRY(launch("setup_item_list", 0, s, [&] {
-            k_item_list<<<1, kBlock, 0, s>>>(live, nitems, mptr<uint32_t>(ws, lay.items), st);
+        NPS_TRY(launch("setup_validate", (double)ncells(g), s, [&] {
+            k_validate<X><<<vgrid, kBlock, 0, s>>>(labels, g, b, mptr<X>(ws, lay.x[0]), live, zb, partials);
+        }));
+        const SolveParams sp{o.tol, std::max(o.max_iter, 0), o.fixed_iters ? 1 : 0, o.n_ortho, o.method, o.symmetric};
+        NPS_TRY(launch("setup_live_list", 0, s, [&] {
+            k_live_list<<<1, kCtlBlock, 0, s>>>(live, nitems, mptr<uint32_t>(ws, lay.items), partials, vgrid, st,
+                                                mptr<ClassSums>(ws, lay.cls), sp);
         }));
         NPS_HIP(hipMemcpyAsync(hs, st, sizeof(State), hipMemcpyDeviceToHost, s));
         return NPS_OK;
     }
 
-    int enqueue_setup() override {
+    int enqueue_setup() override { return run_setup<T>(net, labels, d, plan, lay, ws, s); }
+
+    void begin() override {
         hf->done = 0;
         hf->iter = 0;
-        nlive = hs->nlive;   // the validation copy has completed
-        return run_setup<T>(net, labels, d, plan, lay, ws, s);
+        nlive = hs->nlive;
     }
 
     int nlive = 0;   // live items of the 7-point kernels (set-up)
@@ -1040,7 +1046,7 @@ struct SolverT : Solver {
         const bool res_in_bottom = plan.lb <= net->levels;
         if (!res_in_bottom)
             NPS_TRY(launch("control", 0, s, [&] {
-                k_control<kStageResidual><<<1, kCtlBlock, 0, s>>>(st, pdots, np_res, 0, 0, 0, 0, 0.0, 0.0, 0.0, hf_d);
+                k_control<kStageResidual><<<1, kCtlBlock, 0, s>>>(st, pdots, np_res, hf_d);
             }));
         NPS_TRY(run_down_l1<T>(net, labels, d, plan, lay, ws, r, s));
         if (res_in_bottom) NPS_TRY(run_coarse<T>(net, d, plan, lay, ws, s, &x2, pdots, np_res, hf_d));
@@ -1102,7 +1108,7 @@ Solver* make_solver(int precision) {
 // nps_solve: validate, set up, iterate with a one-body-behind poll, finalize.
 // Events bracketing a solve's phases on its stream (created once per thread).
 struct SolveEvents {
-    hipEvent_t ev[3] = {nullptr, nullptr, nullptr};   // start, setup done, end
+    hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};   // start, setup done, end, validated
     bool ok = false;
     SolveEvents() {
         ok = true;
@@ -1114,12 +1120,20 @@ int run_solve(Solver& sv, double* x_out, nps_info* info) {
     thread_local SolveEvents tev;
     if (!tev.ok) return fail(NPS_EDEVICE, "hipEventCreate failed");
     NPS_HIP(hipEventRecord(tev.ev[0], sv.s));
+    // The set-up kernels read the labels and the weights only: they follow the
+    // validation at once, so the host's wait for its verdict costs the GPU nothing.
     NPS_TRY(sv.enqueue_validate());
-    NPS_HIP(hipStreamSynchronize(sv.s));
-    NPS_TRY(validation_status(sv.hs));
+    NPS_HIP(hipEventRecord(tev.ev[3], sv.s));
+    NPS_TRY(sv.enqueue_setup());
+    NPS_HIP(hipEventRecord(tev.ev[1], sv.s));
+    NPS_HIP(hipEventSynchronize(tev.ev[3]));
+    const int verdict = validation_status(sv.hs);
+    if (verdict != NPS_OK) {
+        NPS_HIP(hipStreamSynchronize(sv.s));
+        return verdict;
+    }
     if (sv.hs->bb != 0.0) {
-        NPS_TRY(sv.enqueue_setup());
-        NPS_HIP(hipEventRecord(tev.ev[1], sv.s));
+        sv.begin();
         const int max_iter = std::max(sv.o.max_iter, 0);
         volatile HostFlags* hf = sv.hf;
         for (int k = 1; k <= max_iter + 1; ++k) {
@@ -1139,8 +1153,6 @@ int run_solve(Solver& sv, double* x_out, nps_info* info) {
             }
             if (hf->done) break;
         }
-    } else {
-        NPS_HIP(hipEventRecord(tev.ev[1], sv.s));
     }
     NPS_TRY(sv.enqueue_finalize(x_out));
     NPS_HIP(hipEventRecord(tev.ev[2], sv.s));
@@ -1158,7 +1170,8 @@ template <class T>
 int precond_impl(const nps_net* net, const uint8_t* labels, nps_dims d, const T* r_in, T* d_out, void* ws,
                  const Plan& plan, const Layout& lay, hipStream_t s) {
     State* st = mptr<State>(ws, lay.state);
-    NPS_TRY(launch("state_init", 0, s, [&] { k_state_init<<<1, 64, 0, s>>>(st, 0, 0, 0, 0, 0); }));
+    ClassSums* cls = mptr<ClassSums>(ws, lay.cls);
+    NPS_TRY(launch("state_init", 0, s, [&] { k_state_init<<<1, kBlock, 0, s>>>(st, cls); }));
     NPS_TRY(run_setup<T>(net, labels, d, plan, lay, ws, s));
     NPS_TRY(run_down_l1<T>(net, labels, d, plan, lay, ws, r_in, s));
     const T* x2 = nullptr;
@@ -1352,6 +1365,7 @@ int admit(nps_server* srv, Slot& sl, Request* r) {
     NPS_HIP(hipMemcpyAsync(base + rl.lab, r->lab_h, r->n, hipMemcpyHostToDevice, sl.s));
     NPS_HIP(hipMemcpyAsync(base + rl.b, r->b_h, 8 * r->n, hipMemcpyHostToDevice, sl.s));
     NPS_TRY(sv->enqueue_validate());
+    NPS_TRY(sv->enqueue_setup());   // behind the validation: nothing of the request is in flight once ev[0] is done
     NPS_HIP(hipEventRecord(sl.ev[0], sl.s));
     r->phase = Request::kValidating;
     return NPS_OK;
@@ -1390,7 +1404,7 @@ int advance(nps_server* srv, Slot& sl) {
                 return NPS_OK;
             }
             if (sl.hs->bb == 0.0) return enqueue_finish(srv, sl);
-            NPS_TRY(sl.sv->enqueue_setup());
+            sl.sv->begin();
             const int last = std::max(r->o.max_iter, 0) + 1;
             for (int k = 1; k <= std::min(2, last); ++k) {
                 NPS_TRY(sl.sv->enqueue_body(k));
@@ -1441,7 +1455,8 @@ int train_forward(const nps_net* net, const uint8_t* labels, nps_dims d, const T
     const Plan plan = make_plan(d, L, vec_bytes(NPS_FP32) == sizeof(T) ? NPS_FP32 : NPS_FP64, true);
     State* st = mptr<State>(ws, lay.state);
     auto wblock = [&](int b) { return bf16w ? cconv_block_bf16<T>(net, b) : cconv_block<T>(net, b); };
-    NPS_TRY(launch("state_init", 0, s, [&] { k_state_init<<<1, 64, 0, s>>>(st, 0, 0, 0, 0, 0); }));
+    ClassSums* cls = mptr<ClassSums>(ws, lay.cls);
+    NPS_TRY(launch("state_init", 0, s, [&] { k_state_init<<<1, kBlock, 0, s>>>(st, cls); }));
     NPS_TRY(run_setup<T>(net, labels, d, plan, lay, ws, s, bf16w));
     auto img = [&](int l) -> const void* {
         return l == 1 ? static_cast<const void*>(labels) : static_cast<const void*>(cptr<uint32_t>(ws, lay.counts[l]));
@@ -1602,7 +1617,7 @@ int train_loss(const uint8_t* labels, nps_dims d, const TrainLayout& tl, void* w
         k_train_residual<T><<<grid, kBlock, 0, s>>>(labels, g, b, y, res, partials);
     }));
     NPS_TRY(launch("control", 0, s, [&] {
-        k_control<kStageLoss><<<1, kCtlBlock, 0, s>>>(st, partials, grid, 0, 0, 0, 0, 0.0, 0.0, 0.0, nullptr);
+        k_control<kStageLoss><<<1, kCtlBlock, 0, s>>>(st, partials, grid, nullptr);
     }));
     NPS_TRY(launch("train_gy", (double)ncells(g), s, [&] { k_train_gy<T><<<grid, kBlock, 0, s>>>(labels, g, res, st, gy, 1.0); }));
     double rr = 0.0;
@@ -1639,7 +1654,7 @@ int train_step(const nps_net* net, const uint8_t* labels, nps_dims d, int batch,
             k_train_residual<T><<<grid, kBlock, 0, s>>>(lab, g, bi, y, res, partials);
         }));
         NPS_TRY(launch("control", 0, s, [&] {
-            k_control<kStageLoss><<<1, kCtlBlock, 0, s>>>(st, partials, grid, 0, 0, 0, 0, 0.0, 0.0, 0.0, nullptr);
+            k_control<kStageLoss><<<1, kCtlBlock, 0, s>>>(st, partials, grid, nullptr);
         }));
         NPS_TRY(launch("train_gy", (double)n, s, [&] { k_train_gy<T><<<grid, kBlock, 0, s>>>(lab, g, res, st, gy, w); }));
         NPS_TRY(launch("train_loss_sum", 0, s, [&] { k_loss_accumulate<<<1, 1, 0, s>>>(st, lacc, w, 0); }));
@@ -1987,7 +2002,8 @@ int nps_apply_precond_transpose(const nps_net* net, const uint8_t* labels_d, nps
     hipStream_t s = static_cast<hipStream_t>(stream);
     const Plan plan = make_plan(dims, net->levels, precision, true);
     State* st = mptr<State>(ws_d, tl.base.state);
-    NPS_TRY(launch("state_init", 0, s, [&] { k_state_init<<<1, 64, 0, s>>>(st, 0, 0, 0, 0, 0); }));
+    ClassSums* cls = mptr<ClassSums>(ws_d, tl.base.cls);
+    NPS_TRY(launch("state_init", 0, s, [&] { k_state_init<<<1, kBlock, 0, s>>>(st, cls); }));
     if (precision == NPS_FP64) {
         NPS_TRY(run_setup<double>(net, labels_d, dims, plan, tl.base, ws_d, s));
         return adjoint_apply<double>(net, labels_d, dims, tl, ws_d, static_cast<const double*>(g_d),

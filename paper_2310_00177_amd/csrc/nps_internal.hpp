@@ -140,6 +140,6 @@ struct HostFlags {
 };
 
 // Control-kernel stages.
-enum Stage : int { kStageScan = 0, kStageAff = 1, kStageResidual = 2, kStageDots = 3, kStageStep = 4, kStageLoss = 5 };
+enum Stage : int { kStageResidual = 0, kStageDots = 1, kStageStep = 2, kStageLoss = 3 };
 
 }  // namespace nps

@@ -562,162 +562,35 @@ __device__ __forceinline__ Acc apply_A(const L* lab_s, const V* v_s, int base, i
 // ---------------------------------------------------------------------------
 // setup kernels
 // ---------------------------------------------------------------------------
-__global__ void k_state_init(State* st, int max_iter, int fixed, int n_ortho, int method, int sym) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        State s = {};
-        s.max_iter = max_iter;
-        s.fixed = fixed;
-        s.n_ortho = n_ortho;
-        s.method = method;
-        s.sym = sym;
-        s.scale = 1.0;
-        *st = s;
-    }
-}
-
-// Validate labels and b, count fluid cells, ||b||^2, x0 = 0.
-template <class X>
-__global__ __launch_bounds__(kBlock) void k_scan(const uint8_t* __restrict__ lab, const double* __restrict__ b,
-                                                 size_t n, X* x, double* partials) {
-    double v[kRedWidth] = {0.0, 0.0, 0.0, 0.0};   // bb, n_fluid, bad labels, non-finite
-    for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (size_t)gridDim.x * kBlock) {
-        const uint8_t l = lab[i];
-        const double bv = b[i];   // read with the label (used on fluid cells only)
-        if (l > kSolid) v[2] += 1.0;
-        if (l == kFluid) {
-            v[1] += 1.0;
-            if (!isfinite(bv)) v[3] += 1.0;
-            else v[0] += bv * bv;
-        }
-        x[i] = X(0);
-    }
-    block_partials<kBlock>(v, partials);
-}
-
-// Counts of level l+1 from level l: sums of the 2x2x2 children.
-template <bool FROM_LABELS>
-__global__ __launch_bounds__(kBlock) void k_pool_counts(const void* __restrict__ in, Grid gin,
-                                                        uint32_t* __restrict__ out, Grid gout) {
-    const size_t n = ncells(gout);
-    for (size_t q = (size_t)blockIdx.x * kBlock + threadIdx.x; q < n; q += (size_t)gridDim.x * kBlock) {
-        const int x = (int)(q % gout.nx), y = (int)((q / gout.nx) % gout.ny), z = (int)(q / ((size_t)gout.nx * gout.ny));
-        uint32_t n0 = 0, n1 = 0;
-        for (int k = 0; k < 8; ++k) {
-            const size_t c = cell_index(gin, 2 * z + (k >> 2), 2 * y + ((k >> 1) & 1), 2 * x + (k & 1));
-            if (FROM_LABELS) {
-                const uint8_t l = static_cast<const uint8_t*>(in)[c];
-                n0 += l == kFluid;
-                n1 += l == kAir;
-            } else {
-                const uint32_t v = static_cast<const uint32_t*>(in)[c];
-                n0 += v & 0xffffu;
-                n1 += v >> 16;
-            }
-        }
-        out[q] = n0 | (n1 << 16);
-    }
-}
-
-// The image-window sums of Aff_1^l and Aff_2^l (global means), in double:
-// S = sum_p sum_o sum_c w[c][o] i_c(p + o), the image solid outside the grid.
-// With q = p + o the in-grid part is sum_q sum_c i_c(q) W_c(q), where
-// W_c(q) = sum of w[c][o] over the o with q - o in the grid (all 27 for an
-// interior cell), so each cell is read once; the out-of-grid part is
-// sum_o w[solid][o] (n - #{p : p + o in the grid}), with that count the
-// product over the axes of (N_a - |o_a|), added by one thread.
-template <bool L1>
-__global__ __launch_bounds__(kBlock) void k_aff(const void* __restrict__ img, Grid g, double inv_full,
-                                                const AffW* __restrict__ a1, const AffW* __restrict__ a2,
-                                                double* partials) {
-    const size_t n = ncells(g);
-    double v[kRedWidth] = {0.0, 0.0, 0.0, 0.0};
-    __shared__ double full_s[6];   // W_c of an interior cell, for Aff_1 and Aff_2
-    if (threadIdx.x < 6) {
-        const AffW* a = threadIdx.x < 3 ? a1 : a2;
-        double t = 0.0;
-        for (int o = 0; o < kTaps; ++o) t += a->w[threadIdx.x % 3][o];
-        full_s[threadIdx.x] = t;
-    }
-    __syncthreads();
-    const double full1[3] = {full_s[0], full_s[1], full_s[2]}, full2[3] = {full_s[3], full_s[4], full_s[5]};
-    for (size_t p = (size_t)blockIdx.x * kBlock + threadIdx.x; p < n; p += (size_t)gridDim.x * kBlock) {
-        const int x = (int)(p % g.nx), y = (int)((p / g.nx) % g.ny), z = (int)(p / ((size_t)g.nx * g.ny));
-        double i0, i1;
-        if (L1) {
-            const uint8_t l = static_cast<const uint8_t*>(img)[p];
-            i0 = l == kFluid;
-            i1 = l == kAir;
-        } else {
-            const uint32_t c = static_cast<const uint32_t*>(img)[p];
-            i0 = (double)(c & 0xffffu) * inv_full;
-            i1 = (double)(c >> 16) * inv_full;
-        }
-        const double i2 = 1.0 - i0 - i1;
-        double W1[3] = {full1[0], full1[1], full1[2]}, W2[3] = {full2[0], full2[1], full2[2]};
-        const bool interior = x >= 1 && y >= 1 && z >= 1 && x + 1 < g.nx && y + 1 < g.ny && z + 1 < g.nz;
-        if (!interior) {
-            for (int c = 0; c < 3; ++c) W1[c] = W2[c] = 0.0;
-            for (int o = 0; o < kTaps; ++o) {
-                if (!in_grid(g, z - (o / 9 - 1), y - ((o / 3) % 3 - 1), x - (o % 3 - 1))) continue;
-                for (int c = 0; c < 3; ++c) {
-                    W1[c] += a1->w[c][o];
-                    W2[c] += a2->w[c][o];
-                }
-            }
-        }
-        v[0] += i0 * W1[0] + i1 * W1[1] + i2 * W1[2];
-        v[1] += i0 * W2[0] + i1 * W2[1] + i2 * W2[2];
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {   // the solid padding
-        for (int o = 0; o < kTaps; ++o) {
-            const double in = (double)max(g.nz - abs(o / 9 - 1), 0) * (double)max(g.ny - abs((o / 3) % 3 - 1), 0) *
-                              (double)max(g.nx - abs(o % 3 - 1), 0);
-            v[0] += a1->w[2][o] * ((double)n - in);
-            v[1] += a2->w[2][o] * ((double)n - in);
-        }
-    }
-    block_partials<kBlock>(v, partials);
-}
-
-// K[t][cell] of one CConv block on one level, formed in double (setup).
-template <class T, bool L1, int TG>
+// K[t][cell] of one CConv block on one large level (training and the
+// symmetric variant), formed in double: one thread per cell, whose window is
+// read once for all 27 taps; the taps share uniform weight loads.
+template <class T, bool L1>
 __global__ __launch_bounds__(kBlock) void k_kgen_store(const void* __restrict__ img, Grid g,
                                                        const CConvW<double>* __restrict__ w, T* __restrict__ kst) {
-    // one thread per (group j of TG taps, cell p), i = j n + p: the taps of a
-    // block share their weights (uniform loads), the stores are contiguous;
-    // each tap sums its 27 window terms in window order.  TG = 1 spreads a
-    // small level over many threads; TG = 27 reads each window once on a
-    // large one (27 taps per thread would re-read it 27 times)
-    static_assert(kTaps % TG == 0, "whole tap groups");
     const size_t n = ncells(g);
-    for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < (size_t)(kTaps / TG) * n;
-         i += (size_t)gridDim.x * kBlock) {
-        const int t0 = (int)(i / n) * TG;
-        const size_t p = i - (size_t)(t0 / TG) * n;
+    for (size_t p = (size_t)blockIdx.x * kBlock + threadIdx.x; p < n; p += (size_t)gridDim.x * kBlock) {
         const int x = (int)(p % g.nx), y = (int)((p / g.nx) % g.ny), z = (int)(p / ((size_t)g.nx * g.ny));
-        double K[TG];
+        double K[kTaps];
 #pragma unroll
-        for (int u = 0; u < TG; ++u) K[u] = w->C[t0 + u];
-        // the window loop is unrolled for one tap; with all 27 it stays a loop
-        // (27 x 27 unrolled terms would not fit the instruction cache)
-        constexpr int UO = TG == 1 ? kTaps : 1;
-#pragma unroll UO
+        for (int u = 0; u < kTaps; ++u) K[u] = w->C[u];
+        // a loop, not unrolled: 27 x 27 terms would not fit the instruction cache
+#pragma unroll 1
         for (int o = 0; o < kTaps; ++o) {
             // solid padding (no fluid, no air) outside the grid: the cell itself is
-            // read there and its weights zeroed, so the 27 reads are unconditional
+            // read there and its counts dropped, so the 27 reads are unconditional
             const int qz = z + o / 9 - 1, qy = y + (o / 3) % 3 - 1, qx = x + o % 3 - 1;
             const bool in = in_grid(g, qz, qy, qx);
             const size_t q = in ? cell_index(g, qz, qy, qx) : p;
             const uint32_t v = L1 ? (uint32_t)static_cast<const uint8_t*>(img)[q] : static_cast<const uint32_t*>(img)[q];
             uint32_t c0, c1;
             counts_of<L1>(v, c0, c1);
-            const double m = in ? 1.0 : 0.0;
+            const double m0 = in ? (double)c0 : 0.0, m1 = in ? (double)c1 : 0.0;
 #pragma unroll
-            for (int u = 0; u < TG; ++u)
-                K[u] += (w->D[o][t0 + u][0] * m) * (double)c0 + (w->D[o][t0 + u][1] * m) * (double)c1;
+            for (int u = 0; u < kTaps; ++u) K[u] = fma(w->D[o][u][0], m0, fma(w->D[o][u][1], m1, K[u]));
         }
 #pragma unroll
-        for (int u = 0; u < TG; ++u) kst[(size_t)(t0 + u) * n + p] = (T)K[u];
+        for (int u = 0; u < kTaps; ++u) kst[(size_t)u * n + p] = (T)K[u];
     }
 }
 
@@ -728,9 +601,10 @@ __global__ __launch_bounds__(kBlock) void k_kgen_store(const void* __restrict__ 
 // piece, the bf16 training leg), B from the 27 window cells' counts (exact in
 // bf16 up to level 3; solid outside the grid).  Lane (g, n) holds taps
 // 16 mb + 4 g + j of cell n and stores them, 16 consecutive cells per tap.
+// Block b of nb blocks.
 template <int KM, bool L1>
-__global__ __launch_bounds__(kBlock) void k_kgen_store_mfma(const void* __restrict__ img, Grid g,
-                                                            const MfmaW* __restrict__ wm, float* __restrict__ kst) {
+__device__ __forceinline__ void kgen_mfma(const void* __restrict__ img, Grid g, const MfmaW* __restrict__ wm,
+                                          float* __restrict__ kst, int b, int nb) {
     constexpr int P = KM == kMfmaBf16x3 ? kPieces : 1;
     const int lane = threadIdx.x & 63, gl = lane >> 4, n = lane & 15;
     u16x8 a[P][2][2];
@@ -743,8 +617,8 @@ __global__ __launch_bounds__(kBlock) void k_kgen_store_mfma(const void* __restri
     const size_t ncell = ncells(g);
     const int nxg = (g.nx + 15) / 16;
     const size_t ngroups = (size_t)g.nz * g.ny * nxg;
-    const int waves = (int)(gridDim.x * (kBlock / 64));
-    for (size_t grp = (size_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); grp < ngroups; grp += waves) {
+    const int waves = nb * (kBlock / 64);
+    for (size_t grp = (size_t)b * (kBlock / 64) + (threadIdx.x >> 6); grp < ngroups; grp += waves) {
         const int xb = (int)(grp % nxg), y = (int)((grp / nxg) % g.ny), z = (int)(grp / ((size_t)nxg * g.ny));
         const int x = 16 * xb + n;
         const bool valid = x < g.nx;
@@ -787,12 +661,15 @@ __global__ __launch_bounds__(kBlock) void k_kgen_store_mfma(const void* __restri
     }
 }
 
+template <int KM, bool L1>
+__global__ __launch_bounds__(kBlock) void k_kgen_store_mfma(const void* __restrict__ img, Grid g,
+                                                            const MfmaW* __restrict__ wm, float* __restrict__ kst) {
+    kgen_mfma<KM, L1>(img, g, wm, kst, (int)blockIdx.x, (int)gridDim.x);
+}
+
 // ---------------------------------------------------------------------------
 // the one-block control kernel
 // ---------------------------------------------------------------------------
-// Sums nparts per-block partials (structure of arrays, block order: a fixed
-// summation order) and updates the state for one stage of the iteration.
-// The stopping decision is mirrored to host memory (hf) for the host loop.
 // Per-wave CConv modes of one level (see choose_mode), one byte per (tile,
 // z-plane of the tile).  Level 1: m_down for the down kernel (zero where no
 // window of the wave holds fluid), m_up for the up kernel (zero where the
@@ -818,13 +695,6 @@ __global__ __launch_bounds__(kBlock) void k_wave_modes(const void* __restrict__ 
             if (L1) m_up[tile * TZ + lz] = (int8_t)mu;
         }
     }
-}
-
-// Rows of partials each stage sums.
-template <int STAGE>
-constexpr int ctl_width() {
-    return STAGE == kStageScan ? 4 : STAGE == kStageAff ? 2 : STAGE == kStageResidual ? 1
-         : STAGE == kStageDots ? kMaxOrtho : STAGE == kStageLoss ? 1 : 2;
 }
 
 // Partial sums (sum_partials below) in two parts: head_partials issues the
@@ -1026,50 +896,21 @@ __device__ __forceinline__ int residual_stage(State* st, const ResidualIn& in, d
     return done;
 }
 
-// The state update of one stage from its summed partials v (one thread).
-// The stopping decision is mirrored to host memory (hf) for the host loop.
-// The Dots stage may run in every block of a kernel at once (each with the
-// same sums): it reads no field it writes.
-template <int STAGE>
-__device__ __forceinline__ void control_update(State* st, const double* v, int i0, int i1, int i2, int i3, double d0,
-                                               double d1, double d2, HostFlags* hf) {
-    if constexpr (STAGE == kStageScan) {            // d0 = tol
-        st->bb = v[0];
-        st->n_fluid = (int)v[1];
-        st->bad_label = (int)v[2];
-        st->nonfinite = (int)v[3];
-        st->tol2bb = d0 * d0 * v[0];
-    } else if constexpr (STAGE == kStageAff) {      // i0 = level index, d0/d1 = Aff biases, d2 = 27 n_l
-        st->c1[i0] = d0 + v[0] / d2;
-        st->c2[i0] = d1 + v[1] / d2;
-    } else if constexpr (STAGE == kStageResidual) { // ||b - A x_k||^2 of the iterate down_l1 just formed
-        residual_stage(st, residual_in(st), v[0], hf);
-    } else if constexpr (STAGE == kStageDots) {     // i0..i3: ring slots of d_(k-1), d_(k-2), ...
-        const int sl[kMaxOrtho] = {i0, i1, i2, i3};
-        double beta[kMaxOrtho], rho;
-        dots_betas(dots_in(st, sl), v, beta, rho);
-        for (int j = 0; j < kMaxOrtho; ++j) st->beta[j] = beta[j];
-        if (st->method != 0) st->rho = rho;
-    } else if constexpr (STAGE == kStageLoss) {     // training loss: ||b - A y||^2
-        st->rr = v[0];
-    } else if constexpr (STAGE == kStageStep) {     // i0: ring slot of the new direction
-        step_update(st, step_in(st), i0, v[0], v[1], hf);
-    }
-}
-
 // The one-block control kernel: sums nparts per-block partials and updates
-// the state for one stage of the iteration.
+// the state: the Residual stage of solves without a bottom workgroup, or the
+// training loss ||b - A y||^2.
 template <int STAGE>
 __global__ __launch_bounds__(kCtlBlock) void k_control(State* st, const double* __restrict__ partials, int nparts,
-                                                       int i0, int i1, int i2, int i3, double d0, double d1,
-                                                       double d2, HostFlags* hf) {
+                                                       HostFlags* hf) {
     // the stop flag is read alongside the partials and tested after them
-    const int done = STAGE == kStageResidual || STAGE == kStageDots || STAGE == kStageStep ? st->done : 0;
-    constexpr int W = ctl_width<STAGE>();
-    double v[W];
-    sum_partials<W, kCtlBlock>(partials, nparts, W, v);
+    const int done = STAGE == kStageResidual ? st->done : 0;
+    double v[1];
+    sum_partials<1, kCtlBlock>(partials, nparts, 1, v);
     if (done) return;
-    if (threadIdx.x == 0) control_update<STAGE>(st, v, i0, i1, i2, i3, d0, d1, d2, hf);
+    if (threadIdx.x == 0) {
+        if constexpr (STAGE == kStageResidual) residual_stage(st, residual_in(st), v[0], hf);
+        else st->rr = v[0];
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1695,70 +1536,6 @@ __host__ __device__ inline Columns columns_of(Grid g) {
     int chunk = 8;
     while (chunk > 2 && ncx * ncy * ((g.nz + chunk - 1) / chunk) < 512) chunk /= 2;
     return Columns{ncx, ncy, (g.nz + chunk - 1) / chunk, chunk};
-}
-
-// Work items of the 7-point kernels that hold no fluid cell.  On such an
-// item r = 0 and A d = 0, and it adds nothing to any dot (every term has a
-// factor r or A d), so once its cells hold zeros in the solver's vectors the
-// kernels need not visit it: they walk a list of the other ("live") items.
-// Buffers zeroed on the items without fluid at set-up (2, 4 or 8 B elements).
-struct ZeroBufs {
-    void* p[2 * kRing + 3];
-    int bytes[2 * kRing + 3];
-    int n;
-};
-
-// One block per item (a thread per column, columns_of order): live[w] = 1
-// when item w holds a fluid cell; otherwise the item's cells are zeroed in
-// every buffer of zb.
-__global__ __launch_bounds__(kBlock) void k_item_live(const uint8_t* __restrict__ lab, Grid g,
-                                                      uint8_t* __restrict__ live, ZeroBufs zb) {
-    const Columns cl = columns_of(g);
-    const int w = blockIdx.x;
-    const int x0 = (w % cl.ncx) * PX, y0 = ((w / cl.ncx) % cl.ncy) * PY, z0 = (w / (cl.ncx * cl.ncy)) * cl.chunk;
-    const int z1 = min(z0 + cl.chunk, g.nz);
-    const int xx = x0 + threadIdx.x % PX, yy = y0 + threadIdx.x / PX;
-    const bool col = xx < g.nx && yy < g.ny;
-    int f = 0;
-    if (col)
-        for (int z = z0; z < z1; ++z) f |= lab[cell_index(g, z, yy, xx)] == kFluid;
-    const int any = __syncthreads_or(f);
-    if (threadIdx.x == 0) live[w] = any ? 1 : 0;
-    if (any || !col) return;
-    for (int i = 0; i < zb.n; ++i)
-        for (int z = z0; z < z1; ++z) {
-            const size_t q = cell_index(g, z, yy, xx);
-            if (zb.bytes[i] == 8) static_cast<double*>(zb.p[i])[q] = 0.0;
-            else if (zb.bytes[i] == 4) static_cast<float*>(zb.p[i])[q] = 0.0f;
-            else static_cast<uint16_t*>(zb.p[i])[q] = 0;
-        }
-}
-
-// One block: items[0 .. nlive) = the live items in increasing order (z-major,
-// so each XCD's contiguous share of the list is a z-range), st->nlive = nlive.
-__global__ __launch_bounds__(kBlock) void k_item_list(const uint8_t* __restrict__ live, int count,
-                                                      uint32_t* __restrict__ items, State* st) {
-    constexpr int W = kBlock / 64;
-    __shared__ uint32_t wsum[W];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    uint32_t base = 0;
-    for (int i0 = 0; i0 < count; i0 += kBlock) {
-        const int i = i0 + threadIdx.x;
-        const bool f = i < count && live[i] != 0;
-        const uint64_t m = __ballot(f);
-        if (lane == 0) wsum[wv] = (uint32_t)__popcll(m);
-        __syncthreads();
-        uint32_t off = base, tot = 0;
-#pragma unroll
-        for (int k = 0; k < W; ++k) {
-            off += k < wv ? wsum[k] : 0u;
-            tot += wsum[k];
-        }
-        if (f) items[off + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = (uint32_t)i;
-        base += tot;
-        __syncthreads();   // wsum is rewritten by the next round
-    }
-    if (threadIdx.x == 0) st->nlive = (int)base;
 }
 
 // d = dhat - sum_j beta_j d_(k-1-j) (classical Gram-Schmidt in the A inner

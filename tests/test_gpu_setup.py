@@ -1,0 +1,64 @@
+"""Set-up of a network evaluation (GPU): the image pyramid in 32^3 cubes, the
+boundary sums behind the Aff scalars, and the stored kernels of the small levels.
+
+Random labels put fluid and air on every face, edge and corner of the grid, so
+every boundary class enters the Aff scalars; the grids leave the last cube
+partly filled along each axis and give one cube, several, and rows that are and
+are not whole 16-byte words."""
+import numpy as np
+import pytest
+import torch
+
+import nps_inputs as gi
+from oracle import network as onet
+
+pytestmark = pytest.mark.gpu
+
+nps = pytest.importorskip("paper_2310_00177_amd")
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+
+def random_blob(levels, seed):
+    rng = np.random.default_rng(seed)
+    blob = gi.xavier_params(levels, seed)
+    for name, _, off, size in gi.blob_layout(levels):
+        if name.endswith("B"):
+            blob[off:off + size] = 0.1 * rng.standard_normal(size)
+    return blob
+
+
+@pytest.mark.parametrize("shape,levels", [((4, 4, 4), 3), ((32, 32, 32), 6), ((48, 16, 80), 5), ((34, 70, 66), 2),
+                                          ((40, 72, 24), 4), ((64, 96, 32), 6)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_setup_parity(shape, levels, offset):
+    """FP64 evaluation against the oracle (the bound of the other FP64 parity tests, 1e-12), with labels
+    that start on a 16-byte boundary and one byte past it."""
+    rng = np.random.default_rng(sum(shape) + levels)
+    lab = rng.choice(3, size=shape, p=(0.5, 0.3, 0.2)).astype(np.uint8)
+    r = rng.standard_normal(shape)
+    blob = random_blob(levels, 3)
+    buf = torch.empty(lab.size + 16, dtype=torch.uint8, device="cuda")
+    labels = buf[offset:offset + lab.size].view(shape)
+    labels.copy_(torch.from_numpy(lab))
+    got = nps.apply_precond(nps.Net(blob, levels), labels, torch.from_numpy(r).cuda()).cpu().numpy()
+    ref = onet.Network(blob, levels, lab).apply(r)
+    assert np.linalg.norm(got - ref) / np.linalg.norm(ref) < 1e-12
+    assert np.abs(got - ref).max() < 1e-12 * np.abs(ref).max()
+
+
+def test_invalid_solve_leaves_no_work_behind():
+    """A solve that is rejected after its set-up was enqueued returns with the stream idle, its x untouched."""
+    lab = gi.gen_labels(gi.scene_c1(), seed=1)
+    b = gi.gen_rhs(lab, seed=2)
+    bad = b.copy()
+    bad[tuple(np.argwhere(lab == gi.FLUID)[0])] = np.nan
+    net, labels = nps.Net(gi.multilevel_params(6), 6), torch.from_numpy(lab).cuda()
+    x = torch.full(lab.shape, 7.0, dtype=torch.float64, device="cuda")
+    with pytest.raises(nps.NpsError) as e:
+        nps.solve(net, labels, torch.from_numpy(bad).cuda(), x=x)
+    assert e.value.code == -5 and torch.cuda.current_stream().query()
+    assert bool((x == 7.0).all())
+    _, info = nps.solve(net, labels, torch.from_numpy(b).cuda(), x=x)
+    assert info.status == 0 and info.n_fluid == int((lab == gi.FLUID).sum())

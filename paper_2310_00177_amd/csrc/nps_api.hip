@@ -487,6 +487,17 @@ bool wide_labels(const uint8_t* labels, Grid g) {
     return g.nx % 16 == 0 && reinterpret_cast<uintptr_t>(labels) % 16 == 0;
 }
 
+// Rows of four can be read as one word (labels) and one float4 (r, when given) each.
+bool wide_quads(const uint8_t* labels, const void* r, Grid g) {
+    return g.nx % 4 == 0 && reinterpret_cast<uintptr_t>(labels) % 4 == 0 && reinterpret_cast<uintptr_t>(r) % 16 == 0;
+}
+
+// f(planes per work item of the level-1 network kernels) as a constant.
+template <class F>
+int with_chunk(Grid g, F&& f) {
+    return march_columns(g).chunk == 4 ? f(std::integral_constant<int, 4>()) : f(std::integral_constant<int, 2>());
+}
+
 // Image pyramid as counts, Aff scalars, modes, and the stored kernels.  The
 // state and the cleared class sums are already in the workspace.
 template <class T>
@@ -572,16 +583,12 @@ int run_setup(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
     }));
     if (is_mfma(plan.km[1])) {
         const Grid g = level_grid(d, 1);
-        const size_t threads = group_mode_bytes(g) * 16;
-        NPS_TRY(launch("setup_group_modes", (double)ncells(g), s, [&] {
-            k_group_modes<<<(unsigned)((threads + kBlock - 1) / kBlock), kBlock, 0, s>>>(
-                labels, g, mptr<uint8_t>(ws, lay.gmode[0]), mptr<uint8_t>(ws, lay.gmode[1]));
-        }));
-        const int items = march_columns(g).count();
-        NPS_TRY(launch("setup_item_zero", (double)items, s, [&] {
-            k_item_zero<<<(unsigned)((items + kBlock - 1) / kBlock), kBlock, 0, s>>>(
-                g, cptr<uint32_t>(ws, lay.gmode[0]), cptr<uint32_t>(ws, lay.gmode[1]), mptr<uint8_t>(ws, lay.izero[0]),
-                mptr<uint8_t>(ws, lay.izero[1]));
+        NPS_TRY(with_chunk(g, [&](auto ch) {
+            return launch("setup_march_modes", (double)ncells(g), s, [&] {
+                k_march_modes<decltype(ch)::value><<<march_columns(g).count(), kBlock, 0, s>>>(
+                    labels, g, mptr<uint8_t>(ws, lay.gmode[0]), mptr<uint8_t>(ws, lay.gmode[1]),
+                    mptr<uint8_t>(ws, lay.izero[0]), mptr<uint8_t>(ws, lay.izero[1]));
+            });
         }));
     }
     for (int l = 1; l <= L; ++l) {
@@ -732,11 +739,16 @@ int run_down_l1(const nps_net* net, const uint8_t* labels, nps_dims d, const Pla
     return with_kmode<T>(plan.km[1], [&](auto km) {
         constexpr int KM = decltype(km)::value;
         if constexpr (is_mfma(KM)) {
-            // as many blocks as fit (the down kernel's registers allow five per CU)
-            const int grid = persist_grid_n(&k_down_l1m<KM>, march_columns(g).count());
-            return launch("net_down_l1", (double)ncells(g), s, [&] {
-                k_down_l1m<KM><<<grid, kBlock, 0, s>>>(labels, g, r, x1, rnext, w, wm, st,
-                                                       cptr<uint32_t>(ws, lay.gmode[0]), cptr<uint8_t>(ws, lay.izero[0]));
+            // as many blocks as fit
+            return with_chunk(g, [&](auto ch) {
+                constexpr int CH = decltype(ch)::value;
+                const int grid = persist_grid_n(&k_down_l1m<KM, CH>, march_columns(g).count());
+                return launch("net_down_l1", (double)ncells(g), s, [&] {
+                    k_down_l1m<KM, CH><<<grid, kBlock, 0, s>>>(labels, g, r, x1, rnext, w, wm, st,
+                                                               cptr<uint32_t>(ws, lay.gmode[0]),
+                                                               cptr<uint8_t>(ws, lay.izero[0]),
+                                                               wide_quads(labels, r, g) ? 1 : 0);
+                });
             });
         } else {
             const int grid = persist_grid(&k_down_l1<T, KM>, g);
@@ -767,13 +779,16 @@ int run_up_l1(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
             auto go = [&](auto nd) {
                 constexpr int ND = decltype(nd)::value;
                 constexpr bool H = HOOK;
-                const int grid = persist_grid_n(&k_up_l1m<KM, H, H ? 0 : ND>, march_columns(g).count() / 2);
-                if (nparts) *nparts = grid;
-                return launch("net_up_l1", (double)ncells(g), s, [&] {
-                    k_up_l1m<KM, H, H ? 0 : ND><<<grid, kBlock, 0, s>>>(labels, g, x2, x1, dhat, w, wm, st, partials,
-                                                                       ad[0], ad[1], ad[2], ad[3],
-                                                                       cptr<uint32_t>(ws, lay.gmode[1]),
-                                                                       cptr<uint8_t>(ws, lay.izero[1]));
+                return with_chunk(g, [&](auto ch) {
+                    constexpr int CH = decltype(ch)::value;
+                    const int grid = persist_grid_n(&k_up_l1m<KM, H, H ? 0 : ND, CH>, march_columns(g).count());
+                    if (nparts) *nparts = grid;
+                    return launch("net_up_l1", (double)ncells(g), s, [&] {
+                        k_up_l1m<KM, H, H ? 0 : ND, CH><<<grid, kBlock, 0, s>>>(
+                            labels, g, x2, x1, dhat, w, wm, st, partials, ad[0], ad[1], ad[2], ad[3],
+                            cptr<uint32_t>(ws, lay.gmode[1]), cptr<uint8_t>(ws, lay.izero[1]),
+                            wide_quads(labels, nullptr, g) ? 1 : 0);
+                    });
                 });
             };
             if (HOOK || max_dots <= 0) return go(std::integral_constant<int, 0>());

@@ -163,8 +163,8 @@ __device__ __forceinline__ void stage_batched(Get get, Put put) {
 // address space like the arrays they stand in for and a select between the
 // two stays a global (not a flat) load: flat loads share the LDS counter and
 // would make every LDS wait also wait for the loads in flight.
-__device__ uint64_t g_pad_zero[2] = {0, 0};
-__device__ uint8_t g_pad_solid[8] = {kSolid, kSolid, kSolid, kSolid, kSolid, kSolid, kSolid, kSolid};
+__device__ __attribute__((aligned(16))) uint64_t g_pad_zero[2] = {0, 0};
+__device__ __attribute__((aligned(16))) uint8_t g_pad_solid[8] = {kSolid, kSolid, kSolid, kSolid, kSolid, kSolid, kSolid, kSolid};
 
 template <class V>
 __device__ __forceinline__ const V* pad_zero() {

@@ -1,30 +1,34 @@
-// Level-1 network kernels on matrix cores, marching column footprints
-// through z (Alg. 2, first level: CConv_1^1 + pool down, interpolation +
-// CConv_2^1 + combine up).
+// Level-1 network kernels on matrix cores, one work item (a 64 x 4 column
+// footprint over 4 or 2 z-planes) at a time (Alg. 2, first level: CConv_1^1 +
+// pool down, interpolation + CConv_2^1 + combine up).
 //
-// A block owns a footprint of PX x PY = 64 x 4 columns and walks it through a
-// chunk of z-planes.  Every plane is staged once in LDS, with its x/y border,
-// as one 8-byte record per cell: the CConv input (float) and the cell's two
-// MFMA features (fluid and air counts as a bf16 / fp16 pair).  Four plane
-// buffers form a ring, so the output plane c reads planes c-1, c, c+1 while
-// plane c+2 is being written: one barrier per plane.
+// These kernels are bound by instruction issue (their traffic is 1 TB/s), so
+// the item is staged and evaluated with as few instructions per cell as
+// possible.  All planes of the item, with their one-cell border, are staged in
+// LDS in one go, as one 8-byte record per cell: the CConv input (float) and the
+// cell's two MFMA features (fluid and air counts as a bf16 / fp16 pair).  One
+// barrier separates staging from the CConv, and every LDS address of the CConv
+// is a per-lane base plus a constant.
 //
-// Wave w covers x = 16 w .. 16 w + 15 of the footprint and its four rows;
-// row q is one 16-cell group, the N dimension of v_mfma_f32_16x16x32.  For a
-// group the per-cell kernels K^T[tap][cell] = A[tap][feature] B[feature][cell]
-// come out of the matrix cores with lane (g, n) (g = lane / 16, n = lane % 16)
-// holding the taps of window positions {4g + i, 16 + 4g + i : i < 4} of cell
-// n; the lane reads the CConv input at exactly those positions (the feature
-// and tap enumerations coincide), so the eight records it reads give both its
-// B fragment and its eight input values.  The four partial sums of a cell (one
-// per lane group) are combined for the four groups together with a
-// reduce-scatter over the lane groups (two gfx950 permlane swaps): afterwards
-// lane (g, n) holds the output of cell (x = 16 w + n, y = g).
-//
-// Groups are classified once per solve (k_group_modes; the labels do not
-// change during a solve): zero (every output is zero), pure (every cell that
-// matters has an all-fluid window: the constant fluid kernel) or general
-// (matrix cores).  A wave reads its four group modes with one scalar load.
+// Wave w covers x = 16 w .. 16 w + 15 of the footprint and its four rows; lane
+// (g, n) (g = lane / 16, n = lane % 16) owns cell (x = 16 w + n, y = g) of each
+// plane, and row q of a plane is one 16-cell group.  Groups are classified once
+// per solve (k_march_modes; the labels do not change during a solve):
+//   zero     every output is zero;
+//   pure     every cell that matters has an all-fluid window, i.e. the constant
+//            fluid kernel.  A wave with any pure group applies that kernel to
+//            all its cells: the 9 inputs of a plane around the lane's column
+//            are read once and enter the sums of the three output planes that
+//            see them (27 multiply-adds and 13 reads per cell of a 4-plane
+//            item, the kernel in scalar registers);
+//   general  matrix cores.  The per-cell kernels K^T[tap][cell] = A[tap][feature]
+//            B[feature][cell] come out with lane (g, n) holding the taps of
+//            window positions {4g + i, 16 + 4g + i : i < 4} of cell n; the lane
+//            reads the records at exactly those positions (the feature and tap
+//            enumerations coincide), so they give both its B fragment and its
+//            eight input values.  The four partial sums of a cell (one per lane
+//            group) are combined for the four groups together with a
+//            reduce-scatter over the lane groups (two gfx950 permlane swaps).
 #pragma once
 
 #include "nps_kernels.hpp"
@@ -32,21 +36,52 @@
 namespace nps {
 
 enum GroupMode : uint32_t { kGZero = 0, kGPure = 1, kGGeneral = 2 };
+constexpr uint32_t kAnyPure = 0x01010101u, kAnyGeneral = 0x02020202u;   // over a wave's four modes
 
-// Work items of the marching network kernels: a 64 x 4 column footprint
+// Work items of the level-1 network kernels: a 64 x 4 column footprint
 // over a chunk of 4 z-planes (2 on grids with fewer than 1024 such items).
 // Shorter items than the 7-point kernels' keep the per-block work even: an
-// item's cost depends on its group modes (interface footprints cost up to
-// 1.7x empty ones) and the cost field is smooth in space.  When the grid of
-// blocks is a multiple of the XCD count, XCD x (blocks b with b % 8 == x)
-// takes the z-chunks zc with zc % 8 == x, every footprint of each, so its
-// blocks share the y halos of a slab in their L2 while every XCD gets slabs
-// from the whole height; its blocks take the XCD's items round-robin.  A
-// function of the grid alone: launches and kernels agree on it.
+// item's cost depends on its group modes and the cost field is smooth in
+// space.  When the grid of blocks is a multiple of the XCD count, XCD x
+// (blocks b with b % 8 == x) takes the z-chunks zc with zc % 8 == x, every
+// footprint of each, so its blocks share the y halos of a slab in their L2
+// while every XCD gets slabs from the whole height; its blocks take the XCD's
+// items round-robin.  A function of the grid alone: launches and kernels agree
+// on it.
 __host__ __device__ inline Columns march_columns(Grid g) {
     const int ncx = (g.nx + PX - 1) / PX, ncy = (g.ny + PY - 1) / PY;
     const int chunk = ncx * ncy * ((g.nz + 3) / 4) >= 1024 ? 4 : 2;
     return Columns{ncx, ncy, (g.nz + chunk - 1) / chunk, chunk};
+}
+
+// The items of a block, in the order above.
+struct MarchItems {
+    int per, count, xcd, zmul, li, step;
+};
+
+__device__ __forceinline__ MarchItems march_items(Columns cl) {
+    const bool xs = gridDim.x % kXcds == 0;
+    MarchItems m;
+    m.xcd = xs ? (int)(blockIdx.x % kXcds) : 0;
+    m.zmul = xs ? kXcds : 1;
+    m.per = cl.ncx * cl.ncy;
+    m.count = m.per * (xs ? (cl.ncz - m.xcd + kXcds - 1) / kXcds : cl.ncz);
+    m.li = xs ? (int)blockIdx.x / kXcds : (int)blockIdx.x;
+    m.step = xs ? (int)gridDim.x / kXcds : (int)gridDim.x;
+    return m;
+}
+
+struct MarchItem {
+    int cx, cy, zc, rest;
+};
+
+__device__ __forceinline__ MarchItem march_item(const MarchItems& m, int li, Columns cl) {
+    MarchItem it;
+    it.zc = m.xcd + m.zmul * (li / m.per);
+    it.rest = li % m.per;
+    it.cx = it.rest % cl.ncx;
+    it.cy = it.rest / cl.ncx;
+    return it;
 }
 
 // One mode byte per (footprint, z, wave, row): index ((z ncy + cy) ncx + cx)
@@ -56,94 +91,104 @@ __host__ __device__ inline size_t group_mode_bytes(Grid g) {
     return (size_t)cl.ncx * cl.ncy * g.nz * 16;
 }
 
-// Labels of a level-1 window (solid outside the grid): all fluid, any fluid.
-__device__ __forceinline__ void window_flags(const uint8_t* __restrict__ lab, Grid g, int z, int y, int x,
-                                             bool& all_fluid, bool& any_fluid) {
-    all_fluid = true;
-    any_fluid = false;
-#pragma unroll
-    for (int o = 0; o < kTaps; ++o) {
-        const int zz = z + o / 9 - 1, yy = y + (o / 3) % 3 - 1, xx = x + o % 3 - 1;
-        const uint8_t l = in_grid(g, zz, yy, xx) ? lab[cell_index(g, zz, yy, xx)] : (uint8_t)kSolid;
-        all_fluid &= l == kFluid;
-        any_fluid |= l == kFluid;
-    }
-}
-
 // Group modes of the level-1 down (CConv_1, input zero off fluid) and up
-// (CConv_2, output restricted to fluid) kernels.  One thread per cell, 16
-// consecutive threads per group.
+// (CConv_2, output restricted to fluid) kernels, and one byte per item and
+// kernel that is set when all its groups are zero.  One block per item
+// (CH planes).
 //   down: zero when no window of the group holds fluid; pure when every
 //         window that holds fluid is all fluid (a window without fluid
 //         outputs zero under any kernel);
 //   up:   zero when no cell of the group is fluid; pure when every fluid
 //         cell's window is all fluid (other outputs are masked).
-__global__ __launch_bounds__(kBlock) void k_group_modes(const uint8_t* __restrict__ lab, Grid g,
-                                                        uint8_t* __restrict__ mdown, uint8_t* __restrict__ mup) {
-    const Columns cl = columns_of(g);
-    const size_t total = (size_t)cl.ncx * cl.ncy * g.nz * 256;   // 16 groups x 16 cells per (footprint, z)
-    const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    const size_t grp = i >> 4;
-    const int k = (int)(i & 15), q = (int)(grp & 3), w = (int)((grp >> 2) & 3);
-    const size_t rest = grp >> 4;
-    const int cx = (int)(rest % cl.ncx), cy = (int)((rest / cl.ncx) % cl.ncy), z = (int)(rest / ((size_t)cl.ncx * cl.ncy));
-    const int x = cx * PX + 16 * w + k, y = cy * PY + q;
-    bool valid = i < total && in_grid(g, z, y, x), all_f = true, any_f = false, own_f = false;
-    if (valid) {
-        window_flags(lab, g, z, y, x, all_f, any_f);
-        own_f = lab[cell_index(g, z, y, x)] == kFluid;
-    }
-    // per lane: 1 = the cell needs work, 2 = its window is not all fluid
-    const uint64_t dn_any = __ballot(valid && any_f), dn_mixed = __ballot(valid && any_f && !all_f);
-    const uint64_t up_any = __ballot(valid && own_f), up_mixed = __ballot(valid && own_f && !all_f);
-    if (k == 0 && i < total) {
-        const int sh = threadIdx.x & 48;   // the group's 16 lanes
-        auto mode = [&](uint64_t any, uint64_t mixed) -> uint8_t {
-            if (((any >> sh) & 0xffffu) == 0) return kGZero;
-            return ((mixed >> sh) & 0xffffu) ? kGGeneral : kGPure;
-        };
-        mdown[grp] = mode(dn_any, dn_mixed);
-        mup[grp] = mode(up_any, up_mixed);
-    }
-}
-
-// One byte per work item (march_columns order), per kernel: 1 when every
-// group of the item's planes is zero for that kernel (down: no window holds
-// fluid; up: no fluid cell).  Such an item only writes its zero outputs.
-__global__ __launch_bounds__(kBlock) void k_item_zero(Grid g, const uint32_t* __restrict__ mdown,
-                                                      const uint32_t* __restrict__ mup, uint8_t* __restrict__ zdown,
-                                                      uint8_t* __restrict__ zup) {
+// A row of 64 labels becomes a 64-bit mask (one ballot), so the windows are
+// shifts and a few ANDs and ORs of row masks: one label load per cell and halo
+// cell, where one thread per cell read its 27 window labels (128^3: 30.5 us,
+// and 4.5 us for the item flags in a launch of their own).
+template <int CH>
+__global__ __launch_bounds__(kBlock) void k_march_modes(const uint8_t* __restrict__ lab, Grid g,
+                                                        uint8_t* __restrict__ mdown, uint8_t* __restrict__ mup,
+                                                        uint8_t* __restrict__ zdown, uint8_t* __restrict__ zup) {
+    constexpr int R = (CH + 2) * PHY;
+    __shared__ uint64_t own_s[R], any_s[R], all_s[R];   // fluid cells; windows along x with any / only fluid
     const Columns cl = march_columns(g);
-    const int i = (int)(blockIdx.x * kBlock + threadIdx.x);
-    if (i >= cl.count()) return;
-    const int cx = i % cl.ncx, cy = (i / cl.ncx) % cl.ncy, z0 = (i / (cl.ncx * cl.ncy)) * cl.chunk;
-    const int z1 = min(z0 + cl.chunk, g.nz);
-    uint32_t od = 0u, ou = 0u;
-    for (int z = z0; z < z1; ++z) {
-        const size_t row = (((size_t)z * cl.ncy + cy) * cl.ncx + cx) * 4;   // a plane's 16 mode bytes
+    const int per = cl.ncx * cl.ncy, rest = (int)blockIdx.x % per, zc = (int)blockIdx.x / per;
+    const int cx = rest % cl.ncx, cy = rest / cl.ncx, x0 = cx * PX, y0 = cy * PY, z0 = zc * CH;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint8_t own[R / 4], edge[R / 4];
+    static_assert(R % 4 == 0, "whole rounds of four waves");
 #pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            od |= mdown[row + w];
-            ou |= mup[row + w];
+    for (int k = 0; k < R / 4; ++k) {
+        const int r = wv + 4 * k, z = z0 + r / PHY - 1, y = y0 + r % PHY - 1;
+        const bool row = z >= 0 && z < g.nz && y >= 0 && y < g.ny;
+        const int x = x0 + lane, xe = lane == 0 ? x0 - 1 : x0 + PX;   // lanes 0, 1: the cells beside the row
+        const bool in = row && x < g.nx, ine = row && lane < 2 && xe >= 0 && xe < g.nx;
+        own[k] = *at_or(lab, in ? cell_index(g, z, y, x) : 0, in, g_pad_solid);
+        edge[k] = *at_or(lab, ine ? cell_index(g, z, y, xe) : 0, ine, g_pad_solid);
+    }
+#pragma unroll
+    for (int k = 0; k < R / 4; ++k) {
+        const uint64_t f = __ballot(own[k] == kFluid), e = __ballot(edge[k] == kFluid);
+        const uint64_t lo = (f << 1) | (e & 1u), hi = (f >> 1) | ((e >> 1) << 63);
+        if (lane == 0) {
+            own_s[wv + 4 * k] = f;
+            any_s[wv + 4 * k] = f | lo | hi;
+            all_s[wv + 4 * k] = f & lo & hi;
         }
     }
-    zdown[i] = od == 0u;
-    zup[i] = ou == 0u;
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    // thread (i, q, w): plane i, row q, wave w (threads past CH planes idle)
+    const int w = threadIdx.x & 3, q = (threadIdx.x >> 2) & 3, i = threadIdx.x >> 4;
+    uint32_t md = kGZero, mu = kGZero;
+    if (i < CH && z0 + i < g.nz && y0 + q < g.ny) {
+        uint64_t any = 0u, all = ~(uint64_t)0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                any |= any_s[(i + a) * PHY + q + b];
+                all &= all_s[(i + a) * PHY + q + b];
+            }
+        const uint64_t own_f = own_s[(i + 1) * PHY + q + 1];
+        const int left = g.nx - x0;   // columns of the footprint inside the grid
+        const uint64_t valid = left >= 64 ? ~(uint64_t)0 : (((uint64_t)1 << left) - 1u);
+        auto mode = [&](uint64_t need) -> uint32_t {   // need: the cells that matter
+            need &= valid;
+            if (((need >> (16 * w)) & 0xffffu) == 0) return kGZero;
+            return (((need & ~all) >> (16 * w)) & 0xffffu) ? kGGeneral : kGPure;
+        };
+        md = mode(any);
+        mu = mode(own_f);
+        const size_t at = (((size_t)(z0 + i) * cl.ncy + cy) * cl.ncx + cx) * 16 + 4 * w + q;
+        mdown[at] = (uint8_t)md;
+        mup[at] = (uint8_t)mu;
+    }
+    const uint64_t nd = __ballot(md != kGZero), nu = __ballot(mu != kGZero);
+    if (threadIdx.x == 0) {
+        zdown[blockIdx.x] = nd == 0u;
+        zup[blockIdx.x] = nu == 0u;
+    }
 }
 
-// A wave's MFMA and pure-kernel operands for all its groups.
+// The staged item: (CH + 2) planes of PHY rows of kRS records.  The cell at x
+// offset ix (-1 .. 64) from the footprint is record ix + XO of its row: XO = 2
+// for the down kernel, whose staging writes four cells from ix = 4k at once,
+// 1 for the up kernel, whose staging writes the pair (2j - 1, 2j).
+constexpr int kRS = 68;
+template <int CH>
+constexpr int kRecords = (CH + 2) * PHY * kRS;
+
+// A wave's MFMA operands for all its groups.
 template <int KM>
 struct MarchCtx {
     static constexpr int P = KM == kMfmaBf16x3 ? kPieces : 1;
     u16x8 a[P][2][2];
-    int lofs[8];    // record index of window position j for row 0, relative to a plane buffer
-    int oz[8];      // its z offset (-1, 0, 1)
-    float kp[8];    // the all-fluid kernel at tap j (0 past tap 26)
+    int lofs[8];    // record of window position j of output plane 0, row 0
     bool one;       // lane group 2: position 27 carries the constant feature
 };
 
-template <int KM>
-__device__ __forceinline__ MarchCtx<KM> march_ctx(const MfmaW* __restrict__ wm, const CConvW<float>* __restrict__ w) {
+template <int KM, int XO>
+__device__ __forceinline__ MarchCtx<KM> march_ctx(const MfmaW* __restrict__ wm) {
     MarchCtx<KM> c;
     const int lane = threadIdx.x & 63, g = lane >> 4, n = lane & 15, wv = threadIdx.x >> 6;
 #pragma unroll
@@ -157,12 +202,10 @@ __device__ __forceinline__ MarchCtx<KM> march_ctx(const MfmaW* __restrict__ wm, 
             }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const int o = 16 * (j >> 2) + 4 * g + (j & 3);
-        const int oc = min(o, kTaps - 1);
-        const int oy = (oc / 3) % 3 - 1, ox = oc % 3 - 1;
-        c.oz[j] = oc / 9 - 1;
-        c.lofs[j] = (1 + oy) * PHX + 16 * wv + n + 1 + ox;
-        c.kp[j] = o < kTaps ? w->Kpure[kFluid][o] : 0.0f;
+        const int o = min(16 * (j >> 2) + 4 * g + (j & 3), kTaps - 1);
+        c.lofs[j] = (o / 9 * PHY + o / 3 % 3) * kRS + 16 * wv + n + XO + o % 3 - 1;
+        // one register per position (the compiler re-formed the sums for every group)
+        __asm__ volatile("" : "+v"(c.lofs[j]));
     }
     c.one = g == 2;
     return c;
@@ -171,24 +214,15 @@ __device__ __forceinline__ MarchCtx<KM> march_ctx(const MfmaW* __restrict__ wm, 
 __device__ __forceinline__ uint32_t bits(float v) { return __float_as_uint(v); }
 __device__ __forceinline__ float fbits(uint32_t v) { return __uint_as_float(v); }
 
-// The partial CConv sum of the lane for group q (row q) of output plane c:
-// sum over its eight window positions of K_t(cell) r(cell + t).
+// The partial CConv sum of the lane for a general group (at: the group's
+// record offset, a constant): sum over its eight window positions of
+// K_t(cell) r(cell + t).
 template <int KM>
-__device__ __forceinline__ float march_group(const uint2* ring, const int (&pb)[8], int q, uint32_t mode,
-                                             const MarchCtx<KM>& c) {
-    if (mode == kGZero) return 0.0f;
+__device__ __forceinline__ float march_group(const uint2* rec, int at, const MarchCtx<KM>& c) {
     uint2 rv[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) rv[j] = ring[pb[j] + c.lofs[j] + q * PHX];
+    for (int j = 0; j < 8; ++j) rv[j] = rec[c.lofs[j] + at];
     float pa = 0.0f, pb2 = 0.0f;   // two chains of four
-    if (mode == kGPure) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            pa = fmaf(c.kp[j], fbits(rv[j].x), pa);
-            pb2 = fmaf(c.kp[j + 4], fbits(rv[j + 4].x), pb2);
-        }
-        return pa + pb2;
-    }
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     u16x8 B[2];
     B[0] = __builtin_bit_cast(u16x8, (u32x4){rv[0].y, rv[1].y, rv[2].y, rv[3].y});
@@ -231,181 +265,276 @@ __device__ __forceinline__ float reduce_scatter4(const float (&p)[4]) {
     return fbits(t[0]) + fbits(t[1]);
 }
 
-// One output plane's CConv for the lane's cell: the four groups of the wave,
-// then the reduce-scatter.  modes: the wave's four group modes (one byte each).
-template <int KM>
-__device__ __forceinline__ float march_cconv(const uint2* ring, int c, uint32_t modes, const MarchCtx<KM>& mc) {
-    int pb[8];
+// The CConv of the lane's cell in every plane of the item.  modes[i]: the
+// wave's four group modes in plane i (one byte each, uniform).
+template <int KM, int XO, int CH>
+__device__ __forceinline__ void march_cconv(const uint2* rec, const uint32_t (&modes)[CH], const MarchCtx<KM>& mc,
+                                            const CConvW<float>* __restrict__ w, float (&out)[CH]) {
+    const int lane = threadIdx.x & 63, gq = lane >> 4;
+    uint32_t any = 0u;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) pb[j] = ((c + mc.oz[j]) & 3) * kPlaneP;
-    if (modes == 0) return 0.0f;   // every group zero (wave-uniform)
-    float part[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) part[q] = march_group<KM>(ring, pb, q, (modes >> (8 * q)) & 0xffu, mc);
-    return reduce_scatter4(part);
-}
-
-// The record of one staged cell: input value and features (outside the grid:
-// zero input, solid features).
-template <int KM>
-__device__ __forceinline__ uint2 march_record(float r, uint8_t l) {
-    return uint2{bits(l == kFluid ? r : 0.0f), feat_word<KM, true>(l)};
-}
-
-// The staged elements of a thread in a footprint's plane (element i = thread
-// + k kBlock, clamped to the last one): offset y nx + x inside a plane and
-// whether the column lies in the grid.  Formed once per footprint; a plane's
-// loads then only add its z offset.
-struct StageElems {
-    static constexpr int K = (kPlane + kBlock - 1) / kBlock;
-    uint32_t off[K];
-    bool in[K];
-};
-
-__device__ __forceinline__ StageElems stage_elems(Grid g, int x0, int y0) {
-    StageElems e;
-#pragma unroll
-    for (int k = 0; k < StageElems::K; ++k) {
-        const int i = min((int)threadIdx.x + k * kBlock, kPlane - 1);
-        const int yy = y0 + i / PHX - 1, xx = x0 + i % PHX - 1;
-        e.in[k] = yy >= 0 && yy < g.ny && xx >= 0 && xx < g.nx;
-        e.off[k] = e.in[k] ? (uint32_t)yy * g.nx + xx : 0u;
+    for (int i = 0; i < CH; ++i) {
+        out[i] = 0.0f;
+        any |= modes[i];
     }
-    return e;
+    if (any & kAnyPure) {
+        // the fluid kernel in scalar registers, loaded per item: kept across the
+        // item loop, its 27 registers spilled
+        __asm__ volatile("" : "+s"(w));
+        float kp[kTaps];
+#pragma unroll
+        for (int t = 0; t < kTaps; ++t) kp[t] = w->Kpure[kFluid][t];
+        const uint2* corner = rec + gq * kRS + 16 * (int)(threadIdx.x >> 6) + (lane & 15) + XO - 1;
+#pragma unroll
+        for (int k = 0; k < CH + 2; ++k)
+#pragma unroll
+            for (int d = 0; d < 9; ++d) {
+                const float v = fbits(corner[(k * PHY + d / 3) * kRS + d % 3].x);
+#pragma unroll
+                for (int a = 0; a < 3; ++a)   // the plane is at z offset a - 1 from output plane k - a
+                    if (k - a >= 0 && k - a < CH) out[k - a] = fmaf(kp[9 * a + d], v, out[k - a]);
+            }
+    }
+    if (any & kAnyGeneral) {
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const uint32_t m = modes[i];
+            if (!(m & kAnyGeneral)) continue;
+            float part[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                part[q] = ((m >> (8 * q)) & kGGeneral) ? march_group<KM>(rec, (i * PHY + q) * kRS, mc) : 0.0f;
+            const float red = reduce_scatter4(part);
+            out[i] = ((m >> (8 * gq)) & kGGeneral) ? red : out[i];
+        }
+    }
 }
 
-struct RLab {   // CConv input and label of one staged cell
-    float r;
-    uint8_t l;
+// The wave's modes of the item's planes (zero past the grid).
+template <int CH>
+__device__ __forceinline__ void load_modes(const uint32_t* __restrict__ gmode, Columns cl, const MarchItem& it, int nz,
+                                           uint32_t (&modes)[CH]) {
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+    for (int i = 0; i < CH; ++i) {
+        const int z = it.zc * CH + i;
+        modes[i] = z < nz ? __builtin_amdgcn_readfirstlane(
+                                gmode[(((size_t)z * cl.ncy + it.cy) * cl.ncx + it.cx) * 4 + wv])
+                          : 0u;
+    }
+}
+
+// The thread index as a value of its own in every item: what staging derives
+// from it is then formed per item instead of staying in registers (30 of them,
+// which spilled) across the item loop, of which a block runs one or two rounds.
+__device__ __forceinline__ int item_thread() {
+    int t = (int)threadIdx.x;
+    __asm__ volatile("" : "+v"(t));
+    return t;
+}
+
+// Staging tasks of an item's rows: quads of four cells (a float4 and a word of
+// labels where the rows are aligned), then the two cells beside every row.
+// Whole waves hold one kind (kQuads is a multiple of 64), so the kind of a
+// wave's round k is uniform.
+template <int CH>
+struct StageTasks {
+    static constexpr int kRows = (CH + 2) * PHY;
+    static constexpr int kQuads = kRows * (PX / 4), kAll = kQuads + 2 * kRows;
+    static constexpr int K = (kAll + kBlock - 1) / kBlock;
+    static_assert(kQuads % 64 == 0, "uniform kind of a wave's round");
+    __device__ static __forceinline__ bool quads(int wv, int k) {
+        return (k + 1) * kBlock <= kQuads || 64 * wv + k * kBlock < kQuads;
+    }
+    __device__ static __forceinline__ bool edges(int wv, int k) {
+        return !quads(wv, k) && 64 * wv + k * kBlock < kAll;
+    }
 };
 
-// x1 = CConv_1^1(r) and r^2 = Pool(x1) (the input masked to fluid).  Plane-
-// marching: step s writes plane s into the ring, issues the loads of plane
-// s + 2, then forms output plane s - 1.  The 2x2x2 pool sums x pairs with a
-// DPP quad permutation, y pairs with a permlane swap and z pairs in a
-// register (chunks start on even planes and have even length).
-template <int KM>
-__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(KM == kMfmaBf16x3 ? 3 : 4) void k_down_l1m(const uint8_t* __restrict__ lab, Grid g,
-                                                     const float* __restrict__ r, float* __restrict__ x1,
-                                                     float* __restrict__ rnext, const CConvW<float>* __restrict__ w,
-                                                     const MfmaW* __restrict__ wm, const State* st,
-                                                     const uint32_t* __restrict__ gmode,
-                                                     const uint8_t* __restrict__ izero) {
-    __shared__ uint2 ring[4 * kPlaneP];
+struct StagePos {
+    int rec;              // first record of the task
+    uint32_t base;        // cell index of the first cell
+    int cells;            // cells inside the grid (quads 0 .. 4, edges 0 or 1)
+};
+
+template <int CH, int XO, bool QUAD>
+__device__ __forceinline__ StagePos stage_pos(Grid g, int x0, int y0, int z0, int t) {
+    using S = StageTasks<CH>;
+    const int e = min(t, S::kAll - 1) - S::kQuads;
+    const int row = QUAD ? t / (PX / 4) : e >> 1, ix = QUAD ? 4 * (t % (PX / 4)) : (e & 1) ? PX : -1;
+    const int z = z0 + row / PHY - 1, y = y0 + row % PHY - 1, x = x0 + ix;
+    const bool in = z >= 0 && z < g.nz && y >= 0 && y < g.ny && x >= 0 && x < g.nx;
+    return StagePos{row * kRS + ix + XO, in ? (uint32_t)cell_index(g, z, y, x) : 0u,
+                    in ? (QUAD ? min(4, g.nx - x) : 1) : 0};
+}
+
+// The labels of a task, one byte each (solid outside the grid).  wide: rows of
+// four labels are aligned words, and nx is a multiple of 4.
+template <bool QUAD>
+__device__ __forceinline__ uint32_t stage_labels(const uint8_t* __restrict__ lab, const StagePos& s, int wide) {
+    if constexpr (!QUAD) return *at_or(lab, s.base, s.cells > 0, g_pad_solid);
+    if (wide) return *reinterpret_cast<const uint32_t*>(at_or(lab, s.base, s.cells > 0, g_pad_solid));
+    uint32_t v = 0u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v |= (uint32_t)*at_or(lab, s.base + j, j < s.cells, g_pad_solid) << (8 * j);
+    return v;
+}
+
+template <bool QUAD>
+__device__ __forceinline__ float4 stage_values(const float* __restrict__ r, const StagePos& s, int wide) {
+    if constexpr (!QUAD) return float4{*at_or(r, s.base, s.cells > 0, pad_zero<float>()), 0.0f, 0.0f, 0.0f};
+    if (wide) return *reinterpret_cast<const float4*>(at_or(r, s.base, s.cells > 0, pad_zero<float>()));
+    float v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = *at_or(r, s.base + j, j < s.cells, pad_zero<float>());
+    return float4{v[0], v[1], v[2], v[3]};
+}
+
+// Waves per SIMD of the level-1 kernels: one more hides more of the staging's
+// latency (128^3 mixed: up 21.1 -> 18.8 us, down 16.1 -> 14.8 us; 256^3: up 98
+// -> 86 us, down 78 -> 67 us), yet another one spills (up 26.0 us).  The
+// three-piece weights of FP32 and the operands of more than two dots take
+// registers of one wave each.
+constexpr int march_waves(int km, int nd) { return 5 - (km == kMfmaBf16x3 ? 1 : 0) - (nd > 2 ? 1 : 0); }
+
+// x1 = CConv_1^1(r) and r^2 = Pool(x1) (the input masked to fluid).  The 2x2x2
+// pool sums x pairs with a DPP quad permutation, y pairs with a permlane swap
+// and z pairs in a register (items start on even planes).
+template <int KM, int CH>
+__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, 0)) void k_down_l1m(
+    const uint8_t* __restrict__ lab, Grid g, const float* __restrict__ r, float* __restrict__ x1,
+    float* __restrict__ rnext, const CConvW<float>* __restrict__ w, const MfmaW* __restrict__ wm, const State* st,
+    const uint32_t* __restrict__ gmode, const uint8_t* __restrict__ izero, int wide) {
+    constexpr int XO = 2;
+    using S = StageTasks<CH>;
+    __shared__ __attribute__((aligned(16))) uint2 rec[kRecords<CH>];
     const int done = st->done;   // tested once the first loads are out
-    const MarchCtx<KM> mc = march_ctx<KM>(wm, w);
+    const MarchCtx<KM> mc = march_ctx<KM, XO>(wm);
     const Columns cl = march_columns(g);
     const Grid gc = coarser(g);
     const int lane = threadIdx.x & 63, gq = lane >> 4, n = lane & 15;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t pstride = (uint32_t)g.ny * (uint32_t)g.nx;
-    StageElems se;
-    auto plane = [&](int zz) {
-        Batch<kPlane, RLab> bt;
-        const bool zin = zz >= 0 && zz < g.nz;
-        const uint32_t base = zin ? (uint32_t)zz * pstride : 0u;
-#pragma unroll
-        for (int k = 0; k < StageElems::K; ++k) {
-            const bool in = zin && se.in[k];
-            const size_t q = base + se.off[k];
-            bt.v[k] = RLab{*at_or(r, q, in, pad_zero<float>()), *at_or(lab, q, in, g_pad_solid)};
-        }
-        return bt;
-    };
+    const MarchItems mi = march_items(cl);
     bool first = true;
-    const bool xs = gridDim.x % kXcds == 0;
-    const int xcd = xs ? (int)(blockIdx.x % kXcds) : 0, lstep = xs ? (int)gridDim.x / kXcds : (int)gridDim.x;
-    const int per = cl.ncx * cl.ncy, nzl = xs ? (cl.ncz - xcd + kXcds - 1) / kXcds : cl.ncz, zmul = xs ? kXcds : 1;
-    for (int li = xs ? (int)blockIdx.x / kXcds : (int)blockIdx.x; li < per * nzl; li += lstep) {
-        const int zc = xcd + zmul * (li / per), rest = li % per;
-        const int cx = rest % cl.ncx, cy = rest / cl.ncx, z0 = zc * cl.chunk;
-        const int x0 = cx * PX, y0 = cy * PY, z1 = min(z0 + cl.chunk, g.nz);
+    for (int li = mi.li; li < mi.count; li += mi.step) {
+        const MarchItem it = march_item(mi, li, cl);
+        const int x0 = it.cx * PX, y0 = it.cy * PY, z0 = it.zc * CH;
         const int xx = x0 + 16 * wv + n, yy = y0 + gq;
         const bool col = xx < g.nx && yy < g.ny;
-        if (izero[zc * per + rest]) {   // no window holds fluid: x1 is zero (read nowhere), and so is the pool
+        if (izero[it.zc * mi.per + it.rest]) {   // no window holds fluid: x1 is zero (read nowhere), and so is the pool
             if (done) return;
-            for (int c = z0 + 1; c < z1; c += 2)
-                if (((n | gq) & 1) == 0 && col) rnext[cell_index(gc, c >> 1, yy >> 1, xx >> 1)] = 0.0f;
+#pragma unroll
+            for (int i = 1; i < CH; i += 2)
+                if (((n | gq) & 1) == 0 && col && z0 + i < g.nz)
+                    rnext[cell_index(gc, (z0 + i) >> 1, yy >> 1, xx >> 1)] = 0.0f;
             continue;
         }
-        const uint32_t* mrow = gmode + ((size_t)cy * cl.ncx + cx) * 4 + wv;   // + z * ncy * ncx * 4 words
-        const size_t mstride = (size_t)cl.ncy * cl.ncx * 4;
-        const uint32_t own_off = col ? (uint32_t)yy * g.nx + xx : 0u;
-        se = stage_elems(g, x0, y0);
-        // planes are loaded two steps ahead of their staging
-        auto preA = plane(z0 - 1);
-        auto preB = plane(z0);
+        const int tid = item_thread();
+        uint32_t modes[CH];
+        load_modes<CH>(gmode, cl, it, g.nz, modes);
+        uint32_t lw[S::K];
+        float4 rw[S::K];
+#pragma unroll
+        for (int k = 0; k < S::K; ++k) {
+            if (S::quads(wv, k)) {
+                const StagePos s = stage_pos<CH, XO, true>(g, x0, y0, z0, tid + k * kBlock);
+                rw[k] = stage_values<true>(r, s, wide);
+                lw[k] = stage_labels<true>(lab, s, wide);
+            } else if (S::edges(wv, k)) {
+                const StagePos s = stage_pos<CH, XO, false>(g, x0, y0, z0, tid + k * kBlock);
+                rw[k] = stage_values<false>(r, s, wide);
+                lw[k] = stage_labels<false>(lab, s, wide);
+            }
+        }
         if (first) {
             __asm__ volatile("" ::: "memory");   // the loads stay above the test
             if (done) return;
             first = false;
+        } else {
+            __syncthreads();   // the previous item's reads of the records are done
         }
-        __syncthreads();   // the previous footprint's reads of the ring are done
+#pragma unroll
+        for (int k = 0; k < S::K; ++k) {
+            const float v[4] = {rw[k].x, rw[k].y, rw[k].z, rw[k].w};
+            auto record = [&](int j) {
+                const uint32_t l = (lw[k] >> (8 * j)) & 255u;
+                return uint2{bits(l == kFluid ? v[j] : 0.0f), feat_word<KM, true>(l)};
+            };
+            if (S::quads(wv, k)) {
+                const uint2 e0 = record(0), e1 = record(1), e2 = record(2), e3 = record(3);
+                uint4* dst = reinterpret_cast<uint4*>(rec + stage_pos<CH, XO, true>(g, x0, y0, z0, tid + k * kBlock).rec);
+                dst[0] = uint4{e0.x, e0.y, e1.x, e1.y};
+                dst[1] = uint4{e2.x, e2.y, e3.x, e3.y};
+            } else if (S::edges(wv, k)) {   // lanes past the last task repeat it
+                rec[stage_pos<CH, XO, false>(g, x0, y0, z0, tid + k * kBlock).rec] = record(0);
+            }
+        }
+        __syncthreads();   // the item is staged
+        float out[CH];
+        march_cconv<KM, XO, CH>(rec, modes, mc, w, out);
+        const uint32_t own = col ? (uint32_t)z0 * pstride + (uint32_t)yy * g.nx + xx : 0u;
         float pool = 0.0f;
-        auto step = [&](int s, auto& pre) {
-            uint2* buf = ring + (s & 3) * kPlaneP;
-            put_batch(pre, [&](int i, RLab e) { buf[i] = march_record<KM>(e.r, e.l); });
-            if (s + 2 <= z1) pre = plane(s + 2);
-            const int c = s - 1;
-            const uint32_t modes = c >= z0 ? __builtin_amdgcn_readfirstlane(mrow[(size_t)c * mstride]) : 0u;
-            __syncthreads();   // plane s is staged
-            if (c < z0) return;
-            const float out = march_cconv<KM>(ring, c, modes, mc);
-            if (col) x1[(size_t)c * pstride + own_off] = out;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const bool zin = z0 + i < g.nz;
+            if (col && zin) x1[(size_t)own + (size_t)i * pstride] = out[i];
             // 2x2x2 pool: x pair (DPP quad_perm [1,0,3,2]), y pair (rows 2k, 2k+1)
-            const float px = out + fbits(__builtin_amdgcn_update_dpp(0u, bits(out), 0xB1, 0xF, 0xF, false));
+            const float px = out[i] + fbits(__builtin_amdgcn_update_dpp(0u, bits(out[i]), 0xB1, 0xF, 0xF, false));
             const auto t = __builtin_amdgcn_permlane16_swap(bits(px), bits(px), false, false);
             pool += fbits(t[0]) + fbits(t[1]);
-            if (c & 1) {
-                if (((n | gq) & 1) == 0 && col)
-                    rnext[cell_index(gc, c >> 1, yy >> 1, xx >> 1)] = pool * 0.125f;
+            if (i & 1) {
+                if (((n | gq) & 1) == 0 && col && zin)
+                    rnext[cell_index(gc, (z0 + i) >> 1, yy >> 1, xx >> 1)] = pool * 0.125f;
                 pool = 0.0f;
             }
-        };
-        // z1 - z0 is even, so the steps z0 - 1 .. z1 come in pairs
-        for (int s = z0 - 1; s <= z1; s += 2) {
-            step(s, preA);
-            step(s + 1, preB);
         }
     }
 }
 
 // Level-1 up: dhat = (c1 x1 + c2 CConv_2^1(Interp(x^2))) / ||r|| on fluid
 // cells (0 elsewhere) and the state's ndots partial dots of dhat with ad0..
-// The interpolation (trilinear, cell-centred, edges clamped) is formed while
-// staging each fine plane, from the two coarse planes it lies between, kept
-// in a ring of three LDS planes of 34 x 4 coarse cells (the footprint's
-// coarse cells with a one-cell border, coordinates clamped into the coarse
-// grid, which is the interpolation's edge rule).
+// The coarse cells the item interpolates from (coordinates clamped into the
+// coarse grid, which is the interpolation's edge rule) are staged first, with
+// the labels' features.  The trilinear interpolation (cell-centred, edges
+// clamped) then runs per octet: the 2x2x2 coarse cells (j - 1, j) along each
+// axis give the 2x2x2 fine cells (2j - 1, 2j), whose weights along an axis are
+// (3/4, 1/4) and (1/4, 3/4); shared along x, y and z that is 4.5 operations
+// and one LDS read per fine cell (formed cell by cell: 14 and 8).
 constexpr int kCX = PX / 2 + 2, kCY = PY / 2 + 2, kCPlane = kCX * kCY;
-static_assert(kCPlane <= kBlock, "one coarse cell per thread");
+template <int CH>
+constexpr int kCoarseCells = (CH / 2 + 2) * kCPlane;
+template <int CH>
+constexpr int kOctets = (CH / 2 + 1) * (PY / 2 + 1) * (PX / 2 + 1);
 
-template <int ND>
-struct UpCell {   // operands of the lane's own cell for one output plane
-    float x1;
-    float ad[ND > 0 ? ND : 1];
-};
+// The pair of fine values between coarse values lo and hi: 3/4 lo + 1/4 hi, 1/4 lo + 3/4 hi.
+__device__ __forceinline__ void interp_pair(float lo, float hi, float& a, float& b) {
+    const float d = hi - lo;
+    a = fmaf(0.25f, d, lo);
+    b = fmaf(-0.25f, d, hi);
+}
 
 // ND: the most dots the state can ask for (NPSDO: n_ortho; PCG 1; flexible
 // PCG 2; 0 for the hook and the symmetric variant); HOOK: the parity hook
 // (no scaling, no dots).
-template <int KM, bool HOOK, int ND>
-__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(KM == kMfmaBf16x3 ? 3 : 4) void k_up_l1m(const uint8_t* __restrict__ lab, Grid g,
-                                                   const float* __restrict__ xc, const float* __restrict__ x1,
-                                                   float* __restrict__ dhat, const CConvW<float>* __restrict__ w,
-                                                   const MfmaW* __restrict__ wm, const State* st,
-                                                   double* __restrict__ partials, const float* __restrict__ ad0,
-                                                   const float* __restrict__ ad1, const float* __restrict__ ad2,
-                                                   const float* __restrict__ ad3, const uint32_t* __restrict__ gmode,
-                                                   const uint8_t* __restrict__ izero) {
+template <int KM, bool HOOK, int ND, int CH>
+__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, ND)) void k_up_l1m(
+    const uint8_t* __restrict__ lab, Grid g, const float* __restrict__ xc, const float* __restrict__ x1,
+    float* __restrict__ dhat, const CConvW<float>* __restrict__ w, const MfmaW* __restrict__ wm, const State* st,
+    double* __restrict__ partials, const float* __restrict__ ad0, const float* __restrict__ ad1,
+    const float* __restrict__ ad2, const float* __restrict__ ad3, const uint32_t* __restrict__ gmode,
+    const uint8_t* __restrict__ izero, int wide) {
     static_assert(!HOOK || ND == 0, "the hook forms no dots");
-    __shared__ uint2 ring[4 * kPlaneP];
-    __shared__ float csh[3][kCPlane];
+    constexpr int XO = 1;
+    using S = StageTasks<CH>;
+    constexpr int KC = (kCoarseCells<CH> + kBlock - 1) / kBlock, KO = (kOctets<CH> + kBlock - 1) / kBlock;
+    __shared__ __attribute__((aligned(16))) uint2 rec[kRecords<CH>];
+    __shared__ float csh[KC * kBlock];
     const int done = st->done;
     const float c1 = (float)st->c1[0], c2 = (float)st->c2[0];
     const float scale = HOOK ? 1.0f : (float)st->scale;
     const int ndots = HOOK || st->sym ? 0 : min(st->ndots, ND);   // the symmetric variant dots after P^T
-    const MarchCtx<KM> mc = march_ctx<KM>(wm, w);
+    const MarchCtx<KM> mc = march_ctx<KM, XO>(wm);
     const Columns cl = march_columns(g);
     const Grid gc = coarser(g);
     const int lane = threadIdx.x & 63, gq = lane >> 4, n = lane & 15;
@@ -413,147 +542,120 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(KM == kMfmaBf16x3 ? 3 : 4)
     const float* adp[kMaxOrtho] = {ad0, ad1, ad2, ad3};
     const uint32_t fluid_word = feat_word<KM, true>(kFluid);
     double v[kRedWidth] = {0.0, 0.0, 0.0, 0.0};
-    const uint32_t pstride = (uint32_t)g.ny * (uint32_t)g.nx, cstride = (uint32_t)gc.ny * (uint32_t)gc.nx;
-    StageElems se;
-    // per staged element: its four coarse cells (rows ly, lyn x columns lx, lxn of
-    // the staged coarse block, one byte each), formed once per footprint
-    uint32_t ipos[StageElems::K];
-    uint32_t coff = 0;   // the thread's coarse cell (jy, jx) of the staged block, clamped
-    // staged element i of a plane: fine (y0 - 1 + i / PHX, x0 - 1 + i % PHX)
-    auto labels = [&](int zz) {
-        Batch<kPlane, uint8_t> bt;
-        const bool zin = zz >= 0 && zz < g.nz;
-        const uint32_t base = zin ? (uint32_t)zz * pstride : 0u;
-#pragma unroll
-        for (int k = 0; k < StageElems::K; ++k) {
-            const bool in = zin && se.in[k];
-            bt.v[k] = *at_or(lab, (size_t)base + se.off[k], in, g_pad_solid);
-        }
-        return bt;
-    };
-    // coarse plane m (clamped) of the footprint
-    auto coarse = [&](int m) {
-        const int jz = min(max(m, 0), gc.nz - 1);
-        return xc[(size_t)jz * cstride + coff];
-    };
-    auto put_coarse = [&](int m, float val) {
-        if (threadIdx.x < kCPlane) csh[(m + 3) % 3][threadIdx.x] = val;
-    };
-    // the lane cell's operands of output plane zz (an unused dot slot reads x1)
-    auto cell_ops = [&](int zz, uint32_t own_off) {
-        const size_t q = (size_t)zz * pstride + own_off;
-        UpCell<ND> u;
-        u.x1 = x1[q];
-#pragma unroll
-        for (int j = 0; j < ND; ++j) u.ad[j] = (j < ndots ? adp[j] : x1)[q];
-        return u;
-    };
+    const uint32_t pstride = (uint32_t)g.ny * (uint32_t)g.nx;
+    const MarchItems mi = march_items(cl);
     bool first = true;
-    const bool xs = gridDim.x % kXcds == 0;
-    const int xcd = xs ? (int)(blockIdx.x % kXcds) : 0, lstep = xs ? (int)gridDim.x / kXcds : (int)gridDim.x;
-    const int per = cl.ncx * cl.ncy, nzl = xs ? (cl.ncz - xcd + kXcds - 1) / kXcds : cl.ncz, zmul = xs ? kXcds : 1;
-    for (int li = xs ? (int)blockIdx.x / kXcds : (int)blockIdx.x; li < per * nzl; li += lstep) {
-        const int zc = xcd + zmul * (li / per), rest = li % per;
-        const int cx = rest % cl.ncx, cy = rest / cl.ncx, z0 = zc * cl.chunk;
-        const int x0 = cx * PX, y0 = cy * PY, z1 = min(z0 + cl.chunk, g.nz);
+    for (int li = mi.li; li < mi.count; li += mi.step) {
+        const MarchItem it = march_item(mi, li, cl);
+        const int x0 = it.cx * PX, y0 = it.cy * PY, z0 = it.zc * CH;
         const int xx = x0 + 16 * wv + n, yy = y0 + gq;
         const bool col = xx < g.nx && yy < g.ny;
-        if (izero[zc * per + rest]) {   // no fluid cell: the output is zero, the dots get nothing
+        const uint32_t own = col ? (uint32_t)z0 * pstride + (uint32_t)yy * g.nx + xx : 0u;
+        if (izero[it.zc * mi.per + it.rest]) {   // no fluid cell: the output is zero, the dots get nothing
             if (done) return;
-            if (col)
-                for (int c = z0; c < z1; ++c) dhat[(size_t)c * pstride + (uint32_t)yy * g.nx + xx] = 0.0f;
+#pragma unroll
+            for (int i = 0; i < CH; ++i)
+                if (col && z0 + i < g.nz) dhat[(size_t)own + (size_t)i * pstride] = 0.0f;
             continue;
         }
-        const int own = (gq + 1) * PHX + 16 * wv + n + 1;
-        const uint32_t own_off = col ? (uint32_t)yy * g.nx + xx : 0u;
-        const uint32_t* mrow = gmode + ((size_t)cy * cl.ncx + cx) * 4 + wv;
-        const size_t mstride = (size_t)cl.ncy * cl.ncx * 4;
-        const int m0 = z0 / 2;
-        se = stage_elems(g, x0, y0);
-        {
-            const int i = min((int)threadIdx.x, kCPlane - 1);
-            const int jy = min(max(y0 / 2 - 1 + i / kCX, 0), gc.ny - 1), jx = min(max(x0 / 2 - 1 + i % kCX, 0), gc.nx - 1);
-            coff = (uint32_t)jy * gc.nx + jx;
-        }
+        const int tid = item_thread();
+        uint32_t modes[CH];
+        load_modes<CH>(gmode, cl, it, g.nz, modes);
+        float cw[KC];
 #pragma unroll
-        for (int k = 0; k < StageElems::K; ++k) {
-            // along each axis the own coarse cell f >> 1 (weight 3/4) and its
-            // neighbour on f's side (1/4), as indices into the staged block
-            const int i = min((int)threadIdx.x + k * kBlock, kPlane - 1);
-            const int fy = y0 + i / PHX - 1, fx = x0 + i % PHX - 1;
-            const int ly = (fy >> 1) - (y0 / 2 - 1), lyn = (fy & 1) ? ly + 1 : ly - 1;
-            const int lx = (fx >> 1) - (x0 / 2 - 1), lxn = (fx & 1) ? lx + 1 : lx - 1;
-            ipos[k] = se.in[k] ? (uint32_t)(ly * kCX + lx) | (uint32_t)(ly * kCX + lxn) << 8 |
-                                     (uint32_t)(lyn * kCX + lx) << 16 | (uint32_t)(lyn * kCX + lxn) << 24
-                               : 0u;
+        for (int k = 0; k < KC; ++k) {
+            const int i = min(tid + k * kBlock, kCoarseCells<CH> - 1);
+            const int jz = min(max(z0 / 2 - 1 + i / kCPlane, 0), gc.nz - 1),
+                      jy = min(max(y0 / 2 - 1 + i / kCX % kCY, 0), gc.ny - 1),
+                      jx = min(max(x0 / 2 - 1 + i % kCX, 0), gc.nx - 1);
+            cw[k] = xc[cell_index(gc, jz, jy, jx)];
         }
-        // loads run two steps ahead: fine-plane labels, the coarse plane the
-        // next even step writes, the cell operands of the plane a step computes
-        const float cm0 = coarse(m0 - 1), cm1 = coarse(m0);
-        float cpre = coarse(m0 + 1);
-        auto lA = labels(z0 - 1);
-        auto lB = labels(z0);
-        UpCell<ND> oA, oB;
+        uint32_t lw[S::K];
+#pragma unroll
+        for (int k = 0; k < S::K; ++k) {
+            if (S::quads(wv, k))
+                lw[k] = stage_labels<true>(lab, stage_pos<CH, XO, true>(g, x0, y0, z0, tid + k * kBlock), wide);
+            else if (S::edges(wv, k))
+                lw[k] = stage_labels<false>(lab, stage_pos<CH, XO, false>(g, x0, y0, z0, tid + k * kBlock), wide);
+        }
         if (first) {
             __asm__ volatile("" ::: "memory");
             if (done) return;
             first = false;
+        } else {
+            __syncthreads();   // the previous item's reads of the records are done
         }
-        __syncthreads();   // the previous footprint's reads of the ring and the coarse planes are done
-        put_coarse(m0 - 1, cm0);
-        put_coarse(m0, cm1);
-        __syncthreads();
-        auto step = [&](int s, auto& lpre, UpCell<ND>& ops) {
-            // stage fine plane s: interpolation from coarse planes s >> 1 and its neighbour on s's side
-            uint2* buf = ring + (s & 3) * kPlaneP;
-            const bool zin = s >= 0 && s < g.nz;
-            const int jz = s >> 1, jzn = (s & 1) ? jz + 1 : jz - 1;   // virtual planes, clamped when staged
-            const float* cz0 = csh[(jz + 3) % 3];
-            const float* cz1 = csh[(jzn + 3) % 3];
 #pragma unroll
-            for (int k = 0; k < StageElems::K; ++k) {
-                const int i = threadIdx.x + k * kBlock;
-                float val = 0.0f;
-                if (zin && se.in[k] && i < kPlane) {
-                    const uint32_t w = ipos[k];
-                    const int a00 = w & 255, a01 = (w >> 8) & 255, a10 = (w >> 16) & 255, a11 = w >> 24;
-                    auto bil = [&](const float* p) {
-                        const float a = fmaf(0.25f, p[a01] - p[a00], p[a00]);
-                        const float b = fmaf(0.25f, p[a11] - p[a10], p[a10]);
-                        return fmaf(0.25f, b - a, a);
-                    };
-                    const float v0 = bil(cz0), v1 = bil(cz1);
-                    val = fmaf(0.25f, v1 - v0, v0);
-                }
-                // the CConv_2 input is not masked (only the level's output is)
-                buf[i] = uint2{bits(val), feat_word<KM, true>(lpre.v[k])};
-            }
-            // an even step writes coarse plane (s >> 1) + 1, which the odd fine plane s + 1 needs
-            if (!(s & 1) && s < z1) {
-                put_coarse((s >> 1) + 1, cpre);
-                if (s + 2 < z1) cpre = coarse((s >> 1) + 2);
-            }
-            if (s + 2 <= z1) lpre = labels(s + 2);
-            const int c = s - 1;
-            const uint32_t modes = c >= z0 ? __builtin_amdgcn_readfirstlane(mrow[(size_t)c * mstride]) : 0u;
-            __syncthreads();   // plane s (and the coarse plane) staged
-            if (c >= z0) {
-                const float x2 = march_cconv<KM>(ring, c, modes, mc);
-                const bool fl = ring[(c & 3) * kPlaneP + own].y == fluid_word;
-                const float out = fl ? (c1 * ops.x1 + c2 * x2) * scale : 0.0f;
-                if (col) {
-                    dhat[(size_t)c * pstride + own_off] = out;
+        for (int k = 0; k < KC; ++k) csh[tid + k * kBlock] = cw[k];
 #pragma unroll
-                    for (int j = 0; j < ND; ++j)
-                        if (j < ndots) v[j] = fma((double)out, (double)ops.ad[j], v[j]);
-                }
+        for (int k = 0; k < S::K; ++k) {
+            if (S::quads(wv, k)) {
+                uint2* dst = rec + stage_pos<CH, XO, true>(g, x0, y0, z0, tid + k * kBlock).rec;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) dst[j].y = feat_word<KM, true>((lw[k] >> (8 * j)) & 255u);
+            } else if (S::edges(wv, k)) {   // lanes past the last task repeat it
+                rec[stage_pos<CH, XO, false>(g, x0, y0, z0, tid + k * kBlock).rec].y = feat_word<KM, true>(lw[k]);
             }
-            if (s + 1 < z1) ops = cell_ops(s + 1, own_off);   // plane s + 1, formed at step s + 2
-        };
-        // z1 - z0 is even, so the steps z0 - 1 .. z1 come in pairs
-        for (int s = z0 - 1; s <= z1; s += 2) {
-            step(s, lA, oA);
-            step(s + 1, lB, oB);
+        }
+        __syncthreads();   // coarse cells and features staged
+#pragma unroll
+        for (int k = 0; k < KO; ++k) {
+            const int o = tid + k * kBlock;
+            if (o < kOctets<CH>) {
+                constexpr int OX = PX / 2 + 1, OY = PY / 2 + 1;
+                const int ox = o % OX, oy = o / OX % OY, oz = o / (OX * OY);
+                const float* c = csh + (oz * kCY + oy) * kCX + ox;   // coarse cell (j - 1) of each axis
+                float f[2][2][2], fy[2][2][2];
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+                        interp_pair(c[(a * kCY + b) * kCX], c[(a * kCY + b) * kCX + 1], f[a][b][0], f[a][b][1]);
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) interp_pair(f[a][0][x], f[a][1][x], fy[a][0][x], fy[a][1][x]);
+#pragma unroll
+                for (int b = 0; b < 2; ++b)
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) interp_pair(fy[0][b][x], fy[1][b][x], f[0][b][x], f[1][b][x]);
+                // the CConv_2 input is zero outside the grid and not masked inside (only the level's output is)
+                const int fz = z0 + 2 * oz - 1, fyy = y0 + 2 * oy - 1, fx = x0 + 2 * ox - 1;
+                const bool xin[2] = {fx >= 0 && fx < g.nx, fx + 1 < g.nx};
+                uint2* dst = rec + (2 * oz * PHY + 2 * oy) * kRS + 2 * ox;
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        const bool yz = fz + a >= 0 && fz + a < g.nz && fyy + b >= 0 && fyy + b < g.ny;
+#pragma unroll
+                        for (int x = 0; x < 2; ++x)
+                            dst[(a * PHY + b) * kRS + x].x = bits(yz && xin[x] ? f[a][b][x] : 0.0f);
+                    }
+            }
+        }
+        // the lane cell's operands (an unused dot slot reads x1; planes past the grid read the first)
+        float x1v[CH], adv[CH][ND > 0 ? ND : 1];
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const size_t q = (size_t)own + (z0 + i < g.nz ? (size_t)i * pstride : 0);
+            x1v[i] = x1[q];
+#pragma unroll
+            for (int j = 0; j < ND; ++j) adv[i][j] = (j < ndots ? adp[j] : x1)[q];
+        }
+        __syncthreads();   // the item is staged
+        float x2[CH];
+        march_cconv<KM, XO, CH>(rec, modes, mc, w, x2);
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const bool fl = rec[((i + 1) * PHY + gq + 1) * kRS + 16 * wv + n + XO].y == fluid_word;
+            const float out = fl ? (c1 * x1v[i] + c2 * x2[i]) * scale : 0.0f;
+            if (col && z0 + i < g.nz) {
+                dhat[(size_t)own + (size_t)i * pstride] = out;
+#pragma unroll
+                for (int j = 0; j < ND; ++j)
+                    if (j < ndots) v[j] = fma((double)out, (double)adv[i][j], v[j]);
+            }
         }
     }
     if (!HOOK && !done) block_partials<kBlock>(v, partials);

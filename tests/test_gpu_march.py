@@ -1,0 +1,89 @@
+"""Level-1 network kernels of the float modes (GPU): one work item of 64 x 4
+columns over 4 or 2 z-planes at a time, staged four cells at once where rows of
+four are aligned, cell by cell elsewhere.
+
+The FP64 path (tile kernels, matched to the oracle at 1e-12 elsewhere) is the
+reference: the float modes' bars are the repository's (FP32 1e-5 in norm and per
+cell, mixed as in the parity tests).  Scenes of boxes give groups of every kind:
+without fluid, inside the fluid (the constant kernel) and at interfaces."""
+import numpy as np
+import pytest
+import torch
+
+import nps_inputs as gi
+
+pytestmark = pytest.mark.gpu
+
+nps = pytest.importorskip("paper_2310_00177_amd")
+
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+
+def box_labels(shape, seed, boxes=12):
+    """Fluid below an air layer, with solid and air boxes of random extent (some against the faces)."""
+    rng = np.random.default_rng(seed)
+    lab = np.zeros(shape, dtype=np.uint8)
+    lab[3 * shape[0] // 4:] = gi.AIR
+    for i in range(boxes):
+        lo = [int(rng.integers(0, n)) for n in shape]
+        hi = [min(n, at + int(rng.integers(1, max(2, n // 4)))) for n, at in zip(shape, lo)]
+        lab[lo[0]:hi[0], lo[1]:hi[1], lo[2]:hi[2]] = gi.SOLID if i % 2 else gi.AIR
+    return lab
+
+
+def blob(levels, seed):
+    rng = np.random.default_rng(seed)
+    p = gi.xavier_params(levels, seed)
+    for name, _, off, size in gi.blob_layout(levels):
+        if name.endswith("B"):
+            p[off:off + size] = 0.1 * rng.standard_normal(size)
+    return p
+
+
+def offset_copy(a, off):
+    """The same values `off` elements past an aligned address."""
+    buf = torch.empty(a.numel() + 16, dtype=a.dtype, device="cuda")
+    v = buf[off:off + a.numel()].view(a.shape)
+    v.copy_(a)
+    return v
+
+
+# 2-plane items: a footprint of 6 columns behind a whole one, rows not of four cells,
+# a last row of 2; 4-plane items (from 1024 on): a last chunk of 2 planes, a last
+# footprint of 4 columns, a last row of 2; rows that are whole footprints.
+SHAPES = [(34, 38, 70), (36, 32, 64), (70, 62, 260), (66, 66, 254), (64, 64, 256)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("precision,bar", [("FP32", 1e-5), ("MIXED_BF16", 8e-3), ("MIXED_FP16", 8e-4)])
+def test_items_match_fp64(shape, precision, bar):
+    lab = torch.from_numpy(box_labels(shape, sum(shape))).cuda()
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    r = torch.randn(shape, generator=gen, device="cuda", dtype=torch.float64)
+    net = nps.Net(blob(2, 7), 2)
+    ref = nps.apply_precond(net, lab, r)
+    got = nps.apply_precond(net, lab, r.float(), precision=getattr(nps, precision))
+    err = (got.double() - ref).abs()
+    assert float(torch.linalg.norm(err) / torch.linalg.norm(ref)) < bar
+    assert float(err.max()) < bar * float(ref.abs().max())
+    # rows that cannot be read four cells at once give the same bits
+    for lo, ro in ((1, 0), (0, 1), (2, 2)):
+        again = nps.apply_precond(net, offset_copy(lab, lo), offset_copy(r.float(), ro),
+                                  precision=getattr(nps, precision))
+        assert torch.equal(again, got), (lo, ro)
+
+
+@pytest.mark.parametrize("n_ortho", [0, 1, 2, 3, 4])
+def test_dots_of_every_width(n_ortho):
+    """The float up kernel forms n_ortho dots; its iterates follow FP64's (the bar of the
+    ragged-footprint tests, 1e-4)."""
+    shape = (34, 38, 70)
+    lab = torch.from_numpy(box_labels(shape, 3)).cuda()
+    b = torch.from_numpy(gi.gen_rhs(lab.cpu().numpy(), seed=4)).cuda()
+    net = nps.Net(gi.multilevel_params(2), 2)
+    kw = dict(max_iter=6, fixed_iters=True, n_ortho=n_ortho)
+    ref, _ = nps.solve(net, lab, b, precision=nps.FP64, **kw)
+    got, info = nps.solve(net, lab, b, precision=nps.FP32, **kw)
+    assert info.iterations == 6
+    assert float(torch.linalg.norm(got - ref) / torch.linalg.norm(ref)) < 1e-4

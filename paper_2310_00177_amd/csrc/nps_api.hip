@@ -213,15 +213,12 @@ Layout make_layout(nps_dims d, int levels, int precision, int n_ortho, bool solv
 struct TrainLayout {
     Layout base;                 // state, partials, counts, x1, rb (= down inputs), stored K
     size_t xup[kMaxLevels + 1], x2[kMaxLevels + 1];
-    size_t gx[kMaxLevels + 1], gx1[kMaxLevels + 1], gr1[kMaxLevels + 1], gr2[kMaxLevels + 1];
-    size_t wpart, spart, dc, res;
+    size_t gx[kMaxLevels + 1], gr1[kMaxLevels + 1], gr2[kMaxLevels + 1];
+    size_t wpart, dc[kMaxLevels + 1], res;
     size_t y, gy, lacc;          // the batch step: network output, its loss gradient, the loss sum
     size_t dsym;                 // solve with P^T o P: the direction after P^T
     size_t total;
 };
-
-constexpr int kSumBlocks = 1024;  // most blocks of k_image_sums (five per CU fit)
-int sum_blocks(Grid g) { return (int)std::min<size_t>(kSumBlocks, std::max<size_t>((ncells(g) + kBlock - 1) / kBlock, 1)); }
 
 TrainLayout make_train_layout(nps_dims d, int levels, int precision, bool solve = false, int n_ortho = 0) {
     TrainLayout t = {};
@@ -238,7 +235,7 @@ TrainLayout make_train_layout(nps_dims d, int levels, int precision, bool solve 
         if (l >= 2 && l < levels) t.xup[l] = put(s * nl);
         if (l < levels) {
             t.x2[l] = put(s * nl);
-            t.gx1[l] = put(s * nl);
+            t.dc[l] = put(sizeof(double) * 2 * kMaxRedBlocks);
             t.gr2[l] = put(s * nl);
         }
         if (l >= 2) {
@@ -246,9 +243,7 @@ TrainLayout make_train_layout(nps_dims d, int levels, int precision, bool solve 
             t.gr1[l] = put(s * nl);
         }
     }
-    t.wpart = put(sizeof(double) * kWPart * kTrainBlocks);
-    t.spart = put(sizeof(double) * 3 * kTaps * kSumBlocks * levels);
-    t.dc = put(sizeof(double) * 2 * levels);
+    t.wpart = put(sizeof(double) * kWPart * kWRows);
     t.res = put(s * ncells(level_grid(d, 1)));
     t.y = put(s * ncells(level_grid(d, 1)));
     t.gy = put(s * ncells(level_grid(d, 1)));
@@ -807,59 +802,64 @@ int run_up_l1(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
     });
 }
 
-// y = P^T g, the adjoint of the network in its input vector (P is linear in
-// it): Alg. 2 backwards with each linear step replaced by its adjoint, on
-// the stored kernels of every level (the setup of the layout tl must have
-// run).  g and y are level-1 vectors; tl's gradient buffers are scratch.
+// The adjoint sweep: Alg. 2 backwards with each linear step replaced by its
+// adjoint, on the stored kernels of every level (the setup of the layout tl
+// must have run).  g_in: gradient of the network's output (level 1).  With y,
+// y = P^T g_in (P is linear in its input vector); in training (dcparts: the
+// partials per level of dL/dc1, dL/dc2, left in tl.dc) the sweep ends at level 2.
 template <class T>
-int adjoint_apply(const nps_net* net, const uint8_t* labels, nps_dims d, const TrainLayout& tl, void* ws,
-                  const T* g_in, T* y, hipStream_t s) {
+int adjoint_sweep(const nps_net* net, const uint8_t* labels, nps_dims d, const TrainLayout& tl, void* ws,
+                  const T* g_in, T* y, int* dcparts, hipStream_t s) {
     const int L = net->levels;
     const Layout& lay = tl.base;
     const State* st = cptr<State>(ws, lay.state);
-    auto img = [&](int l) -> const void* {
-        return l == 1 ? static_cast<const void*>(labels) : static_cast<const void*>(cptr<uint32_t>(ws, lay.counts[l]));
-    };
     for (int l = 1; l < L; ++l) {   // up sweep, reversed
         const Grid g = level_grid(d, l);
-        const int grid = tile_grid(g);
         const T* gin = l == 1 ? g_in : cptr<T>(ws, tl.gx[l]);
         const T* k2 = cptr<T>(ws, lay.k2[l]);
-        T* gx1 = mptr<T>(ws, tl.gx1[l]);
+        const T* x1 = dcparts ? cptr<T>(ws, lay.x1[l]) : nullptr;
+        const T* x2 = dcparts ? cptr<T>(ws, tl.x2[l]) : nullptr;
         T* gr2 = mptr<T>(ws, tl.gr2[l]);
-        if (l == 1)
-            NPS_TRY(launch("adj_up", (double)ncells(g), s, [&] {
-                k_bwd_up<T, true, false><<<grid, kBlock, 0, s>>>(img(l), g, gin, nullptr, nullptr, nullptr, k2, st, l - 1,
-                                                                 gx1, gr2, nullptr);
-            }));
-        else
-            NPS_TRY(launch("adj_up", (double)ncells(g), s, [&] {
-                k_bwd_up<T, false, false><<<grid, kBlock, 0, s>>>(img(l), g, gin, nullptr, nullptr, nullptr, k2, st, l - 1,
-                                                                  gx1, gr2, nullptr);
-            }));
+        double* part = mptr<double>(ws, tl.dc[l]);
+        auto up = [&](auto l1) {
+            constexpr bool L1 = decltype(l1)::value;
+            const int grid = persist_grid(&k_adj<T, L1, true>, g);
+            if (dcparts) dcparts[l] = grid;
+            return launch("adj_up", (double)ncells(g), s, [&] {
+                k_adj<T, L1, true><<<grid, kBlock, 0, s>>>(labels, g, gin, nullptr, k2, st, l - 1, x1, x2, gr2, part);
+            });
+        };
+        NPS_TRY(l == 1 ? up(std::true_type{}) : up(std::false_type{}));
         const Grid gc = level_grid(d, l + 1);
         T* gxc = mptr<T>(ws, tl.gx[l + 1]);
         NPS_TRY(launch("adj_interp", (double)ncells(gc), s, [&] {
-            k_bwd_interp<T><<<elem_grid(ncells(gc)), kBlock, 0, s>>>(gc, gr2, gxc);
+            k_adj_interp<T><<<elem_grid(ncells(gc)), kBlock, 0, s>>>(gc, gr2, gxc);
         }));
     }
-    for (int l = L; l >= 1; --l) {   // down sweep, reversed (the coarsest output gradient is gx^L)
+    for (int l = L; l >= (y ? 1 : 2); --l) {   // down sweep, reversed
         const Grid g = level_grid(d, l);
-        const int grid = tile_grid(g);
-        const T* gx1 = l == L ? cptr<T>(ws, tl.gx[L]) : cptr<T>(ws, tl.gx1[l]);
-        const T* gr_next = l < L ? cptr<T>(ws, tl.gr1[l + 1]) : nullptr;
+        const T* gx = l == 1 ? g_in : cptr<T>(ws, tl.gx[l]);
+        const T* gnext = l < L ? cptr<T>(ws, tl.gr1[l + 1]) : nullptr;
         const T* k1 = cptr<T>(ws, lay.k1[l]);
         T* gr1 = l > 1 ? mptr<T>(ws, tl.gr1[l]) : y;
-        if (l == 1)
-            NPS_TRY(launch("adj_down", (double)ncells(g), s, [&] {
-                k_bwd_down<T, true, false><<<grid, kBlock, 0, s>>>(img(l), g, gx1, gr_next, nullptr, k1, gr1, nullptr);
-            }));
-        else
-            NPS_TRY(launch("adj_down", (double)ncells(g), s, [&] {
-                k_bwd_down<T, false, false><<<grid, kBlock, 0, s>>>(img(l), g, gx1, gr_next, nullptr, k1, gr1, nullptr);
-            }));
+        auto down = [&](auto l1) {
+            constexpr bool L1 = decltype(l1)::value;
+            const int grid = persist_grid(&k_adj<T, L1, false>, g);
+            return launch("adj_down", (double)ncells(g), s, [&] {
+                k_adj<T, L1, false><<<grid, kBlock, 0, s>>>(labels, g, gx, gnext, k1, st, l < L ? l - 1 : -1, nullptr,
+                                                            nullptr, gr1, nullptr);
+            });
+        };
+        NPS_TRY(l == 1 ? down(std::true_type{}) : down(std::false_type{}));
     }
     return NPS_OK;
+}
+
+// y = P^T g.
+template <class T>
+int adjoint_apply(const nps_net* net, const uint8_t* labels, nps_dims d, const TrainLayout& tl, void* ws,
+                  const T* g_in, T* y, hipStream_t s) {
+    return adjoint_sweep<T>(net, labels, d, tl, ws, g_in, y, nullptr, s);
 }
 
 int check_opts(const nps_opts& o) {
@@ -1476,15 +1476,6 @@ int train_forward(const nps_net* net, const uint8_t* labels, nps_dims d, const T
     auto img = [&](int l) -> const void* {
         return l == 1 ? static_cast<const void*>(labels) : static_cast<const void*>(cptr<uint32_t>(ws, lay.counts[l]));
     };
-    for (int l = 1; l < L; ++l) {   // image-window sums for the Aff gradients
-        const Grid g = level_grid(d, l);
-        double* sp = mptr<double>(ws, tl.spart) + (size_t)(l - 1) * 3 * kTaps * kSumBlocks;
-        const double inv_full = std::ldexp(1.0, -3 * (l - 1));
-        if (l == 1)
-            NPS_TRY(launch("train_image_sums", (double)ncells(g), s, [&] { k_image_sums<true><<<sum_blocks(g), kBlock, 0, s>>>(img(l), g, inv_full, sp); }));
-        else
-            NPS_TRY(launch("train_image_sums", (double)ncells(g), s, [&] { k_image_sums<false><<<sum_blocks(g), kBlock, 0, s>>>(img(l), g, inv_full, sp); }));
-    }
     NPS_TRY(run_down_l1<T>(net, labels, d, plan, lay, ws, r, s, bf16w));
     for (int l = 2; l <= L; ++l) {
         const Grid g = level_grid(d, l);
@@ -1539,84 +1530,85 @@ int train_forward(const nps_net* net, const uint8_t* labels, nps_dims d, const T
     return NPS_OK;
 }
 
-// The weight-gradient sums of one CConv block from nparts per-block rows:
-// chunk sums in place, then the final reduction into gW (and dc).
-int wgrad_reduce(double* wpart, int nparts, double scale, double* gW, double* dc, hipStream_t s) {
-    const dim3 cgrid((nparts + kWChunk - 1) / kWChunk, (kWPart + kBlock - 1) / kBlock);
-    NPS_TRY(launch("train_wgrad_chunks", 0, s, [&] { k_wgrad_chunks<<<cgrid, kBlock, 0, s>>>(wpart, nparts); }));
-    return launch("train_wgrad_reduce", 0, s, [&] {
-        k_wgrad_reduce<<<1, kBlock, 0, s>>>(wpart, nparts, scale, gW, gW + 27 * 81, dc);
-    });
-}
-
-template <class T, int WP = std::is_same<T, float>::value ? kWgMfma32 : kWgVector>
-int train_backward(const nps_net* net, const uint8_t* labels, nps_dims d, const TrainLayout& tl, void* ws,
-                   const T* r, const T* gy, double* grad, hipStream_t s) {
+// The CConv blocks of a system for k_wgrad: the blocks (rows of partial sums)
+// are shared out by the work of a block's tiles, where an up block interpolates
+// its input and a count beyond level 3 has two pieces.
+template <class T>
+WgradArgs wgrad_args(const nps_net* net, const uint8_t* labels, nps_dims d, const TrainLayout& tl, void* ws, const T* r,
+                     const T* gy, int add) {
     const int L = net->levels;
     const Layout& lay = tl.base;
-    State* st = mptr<State>(ws, lay.state);
+    WgradArgs a{};
+    a.add = add;
+    double work[kMaxWSegs], total = 0.0;
+    for (int l = 1; l <= L; ++l)
+        for (int up = 0; up < (l < L ? 2 : 1); ++up) {
+            WgradSeg& sg = a.seg[a.nseg];
+            sg.img = l == 1 ? static_cast<const void*>(labels) : static_cast<const void*>(cptr<uint32_t>(ws, lay.counts[l]));
+            sg.g = level_grid(d, l);
+            sg.gx = l == 1 ? gy : cptr<T>(ws, tl.gx[l]);
+            sg.gnext = !up && l < L ? cptr<T>(ws, tl.gr1[l + 1]) : nullptr;
+            if (up) sg.r = l + 1 == L ? cptr<T>(ws, lay.x1[L]) : cptr<T>(ws, tl.xup[l + 1]);
+            else sg.r = l == 1 ? r : cptr<T>(ws, lay.rb[l]);
+            sg.l1 = l == 1;
+            sg.up = up;
+            sg.lvl = l < L ? l - 1 : -1;
+            sg.pieces = l <= kMfmaMaxLevel ? 1 : 2;
+            sg.scale = std::ldexp(1.0, -3 * (l - 1));
+            sg.gw = up ? off_c2(L, l) : off_c1(l);
+            work[a.nseg] = (double)tiles_of(sg.g).count() * (up ? 1.4 : 1.0) * sg.pieces;
+            total += work[a.nseg++];
+        }
+    int row = 0;
+    for (int i = 0; i < a.nseg; ++i) {
+        const int share = 1 + (int)((kWRows - a.nseg) * (work[i] / total));
+        a.seg[i].row0 = row;
+        a.seg[i].rows = std::min(share, tiles_of(a.seg[i].g).count());
+        row += a.seg[i].rows;
+    }
+    return a;
+}
+
+int wgrad_rows(const WgradArgs& a) { return a.seg[a.nseg - 1].row0 + a.seg[a.nseg - 1].rows; }
+
+// Backward of one system: the adjoint sweep, the Aff gradients (added to
+// grad), and the parameter sums of all CConv blocks, left in the rows of
+// tl.wpart (add: on top of the batch's systems before) for wgrad_finish.
+template <class T, int PU>
+int train_backward(const nps_net* net, const uint8_t* labels, nps_dims d, const TrainLayout& tl, void* ws,
+                   const T* r, const T* gy, double* grad, int add, WgradArgs* args, hipStream_t s) {
+    const int L = net->levels;
+    const Layout& lay = tl.base;
+    const State* st = cptr<State>(ws, lay.state);
     double* wpart = mptr<double>(ws, tl.wpart);
-    double* dc = mptr<double>(ws, tl.dc);
-    auto img = [&](int l) -> const void* {
-        return l == 1 ? static_cast<const void*>(labels) : static_cast<const void*>(cptr<uint32_t>(ws, lay.counts[l]));
-    };
-    auto x_of = [&](int l) -> const T* { return l == L ? cptr<T>(ws, lay.x1[L]) : cptr<T>(ws, tl.xup[l]); };
-    // up sweep, reversed
+    int dcparts[kMaxLevels + 1] = {};
+    NPS_TRY(adjoint_sweep<T>(net, labels, d, tl, ws, gy, nullptr, dcparts, s));
+    *args = wgrad_args<T>(net, labels, d, tl, ws, r, gy, add);
+    const WgradArgs a = *args;
+    NPS_TRY(launch("train_wgrad", (double)ncells(level_grid(d, 1)), s, [&] {
+        k_wgrad<T, PU><<<wgrad_rows(a), kBlock, 0, s>>>(a, st, wpart);
+    }));
+    AffGradArgs f{};
+    f.g = level_grid(d, 1);
+    f.pyr = pyramid_blocks(f.g);
+    f.cls = cptr<ClassSums>(ws, lay.cls);
+    f.tot = cptr<uint2>(ws, lay.tot);
     for (int l = 1; l < L; ++l) {
-        const Grid g = level_grid(d, l);
-        const int grid = std::min(tile_grid(g), kTrainBlocks);
-        const T* gin = l == 1 ? gy : cptr<T>(ws, tl.gx[l]);
-        const T* xc = x_of(l + 1);
-        const T* x1 = cptr<T>(ws, lay.x1[l]);
-        const T* x2 = cptr<T>(ws, tl.x2[l]);
-        const T* k2 = cptr<T>(ws, lay.k2[l]);
-        T* gx1 = mptr<T>(ws, tl.gx1[l]);
-        T* gr2 = mptr<T>(ws, tl.gr2[l]);
-        if (l == 1)
-            NPS_TRY(launch("train_bwd_up", (double)ncells(g), s, [&] {
-                k_bwd_up<T, true, true, WP><<<grid, kBlock, 0, s>>>(img(l), g, gin, xc, x1, x2, k2, st, l - 1, gx1, gr2, wpart);
-            }));
-        else
-            NPS_TRY(launch("train_bwd_up", (double)ncells(g), s, [&] {
-                k_bwd_up<T, false, true, WP><<<grid, kBlock, 0, s>>>(img(l), g, gin, xc, x1, x2, k2, st, l - 1, gx1, gr2, wpart);
-            }));
-        const double scale = std::ldexp(1.0, -3 * (l - 1));
-        double* gW = grad + off_c2(L, l);
-        double* dcl = dc + 2 * (l - 1);
-        NPS_TRY(wgrad_reduce(wpart, grid, scale, gW, dcl, s));
-        const double* sp = cptr<double>(ws, tl.spart) + (size_t)(l - 1) * 3 * kTaps * kSumBlocks;
-        double* ga = grad + off_aff(L, l);
-        const double n27 = 27.0 * (double)ncells(g);
-        NPS_TRY(launch("train_aff_grad", 0, s, [&] { k_aff_grad<<<3 * kTaps, kBlock, 0, s>>>(sp, sum_blocks(g), dcl, n27, ga, ga + 82); }));
-        const Grid gc = level_grid(d, l + 1);
-        T* gxc = mptr<T>(ws, tl.gx[l + 1]);
-        NPS_TRY(launch("train_bwd_interp", (double)ncells(gc), s, [&] {
-            k_bwd_interp<T><<<elem_grid(ncells(gc)), kBlock, 0, s>>>(gc, gr2, gxc);
-        }));
+        f.dc[l - 1] = cptr<double>(ws, tl.dc[l]);
+        f.nparts[l - 1] = dcparts[l];
+        f.ga[l - 1] = off_aff(L, l);
     }
-    // down sweep, reversed (the coarsest level's output gradient is gx^L)
-    for (int l = L; l >= 1; --l) {
-        const Grid g = level_grid(d, l);
-        const int grid = std::min(tile_grid(g), kTrainBlocks);
-        const T* gx1 = l == L ? cptr<T>(ws, tl.gx[L]) : cptr<T>(ws, tl.gx1[l]);
-        const T* gr_next = l < L ? cptr<T>(ws, tl.gr1[l + 1]) : nullptr;
-        const T* r1 = l == 1 ? r : cptr<T>(ws, lay.rb[l]);
-        const T* k1 = cptr<T>(ws, lay.k1[l]);
-        T* gr1 = l > 1 ? mptr<T>(ws, tl.gr1[l]) : nullptr;
-        if (l == 1)
-            NPS_TRY(launch("train_bwd_down", (double)ncells(g), s, [&] {
-                k_bwd_down<T, true, true, WP><<<grid, kBlock, 0, s>>>(img(l), g, gx1, gr_next, r1, k1, gr1, wpart);
-            }));
-        else
-            NPS_TRY(launch("train_bwd_down", (double)ncells(g), s, [&] {
-                k_bwd_down<T, false, true, WP><<<grid, kBlock, 0, s>>>(img(l), g, gx1, gr_next, r1, k1, gr1, wpart);
-            }));
-        const double scale = std::ldexp(1.0, -3 * (l - 1));
-        double* gW = grad + off_c1(l);
-        NPS_TRY(wgrad_reduce(wpart, grid, scale, gW, nullptr, s));
-    }
-    (void)st;
-    return NPS_OK;
+    return launch("train_aff_grad", 0, s, [&] { k_aff_grad<<<L - 1, kBlock, 0, s>>>(f, grad); });
+}
+
+// The rows of all systems into the CConv gradients.
+int wgrad_finish(const WgradArgs& a, const TrainLayout& tl, void* ws, double* grad, hipStream_t s) {
+    double* wpart = mptr<double>(ws, tl.wpart);
+    int chunks = 1;
+    for (int i = 0; i < a.nseg; ++i) chunks = std::max(chunks, (a.seg[i].rows + kWChunk - 1) / kWChunk);
+    const dim3 grid(chunks, (kWGrad + kBlock - 1) / kBlock, a.nseg);
+    NPS_TRY(launch("train_wgrad_chunks", 0, s, [&] { k_wgrad_chunks<<<grid, kBlock, 0, s>>>(a, wpart); }));
+    return launch("train_wgrad_reduce", 0, s, [&] { k_wgrad_reduce<<<a.nseg, kBlock, 0, s>>>(a, wpart, grad); });
 }
 
 template <class T>
@@ -1646,7 +1638,7 @@ int train_loss(const uint8_t* labels, nps_dims d, const TrainLayout& tl, void* w
 // one after another in the same workspace, each forward keeping its per-level
 // activations for its own backward; the loss gradient of each is weighed by
 // 1/batch, so the backward passes add the gradient of the mean.
-template <class T, int WP>
+template <class T, int PU>
 int train_step(const nps_net* net, const uint8_t* labels, nps_dims d, int batch, const T* b, double* grad,
                double* loss_h, const TrainLayout& tl, void* ws, hipStream_t s, bool bf16w) {
     const Layout& lay = tl.base;
@@ -1660,6 +1652,7 @@ int train_step(const nps_net* net, const uint8_t* labels, nps_dims d, int batch,
     double* lacc = mptr<double>(ws, tl.lacc);
     const double w = 1.0 / batch;
     const int grid = tile_grid(g);
+    WgradArgs wa{};
     NPS_TRY(launch("train_loss_sum", 0, s, [&] { k_loss_accumulate<<<1, 1, 0, s>>>(st, lacc, 0.0, 1); }));
     for (int i = 0; i < batch; ++i) {
         const uint8_t* lab = labels + (size_t)i * n;
@@ -1673,8 +1666,9 @@ int train_step(const nps_net* net, const uint8_t* labels, nps_dims d, int batch,
         }));
         NPS_TRY(launch("train_gy", (double)n, s, [&] { k_train_gy<T><<<grid, kBlock, 0, s>>>(lab, g, res, st, gy, w); }));
         NPS_TRY(launch("train_loss_sum", 0, s, [&] { k_loss_accumulate<<<1, 1, 0, s>>>(st, lacc, w, 0); }));
-        NPS_TRY((train_backward<T, WP>(net, lab, d, tl, ws, bi, gy, grad, s)));
+        NPS_TRY((train_backward<T, PU>(net, lab, d, tl, ws, bi, gy, grad, i > 0, &wa, s)));
     }
+    NPS_TRY(wgrad_finish(wa, tl, ws, grad, s));
     NPS_HIP(hipMemcpyAsync(loss_h, lacc, sizeof(double), hipMemcpyDeviceToHost, s));
     NPS_HIP(hipStreamSynchronize(s));
     return NPS_OK;
@@ -1961,14 +1955,17 @@ int nps_net_backward(const nps_net* net, const uint8_t* labels_d, nps_dims dims,
     const TrainLayout tl = make_train_layout(dims, net->levels, precision);
     if (ws_bytes < tl.total) return fail(NPS_ENOMEM, "workspace has %zu bytes, needs %zu", ws_bytes, tl.total);
     hipStream_t s = static_cast<hipStream_t>(stream);
+    WgradArgs wa{};
     if (precision == NPS_FP64)
-        return train_backward<double>(net, labels_d, dims, tl, ws_d, static_cast<const double*>(r_d),
-                                      static_cast<const double*>(gy_d), grad_d, s);
-    if (precision == NPS_MIXED_BF16)
-        return train_backward<float, kWgMfmaBf16>(net, labels_d, dims, tl, ws_d, static_cast<const float*>(r_d),
-                                                  static_cast<const float*>(gy_d), grad_d, s);
-    return train_backward<float>(net, labels_d, dims, tl, ws_d, static_cast<const float*>(r_d),
-                                 static_cast<const float*>(gy_d), grad_d, s);
+        NPS_TRY((train_backward<double, 1>(net, labels_d, dims, tl, ws_d, static_cast<const double*>(r_d),
+                                           static_cast<const double*>(gy_d), grad_d, 0, &wa, s)));
+    else if (precision == NPS_MIXED_BF16)
+        NPS_TRY((train_backward<float, 1>(net, labels_d, dims, tl, ws_d, static_cast<const float*>(r_d),
+                                          static_cast<const float*>(gy_d), grad_d, 0, &wa, s)));
+    else
+        NPS_TRY((train_backward<float, kPieces>(net, labels_d, dims, tl, ws_d, static_cast<const float*>(r_d),
+                                                static_cast<const float*>(gy_d), grad_d, 0, &wa, s)));
+    return wgrad_finish(wa, tl, ws_d, grad_d, s);
 }
 
 int nps_train_step(const nps_net* net, const uint8_t* labels_d, nps_dims dims, int batch, const void* b_d,
@@ -1982,12 +1979,12 @@ int nps_train_step(const nps_net* net, const uint8_t* labels_d, nps_dims dims, i
     if (reinterpret_cast<uintptr_t>(ws_d) % 256) return fail(NPS_EINVAL, "workspace not 256-byte aligned");
     hipStream_t s = static_cast<hipStream_t>(stream);
     if (precision == NPS_FP64)
-        return train_step<double, kWgVector>(net, labels_d, dims, batch, static_cast<const double*>(b_d), grad_d, loss_h,
+        return train_step<double, 1>(net, labels_d, dims, batch, static_cast<const double*>(b_d), grad_d, loss_h,
                                              tl, ws_d, s, false);
     if (precision == NPS_MIXED_BF16)
-        return train_step<float, kWgMfmaBf16>(net, labels_d, dims, batch, static_cast<const float*>(b_d), grad_d, loss_h,
+        return train_step<float, 1>(net, labels_d, dims, batch, static_cast<const float*>(b_d), grad_d, loss_h,
                                               tl, ws_d, s, true);
-    return train_step<float, kWgMfma32>(net, labels_d, dims, batch, static_cast<const float*>(b_d), grad_d, loss_h, tl,
+    return train_step<float, kPieces>(net, labels_d, dims, batch, static_cast<const float*>(b_d), grad_d, loss_h, tl,
                                         ws_d, s, false);
 }
 

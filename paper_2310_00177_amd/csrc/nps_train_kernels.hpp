@@ -7,13 +7,15 @@
 // In count form I_c = n_c / 8^(l-1) for fluid and air, and the solid channel
 // follows from sum_c I_c = 1 (also for the solid padding):
 //   dL/dW[t,solid,o] = U_t - dL/dW[t,fluid,o] - dL/dW[t,air,o].
-// Each block accumulates the 27 x 55 sums (54 counts and the constant 1) of
-// its tiles and writes them as one partial; a reduce kernel sums the partials
-// in block order into the double gradient blob.  All levels use kernels K
-// formed at setup (tap-major), so the transposed apply is a gather.
+// Only the transposed applies form a chain (k_adj, level by level, on kernels K
+// formed at setup).  The 27 x 55 sums of every block (54 counts and the
+// constant 1) need just the gradients the chain leaves behind, so in float one
+// launch (k_wgrad) contracts all blocks of all levels once the chain is done,
+// and its per-block partials are added up once per step.
 #pragma once
 
 #include "nps_kernels.hpp"
+#include "nps_setup_kernels.hpp"
 
 #include <type_traits>
 
@@ -21,390 +23,423 @@ namespace nps {
 
 constexpr int kFeat = 2 * kTaps + 1;            // 54 counts + the constant
 constexpr int kWGrad = kTaps * kFeat;           // 1485 sums per CConv block
-constexpr int kWPart = kWGrad + 3;              // + dL/dc1, dL/dc2 partials, padding
-constexpr int kTrainBlocks = 1024;              // grid of the backward tile kernels
-constexpr int kUStride = kBlock + 1;            // padded row of the u table in LDS
+constexpr int kWPart = kWGrad + 3;              // a row of partial sums, padded
+constexpr int kWRows = 1024;                    // rows (blocks) of all CConv blocks together
 
-// Accumulate this tile's contribution to the 27 x 55 sums.  u_s[t][p] holds
-// g(p) r(p + a_t) for the tile's cells (row stride kUStride), img_s the
-// haloed image.  Thread i owns sums i, i + kBlock, ...
-template <class T, bool L1>
-__device__ __forceinline__ void accumulate_wgrad(const T* u_s, const uint32_t* img_s, T (&acc)[(kWGrad + kBlock - 1) / kBlock]) {
-    constexpr int NO = (kWGrad + kBlock - 1) / kBlock;
-#pragma unroll
-    for (int j = 0; j < NO; ++j) {
-        const int idx = threadIdx.x + j * kBlock;
-        if (idx >= kWGrad) break;
-        const int t = idx / kFeat, k = idx % kFeat;
-        T s = T(0);
-        if (k == kFeat - 1) {
-            for (int p = 0; p < kBlock; ++p) s += u_s[t * kUStride + p];
-        } else {
-            const int o = k >> 1, c = k & 1;
-            const int off = halo_off_rt(o);
-            for (int p = 0; p < kBlock; ++p) {
-                const int lx = p % TX, ly = (p / TX) % TY, lz = p / (TX * TY);
-                uint32_t n0, n1;
-                counts_of<L1>(img_s[halo_base(lx, ly, lz) + off], n0, n1);
-                const uint32_t n = c ? n1 : n0;
-                if (n) s += u_s[t * kUStride + p] * (T)n;
-            }
-        }
-        acc[j] += s;
-    }
-}
-
-// Float: the tile's contribution as a matrix product on the matrix cores,
-// sums[t][f] += sum_p U[t][p] F[f][p] with U[t][p] = g(p) r(p + a_t) (from
-// u_s) and F[f][p] the f-th count feature of cell p (f = 2 o + c: count of
-// channel c at window position o; f = 54 the constant 1), contracted over the
-// tile's 256 cells four at a time on v_mfma_f32_16x16x4_f32 (exact fp32
-// products, fp32 accumulation).  Wave w owns the feature block f = 16 w ..
-// 16 w + 15 and both tap blocks; lane (k, n) supplies U[16 mb + n][p0 + k]
-// and F[16 w + n][p0 + k].  acc[mb][i] ends as sums[16 mb + 4 k + i][16 w + n].
-template <bool L1>
-__device__ __forceinline__ void accumulate_wgrad_mfma(const float* u_s, const uint32_t* img_s, f32x4 (&acc)[2]) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int n = lane & 15, k = lane >> 4;
-    const int f = 16 * wv + n, o = min(f >> 1, kTaps - 1), ch = f & 1;
-    const int off = halo_off_rt(o);
-    // unrolled so that several steps' LDS reads are in flight ahead of their MFMAs
-#pragma unroll 8
-    for (int p0 = 0; p0 < kBlock; p0 += 4) {
-        const int p = p0 + k;
-        const int lx = p % TX, ly = (p / TX) % TY, lz = p / (TX * TY);
-        float b;
-        if (f < 2 * kTaps) {
-            uint32_t n0, n1;
-            counts_of<L1>(img_s[halo_base(lx, ly, lz) + off], n0, n1);
-            b = (float)(ch ? n1 : n0);
-        } else {
-            b = f == 2 * kTaps ? 1.0f : 0.0f;
-        }
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
-            const int t = 16 * mb + n;
-            const float a = t < kTaps ? u_s[t * kUStride + p] : 0.0f;
-            acc[mb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[mb], 0, 0, 0);
-        }
-    }
-}
-
-// The same product with bf16 operands and fp32 accumulation (the bf16
-// training leg): v_mfma_f32_16x16x32_bf16 contracts 32 cells at a time, lane
-// (k, n) supplying U and F at cells p0 + 8 k .. p0 + 8 k + 7 (U rounded to
-// nearest even; the counts are small integers, exact).
-__device__ __forceinline__ uint16_t bf16_bits_rne(float v) {
-    uint32_t u = __float_as_uint(v);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-
-template <bool L1>
-__device__ __forceinline__ void accumulate_wgrad_bf16(const float* u_s, const uint32_t* img_s, f32x4 (&acc)[2]) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int n = lane & 15, k = lane >> 4;
-    const int f = 16 * wv + n, o = min(f >> 1, kTaps - 1), ch = f & 1;
-    const int off = halo_off_rt(o);
-#pragma unroll 2
-    for (int p0 = 0; p0 < kBlock; p0 += 32) {
-        u16x8 b, a[2];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int p = p0 + 8 * k + j;
-            const int lx = p % TX, ly = (p / TX) % TY, lz = p / (TX * TY);
-            float fv;
-            if (f < 2 * kTaps) {
-                uint32_t n0, n1;
-                counts_of<L1>(img_s[halo_base(lx, ly, lz) + off], n0, n1);
-                fv = (float)(ch ? n1 : n0);
-            } else {
-                fv = f == 2 * kTaps ? 1.0f : 0.0f;
-            }
-            b[j] = bf16_bits_rne(fv);
-#pragma unroll
-            for (int mb = 0; mb < 2; ++mb) {
-                const int t = 16 * mb + n;
-                a[mb][j] = bf16_bits_rne(t < kTaps ? u_s[t * kUStride + p] : 0.0f);
-            }
-        }
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-            acc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[mb]),
-                                                              __builtin_bit_cast(bf16x8, b), acc[mb], 0, 0, 0);
-    }
-}
-
-__device__ __forceinline__ void write_wgrad_partial_mfma(const f32x4 (&acc)[2], double* part, double gc1, double gc2) {
-    double* mine = part + (size_t)blockIdx.x * kWPart;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int n = lane & 15, k = lane >> 4, f = 16 * wv + n;
-#pragma unroll
-    for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int t = 16 * mb + 4 * k + i;
-            if (t < kTaps && f < kFeat) mine[t * kFeat + f] = (double)acc[mb][i];
-        }
-    if (threadIdx.x == 0) {
-        mine[kWGrad] = gc1;
-        mine[kWGrad + 1] = gc2;
-        mine[kWGrad + 2] = 0.0;
-    }
-}
-
-// How the parameter sums are contracted: per-thread sums on the vector ALU
-// (double), fp32 matrix cores (float), bf16 matrix cores with fp32
-// accumulation (the bf16 training leg).
-enum WgradPath : int { kWgVector = 0, kWgMfma32 = 1, kWgMfmaBf16 = 2 };
-
-// Per-block accumulator of a CConv block's parameter sums.
-template <class T, int WP = std::is_same<T, float>::value ? kWgMfma32 : kWgVector>
-struct WgradAcc {
-    static constexpr bool kMfma = WP != kWgVector;
-    static_assert(!kMfma || std::is_same<T, float>::value, "matrix-core sums are float");
-    T v[kMfma ? 1 : (kWGrad + kBlock - 1) / kBlock];
-    f32x4 m[kMfma ? 2 : 1];
-    __device__ __forceinline__ void init() {
-        if constexpr (kMfma) {
-            m[0] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            m[1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        } else {
-#pragma unroll
-            for (int j = 0; j < (kWGrad + kBlock - 1) / kBlock; ++j) v[j] = T(0);
-        }
-    }
-    template <bool L1>
-    __device__ __forceinline__ void add(const T* u_s, const uint32_t* img_s) {
-        if constexpr (WP == kWgMfmaBf16) accumulate_wgrad_bf16<L1>(u_s, img_s, m);
-        else if constexpr (WP == kWgMfma32) accumulate_wgrad_mfma<L1>(u_s, img_s, m);
-        else accumulate_wgrad<T, L1>(u_s, img_s, v);
-    }
-};
-
-template <class T>
-__device__ __forceinline__ void write_wgrad_partial_vec(const T (&acc)[(kWGrad + kBlock - 1) / kBlock], double* part,
-                                           double gc1, double gc2) {
-    constexpr int NO = (kWGrad + kBlock - 1) / kBlock;
-    double* mine = part + (size_t)blockIdx.x * kWPart;
-#pragma unroll
-    for (int j = 0; j < NO; ++j) {
-        const int idx = threadIdx.x + j * kBlock;
-        if (idx < kWGrad) mine[idx] = (double)acc[j];
-    }
-    if (threadIdx.x == 0) {
-        mine[kWGrad] = gc1;
-        mine[kWGrad + 1] = gc2;
-        mine[kWGrad + 2] = 0.0;
-    }
-}
-
-template <class T, int WP>
-__device__ __forceinline__ void write_wgrad_partial(const WgradAcc<T, WP>& a, double* part, double gc1, double gc2) {
-    if constexpr (WgradAcc<T, WP>::kMfma) write_wgrad_partial_mfma(a.m, part, gc1, gc2);
-    else write_wgrad_partial_vec<T>(a.v, part, gc1, gc2);
-}
-
-// Backward of one up block at level l:  x = c1 x1 + c2 CConv_2(Interp(xc)).
-// Given gx = dL/dx: writes gx1 = c1 gx (the x1 share), gr2 = CConv_2^T(c2 gx),
-// and (WGRAD) a partial of the CConv_2 parameter sums and of dL/dc1 = gx.x1,
-// dL/dc2 = gx.x2.  Level 1 (L1): gx is masked to fluid first.  Without
-// WGRAD this is the up block's part of the adjoint P^T (xc, x1, x2 and part
-// are not read).
-template <class T, bool L1, bool WGRAD, int WP = std::is_same<T, float>::value ? kWgMfma32 : kWgVector>
-__global__ __launch_bounds__(kBlock) void k_bwd_up(const void* __restrict__ img, Grid g, const T* __restrict__ gx_in,
-                                                   const T* __restrict__ xc, const T* __restrict__ x1,
-                                                   const T* __restrict__ x2, const T* __restrict__ k2, const State* st,
-                                                   int lvl, T* __restrict__ gx1, T* __restrict__ gr2, double* part) {
-    const T c1 = (T)st->c1[lvl], c2 = (T)st->c2[lvl];
-    __shared__ uint32_t img_s[kHaloP];
-    __shared__ T r_s[WGRAD ? kHaloP : 1];       // Interp(xc): the block's input
-    __shared__ T g_s[kHaloP];       // gx (masked at level 1); the block's output gradient is c2 gx
-    __shared__ T c_s[WGRAD ? kCoarseTileP : 1];
-    __shared__ T u_s[WGRAD ? kTaps * kUStride : 1];
-    WgradAcc<T, WP> acc;
-    acc.init();
-    double gc1 = 0.0, gc2 = 0.0;
-    const Tiles tl = tiles_of(g);
-    const size_t n = ncells(g);
-    const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
-    const int base = halo_base(lx, ly, lz);
-    for (TileSpan sp = tile_span(tl.count()); sp.t0 < sp.t1; sp.t0 += sp.step) {
-        const TileOrigin o = tile_origin(sp.t0, tl);
-        __syncthreads();
-        if constexpr (WGRAD) stage_image_interp<L1, kStored, T>(img_s, nullptr, img, r_s, c_s, xc, g, o);
-        else stage_image<L1>(img_s, img, g, o);
-        for (int i = threadIdx.x; i < kHalo; i += kBlock) {
-            const int hx = i % HX, hy = (i / HX) % HY, hz = i / (HX * HY);
-            const int xx = o.x0 + hx - 1, yy = o.y0 + hy - 1, zz = o.z0 + hz - 1;
-            T v = T(0);
-            if (in_grid(g, zz, yy, xx)) {
-                const size_t q = cell_index(g, zz, yy, xx);
-                v = gx_in[q];
-                if (L1 && static_cast<const uint8_t*>(img)[q] != kFluid) v = T(0);
-            }
-            g_s[i] = v;
-        }
-        __syncthreads();
-        const int xx = o.x0 + lx, yy = o.y0 + ly, zz = o.z0 + lz;
-        const bool active = in_grid(g, zz, yy, xx);
-        const size_t idx = active ? cell_index(g, zz, yy, xx) : 0;
-        const T gxp = g_s[base];
-        const T gself = c2 * gxp;    // dL/dx2(p)
-        if constexpr (WGRAD)
-            for (int t = 0; t < kTaps; ++t) u_s[t * kUStride + threadIdx.x] = active ? gself * r_s[base + halo_off(t)] : T(0);
-        if (active) {
-            gx1[idx] = c1 * gxp;
-            if constexpr (WGRAD) {
-                gc1 += (double)gxp * (double)x1[idx];
-                gc2 += (double)gxp * (double)x2[idx];
-            }
-            T s = T(0);
-#pragma unroll
-            for (int t = 0; t < kTaps; ++t) {
-                const int qz = zz - (t / 9 - 1), qy = yy - ((t / 3) % 3 - 1), qx = xx - (t % 3 - 1);
-                if (in_grid(g, qz, qy, qx)) s = fma(k2[(size_t)t * n + cell_index(g, qz, qy, qx)], c2 * g_s[base - halo_off(t)], s);
-            }
-            gr2[idx] = s;
-        }
-        if constexpr (WGRAD) {
-            __syncthreads();
-            acc.template add<L1>(u_s, img_s);
-        }
-    }
-    if constexpr (!WGRAD) return;
-    // dL/dc partials: block sums
-    double v[kRedWidth] = {gc1, gc2, 0.0, 0.0};
-    __shared__ double sh[kRedWidth][kBlock / 64];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    for (int w = 0; w < 2; ++w) v[w] = wave_sum(v[w]);
-    __syncthreads();
-    if (lane == 0) {
-        sh[0][wid] = v[0];
-        sh[1][wid] = v[1];
-    }
-    __syncthreads();
-    double b1 = 0.0, b2 = 0.0;
-    for (int i = 0; i < kBlock / 64; ++i) {
-        b1 += sh[0][i];
-        b2 += sh[1][i];
-    }
-    write_wgrad_partial(acc, part, b1, b2);
-}
-
-// Backward of one down block at level l:  x1 = CConv_1(r1).  The output
-// gradient is gx1 plus, below the coarsest level, the pool adjoint of the
-// next level's input gradient (gr_next / 8 of the parent cell).  Writes
-// gr1 = CConv_1^T(g) (unless gr1 is null; at level 1 restricted to fluid,
-// where the input was) and (WGRAD) a partial of the parameter sums.
-// Without WGRAD this is the down block's part of the adjoint P^T (r1 and
-// part are not read).
-template <class T, bool L1, bool WGRAD, int WP = std::is_same<T, float>::value ? kWgMfma32 : kWgVector>
-__global__ __launch_bounds__(kBlock) void k_bwd_down(const void* __restrict__ img, Grid g, const T* __restrict__ gx1,
-                                                     const T* __restrict__ gr_next, const T* __restrict__ r1,
-                                                     const T* __restrict__ k1, T* __restrict__ gr1, double* part) {
-    __shared__ uint32_t img_s[kHaloP];
-    __shared__ T r_s[WGRAD ? kHaloP : 1];
+// ---------------------------------------------------------------------------
+// the adjoint chain
+// ---------------------------------------------------------------------------
+// The transposed apply of one CConv block on stored kernels.  UP, the up block
+// x = c1 x1 + c2 CConv_2(Interp(xc)): out = CConv_2^T(c2 gx), and with x1 also
+// the block's partials of dL/dc1 = gx.x1 and dL/dc2 = gx.x2 (part[b], part[grid
+// + b]).  Down block x1 = CConv_1(r): out = CConv_1^T(g) with g = coef gx + the
+// pool adjoint of the next level's input gradient (gnext / 8 of the parent
+// cell), coef = c1, or 1 on the coarsest level (lvl < 0); at level 1 the output
+// is restricted to fluid, where the input was.  At level 1 (L1) gx counts on
+// fluid cells only.
+// The gather reads K_t at 27 neighbours: all 27 loads go out ahead of the
+// staging, at the cell itself where a neighbour lies outside (its g is zero).
+// Tests around the loads had serialised them (16^3 level: 10 -> 4 us).
+template <class T, bool L1, bool UP>
+__global__ __launch_bounds__(kBlock) void k_adj(const uint8_t* __restrict__ lab, Grid g, const T* __restrict__ gx,
+                                                const T* __restrict__ gnext, const T* __restrict__ kst,
+                                                const State* st, int lvl, const T* __restrict__ x1,
+                                                const T* __restrict__ x2, T* __restrict__ out,
+                                                double* __restrict__ part) {
     __shared__ T g_s[kHaloP];
-    __shared__ T u_s[WGRAD ? kTaps * kUStride : 1];
-    WgradAcc<T, WP> acc;
-    acc.init();
+    const T coef = UP ? (T)st->c2[lvl] : lvl >= 0 ? (T)st->c1[lvl] : T(1);
     const Tiles tl = tiles_of(g);
-    const size_t n = ncells(g);
+    const int n = (int)ncells(g);
     const Grid gc = coarser(g);
     const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
     const int base = halo_base(lx, ly, lz);
+    double v[2] = {0.0, 0.0};
+    struct E {
+        T gx, gn;
+        uint8_t l;
+    };
     for (TileSpan sp = tile_span(tl.count()); sp.t0 < sp.t1; sp.t0 += sp.step) {
         const TileOrigin o = tile_origin(sp.t0, tl);
-        __syncthreads();
-        stage_image<L1>(img_s, img, g, o);
-        for (int i = threadIdx.x; i < kHalo; i += kBlock) {
-            const int hx = i % HX, hy = (i / HX) % HY, hz = i / (HX * HY);
-            const int xx = o.x0 + hx - 1, yy = o.y0 + hy - 1, zz = o.z0 + hz - 1;
-            T gv = T(0), rv = T(0);
-            if (in_grid(g, zz, yy, xx)) {
-                const size_t q = cell_index(g, zz, yy, xx);
-                gv = gx1[q];
-                if (gr_next) gv += gr_next[cell_index(gc, zz >> 1, yy >> 1, xx >> 1)] * T(0.125);
-                if constexpr (WGRAD) {
-                    rv = r1[q];
-                    if (L1 && static_cast<const uint8_t*>(img)[q] != kFluid) rv = T(0);   // input padded with zeros
-                }
-            }
-            g_s[i] = gv;
-            if constexpr (WGRAD) r_s[i] = rv;
-        }
-        __syncthreads();
         const int xx = o.x0 + lx, yy = o.y0 + ly, zz = o.z0 + lz;
         const bool active = in_grid(g, zz, yy, xx);
-        const T gself = g_s[base];
-        if constexpr (WGRAD)
-            for (int t = 0; t < kTaps; ++t) u_s[t * kUStride + threadIdx.x] = active ? gself * r_s[base + halo_off(t)] : T(0);
-        if (active && gr1) {
-            T s = T(0);
+        const int idx = active ? (int)cell_index(g, zz, yy, xx) : 0;
+        T kv[kTaps];
 #pragma unroll
-            for (int t = 0; t < kTaps; ++t) {
-                const int qz = zz - (t / 9 - 1), qy = yy - ((t / 3) % 3 - 1), qx = xx - (t % 3 - 1);
-                if (in_grid(g, qz, qy, qx)) s = fma(k1[(size_t)t * n + cell_index(g, qz, qy, qx)], g_s[base - halo_off(t)], s);
-            }
-            if (L1 && img_s[base] != (uint32_t)kFluid) s = T(0);
-            gr1[cell_index(g, zz, yy, xx)] = s;
+        for (int t = 0; t < kTaps; ++t) {
+            const int dz = t / 9 - 1, dy = (t / 3) % 3 - 1, dx = t % 3 - 1;
+            const bool in = active && in_grid(g, zz - dz, yy - dy, xx - dx);
+            kv[t] = kst[(size_t)t * n + (in ? idx - ((dz * g.ny + dy) * g.nx + dx) : idx)];
         }
-        if constexpr (WGRAD) {
-            __syncthreads();
-            acc.template add<L1>(u_s, img_s);
+        const auto e = load_batch<kHalo, E>([&](int i) {
+            int x, y, z;
+            halo_coords(i, o, x, y, z);
+            const bool in = in_grid(g, z, y, x);
+            const size_t q = in ? cell_index(g, z, y, x) : 0;
+            E r{*at_or(gx, q, in, pad_zero<T>()), T(0), (uint8_t)kFluid};
+            if constexpr (L1) r.l = *at_or(lab, q, in, g_pad_solid);
+            if constexpr (!UP)
+                if (gnext) r.gn = *at_or(gnext, in ? cell_index(gc, z >> 1, y >> 1, x >> 1) : 0, in, pad_zero<T>());
+            return r;
+        });
+        uint8_t own = kFluid;
+        if constexpr (L1) own = active ? lab[idx] : (uint8_t)kSolid;
+        T x1v = T(0), x2v = T(0);
+        if (UP && x1) {
+            x1v = x1[idx];
+            x2v = x2[idx];
+        }
+        __syncthreads();   // the previous tile's reads are done
+        put_batch(e, [&](int i, E r) {
+            const T m = r.l == kFluid ? r.gx : T(0);
+            g_s[i] = UP ? m : coef * m + r.gn * T(0.125);
+        });
+        __syncthreads();
+        T s = T(0);
+#pragma unroll
+        for (int t = 0; t < kTaps; ++t) s = fma(kv[t], g_s[base - halo_off(t)], s);
+        if constexpr (UP) s *= coef;
+        if (L1 && !UP && own != kFluid) s = T(0);
+        if (active) out[idx] = s;
+        if (UP && active && own == kFluid) {   // x1, x2 may hold anything where the output is masked
+            v[0] += (double)g_s[base] * (double)x1v;
+            v[1] += (double)g_s[base] * (double)x2v;
         }
     }
-    if constexpr (WGRAD) write_wgrad_partial(acc, part, 0.0, 0.0);
+    if (!UP || !x1) return;
+    __shared__ double sh[2][kBlock / 64];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const double s0 = wave_sum(v[0]), s1 = wave_sum(v[1]);
+    if (lane == 0) {
+        sh[0][wid] = s0;
+        sh[1][wid] = s1;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        double t = 0.0;
+#pragma unroll
+        for (int i = 0; i < kBlock / 64; ++i) t += sh[threadIdx.x][i];
+        part[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = t;
+    }
 }
 
 // Adjoint of the 2x trilinear upsampling: gc(j) = sum over fine cells f of
 // w(f -> j) gf(f).  Along one axis a fine cell f feeds f/2 with 3/4 and its
 // neighbour on f's side (clamped) with 1/4, so coarse j collects f = 2j, 2j+1
 // (3/4), 2j-1, 2j+2 (1/4), and at the ends the clamped quarter of f = 0 or
-// f = 2n-1 once more.
-__device__ __forceinline__ int up_adjoint_axis(int j, int nc, int* f, double* w) {
-    int m = 0;
-    f[m] = 2 * j; w[m++] = 0.75;
-    f[m] = 2 * j + 1; w[m++] = 0.75;
-    if (j > 0) { f[m] = 2 * j - 1; w[m++] = 0.25; }
-    else { f[m] = 0; w[m++] = 0.25; }
-    if (j < nc - 1) { f[m] = 2 * j + 2; w[m++] = 0.25; }
-    else { f[m] = 2 * nc - 1; w[m++] = 0.25; }
-    return m;
-}
-
+// f = 2n-1 once more: always four terms, with the outer two clamped.  Axis by
+// axis in double; the 64 loads are independent.
 template <class T>
-__global__ __launch_bounds__(kBlock) void k_bwd_interp(Grid gcoarse, const T* __restrict__ gf, T* __restrict__ gcout) {
+__global__ __launch_bounds__(kBlock) void k_adj_interp(Grid gcoarse, const T* __restrict__ gf, T* __restrict__ gcout) {
     const Grid gfine{2 * gcoarse.nz, 2 * gcoarse.ny, 2 * gcoarse.nx};
-    const size_t n = ncells(gcoarse);
-    for (size_t q = (size_t)blockIdx.x * kBlock + threadIdx.x; q < n; q += (size_t)gridDim.x * kBlock) {
-        const int x = (int)(q % gcoarse.nx), y = (int)((q / gcoarse.nx) % gcoarse.ny),
-                  z = (int)(q / ((size_t)gcoarse.nx * gcoarse.ny));
+    const int n = (int)ncells(gcoarse);
+    auto cells = [](int j, int nf, int (&f)[4]) {
+        f[0] = max(2 * j - 1, 0);
+        f[1] = 2 * j;
+        f[2] = 2 * j + 1;
+        f[3] = min(2 * j + 2, nf - 1);
+    };
+    auto sum4 = [](double a, double b, double c, double d) { return 0.75 * (b + c) + 0.25 * (a + d); };
+    for (int q = (int)(blockIdx.x * kBlock + threadIdx.x); q < n; q += (int)(gridDim.x * kBlock)) {
+        const int x = q % gcoarse.nx, y = q / gcoarse.nx % gcoarse.ny, z = q / (gcoarse.nx * gcoarse.ny);
         int fx[4], fy[4], fz[4];
-        double wx[4], wy[4], wz[4];
-        const int mx = up_adjoint_axis(x, gcoarse.nx, fx, wx), my = up_adjoint_axis(y, gcoarse.ny, fy, wy),
-                  mz = up_adjoint_axis(z, gcoarse.nz, fz, wz);
-        double s = 0.0;
-        for (int a = 0; a < mz; ++a)
-            for (int bb = 0; bb < my; ++bb)
-                for (int c = 0; c < mx; ++c)
-                    s += wz[a] * wy[bb] * wx[c] * (double)gf[cell_index(gfine, fz[a], fy[bb], fx[c])];
-        gcout[q] = (T)s;
+        cells(x, gfine.nx, fx);
+        cells(y, gfine.ny, fy);
+        cells(z, gfine.nz, fz);
+        T v[4][4][4];
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[a][b][c] = gf[cell_index(gfine, fz[a], fy[b], fx[c])];
+        double sz[4];
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            double sy[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                sy[b] = sum4((double)v[a][b][0], (double)v[a][b][1], (double)v[a][b][2], (double)v[a][b][3]);
+            sz[a] = sum4(sy[0], sy[1], sy[2], sy[3]);
+        }
+        gcout[q] = (T)sum4(sz[0], sz[1], sz[2], sz[3]);
     }
 }
 
-// The per-block partials of the parameter sums are reduced in two passes
-// of fixed order: k_wgrad_chunks sums each chunk of kWChunk consecutive rows
-// into the chunk's first row (in place: no other block reads that chunk),
-// then k_wgrad_reduce sums the first rows in chunk order.  One workgroup
-// summing every row itself had 12 MB to read per CConv block.
+// ---------------------------------------------------------------------------
+// parameter sums
+// ---------------------------------------------------------------------------
+// One CConv block: G[t][f] = sum_p g(p) r(p + a_t) F_f(p) over the level's
+// cells, F the 54 window counts and the constant 1.
+struct WgradSeg {
+    const void* img;                  // labels (level 1) or counts
+    Grid g;
+    const void *gx, *gnext, *r;       // as in k_adj; r: the block's input (up: the coarse x it interpolates)
+    int l1, up, lvl;                  // lvl: index of the coefficient of gx (< 0: 1)
+    int pieces;                       // pieces of a count: 1 up to level 3 (exact in bf16), else 2
+    int row0, rows;                   // blocks (rows of partial sums) of this CConv block
+    double scale;                     // 8^-(l-1)
+    size_t gw;                        // W of the block in the gradient blob
+};
+
+constexpr int kMaxWSegs = 2 * kMaxLevels;
+
+struct WgradArgs {
+    int nseg, add;                    // add: to the rows of the systems before (a batch)
+    WgradSeg seg[kMaxWSegs];
+};
+
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// bf16 of a pair, rounded to nearest even, as one word; and its values.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){a, b}, bf16x2));
+}
+__device__ __forceinline__ float pair_lo(uint32_t w) { return __uint_as_float(w << 16); }
+__device__ __forceinline__ float pair_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
+
+// LDS of a block: the staged tile, then the waves' sums of one tap block.
+template <class T>
+struct WgradLds {
+    static constexpr int kR = 2 * kHaloP * 4, kG = kR + kHaloP * (int)sizeof(T), kC = kG + kBlock * (int)sizeof(T);
+    static constexpr int kTile = kC + kCoarseTileP * (int)sizeof(T);
+    static constexpr int kSums = 4 * 16 * 64 * (int)sizeof(T);
+    static constexpr int kBytes = kTile > kSums ? kTile : kSums;
+};
+
+// The sums of one block's tiles on the matrix cores: G is a 27 x 55 matrix
+// product contracted over the cells, U[t][p] = g(p) r(p + a_t) times F[f][p].
+// A wave owns the 64 cells of its z-plane of the tile and all of G (2 x 4 blocks
+// of 16 x 16); lane (k, n) supplies tap 16 mb + n and feature 16 fb + n.
+//   float   v_mfma_f32_16x16x32_bf16, 32 cells at a time (lane k: 8 cells along
+//           x): U is split into PU = 3 bf16 pieces whose sum is the float
+//           exactly, the counts are exact in one piece up to level 3 and in two
+//           beyond, so all products are exact and the sums are fp32, as on the
+//           fp32 matrix cores, at 3/16 of their time.  PU = 1: the bf16 leg.
+//   double  v_mfma_f64_16x16x4_f64.
+// What bounds it is forming U (16 products and their pieces per lane and 32
+// cells) beside 24 matrix instructions.  A wave whose g is all zero skips its
+// cells, a level-1 down tile without fluid in reach the tile.  Partial sums in
+// float, and per-thread sums on the vector ALU in double, as before: level 1
+// of a 128^3 system 230 us (up, with the transposed apply) and 140 us (down).
+template <class T, int PU, int NF, bool L1, bool UP>
+__device__ __forceinline__ void wgrad_block(const WgradSeg& sg, const State* st, int add, char* lds,
+                                            double* __restrict__ row) {
+    constexpr bool F64 = sizeof(T) == 8;
+    using M = WgradLds<T>;
+    uint32_t* f_s = reinterpret_cast<uint32_t*>(lds);                  // float: bf16 count pairs; double: image words
+    uint32_t* f2_s = f_s + kHaloP;                                     // their second pieces
+    T* r_s = reinterpret_cast<T*>(lds + M::kR);
+    T* g_s = reinterpret_cast<T*>(lds + M::kG);
+    T* c_s = reinterpret_cast<T*>(lds + M::kC);
+    const Grid g = sg.g, gc = coarser(g);
+    const T coef = sg.lvl < 0 ? T(1) : UP ? (T)st->c2[sg.lvl] : (T)st->c1[sg.lvl];
+    const T* gx = static_cast<const T*>(sg.gx);
+    const T* gnext = static_cast<const T*>(sg.gnext);
+    const T* r = static_cast<const T*>(sg.r);
+    const Tiles tl = tiles_of(g);
+    const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
+    const int lane = threadIdx.x & 63, n = lane & 15, k = lane >> 4;
+    int toff[2], foff[4];   // LDS offsets of the lane's taps and window positions
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb) toff[mb] = halo_off_rt(min(16 * mb + n, kTaps - 1));
+#pragma unroll
+    for (int fb = 0; fb < 4; ++fb) foff[fb] = halo_off_rt(min(8 * fb + (n >> 1), kTaps - 1));
+    const bool air = n & 1, one = n == 2 * kTaps - 48;   // feature 54 = 48 + n
+    using Acc = typename std::conditional<F64, f64x4, f32x4>::type;
+    Acc acc[2][4];
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int fb = 0; fb < 4; ++fb) acc[mb][fb] = Acc{0, 0, 0, 0};
+    InterpSlots isl;
+    if constexpr (UP) isl = interp_slots();
+    for (int tile = (int)blockIdx.x - sg.row0; tile < tl.count(); tile += sg.rows) {
+        const TileOrigin o = tile_origin(tile, tl);
+        const int xx = o.x0 + lx, yy = o.y0 + ly, zz = o.z0 + lz;
+        const bool active = in_grid(g, zz, yy, xx);
+        const size_t idx = active ? cell_index(g, zz, yy, xx) : 0;
+        // loads
+        T gv = active ? gx[idx] : T(0);
+        const T gn = !UP && gnext && active ? gnext[cell_index(gc, zz >> 1, yy >> 1, xx >> 1)] : T(0);
+        uint8_t own = kFluid;
+        if constexpr (L1) own = active ? static_cast<const uint8_t*>(sg.img)[idx] : (uint8_t)kSolid;
+        UpLoads<T> ul;
+        Batch<kHalo, T> rl;
+        if constexpr (UP) {
+            ul = load_image_interp<L1, T>(sg.img, r, g, o);
+        } else {
+            ul.img = load_batch<kHalo, uint32_t>([&](int i) { return image_load<L1>(sg.img, g, o, i); });
+            rl = load_batch<kHalo, T>([&](int i) {
+                const HaloCell c = halo_cell(g, o, i);
+                return *at_or(r, c.q, c.in, pad_zero<T>());
+            });
+        }
+        __syncthreads();   // the previous tile's reads are done
+        put_batch(ul.img, [&](int i, uint32_t v) {
+            if constexpr (F64) {
+                f_s[i] = v;
+            } else {
+                uint32_t c0, c1;
+                counts_of<L1>(v, c0, c1);
+                const float a = (float)c0, b = (float)c1;
+                const uint32_t h = (__float_as_uint(a) >> 16) | (__float_as_uint(b) & 0xffff0000u);
+                f_s[i] = h;
+                if constexpr (NF == 2) {
+                    const float a2 = a - pair_lo(h), b2 = b - pair_hi(h);
+                    f2_s[i] = (__float_as_uint(a2) >> 16) | (__float_as_uint(b2) & 0xffff0000u);
+                }
+            }
+        });
+        if (L1 && own != kFluid) gv = T(0);
+        gv = UP ? coef * gv : coef * gv + gn * T(0.125);
+        g_s[threadIdx.x] = gv;
+        const bool work = __any(gv != T(0));   // the wave's cells are its z-plane's (a NaN differs from zero)
+        if constexpr (UP) {
+            put_batch(ul.c, [&](int i, T v) { c_s[i] = v; });
+            __syncthreads();
+            interp_tile<T>(r_s, c_s, g, o, isl);
+            __syncthreads();
+        } else {
+            bool any = false;
+#pragma unroll
+            for (int j = 0; j < Batch<kHalo, T>::K; ++j) {
+                const T v = !L1 || ul.img.v[j] == (uint32_t)kFluid ? rl.v[j] : T(0);   // the input is padded with zeros
+                r_s[threadIdx.x + j * kBlock] = v;
+                any = any || v != T(0);
+            }
+            if (L1) {
+                if (!__syncthreads_or(any)) continue;
+            } else {
+                __syncthreads();
+            }
+        }
+        if (!work) continue;
+        if constexpr (F64) {
+#pragma unroll 4
+            for (int s = 0; s < 16; ++s) {   // cells 4 s + k of the wave's plane
+                const int x = 4 * (s & 3) + k, y = s >> 2, hb = halo_base(x, y, lz);
+                const T gp = g_s[(lz * TY + y) * TX + x];
+                T u[2];
+#pragma unroll
+                for (int mb = 0; mb < 2; ++mb) u[mb] = gp * r_s[hb + toff[mb]];
+#pragma unroll
+                for (int fb = 0; fb < 4; ++fb) {
+                    uint32_t c0, c1;
+                    counts_of<L1>(f_s[hb + foff[fb]], c0, c1);
+                    T b = (T)(air ? c1 : c0);
+                    if (fb == 3) b = one ? T(1) : b;
+#pragma unroll
+                    for (int mb = 0; mb < 2; ++mb)
+                        acc[mb][fb] = __builtin_amdgcn_mfma_f64_16x16x4f64(u[mb], b, acc[mb][fb], 0, 0, 0);
+                }
+            }
+        } else {
+            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+            const uint32_t sel = air ? 0x07060302u : 0x05040100u;   // the lane's channel of two words
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {    // rows 2 s + (k >> 1), cells 8 (k & 1) + 0 .. 7
+                const int x = 8 * (k & 1), y = 2 * s + (k >> 1), hb = halo_base(x, y, lz);
+                const float4* gp = reinterpret_cast<const float4*>(g_s + (lz * TY + y) * TX + x);
+                const float4 g0 = gp[0], g1 = gp[1];
+                const float gq[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+                u32x4 U[PU][2];
+#pragma unroll
+                for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        float a = gq[2 * j] * r_s[hb + toff[mb] + 2 * j], b = gq[2 * j + 1] * r_s[hb + toff[mb] + 2 * j + 1];
+#pragma unroll
+                        for (int p = 0; p < PU; ++p) {
+                            const uint32_t w = bf16_pair(a, b);
+                            U[p][mb][j] = w;
+                            a -= pair_lo(w);
+                            b -= pair_hi(w);
+                        }
+                    }
+#pragma unroll
+                for (int fb = 0; fb < 4; ++fb)
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) {
+                        const uint32_t* src = (f ? f2_s : f_s) + hb + foff[fb];
+                        u32x4 F;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            F[j] = __builtin_amdgcn_perm(src[2 * j + 1], src[2 * j], sel);
+                            if (fb == 3) F[j] = one ? (f ? 0u : 0x3f803f80u) : F[j];
+                        }
+#pragma unroll
+                        for (int p = 0; p < PU; ++p)
+#pragma unroll
+                            for (int mb = 0; mb < 2; ++mb)
+                                acc[mb][fb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                    __builtin_bit_cast(bf16x8, U[p][mb]), __builtin_bit_cast(bf16x8, F), acc[mb][fb], 0,
+                                    0, 0);
+                    }
+            }
+        }
+    }
+    // the four waves' sums, one tap block at a time, added in wave order; lane
+    // (k, n) holds rows 4 k + i (float) or 4 i + k (double) of column n
+    T* sum_s = reinterpret_cast<T*>(lds);
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb) {
+        __syncthreads();
+#pragma unroll
+        for (int fb = 0; fb < 4; ++fb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int m = F64 ? 4 * i + k : 4 * k + i;
+                sum_s[(lz * 16 + m) * 64 + 16 * fb + n] = acc[mb][fb][i];
+            }
+        __syncthreads();
+        for (int e = threadIdx.x; e < 16 * 64; e += kBlock) {
+            const int t = 16 * mb + (e >> 6), f = e & 63;
+            if (t >= kTaps || f >= kFeat) continue;
+            double v = 0.0;
+#pragma unroll
+            for (int w = 0; w < kBlock / 64; ++w) v += (double)sum_s[w * 1024 + e];
+            double* dst = row + t * kFeat + f;
+            *dst = add ? *dst + v : v;
+        }
+    }
+}
+
+// All CConv blocks of a system; block b's sums go to row b of part.
+template <class T, int PU>
+__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(sizeof(T) == 8 ? 2 : 4) void k_wgrad(WgradArgs a, const State* st,
+                                                                                          double* __restrict__ part) {
+    __shared__ __attribute__((aligned(16))) char lds[WgradLds<T>::kBytes];
+    int i = 0;
+    while (i < a.nseg - 1 && (int)blockIdx.x >= a.seg[i + 1].row0) ++i;
+    const WgradSeg sg = a.seg[i];
+    double* row = part + (size_t)blockIdx.x * kWPart;
+    constexpr int N2 = sizeof(T) == 8 ? 1 : 2;   // doubles hold every count
+    if (sg.l1) {
+        if (sg.up) wgrad_block<T, PU, 1, true, true>(sg, st, a.add, lds, row);
+        else wgrad_block<T, PU, 1, true, false>(sg, st, a.add, lds, row);
+    } else if (sg.pieces == 1) {
+        if (sg.up) wgrad_block<T, PU, 1, false, true>(sg, st, a.add, lds, row);
+        else wgrad_block<T, PU, 1, false, false>(sg, st, a.add, lds, row);
+    } else {
+        if (sg.up) wgrad_block<T, PU, N2, false, true>(sg, st, a.add, lds, row);
+        else wgrad_block<T, PU, N2, false, false>(sg, st, a.add, lds, row);
+    }
+}
+
+// The rows are added up in two passes of fixed order: k_wgrad_chunks sums
+// each chunk of kWChunk consecutive rows of a CConv block into the chunk's
+// first row (in place: no other block reads that chunk), then k_wgrad_reduce
+// sums the first rows in chunk order.
 constexpr int kWChunk = 32;
 
-__global__ __launch_bounds__(kBlock) void k_wgrad_chunks(double* __restrict__ part, int nparts) {
+__global__ __launch_bounds__(kBlock) void k_wgrad_chunks(WgradArgs a, double* __restrict__ part) {
+    const WgradSeg& sg = a.seg[blockIdx.z];
     const int idx = blockIdx.y * kBlock + threadIdx.x;   // column
-    const int b0 = blockIdx.x * kWChunk, b1 = min(b0 + kWChunk, nparts);
-    if (idx >= kWPart) return;
+    const int c0 = (int)blockIdx.x * kWChunk;
+    if (idx >= kWGrad || c0 >= sg.rows) return;
+    const int b0 = sg.row0 + c0, b1 = sg.row0 + min(c0 + kWChunk, sg.rows);
     constexpr int U = 8;
     double s = 0.0;
     for (int b = b0; b < b1; b += U) {
@@ -417,23 +452,22 @@ __global__ __launch_bounds__(kBlock) void k_wgrad_chunks(double* __restrict__ pa
     part[(size_t)b0 * kWPart + idx] = s;
 }
 
-// Sums the chunk sums (rows 0, kWChunk, 2 kWChunk, ... below nparts) of one
-// CConv block's parameter sums into the gradient blob: W[t][c][o] (c =
-// fluid, air scaled by 1/8^(l-1); solid from U_t), B[t] = U_t.  Also
-// returns dL/dc1, dL/dc2 into dc.
-__global__ __launch_bounds__(kBlock) void k_wgrad_reduce(const double* __restrict__ part, int nparts, double scale,
-                                                         double* __restrict__ gW, double* __restrict__ gB,
-                                                         double* __restrict__ dc) {
-    __shared__ double sums[kWPart];
-    const int nchunks = (nparts + kWChunk - 1) / kWChunk;
-    for (int idx = threadIdx.x; idx < kWPart; idx += kBlock) {
+// One block per CConv block: its sums into the gradient blob: W[t][c][o] (c =
+// fluid, air scaled by 1/8^(l-1); solid from U_t), B[t] = U_t.
+__global__ __launch_bounds__(kBlock) void k_wgrad_reduce(WgradArgs a, const double* __restrict__ part,
+                                                         double* __restrict__ grad) {
+    __shared__ double sums[kWGrad];
+    const WgradSeg& sg = a.seg[blockIdx.x];
+    double* gW = grad + sg.gw;
+    double* gB = gW + kTaps * 3 * kTaps;
+    for (int idx = threadIdx.x; idx < kWGrad; idx += kBlock) {
         constexpr int U = 8;
         double s = 0.0;
-        for (int c = 0; c < nchunks; c += U) {
+        for (int c = 0; c < sg.rows; c += U * kWChunk) {
             double t[U];
 #pragma unroll
             for (int u = 0; u < U; ++u)
-                t[u] = c + u < nchunks ? part[(size_t)(c + u) * kWChunk * kWPart + idx] : 0.0;
+                t[u] = c + u * kWChunk < sg.rows ? part[(size_t)(sg.row0 + c + u * kWChunk) * kWPart + idx] : 0.0;
 #pragma unroll
             for (int u = 0; u < U; ++u) s += t[u];
         }
@@ -443,111 +477,96 @@ __global__ __launch_bounds__(kBlock) void k_wgrad_reduce(const double* __restric
     for (int idx = threadIdx.x; idx < kTaps * kTaps; idx += kBlock) {   // (t, o)
         const int t = idx / kTaps, o = idx % kTaps;
         const double u = sums[t * kFeat + kFeat - 1];
-        const double gf = scale * sums[t * kFeat + 2 * o], ga = scale * sums[t * kFeat + 2 * o + 1];
+        const double gf = sg.scale * sums[t * kFeat + 2 * o], ga = sg.scale * sums[t * kFeat + 2 * o + 1];
         gW[(t * 3 + kFluid) * kTaps + o] += gf;
         gW[(t * 3 + kAir) * kTaps + o] += ga;
         gW[(t * 3 + kSolid) * kTaps + o] += u - gf - ga;
     }
     for (int t = threadIdx.x; t < kTaps; t += kBlock) gB[t] += sums[t * kFeat + kFeat - 1];
-    if (threadIdx.x == 0 && dc) {
-        dc[0] = sums[kWGrad];
-        dc[1] = sums[kWGrad + 1];
-    }
 }
 
-// Image-window sums S[c][o] = sum_p I_c(p + o) of one level (solid padding),
-// the derivative of an Aff scalar with respect to its weights times 27 n_l.
-// The channels are counts times 8^-(l-1), so the fluid and air sums are
-// accumulated as integer counts (exact, in registers); the solid channel
-// follows from I_solid = 1 - I_fluid - I_air, which the padding satisfies
-// too: S[solid][o] = (cells) - S[fluid][o] - S[air][o].  Every partial is a
-// multiple of 8^-(l-1) below 2^32, exact in double, so the sums do not depend
-// on their order.
-template <bool L1>
-__global__ __launch_bounds__(kBlock) void k_image_sums(const void* __restrict__ img, Grid g, double inv_full,
-                                                       double* __restrict__ part) {
-    const size_t n = ncells(g);
-    uint32_t s0[kTaps], s1[kTaps], cells = 0;
-#pragma unroll
-    for (int o = 0; o < kTaps; ++o) s0[o] = s1[o] = 0u;
-    for (size_t p = (size_t)blockIdx.x * kBlock + threadIdx.x; p < n; p += (size_t)gridDim.x * kBlock) {
-        const int x = (int)(p % g.nx), y = (int)((p / g.nx) % g.ny), z = (int)(p / ((size_t)g.nx * g.ny));
-        cells += 1u;
-#pragma unroll
-        for (int o = 0; o < kTaps; ++o) {
-            const int qz = z + o / 9 - 1, qy = y + (o / 3) % 3 - 1, qx = x + o % 3 - 1;
-            if (in_grid(g, qz, qy, qx)) {
-                const size_t q = cell_index(g, qz, qy, qx);
-                const uint32_t v = L1 ? (uint32_t)static_cast<const uint8_t*>(img)[q] : static_cast<const uint32_t*>(img)[q];
-                uint32_t c0, c1;
-                counts_of<L1>(v, c0, c1);
-                s0[o] += c0;
-                s1[o] += c1;
-            }
-        }
+// Aff gradients: dL/dWbar = dL/dc * S / (27 n_l), dL/dBbar = dL/dc, for Aff_1
+// and Aff_2 of every level (one block each), with the image-window sums
+// S[c][o] = sum_p I_c(p + o) (solid padding), the derivative of an Aff scalar
+// with respect to its weights times 27 n_l.  They come from the set-up's
+// boundary sums: S[c][o] adds the classes whose cells q have q - o in the grid,
+// and the solid channel follows from sum_c I_c = 1.  Integers, exact in double.
+// (A pass over the image per level before: 115 us of a 128^3 system.)
+struct AffGradArgs {
+    Grid g;                                // level 1
+    int pyr;                               // pyramid blocks
+    const ClassSums* cls;
+    const uint2* tot;
+    const double* dc[kMaxLevels];          // dL/dc1, dL/dc2 partials of a level ([2][nparts])
+    int nparts[kMaxLevels];
+    size_t ga[kMaxLevels];                 // Aff_1 of the level in the gradient blob (Aff_2 follows)
+};
+
+__global__ __launch_bounds__(kBlock) void k_aff_grad(AffGradArgs a, double* __restrict__ grad) {
+    __shared__ double sh[4][kBlock / 64], dc_s[2];
+    __shared__ double n_s[2][kClasses];
+    const int s = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};    // dL/dc1, dL/dc2, fluid and air cells of the grid
+    for (int b = threadIdx.x; b < a.nparts[s]; b += kBlock) {
+        v[0] += a.dc[s][b];
+        v[1] += a.dc[s][a.nparts[s] + b];
     }
-    // every wave reduces its sums, then one barrier and one thread per sum
-    // adds the waves in order
-    __shared__ uint32_t sh[kBlock / 64][2 * kTaps + 1];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    auto wave_total = [](uint32_t v) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += (uint32_t)__shfl_xor((int)v, off, 64);
-        return v;
-    };
-#pragma unroll
-    for (int o = 0; o < kTaps; ++o) {
-        const uint32_t a = wave_total(s0[o]), b = wave_total(s1[o]);
-        if (lane == 0) {
-            sh[wid][o] = a;
-            sh[wid][kTaps + o] = b;
-        }
+    for (int b = threadIdx.x; b < a.pyr; b += kBlock) {
+        v[2] += (double)a.tot[b].x;
+        v[3] += (double)a.tot[b].y;
     }
-    const uint32_t c = wave_total(cells);
-    if (lane == 0) sh[wid][2 * kTaps] = c;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        v[w] = wave_sum(v[w]);
+        if (lane == 0) sh[w][wv] = v[w];
+    }
     __syncthreads();
-    for (int o = threadIdx.x; o < kTaps; o += kBlock) {
-        uint32_t a = 0u, b = 0u, m = 0u;
-        for (int k = 0; k < kBlock / 64; ++k) {
-            a += sh[k][o];
-            b += sh[k][kTaps + o];
-            m += sh[k][2 * kTaps];
+    if (threadIdx.x < kClasses) {          // wave 0: the class sums, class 0 the rest of the grid
+        const uint32_t c = threadIdx.x;
+        double t[4];
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            t[w] = 0.0;
+#pragma unroll
+            for (int i = 0; i < kBlock / 64; ++i) t[w] += sh[w][i];
         }
-        double* dst = part + (size_t)blockIdx.x * 3 * kTaps;
-        const double f = (double)a * inv_full, ai = (double)b * inv_full;
-        dst[o] = f;
-        dst[kTaps + o] = ai;
-        dst[2 * kTaps + o] = (double)m - f - ai;
+        const double n0 = c ? (double)a.cls->n[s][c][0] : 0.0, n1 = c ? (double)a.cls->n[s][c][1] : 0.0;
+        const double b0 = wave_sum(n0), b1 = wave_sum(n1);
+        n_s[0][c] = c ? n0 : t[2] - b0;
+        n_s[1][c] = c ? n1 : t[3] - b1;
+        if (c < 2) dc_s[c] = t[c];
     }
-}
-
-// Aff gradients of one level: dL/dWbar = dL/dc * S / (27 n_l), dL/dBbar = dL/dc,
-// for Aff_1 (dc[0]) and Aff_2 (dc[1]); S summed from the k_image_sums partials.
-// One block per weight entry e = c * 27 + o (81 blocks): the block adds the
-// entry's partials (exact, see k_image_sums: the order does not matter) and
-// updates its gradient; block 0 also updates Bbar.
-__global__ __launch_bounds__(kBlock) void k_aff_grad(const double* __restrict__ spart, int nparts,
-                                                     const double* __restrict__ dc, double n27,
-                                                     double* __restrict__ gA1, double* __restrict__ gA2) {
-    const int e = blockIdx.x;
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nparts; b += kBlock) s += spart[(size_t)b * 3 * kTaps + e];
-    __shared__ double sh[kBlock / 64];
-    s = wave_sum(s);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        double t = 0.0;
-        for (int k = 0; k < kBlock / 64; ++k) t += sh[k];
-        gA1[e] += dc[0] * t / n27;   // Wbar[c][o]
-        gA2[e] += dc[1] * t / n27;
-        if (e == 0) {
-            gA1[3 * kTaps] += dc[0];   // Bbar
-            gA2[3 * kTaps] += dc[1];
-        }
+    const Grid g{a.g.nz >> s, a.g.ny >> s, a.g.nx >> s};
+    const double n = (double)ncells(g), inv = 1.0 / (double)(1u << (3 * s)), n27 = 27.0 * n;
+    const int o = threadIdx.x;
+    if (o >= kTaps) return;
+    double S[3] = {0.0, 0.0, 0.0};
+    for (uint32_t c = 0; c < kClasses; ++c) {
+        const bool in = class_sees(c, o);
+        S[0] += in ? n_s[0][c] : 0.0;
+        S[1] += in ? n_s[1][c] : 0.0;
+    }
+    S[0] *= inv;
+    S[1] *= inv;
+    S[2] = n - S[0] - S[1];
+    const double d0 = dc_s[0], d1 = dc_s[1];
+    double* g1 = grad + a.ga[s];
+    double* g2 = g1 + 3 * kTaps + 1;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        g1[c * kTaps + o] += d0 * S[c] / n27;
+        g2[c * kTaps + o] += d1 * S[c] / n27;
+    }
+    if (o == 0) {   // Bbar
+        g1[3 * kTaps] += d0;
+        g2[3 * kTaps] += d1;
     }
 }
 
+// ---------------------------------------------------------------------------
+// the loss
+// ---------------------------------------------------------------------------
 // Training loss of one system: res = b - A y on fluid cells; partial ||res||^2,
 // and A res (whose scaled negative is dL/dy) written to ares.
 template <class T>

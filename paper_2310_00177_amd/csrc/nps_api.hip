@@ -111,14 +111,20 @@ size_t bottom_footprint(nps_dims d, int lb, int levels) {
     return e;
 }
 
-Plan make_plan(nps_dims d, int levels, int precision, bool all_stored = false) {
+Plan make_plan(nps_dims d, int levels, int precision, bool all_stored = false, bool bf16w = false) {
     Plan p = {};
     p.L = levels;
     p.lb = levels + 1;
     for (int l = 1; l <= levels; ++l) {
         const size_t n = ncells(level_grid(d, l));
-        if (all_stored) {   // training: every level keeps its kernels, no one-workgroup bottom
-            p.km[l] = kStored;
+        if (all_stored) {
+            // training and the symmetric variant: no one-workgroup bottom, and every
+            // level keeps its kernels but a large level 1 in float, whose adjoint forms
+            // them on matrix cores like the forward (in three pieces also where the
+            // solve's own network is mixed; one in the bf16 training leg)
+            p.km[l] = l == 1 && precision != NPS_FP64 && n > (size_t)kStoreMaxCells
+                          ? (bf16w ? kMfmaBf16 : kMfmaBf16x3)
+                          : kStored;
             continue;
         }
         if (n <= (size_t)kStoreMaxCells) p.km[l] = kStored;
@@ -759,12 +765,13 @@ int run_down_l1(const nps_net* net, const uint8_t* labels, nps_dims d, const Pla
 // grid (the number of partials).
 template <class T, bool HOOK>
 int run_up_l1(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan& plan, const Layout& lay, void* ws,
-              const T* x2, T* dhat, const T* const* ad, hipStream_t s, int* nparts, int max_dots = 0) {
+              const T* x2, T* dhat, const T* const* ad, hipStream_t s, int* nparts, int max_dots = 0,
+              T* x2out = nullptr, bool bf16w = false) {
     const Grid g = level_grid(d, 1);
     State* st = mptr<State>(ws, lay.state);
     double* partials = mptr<double>(ws, lay.dots);
     const T* x1 = cptr<T>(ws, lay.x1[1]);
-    const CConvW<T>* w = cconv_block<T>(net, block_up(net, 1));
+    const CConvW<T>* w = bf16w ? cconv_block_bf16<T>(net, block_up(net, 1)) : cconv_block<T>(net, block_up(net, 1));
     const MfmaW* wm = mfma_block(net, block_up(net, 1));
     const T* kst = plan.km[1] == kStored ? cptr<T>(ws, lay.k2[1]) : nullptr;
     return with_kmode<T>(plan.km[1], [&](auto km) {
@@ -782,7 +789,7 @@ int run_up_l1(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
                         k_up_l1m<KM, H, H ? 0 : ND, CH><<<grid, kBlock, 0, s>>>(
                             labels, g, x2, x1, dhat, w, wm, st, partials, ad[0], ad[1], ad[2], ad[3],
                             cptr<uint32_t>(ws, lay.gmode[1]), cptr<uint8_t>(ws, lay.izero[1]),
-                            wide_quads(labels, nullptr, g) ? 1 : 0);
+                            wide_quads(labels, nullptr, g) ? 1 : 0, x2out);
                     });
                 });
             };
@@ -796,21 +803,46 @@ int run_up_l1(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
             if (nparts) *nparts = grid;
             return launch("net_up_l1", (double)ncells(g), s, [&] {
                 k_up_l1<T, KM, HOOK><<<grid, kBlock, 0, s>>>(labels, g, x2, x1, dhat, w, wm, kst, st, partials, ad[0], ad[1],
-                                                            ad[2], ad[3], nullptr, cptr<int8_t>(ws, lay.wmode[1][1]));
+                                                            ad[2], ad[3], x2out, cptr<int8_t>(ws, lay.wmode[1][1]));
             });
         }
     });
 }
 
+// The level-1 step of the adjoint sweep without stored kernels.
+template <bool UP>
+int adjoint_l1m(const nps_net* net, const uint8_t* labels, nps_dims d, const TrainLayout& tl, void* ws, const float* gx,
+                const float* gnext, const float* x1, const float* x2, float* out, int* nparts, hipStream_t s, bool bf16w) {
+    const Grid g = level_grid(d, 1);
+    const Layout& lay = tl.base;
+    const State* st = cptr<State>(ws, lay.state);
+    const int blk = UP ? block_up(net, 1) : block_down(1);
+    const CConvW<float>* w = bf16w ? cconv_block_bf16<float>(net, blk) : cconv_block<float>(net, blk);
+    const int wide = wide_quads(labels, gx, g) ? 1 : 0;
+    auto go = [&](auto km) {
+        return with_chunk(g, [&](auto ch) {
+            constexpr int KM = decltype(km)::value, CH = decltype(ch)::value;
+            const int grid = persist_grid_n(&k_adj_l1m<KM, UP, CH>, march_columns(g).count());
+            if (nparts) *nparts = grid;
+            return launch(UP ? "adj_up_l1" : "adj_down_l1", (double)ncells(g), s, [&] {
+                k_adj_l1m<KM, UP, CH><<<grid, kBlock, 0, s>>>(labels, g, gx, gnext, w, mfma_block(net, blk), st, x1, x2,
+                                                              out, mptr<double>(ws, tl.dc[1]),
+                                                              cptr<uint32_t>(ws, lay.gmode[1]), wide);
+            });
+        });
+    };
+    return bf16w ? go(std::integral_constant<int, kMfmaBf16>()) : go(std::integral_constant<int, kMfmaBf16x3>());
+}
+
 // The adjoint sweep: Alg. 2 backwards with each linear step replaced by its
-// adjoint, on the stored kernels of every level (the setup of the layout tl
-// must have run).  g_in: gradient of the network's output (level 1).  With y,
+// adjoint (the setup of the layout tl must have run).  g_in: gradient of the network's output (level 1).  With y,
 // y = P^T g_in (P is linear in its input vector); in training (dcparts: the
 // partials per level of dL/dc1, dL/dc2, left in tl.dc) the sweep ends at level 2.
 template <class T>
 int adjoint_sweep(const nps_net* net, const uint8_t* labels, nps_dims d, const TrainLayout& tl, void* ws,
-                  const T* g_in, T* y, int* dcparts, hipStream_t s) {
+                  const T* g_in, T* y, int* dcparts, hipStream_t s, bool bf16w = false) {
     const int L = net->levels;
+    const Plan plan = make_plan(d, L, sizeof(T) == 4 ? NPS_FP32 : NPS_FP64, true, bf16w);
     const Layout& lay = tl.base;
     const State* st = cptr<State>(ws, lay.state);
     for (int l = 1; l < L; ++l) {   // up sweep, reversed
@@ -829,7 +861,14 @@ int adjoint_sweep(const nps_net* net, const uint8_t* labels, nps_dims d, const T
                 k_adj<T, L1, true><<<grid, kBlock, 0, s>>>(labels, g, gin, nullptr, k2, st, l - 1, x1, x2, gr2, part);
             });
         };
-        NPS_TRY(l == 1 ? up(std::true_type{}) : up(std::false_type{}));
+        bool stored = true;
+        if constexpr (std::is_same_v<T, float>)
+            if (l == 1 && is_mfma(plan.km[1])) {
+                stored = false;
+                NPS_TRY((adjoint_l1m<true>(net, labels, d, tl, ws, gin, nullptr, x1, x2, gr2, dcparts ? &dcparts[1] : nullptr,
+                                           s, bf16w)));
+            }
+        if (stored) NPS_TRY(l == 1 ? up(std::true_type{}) : up(std::false_type{}));
         const Grid gc = level_grid(d, l + 1);
         T* gxc = mptr<T>(ws, tl.gx[l + 1]);
         NPS_TRY(launch("adj_interp", (double)ncells(gc), s, [&] {
@@ -850,6 +889,11 @@ int adjoint_sweep(const nps_net* net, const uint8_t* labels, nps_dims d, const T
                                                             nullptr, gr1, nullptr);
             });
         };
+        if constexpr (std::is_same_v<T, float>)
+            if (l == 1 && is_mfma(plan.km[1])) {
+                NPS_TRY((adjoint_l1m<false>(net, labels, d, tl, ws, gx, gnext, nullptr, nullptr, gr1, nullptr, s, bf16w)));
+                continue;
+            }
         NPS_TRY(l == 1 ? down(std::true_type{}) : down(std::false_type{}));
     }
     return NPS_OK;
@@ -1467,7 +1511,7 @@ int train_forward(const nps_net* net, const uint8_t* labels, nps_dims d, const T
                   const T* r, T* y, hipStream_t s, bool bf16w = false) {
     const int L = net->levels;
     const Layout& lay = tl.base;
-    const Plan plan = make_plan(d, L, vec_bytes(NPS_FP32) == sizeof(T) ? NPS_FP32 : NPS_FP64, true);
+    const Plan plan = make_plan(d, L, vec_bytes(NPS_FP32) == sizeof(T) ? NPS_FP32 : NPS_FP64, true, bf16w);
     State* st = mptr<State>(ws, lay.state);
     auto wblock = [&](int b) { return bf16w ? cconv_block_bf16<T>(net, b) : cconv_block<T>(net, b); };
     ClassSums* cls = mptr<ClassSums>(ws, lay.cls);
@@ -1513,21 +1557,8 @@ int train_forward(const nps_net* net, const uint8_t* labels, nps_dims d, const T
                                                          nullptr);
         }));
     }
-    {
-        const Grid g = level_grid(d, 1);
-        const int grid = tile_grid(g);
-        const T* xc = x_of(2);
-        const T* x1 = cptr<T>(ws, lay.x1[1]);
-        T* x2o = mptr<T>(ws, tl.x2[1]);
-        const T* kst = cptr<T>(ws, lay.k2[1]);
-        const CConvW<T>* w = wblock(block_up(net, 1));
-        double* partials = mptr<double>(ws, lay.partials);
-        NPS_TRY(launch("net_up_l1", (double)ncells(g), s, [&] {
-            k_up_l1<T, kStored, true><<<grid, kBlock, 0, s>>>(labels, g, xc, x1, y, w, nullptr, kst, st, partials, nullptr,
-                                                            nullptr, nullptr, nullptr, x2o, nullptr);
-        }));
-    }
-    return NPS_OK;
+    const T* none[kMaxOrtho] = {nullptr, nullptr, nullptr, nullptr};
+    return run_up_l1<T, true>(net, labels, d, plan, lay, ws, x_of(2), y, none, s, nullptr, 0, mptr<T>(ws, tl.x2[1]), bf16w);
 }
 
 // The CConv blocks of a system for k_wgrad: the blocks (rows of partial sums)
@@ -1576,13 +1607,13 @@ int wgrad_rows(const WgradArgs& a) { return a.seg[a.nseg - 1].row0 + a.seg[a.nse
 // tl.wpart (add: on top of the batch's systems before) for wgrad_finish.
 template <class T, int PU>
 int train_backward(const nps_net* net, const uint8_t* labels, nps_dims d, const TrainLayout& tl, void* ws,
-                   const T* r, const T* gy, double* grad, int add, WgradArgs* args, hipStream_t s) {
+                   const T* r, const T* gy, double* grad, int add, WgradArgs* args, hipStream_t s, bool bf16w = false) {
     const int L = net->levels;
     const Layout& lay = tl.base;
     const State* st = cptr<State>(ws, lay.state);
     double* wpart = mptr<double>(ws, tl.wpart);
     int dcparts[kMaxLevels + 1] = {};
-    NPS_TRY(adjoint_sweep<T>(net, labels, d, tl, ws, gy, nullptr, dcparts, s));
+    NPS_TRY(adjoint_sweep<T>(net, labels, d, tl, ws, gy, nullptr, dcparts, s, bf16w));
     *args = wgrad_args<T>(net, labels, d, tl, ws, r, gy, add);
     const WgradArgs a = *args;
     NPS_TRY(launch("train_wgrad", (double)ncells(level_grid(d, 1)), s, [&] {
@@ -1666,7 +1697,7 @@ int train_step(const nps_net* net, const uint8_t* labels, nps_dims d, int batch,
         }));
         NPS_TRY(launch("train_gy", (double)n, s, [&] { k_train_gy<T><<<grid, kBlock, 0, s>>>(lab, g, res, st, gy, w); }));
         NPS_TRY(launch("train_loss_sum", 0, s, [&] { k_loss_accumulate<<<1, 1, 0, s>>>(st, lacc, w, 0); }));
-        NPS_TRY((train_backward<T, PU>(net, lab, d, tl, ws, bi, gy, grad, i > 0, &wa, s)));
+        NPS_TRY((train_backward<T, PU>(net, lab, d, tl, ws, bi, gy, grad, i > 0, &wa, s, bf16w)));
     }
     NPS_TRY(wgrad_finish(wa, tl, ws, grad, s));
     NPS_HIP(hipMemcpyAsync(loss_h, lacc, sizeof(double), hipMemcpyDeviceToHost, s));
@@ -1961,7 +1992,7 @@ int nps_net_backward(const nps_net* net, const uint8_t* labels_d, nps_dims dims,
                                            static_cast<const double*>(gy_d), grad_d, 0, &wa, s)));
     else if (precision == NPS_MIXED_BF16)
         NPS_TRY((train_backward<float, 1>(net, labels_d, dims, tl, ws_d, static_cast<const float*>(r_d),
-                                          static_cast<const float*>(gy_d), grad_d, 0, &wa, s)));
+                                          static_cast<const float*>(gy_d), grad_d, 0, &wa, s, true)));
     else
         NPS_TRY((train_backward<float, kPieces>(net, labels_d, dims, tl, ws_d, static_cast<const float*>(r_d),
                                                 static_cast<const float*>(gy_d), grad_d, 0, &wa, s)));

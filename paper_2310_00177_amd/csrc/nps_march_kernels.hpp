@@ -140,7 +140,7 @@ __global__ __launch_bounds__(kBlock) void k_march_modes(const uint8_t* __restric
     // thread (i, q, w): plane i, row q, wave w (threads past CH planes idle)
     const int w = threadIdx.x & 3, q = (threadIdx.x >> 2) & 3, i = threadIdx.x >> 4;
     uint32_t md = kGZero, mu = kGZero;
-    if (i < CH && z0 + i < g.nz && y0 + q < g.ny) {
+    if (i < CH && z0 + i < g.nz) {   // a row outside the grid is zero
         uint64_t any = 0u, all = ~(uint64_t)0;
 #pragma unroll
         for (int a = 0; a < 3; ++a)
@@ -151,7 +151,7 @@ __global__ __launch_bounds__(kBlock) void k_march_modes(const uint8_t* __restric
             }
         const uint64_t own_f = own_s[(i + 1) * PHY + q + 1];
         const int left = g.nx - x0;   // columns of the footprint inside the grid
-        const uint64_t valid = left >= 64 ? ~(uint64_t)0 : (((uint64_t)1 << left) - 1u);
+        const uint64_t valid = y0 + q >= g.ny ? 0u : left >= 64 ? ~(uint64_t)0 : (((uint64_t)1 << left) - 1u);
         auto mode = [&](uint64_t need) -> uint32_t {   // need: the cells that matter
             need &= valid;
             if (((need >> (16 * w)) & 0xffffu) == 0) return kGZero;
@@ -286,14 +286,21 @@ __device__ __forceinline__ void march_cconv(const uint2* rec, const uint32_t (&m
         for (int t = 0; t < kTaps; ++t) kp[t] = w->Kpure[kFluid][t];
         const uint2* corner = rec + gq * kRS + 16 * (int)(threadIdx.x >> 6) + (lane & 15) + XO - 1;
 #pragma unroll
-        for (int k = 0; k < CH + 2; ++k)
+        for (int k = 0; k < CH + 2; ++k) {
+            float s[3][2];   // the plane is at z offset a - 1 from output plane k - a; short sums round less
 #pragma unroll
             for (int d = 0; d < 9; ++d) {
                 const float v = fbits(corner[(k * PHY + d / 3) * kRS + d % 3].x);
 #pragma unroll
-                for (int a = 0; a < 3; ++a)   // the plane is at z offset a - 1 from output plane k - a
-                    if (k - a >= 0 && k - a < CH) out[k - a] = fmaf(kp[9 * a + d], v, out[k - a]);
+                for (int a = 0; a < 3; ++a) {
+                    float& t = s[a][d >= 5];
+                    t = d == 0 || d == 5 ? kp[9 * a + d] * v : fmaf(kp[9 * a + d], v, t);
+                }
             }
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+                if (k - a >= 0 && k - a < CH) out[k - a] += s[a][0] + s[a][1];
+        }
     }
     if (any & kAnyGeneral) {
 #pragma unroll
@@ -515,15 +522,16 @@ __device__ __forceinline__ void interp_pair(float lo, float hi, float& a, float&
 }
 
 // ND: the most dots the state can ask for (NPSDO: n_ortho; PCG 1; flexible
-// PCG 2; 0 for the hook and the symmetric variant); HOOK: the parity hook
-// (no scaling, no dots).
+// PCG 2; 0 for the hook and the symmetric variant); HOOK: the parity hook and
+// training's forward (no scaling, no dots; x2out, when given, receives the
+// CConv's output on the live items, for the backward).
 template <int KM, bool HOOK, int ND, int CH>
 __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, ND)) void k_up_l1m(
     const uint8_t* __restrict__ lab, Grid g, const float* __restrict__ xc, const float* __restrict__ x1,
     float* __restrict__ dhat, const CConvW<float>* __restrict__ w, const MfmaW* __restrict__ wm, const State* st,
     double* __restrict__ partials, const float* __restrict__ ad0, const float* __restrict__ ad1,
     const float* __restrict__ ad2, const float* __restrict__ ad3, const uint32_t* __restrict__ gmode,
-    const uint8_t* __restrict__ izero, int wide) {
+    const uint8_t* __restrict__ izero, int wide, float* __restrict__ x2out) {
     static_assert(!HOOK || ND == 0, "the hook forms no dots");
     constexpr int XO = 1;
     using S = StageTasks<CH>;
@@ -652,6 +660,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, ND)) void 
             const float out = fl ? (c1 * x1v[i] + c2 * x2[i]) * scale : 0.0f;
             if (col && z0 + i < g.nz) {
                 dhat[(size_t)own + (size_t)i * pstride] = out;
+                if (HOOK && x2out) x2out[(size_t)own + (size_t)i * pstride] = x2[i];
 #pragma unroll
                 for (int j = 0; j < ND; ++j)
                     if (j < ndots) v[j] = fma((double)out, (double)adv[i][j], v[j]);

@@ -15,6 +15,7 @@
 #pragma once
 
 #include "nps_kernels.hpp"
+#include "nps_march_kernels.hpp"
 #include "nps_setup_kernels.hpp"
 
 #include <type_traits>
@@ -29,6 +30,24 @@ constexpr int kWRows = 1024;                    // rows (blocks) of all CConv bl
 // ---------------------------------------------------------------------------
 // the adjoint chain
 // ---------------------------------------------------------------------------
+// Block sums of the partials of dL/dc1 and dL/dc2: part[b] and part[grid + b].
+__device__ __forceinline__ void dc_partials(const double (&v)[2], double* __restrict__ part) {
+    __shared__ double sh[2][kBlock / 64];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const double s0 = wave_sum(v[0]), s1 = wave_sum(v[1]);
+    if (lane == 0) {
+        sh[0][wid] = s0;
+        sh[1][wid] = s1;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        double t = 0.0;
+#pragma unroll
+        for (int i = 0; i < kBlock / 64; ++i) t += sh[threadIdx.x][i];
+        part[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = t;
+    }
+}
+
 // The transposed apply of one CConv block on stored kernels.  UP, the up block
 // x = c1 x1 + c2 CConv_2(Interp(xc)): out = CConv_2^T(c2 gx), and with x1 also
 // the block's partials of dL/dc1 = gx.x1 and dL/dc2 = gx.x2 (part[b], part[grid
@@ -105,21 +124,231 @@ __global__ __launch_bounds__(kBlock) void k_adj(const uint8_t* __restrict__ lab,
             v[1] += (double)g_s[base] * (double)x2v;
         }
     }
-    if (!UP || !x1) return;
-    __shared__ double sh[2][kBlock / 64];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const double s0 = wave_sum(v[0]), s1 = wave_sum(v[1]);
-    if (lane == 0) {
-        sh[0][wid] = s0;
-        sh[1][wid] = s1;
-    }
-    __syncthreads();
-    if (threadIdx.x < 2) {
-        double t = 0.0;
+    if (UP && x1) dc_partials(v, part);
+}
+
+// The same at level 1 in float without stored kernels (108 bytes a cell, which
+// took 107 us to form and two passes to read at 128^3): K is formed on matrix
+// cores as in the forward.  A work item is that of the level-1 network kernels.
+// Plane by plane, the waves form V_t(p) = K_t(p) g(p) for the plane's cells with
+// a one-cell border, 16 cells at a time, into a table of 27 rows in LDS; then
+// each thread gathers V_t(q - a_t) for its column: 9 taps for each of the three
+// output planes that see the plane.  UP: groups without fluid have V = 0 and
+// groups whose fluid cells have all-fluid windows (g is zero on the others) take
+// the constant fluid kernel, by the modes of the forward's up kernel; an item
+// that no group reaches is zero.  The table bounds the occupancy (two blocks a
+// CU); per plane a wave writes 8 values a lane and group and reads 27 a cell.
+constexpr int kAF = 72, kAFRows = PHY + 2;      // feature rows: x offsets -4 .. 67, y offsets -2 .. 5
+constexpr int kAG = 72;                         // g rows: x offsets -4 .. 67 (-1 .. 64 used)
+constexpr int kAVRow = 68, kAV = 420;           // V rows: x offsets -1 .. 64; 4 kAV = 16 mod 64 banks between lane groups
+
+template <int KM, bool UP, int CH>
+__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(2) void k_adj_l1m(
+    const uint8_t* __restrict__ lab, Grid g, const float* __restrict__ gx, const float* __restrict__ gnext,
+    const CConvW<float>* __restrict__ w, const MfmaW* __restrict__ wm, const State* st, const float* __restrict__ x1,
+    const float* __restrict__ x2, float* __restrict__ out, double* __restrict__ part,
+    const uint32_t* __restrict__ gmode, int wide) {
+    constexpr int P = MarchCtx<KM>::P, NPL = CH + 2;
+    using S = StageTasks<CH>;
+    __shared__ __attribute__((aligned(16))) uint32_t f_s[(CH + 4) * kAFRows * kAF];
+    __shared__ __attribute__((aligned(16))) float g_s[NPL * PHY * kAG];
+    __shared__ float v_s[(kTaps + 1) * kAV];
+    __shared__ uint32_t m_s[NPL * 3 * 4];
+    const float coef = UP ? (float)st->c2[0] : (float)st->c1[0];
+    const Columns cl = march_columns(g);
+    const Grid gc = coarser(g);
+    const int lane = threadIdx.x & 63, lg = lane >> 4, n = lane & 15;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t fluid_word = feat_word<KM, true>(kFluid), pstride = (uint32_t)g.ny * (uint32_t)g.nx;
+    u16x8 A[P][2][2];
+    int fofs[8], vofs[8];   // feature offset of window position j; V row of the tap in slot j (past 26: a spare row)
+    float kp[8];            // the all-fluid kernel at those taps
 #pragma unroll
-        for (int i = 0; i < kBlock / 64; ++i) t += sh[threadIdx.x][i];
-        part[(size_t)threadIdx.x * gridDim.x + blockIdx.x] = t;
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) A[p][mb][ks] = *reinterpret_cast<const u16x8*>(&wm->bf16[p][mb][ks][lane][0]);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int t = 16 * (j >> 2) + 4 * lg + (j & 3), o = min(t, kTaps - 1);
+        fofs[j] = ((o / 9 - 1) * kAFRows + o / 3 % 3 - 1) * kAF + o % 3 - 1;
+        vofs[j] = min(t, kTaps) * kAV;
+        kp[j] = t < kTaps ? w->Kpure[kFluid][o] : 0.0f;
     }
+    const bool one = lg == 2;
+    // V of 16 cells: fb the lane's cell in f_s, gi in g_s, vi in a row of v_s
+    auto group = [&](int fb, int gi, int vi, uint32_t mode) {
+        const float gv = g_s[gi];
+        float K[8];
+        if (mode == kGZero) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v_s[vofs[j] + vi] = 0.0f;
+            return;
+        }
+        if (mode == kGPure) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) K[j] = kp[j];
+        } else {
+            uint32_t fw[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) fw[j] = f_s[fb + fofs[j]];
+            fw[7] = one ? feat_one<KM>() : fw[7];
+            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+            const u16x8 B[2] = {__builtin_bit_cast(u16x8, (u32x4){fw[0], fw[1], fw[2], fw[3]}),
+                                __builtin_bit_cast(u16x8, (u32x4){fw[4], fw[5], fw[6], fw[7]})};
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) {
+                f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int p = 0; p < P; ++p)
+#pragma unroll
+                    for (int ks = 0; ks < 2; ++ks)
+                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, A[p][mb][ks]),
+                                                                      __builtin_bit_cast(bf16x8, B[ks]), acc, 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) K[4 * mb + j] = acc[j];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v_s[vofs[j] + vi] = K[j] * gv;
+    };
+    // the edge group: the 12 cells beside the footprint's rows (lanes past them
+    // repeat the last into spare columns)
+    const int en = min(n, 2 * PHY - 1), erow = en >> 1, eix = (en & 1) ? PX : -1;
+    const int evi = n < 2 * PHY ? erow * kAVRow + eix + 1 : PHY * kAVRow + n - 2 * PHY;
+    static_assert(PHY * kAVRow + 16 - 2 * PHY <= kAV, "spare columns");
+    double v[2] = {0.0, 0.0};
+    const MarchItems mi = march_items(cl);
+    for (int li = mi.li; li < mi.count; li += mi.step) {
+        const MarchItem it = march_item(mi, li, cl);
+        const int x0 = it.cx * PX, y0 = it.cy * PY, z0 = it.zc * CH;
+        const int tid = item_thread();
+        const int xx = x0 + lane, yy = y0 + wv;   // the thread's column
+        const bool col = xx < g.nx && yy < g.ny;
+        const uint32_t own = col ? (uint32_t)z0 * pstride + (uint32_t)yy * g.nx + xx : 0u;
+        // modes of the planes' groups: the footprint's rows and its y neighbours' (four waves each)
+        uint32_t mw = 0u;
+        if (tid < NPL * 12) {
+            const int z = z0 - 1 + tid / 12, cy = it.cy - 1 + tid / 4 % 3;
+            const bool in = z >= 0 && z < g.nz && cy >= 0 && cy < cl.ncy;
+            if (in) mw = UP ? gmode[(((size_t)z * cl.ncy + cy) * cl.ncx + it.cx) * 4 + tid % 4] : kAnyGeneral;
+        }
+        float4 gw[S::K];
+        uint32_t lw[S::K];
+        float2 nw[S::K];
+#pragma unroll
+        for (int k = 0; k < S::K; ++k) {
+            auto load = [&](auto quad) {
+                constexpr bool Q = decltype(quad)::value;
+                const int t = tid + k * kBlock;
+                const StagePos s = stage_pos<CH, 0, Q>(g, x0, y0, z0, t);
+                gw[k] = stage_values<Q>(gx, s, wide);
+                lw[k] = stage_labels<Q>(lab, s, wide);
+                nw[k] = float2{0.0f, 0.0f};
+                if (!UP && s.cells > 0) {   // the parents of the task's x pairs (quads start on even x)
+                    const int e = min(t, S::kAll - 1) - S::kQuads, row = Q ? t / (PX / 4) : e >> 1;
+                    const int ix = Q ? 4 * (t % (PX / 4)) : (e & 1) ? PX : -1;
+                    const int z = z0 + row / PHY - 1, y = y0 + row % PHY - 1, x = x0 + ix;
+                    const size_t q = cell_index(gc, z >> 1, y >> 1, x >> 1);
+                    nw[k].x = gnext[q];
+                    nw[k].y = s.cells > 2 ? gnext[q + 1] : 0.0f;
+                }
+            };
+            if (S::quads(wv, k)) load(std::true_type{});
+            else if (S::edges(wv, k)) load(std::false_type{});
+        }
+        // features: rows of 18 words of four labels
+        constexpr int FT = (CH + 4) * kAFRows * (kAF / 4), KF = (FT + kBlock - 1) / kBlock;
+        uint32_t fw[KF];
+#pragma unroll
+        for (int k = 0; k < KF; ++k) {
+            const int t = min(tid + k * kBlock, FT - 1), row = t / (kAF / 4), x = x0 - 4 + 4 * (t % (kAF / 4));
+            const int z = z0 - 2 + row / kAFRows, y = y0 - 2 + row % kAFRows;
+            const bool in = z >= 0 && z < g.nz && y >= 0 && y < g.ny && x >= 0 && x < g.nx;
+            fw[k] = stage_labels<true>(lab, StagePos{0, in ? (uint32_t)cell_index(g, z, y, x) : 0u,
+                                                     in ? min(4, g.nx - x) : 0}, wide);
+        }
+        bool some = mw != 0u;
+        __syncthreads();   // the previous item's reads are done
+        if (tid < NPL * 12) m_s[tid] = mw;
+#pragma unroll
+        for (int k = 0; k < S::K; ++k) {
+            auto put = [&](auto quad) {
+                constexpr bool Q = decltype(quad)::value;
+                const int t = tid + k * kBlock, e = min(t, S::kAll - 1) - S::kQuads;
+                const int at = Q ? t / (PX / 4) * kAG + 4 * (t % (PX / 4)) + 4 : (e >> 1) * kAG + ((e & 1) ? PX : -1) + 4;
+                const float r[4] = {gw[k].x, gw[k].y, gw[k].z, gw[k].w};
+                float q[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float m = ((lw[k] >> (8 * j)) & 255u) == kFluid ? r[j] : 0.0f;
+                    q[j] = UP ? m : fmaf(0.125f, j < 2 ? nw[k].x : nw[k].y, coef * m);
+                }
+                if constexpr (Q) *reinterpret_cast<float4*>(g_s + at) = float4{q[0], q[1], q[2], q[3]};
+                else g_s[at] = q[0];
+                if constexpr (!Q) some = some || q[0] != 0.0f;   // fluid beside the footprint
+            };
+            if (S::quads(wv, k)) put(std::true_type{});
+            else if (S::edges(wv, k)) put(std::false_type{});
+        }
+#pragma unroll
+        for (int k = 0; k < KF; ++k) {
+            const int t = min(tid + k * kBlock, FT - 1);
+            uint32_t e[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) e[j] = feat_word<KM, true>((fw[k] >> (8 * j)) & 255u);
+            *reinterpret_cast<uint4*>(f_s + 4 * t) = uint4{e[0], e[1], e[2], e[3]};
+        }
+        if (!__syncthreads_or(some)) {   // no cell of the item's border or inside contributes
+#pragma unroll
+            for (int i = 0; i < CH; ++i)
+                if (col && z0 + i < g.nz) out[(size_t)own + (size_t)i * pstride] = 0.0f;
+            continue;
+        }
+        float a2 = 0.0f, a1 = 0.0f;   // output planes k - 2 and k - 1 so far
+        for (int k = 0; k < NPL; ++k) {
+            // the wave's words of the rows above, inside and below the footprint
+            const uint32_t mlo = __builtin_amdgcn_readfirstlane(m_s[k * 12 + wv]),
+                           min_ = __builtin_amdgcn_readfirstlane(m_s[k * 12 + 4 + wv]),
+                           mhi = __builtin_amdgcn_readfirstlane(m_s[k * 12 + 8 + wv]);
+            const uint32_t mode[PHY] = {mlo >> 24, min_ & 255u, (min_ >> 8) & 255u, (min_ >> 16) & 255u, min_ >> 24,
+                                        mhi & 255u};
+            const int fb = ((k + 1) * kAFRows + 1) * kAF + 16 * wv + n + 4, gi = k * PHY * kAG + 16 * wv + n + 4;
+#pragma unroll
+            for (int r = 0; r < PHY; ++r) group(fb + r * kAF, gi + r * kAG, r * kAVRow + 16 * wv + n + 1, mode[r]);
+            if (wv == (k & 3))   // the edge cells, in turn
+                group(((k + 1) * kAFRows + 1 + erow) * kAF + eix + 4, (k * PHY + erow) * kAG + eix + 4, evi, kGGeneral);
+            __syncthreads();   // V of the plane
+            // sums of nine as trees: with the products rounded on their own, they keep the
+            // rounding of a chain of fused multiply-adds
+            auto nine = [&](int az) {
+                float q[9];
+#pragma unroll
+                for (int d = 0; d < 9; ++d)
+                    q[d] = v_s[(9 * az + d) * kAV + (wv + 2 - d / 3) * kAVRow + lane + 2 - d % 3];
+                return (((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]))) + q[8];
+            };
+            a2 += nine(0);                 // a_z = -1: output plane k - 2
+            a1 += nine(1);                 // a_z = 0: output plane k - 1
+            const float a0 = nine(2);      // a_z = 1: output plane k
+            const int i = k - 2;
+            if (i >= 0 && z0 + i < g.nz && col) {
+                const bool fl = f_s[((i + 2) * kAFRows + wv + 2) * kAF + lane + 4] == fluid_word;
+                const size_t q = (size_t)own + (size_t)i * pstride;
+                out[q] = UP ? coef * a2 : fl ? a2 : 0.0f;
+                if (UP && x1 && fl) {   // x1, x2 may hold anything where the output is masked
+                    const double gv = (double)g_s[((i + 1) * PHY + wv + 1) * kAG + lane + 4];
+                    v[0] += gv * (double)x1[q];
+                    v[1] += gv * (double)x2[q];
+                }
+            }
+            a2 = a1;
+            a1 = a0;
+            __syncthreads();   // the gather is done
+        }
+    }
+    if (UP && x1) dc_partials(v, part);
 }
 
 // Adjoint of the 2x trilinear upsampling: gc(j) = sum over fine cells f of

@@ -78,3 +78,56 @@ def test_adjoint_matches_oracle(shape, levels, precision, bar):
     got = nps.apply_precond_transpose(nps.Net(params, levels), torch.from_numpy(lab).cuda(),
                                       torch.from_numpy(g).to(dt).cuda()).cpu().double().numpy()
     assert rel(got, ref) <= bar
+
+
+# Level 1 without stored kernels (float, more than 32768 cells): 2-plane items with
+# rows not of four cells, 4-plane items (from 1024 on) with a last chunk of 2 planes
+# and a last footprint of 4 columns, whole footprints.
+LARGE = [(34, 38, 70), (70, 62, 260), (64, 64, 256)]
+
+
+@pytest.mark.parametrize("shape", LARGE)
+def test_float_gradient_and_adjoint_match_fp64_on_large_grids(shape):
+    """Against the FP64 path (matched to the oracle elsewhere), with the oracle tests' bars; boxes
+    of fluid give groups of every kind."""
+    rng = np.random.default_rng(sum(shape))
+    lab = np.zeros(shape, dtype=np.uint8)
+    lab[3 * shape[0] // 4:] = gi.AIR
+    for i in range(10):
+        lo = [int(rng.integers(0, n)) for n in shape]
+        lab[tuple(slice(a, a + int(rng.integers(1, max(2, n // 4)))) for a, n in zip(lo, shape))] = 1 + i % 2
+    labels = torch.from_numpy(lab).cuda()
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    b = torch.randn(shape, generator=gen, device="cuda", dtype=torch.float64) * (labels == gi.FLUID)
+    net, n = nps.Net(blob(2, 3), 2), gi.param_count(2)
+    grads = {}
+    for p in BARS:
+        prec = getattr(nps, p)
+        grad = torch.zeros(n, dtype=torch.float64, device="cuda")
+        bt = b.to(nps.vector_dtype(prec))
+        nps.train_step(net, labels[None], bt[None], grad, nps.train_workspace(shape, 2, prec), precision=prec)
+        grads[p] = grad.cpu().numpy()
+    for p in ("FP32", "MIXED_BF16"):
+        assert rel(grads[p], grads["FP64"]) <= BARS[p], p
+    ref = nps.apply_precond_transpose(net, labels, b)
+    got = nps.apply_precond_transpose(net, labels, b.float())
+    assert float(torch.linalg.norm(got - ref) / torch.linalg.norm(ref)) <= 1e-5
+    # rows that cannot be read four cells at once give the same bits
+    buf = torch.empty(b.numel() + 1, dtype=torch.float32, device="cuda")
+    off = buf[1:].view(shape)
+    off.copy_(b)
+    assert torch.equal(nps.apply_precond_transpose(net, labels, off), got)
+
+
+@pytest.mark.parametrize("precision", ["FP32", "MIXED_BF16"])
+def test_symmetric_iterates_on_a_large_level_1(precision):
+    """The float symmetric variant (three-piece kernels in both sweeps) follows the FP64 iterates at
+    the bar of the other float iterate tests, 1e-4."""
+    shape = (40, 32, 48)
+    lab, b = scene(shape, 11)
+    net = nps.Net(gi.multilevel_params(4), 4)
+    labels, bt = torch.from_numpy(lab).cuda(), torch.from_numpy(b).cuda()
+    kw = dict(max_iter=4, fixed_iters=True, symmetric=True)
+    ref, _ = nps.solve(net, labels, bt, precision=nps.FP64, **kw)
+    got, _ = nps.solve(net, labels, bt, precision=getattr(nps, precision), **kw)
+    assert float(torch.linalg.norm(got - ref) / torch.linalg.norm(ref)) < 1e-4

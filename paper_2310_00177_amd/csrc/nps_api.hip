@@ -526,7 +526,7 @@ int run_setup(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
     fa.aff = aff_block(net, 1, 0);
     for (int i = 0; i < 2 * (L - 1); ++i) fa.aff_b[i] = net->aff_b[i];
     fa.st = mptr<State>(ws, lay.state);
-    int blocks = 1;
+    int blocks = L - 1;
     for (int l = 1; l <= L; ++l) {
         if (plan.km[l] != kStored) continue;
         const Grid g = level_grid(d, l);
@@ -540,8 +540,11 @@ int run_setup(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
             const int blk = which == 0 ? block_down(l) : block_up(net, l);
             const CConvW<double>* w = bf16w ? cconv_block_bf16<double>(net, blk) : cconv_block<double>(net, blk);
             const MfmaW* wm = mfma_block(net, blk);
-            const int mg = elem_grid(((size_t)g.nz * g.ny * ((g.nx + 15) / 16)) * 64);
-            if (n <= (size_t)kStoreMaxCells) {   // beside the other small levels
+// 16-cell groups, a wave each; several per wave once they fill the chip (a
+            // wave's weight fragments are 12 KB)
+            const int groups = g.nz * g.ny * ((g.nx + 15) / 16);
+            const int mg = std::min((groups + 3) / 4, std::max(256, (groups + 31) / 32));
+            if (mfma || n <= (size_t)kStoreMaxCells) {   // beside the other levels
                 KgenSeg& sg = fa.seg[fa.nseg++];
                 sg.img = img(l);
                 sg.g = g;
@@ -551,25 +554,9 @@ int run_setup(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
                 sg.l1 = l == 1;
                 sg.kind = mfma ? kGenMfma : n > 4096 ? kGenTap9 : kGenTap;
                 const int nb = ((int)n + kBlock - 1) / kBlock;
-                sg.blocks = mfma ? mg : (sg.kind == kGenTap9 ? kTaps / 9 : kTaps) * nb;
+                sg.blocks = mfma ? mg : (sg.kind == kGenTap9 ? kTaps / kGenTaps : kTaps) * nb;
                 blocks += sg.blocks;
                 continue;
-            }
-            if constexpr (std::is_same_v<T, float>) {
-                if (mfma) {
-                    auto mf = [&](auto km, auto l1) {
-                        constexpr int KM = decltype(km)::value;
-                        constexpr bool L1 = decltype(l1)::value;
-                        return launch("setup_kgen", (double)n, s, [&] {
-                            k_kgen_store_mfma<KM, L1><<<mg, kBlock, 0, s>>>(img(l), g, wm, out);
-                        });
-                    };
-                    using x3 = std::integral_constant<int, kMfmaBf16x3>;
-                    using b1 = std::integral_constant<int, kMfmaBf16>;
-                    if (bf16w) NPS_TRY(l == 1 ? mf(b1{}, std::true_type{}) : mf(b1{}, std::false_type{}));
-                    else NPS_TRY(l == 1 ? mf(x3{}, std::true_type{}) : mf(x3{}, std::false_type{}));
-                    continue;
-                }
             }
             const int grid = elem_grid(n);
             NPS_TRY(launch("setup_kgen", (double)n, s, [&] {
@@ -1105,7 +1092,7 @@ struct SolverT : Solver {
         const bool res_in_bottom = plan.lb <= net->levels;
         if (!res_in_bottom)
             NPS_TRY(launch("control", 0, s, [&] {
-                k_control<kStageResidual><<<1, kCtlBlock, 0, s>>>(st, pdots, np_res, hf_d);
+                k_control<kStageResidual><<<1, kCtlBlock, 0, s>>>(st, pdots, np_res, hf_d, nullptr, 0.0, 0);
             }));
         NPS_TRY(run_down_l1<T>(net, labels, d, plan, lay, ws, r, s));
         if (res_in_bottom) NPS_TRY(run_coarse<T>(net, d, plan, lay, ws, s, &x2, pdots, np_res, hf_d));
@@ -1650,14 +1637,15 @@ int train_loss(const uint8_t* labels, nps_dims d, const TrainLayout& tl, void* w
     State* st = mptr<State>(ws, lay.state);
     double* partials = mptr<double>(ws, lay.partials);
     T* res = mptr<T>(ws, tl.res);
-    const int grid = tile_grid(g);
+    const int grid = persist_grid_n(&k_train_residual<T>, seven_point_blocks(g));
+    const int ggrid = persist_grid_n(&k_train_gy<T>, seven_point_blocks(g));
     NPS_TRY(launch("train_residual", (double)ncells(g), s, [&] {
         k_train_residual<T><<<grid, kBlock, 0, s>>>(labels, g, b, y, res, partials);
     }));
     NPS_TRY(launch("control", 0, s, [&] {
-        k_control<kStageLoss><<<1, kCtlBlock, 0, s>>>(st, partials, grid, nullptr);
+        k_control<kStageLoss><<<1, kCtlBlock, 0, s>>>(st, partials, grid, nullptr, nullptr, 0.0, 0);
     }));
-    NPS_TRY(launch("train_gy", (double)ncells(g), s, [&] { k_train_gy<T><<<grid, kBlock, 0, s>>>(labels, g, res, st, gy, 1.0); }));
+    NPS_TRY(launch("train_gy", (double)ncells(g), s, [&] { k_train_gy<T><<<ggrid, kBlock, 0, s>>>(labels, g, res, st, gy, 1.0); }));
     double rr = 0.0;
     NPS_HIP(hipMemcpyAsync(&rr, &st->rr, sizeof(double), hipMemcpyDeviceToHost, s));
     NPS_HIP(hipStreamSynchronize(s));
@@ -1682,9 +1670,9 @@ int train_step(const nps_net* net, const uint8_t* labels, nps_dims d, int batch,
     T* gy = mptr<T>(ws, tl.gy);
     double* lacc = mptr<double>(ws, tl.lacc);
     const double w = 1.0 / batch;
-    const int grid = tile_grid(g);
+    const int grid = persist_grid_n(&k_train_residual<T>, seven_point_blocks(g));
+    const int ggrid = persist_grid_n(&k_train_gy<T>, seven_point_blocks(g));
     WgradArgs wa{};
-    NPS_TRY(launch("train_loss_sum", 0, s, [&] { k_loss_accumulate<<<1, 1, 0, s>>>(st, lacc, 0.0, 1); }));
     for (int i = 0; i < batch; ++i) {
         const uint8_t* lab = labels + (size_t)i * n;
         const T* bi = b + (size_t)i * n;
@@ -1693,10 +1681,9 @@ int train_step(const nps_net* net, const uint8_t* labels, nps_dims d, int batch,
             k_train_residual<T><<<grid, kBlock, 0, s>>>(lab, g, bi, y, res, partials);
         }));
         NPS_TRY(launch("control", 0, s, [&] {
-            k_control<kStageLoss><<<1, kCtlBlock, 0, s>>>(st, partials, grid, nullptr);
+            k_control<kStageLoss><<<1, kCtlBlock, 0, s>>>(st, partials, grid, nullptr, lacc, w, i == 0);
         }));
-        NPS_TRY(launch("train_gy", (double)n, s, [&] { k_train_gy<T><<<grid, kBlock, 0, s>>>(lab, g, res, st, gy, w); }));
-        NPS_TRY(launch("train_loss_sum", 0, s, [&] { k_loss_accumulate<<<1, 1, 0, s>>>(st, lacc, w, 0); }));
+        NPS_TRY(launch("train_gy", (double)n, s, [&] { k_train_gy<T><<<ggrid, kBlock, 0, s>>>(lab, g, res, st, gy, w); }));
         NPS_TRY((train_backward<T, PU>(net, lab, d, tl, ws, bi, gy, grad, i > 0, &wa, s, bf16w)));
     }
     NPS_TRY(wgrad_finish(wa, tl, ws, grad, s));

@@ -661,12 +661,6 @@ __device__ __forceinline__ void kgen_mfma(const void* __restrict__ img, Grid g, 
     }
 }
 
-template <int KM, bool L1>
-__global__ __launch_bounds__(kBlock) void k_kgen_store_mfma(const void* __restrict__ img, Grid g,
-                                                            const MfmaW* __restrict__ wm, float* __restrict__ kst) {
-    kgen_mfma<KM, L1>(img, g, wm, kst, (int)blockIdx.x, (int)gridDim.x);
-}
-
 // ---------------------------------------------------------------------------
 // the one-block control kernel
 // ---------------------------------------------------------------------------
@@ -899,17 +893,24 @@ __device__ __forceinline__ int residual_stage(State* st, const ResidualIn& in, d
 // The one-block control kernel: sums nparts per-block partials and updates
 // the state: the Residual stage of solves without a bottom workgroup, or the
 // training loss ||b - A y||^2.
+// For the loss, acc (when given) also takes acc + w ||b - A y|| (a batch's mean;
+// first: its first system, from zero).
 template <int STAGE>
 __global__ __launch_bounds__(kCtlBlock) void k_control(State* st, const double* __restrict__ partials, int nparts,
-                                                       HostFlags* hf) {
+                                                       HostFlags* hf, double* acc, double w, int first) {
     // the stop flag is read alongside the partials and tested after them
     const int done = STAGE == kStageResidual ? st->done : 0;
+    const double before = STAGE == kStageLoss && acc && !first ? *acc : 0.0;
     double v[1];
     sum_partials<1, kCtlBlock>(partials, nparts, 1, v);
     if (done) return;
     if (threadIdx.x == 0) {
-        if constexpr (STAGE == kStageResidual) residual_stage(st, residual_in(st), v[0], hf);
-        else st->rr = v[0];
+        if constexpr (STAGE == kStageResidual) {
+            residual_stage(st, residual_in(st), v[0], hf);
+        } else {
+            st->rr = v[0];
+            if (acc) *acc = before + w * sqrt(v[0]);
+        }
     }
 }
 

@@ -109,7 +109,8 @@ __global__ __launch_bounds__(kBlock) void k_march_modes(const uint8_t* __restric
                                                         uint8_t* __restrict__ mdown, uint8_t* __restrict__ mup,
                                                         uint8_t* __restrict__ zdown, uint8_t* __restrict__ zup) {
     constexpr int R = (CH + 2) * PHY;
-    __shared__ uint64_t own_s[R], any_s[R], all_s[R];   // fluid cells; windows along x with any / only fluid
+    __shared__ uint64_t own_s[R];   // fluid cells of a row
+    __shared__ uint32_t edge_s[R];  // and of the cells beside it (bits 0, 1)
     const Columns cl = march_columns(g);
     const int per = cl.ncx * cl.ncy, rest = (int)blockIdx.x % per, zc = (int)blockIdx.x / per;
     const int cx = rest % cl.ncx, cy = rest / cl.ncx, x0 = cx * PX, y0 = cy * PY, z0 = zc * CH;
@@ -128,11 +129,9 @@ __global__ __launch_bounds__(kBlock) void k_march_modes(const uint8_t* __restric
 #pragma unroll
     for (int k = 0; k < R / 4; ++k) {
         const uint64_t f = __ballot(own[k] == kFluid), e = __ballot(edge[k] == kFluid);
-        const uint64_t lo = (f << 1) | (e & 1u), hi = (f >> 1) | ((e >> 1) << 63);
         if (lane == 0) {
             own_s[wv + 4 * k] = f;
-            any_s[wv + 4 * k] = f | lo | hi;
-            all_s[wv + 4 * k] = f & lo & hi;
+            edge_s[wv + 4 * k] = (uint32_t)e;
         }
     }
     __syncthreads();
@@ -146,8 +145,11 @@ __global__ __launch_bounds__(kBlock) void k_march_modes(const uint8_t* __restric
         for (int a = 0; a < 3; ++a)
 #pragma unroll
             for (int b = 0; b < 3; ++b) {
-                any |= any_s[(i + a) * PHY + q + b];
-                all &= all_s[(i + a) * PHY + q + b];
+                const uint64_t f = own_s[(i + a) * PHY + q + b];
+                const uint32_t e = edge_s[(i + a) * PHY + q + b];
+                const uint64_t lo = (f << 1) | (e & 1u), hi = (f >> 1) | ((uint64_t)(e >> 1) << 63);
+                any |= f | lo | hi;
+                all &= f & lo & hi;
             }
         const uint64_t own_f = own_s[(i + 1) * PHY + q + 1];
         const int left = g.nx - x0;   // columns of the footprint inside the grid

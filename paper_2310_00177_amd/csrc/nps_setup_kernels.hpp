@@ -6,7 +6,7 @@
 // the few megabytes it reads.  It therefore runs as few, wide kernels:
 //   state_init / validate + live_list   the state (a solve also validates its inputs)
 //   pyramid     the counts of every level >= 2 and the boundary sums of every level
-//   finish      the Aff scalars and the stored kernels of every small level
+//   finish      the Aff scalars and the stored kernels of all levels but the largest in double
 // One launch per level and block before (26 launches, 100 us of a 154 us
 // 32^3 evaluation in FP32).
 #pragma once
@@ -117,26 +117,29 @@ __global__ __launch_bounds__(kPyrThreads) void k_pyramid(const uint8_t* __restri
         if (lo) add(1, yz | kXLo | (g.nx == 1 ? kXHi : 0u), lo);
         if (hi) add(1, yz | kXHi, hi);
     }
-    // level 2: add the row of y ^ 1 and the rows of z ^ 1
+    // level 2: add the row of y ^ 1 (DPP quad_perm [1,0,3,2]) and the rows of z ^ 1;
+    // the four lanes that then hold a row's sums write a quarter of it each
     const Grid g2 = coarser(g);
-    const int y2 = (t & 31) >> 1, z2 = t >> 6;
+    const int y2 = (t & 31) >> 1, z2 = t >> 6, sub = (t & 1) | (t >> 4 & 2);
+    uint32_t own[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int i = 0; i < H; ++i) {
         uint32_t v = pair[i];
-        v += __shfl_xor(v, 1, 64);
-        v += __shfl_xor(v, 32, 64);
-        pair[i] = v;
+        v += (uint32_t)__builtin_amdgcn_update_dpp(0u, v, 0xB1, 0xF, 0xF, false);
+        const auto sw = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        v = sw[0] + sw[1];
+        own[i & 3] = (i >> 2) == sub ? v : own[i & 3];
     }
-    if ((t & 33) == 0) {
+    {
         const int yy = (y0 >> 1) + y2, zz = (z0 >> 1) + z2;
 #pragma unroll
-        for (int i = 0; i < H; ++i) {
-            sum[0][(z2 * H + y2) * H + i] = pair[i];
-            const int xx = (x0 >> 1) + i;
+        for (int j = 0; j < 4; ++j) {
+            const int i = 4 * sub + j, xx = (x0 >> 1) + i;
+            sum[0][(z2 * H + y2) * H + i] = own[j];
             if (in_grid(g2, zz, yy, xx)) {
-                out.cnt[2][cell_index(g2, zz, yy, xx)] = pair[i];
+                out.cnt[2][cell_index(g2, zz, yy, xx)] = own[j];
                 const uint32_t c = cell_class(g2, zz, yy, xx);
-                if (c) add(2, c, pair[i]);
+                if (c) add(2, c, own[j]);
             }
         }
     }
@@ -221,19 +224,37 @@ struct FinishArgs {
     KgenSeg seg[kMaxSegs];
 };
 
-// The image-window sums of Aff_1^l and Aff_2^l (global means), one wave per
-// level, one lane per boundary class: S = sum_p sum_o sum_c w[c][o] i_c(p + o),
-// the image solid outside the grid.  With q = p + o the in-grid part is
-// sum over classes of (class sum of i_c) times W_c(class) = sum of w[c][o] over
-// the o with q - o in the grid; the out-of-grid part is sum_o w[solid][o] (n -
-// #{p : p + o in the grid}).
-__device__ __forceinline__ void aff_scalars(const FinishArgs& a) {
-    __shared__ double tsh[2][kBlock / 64];
+// The image-window sums of Aff_1^l and Aff_2^l (global means), one block per
+// level, one wave per sum, one lane per boundary class: S = sum_p sum_o sum_c
+// w[c][o] i_c(p + o), the image solid outside the grid.  With q = p + o the
+// in-grid part is sum over classes of (class sum of i_c) times W_c(class) = sum
+// of w[c][o] over the o with q - o in the grid; the out-of-grid part is sum_o
+// w[solid][o] (n - #{p : p + o in the grid}).  The weights go through LDS: read
+// one by one from memory by a single block for all levels, their latencies were
+// the length of the whole kernel (22 us).
+__device__ __forceinline__ void aff_scalars(const FinishArgs& a, int s) {
+    __shared__ double tsh[2][kBlock / 64], w_s[2][3 * kTaps];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const Grid g{a.g.nz >> s, a.g.ny >> s, a.g.nx >> s};
+    const uint32_t c = (uint32_t)lane;
+    const uint32_t k0 = c ? a.cls->n[s][c][0] : 0u, k1 = c ? a.cls->n[s][c][1] : 0u;
+    if (threadIdx.x < 2 * 3 * kTaps) {
+        const int k = (int)threadIdx.x / (3 * kTaps), e = (int)threadIdx.x % (3 * kTaps);
+        w_s[k][e] = (&a.aff[2 * s + k].w[0][0])[e];
+    }
     double tf = 0.0, ta = 0.0;   // fluid and air cells of the grid (exact integers)
-    for (int b = threadIdx.x; b < a.pyr; b += kBlock) {
-        tf += (double)a.tot[b].x;
-        ta += (double)a.tot[b].y;
+    for (int b0 = 0; b0 < a.pyr; b0 += 4 * kBlock) {
+        uint2 t[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int b = b0 + u * kBlock + (int)threadIdx.x;
+            t[u] = b < a.pyr ? a.tot[b] : uint2{0u, 0u};
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            tf += (double)t[u].x;
+            ta += (double)t[u].y;
+        }
     }
     tf = wave_sum(tf);
     ta = wave_sum(ta);
@@ -242,63 +263,54 @@ __device__ __forceinline__ void aff_scalars(const FinishArgs& a) {
         tsh[1][wv] = ta;
     }
     __syncthreads();
+    if (wv >= 2) return;
     tf = ta = 0.0;
 #pragma unroll
     for (int i = 0; i < kBlock / 64; ++i) {
         tf += tsh[0][i];
         ta += tsh[1][i];
     }
-    for (int l = 1 + wv; l < a.L; l += kBlock / 64) {
-        const int s = l - 1;
-        const Grid g{a.g.nz >> s, a.g.ny >> s, a.g.nx >> s};
-        const double full = (double)(1u << (3 * s)), n = (double)ncells(g);
-        const uint32_t c = (uint32_t)lane;
-        double n0 = c ? (double)a.cls->n[s][c][0] : 0.0, n1 = c ? (double)a.cls->n[s][c][1] : 0.0;
-        const double b0 = wave_sum(n0), b1 = wave_sum(n1);
-        if (c == 0) {
-            n0 = tf - b0;
-            n1 = ta - b1;
-        }
-        const double inv = 1.0 / full, i0 = n0 * inv, i1 = n1 * inv,
-                     i2 = (class_cells(g, c) * full - n0 - n1) * inv;
-        double S[2] = {0.0, 0.0};
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const AffW* w = a.aff + 2 * s + k;
-            double W0 = 0.0, W1 = 0.0, W2 = 0.0;
-            for (int o = 0; o < kTaps; ++o) {
-                const bool in = class_sees(c, o);
-                W0 += in ? w->w[0][o] : 0.0;
-                W1 += in ? w->w[1][o] : 0.0;
-                W2 += in ? w->w[2][o] : 0.0;
-            }
-            double v = i0 * W0 + i1 * W1 + i2 * W2;
-            if (lane < kTaps) {   // the solid padding, one offset per lane
-                const int o = lane;
-                const double in = (double)max(g.nz - abs(o / 9 - 1), 0) * (double)max(g.ny - abs((o / 3) % 3 - 1), 0) *
-                                  (double)max(g.nx - abs(o % 3 - 1), 0);
-                v += w->w[2][o] * (n - in);
-            }
-            S[k] = wave_sum(v);
-        }
-        if (lane == 0) {
-            a.st->c1[s] = a.aff_b[2 * s] + S[0] / (27.0 * n);
-            a.st->c2[s] = a.aff_b[2 * s + 1] + S[1] / (27.0 * n);
-        }
+    const double full = (double)(1u << (3 * s)), n = (double)ncells(g);
+    double n0 = (double)k0, n1 = (double)k1;
+    const double b0 = wave_sum(n0), b1 = wave_sum(n1);
+    if (c == 0) {
+        n0 = tf - b0;
+        n1 = ta - b1;
     }
+    const double inv = 1.0 / full, i0 = n0 * inv, i1 = n1 * inv, i2 = (class_cells(g, c) * full - n0 - n1) * inv;
+    const double* w = w_s[wv];
+    double W0 = 0.0, W1 = 0.0, W2 = 0.0;
+#pragma unroll 9
+    for (int o = 0; o < kTaps; ++o) {
+        const bool in = class_sees(c, o);
+        W0 += in ? w[o] : 0.0;
+        W1 += in ? w[kTaps + o] : 0.0;
+        W2 += in ? w[2 * kTaps + o] : 0.0;
+    }
+    double v = i0 * W0 + i1 * W1 + i2 * W2;
+    if (lane < kTaps) {   // the solid padding, one offset per lane
+        const int o = lane;
+        const double in = (double)max(g.nz - abs(o / 9 - 1), 0) * (double)max(g.ny - abs((o / 3) % 3 - 1), 0) *
+                          (double)max(g.nx - abs(o % 3 - 1), 0);
+        v += w[2 * kTaps + o] * (n - in);
+    }
+    const double S = wave_sum(v);
+    if (lane == 0) (wv == 0 ? a.st->c1 : a.st->c2)[s] = a.aff_b[2 * s + wv] + S / (27.0 * n);
 }
 
-// Taps t0 .. t0 + TG of the cells of block b of a segment, in double: the
-// tap group is uniform in the block, so its weights are scalar loads, and a
-// thread reads the 27 window cells of its cell once for the TG taps.  TG = 1
-// spreads a level of few cells over 27 times as many threads.
+// Taps t0 .. t0 + TG of the cells of block b of a segment, in double: a thread
+// reads the 27 window cells of its cell once for the TG taps.  TG = 1 spreads a
+// level of few cells over 27 times as many threads.  The block's weights go
+// through LDS (w_s): as scalar loads, 500 doubles of them for TG = 9, each
+// waited for in turn (40 x 56 x 72 in FP64: 38 us).
+constexpr int kGenTaps = 9;
+
 template <class T, bool L1, int TG>
-__device__ __forceinline__ void kgen_taps(const KgenSeg& sg, int b) {
-    static_assert(kTaps % TG == 0, "whole tap groups");
+__device__ __forceinline__ void kgen_taps(const KgenSeg& sg, int b, double2* w_s) {
+    static_assert(kTaps % TG == 0 && TG <= kGenTaps, "whole tap groups");
     const Grid g = sg.g;
     const int n = (int)ncells(g), nb = (n + kBlock - 1) / kBlock;
-    const int t0 = (b / nb) * TG, p = (b % nb) * kBlock + (int)threadIdx.x;
-    if (p >= n) return;
+    const int t0 = (b / nb) * TG, p = min((b % nb) * kBlock + (int)threadIdx.x, n - 1);
     const CConvW<double>* __restrict__ w = sg.w;
     const int x = p % g.nx, y = p / g.nx % g.ny, z = p / (g.nx * g.ny);
     uint32_t v[kTaps];
@@ -307,35 +319,46 @@ __device__ __forceinline__ void kgen_taps(const KgenSeg& sg, int b) {
         const int qz = z + o / 9 - 1, qy = y + (o / 3) % 3 - 1, qx = x + o % 3 - 1;
         const bool in = in_grid(g, qz, qy, qx);
         const size_t q = in ? cell_index(g, qz, qy, qx) : 0;
-        if (L1) v[o] = in ? (uint32_t)static_cast<const uint8_t*>(sg.img)[q] : (uint32_t)kSolid;
-        else v[o] = in ? static_cast<const uint32_t*>(sg.img)[q] : 0u;
+        if (L1) v[o] = *at_or(static_cast<const uint8_t*>(sg.img), q, in, g_pad_solid);
+        else v[o] = *at_or(static_cast<const uint32_t*>(sg.img), q, in, pad_zero<uint32_t>());
+    }
+    for (int i = threadIdx.x; i < kTaps * TG; i += kBlock) {
+        const int o = i / TG, u = i % TG;
+        w_s[i] = double2{w->D[o][t0 + u][0], w->D[o][t0 + u][1]};
     }
     double K[TG];
 #pragma unroll
     for (int u = 0; u < TG; ++u) K[u] = w->C[t0 + u];
+    __syncthreads();
 #pragma unroll
     for (int o = 0; o < kTaps; ++o) {
         uint32_t c0, c1;
         counts_of<L1>(v[o], c0, c1);
         const double n0 = (double)c0, n1 = (double)c1;
 #pragma unroll
-        for (int u = 0; u < TG; ++u) K[u] = fma(w->D[o][t0 + u][0], n0, fma(w->D[o][t0 + u][1], n1, K[u]));
+        for (int u = 0; u < TG; ++u) {
+            const double2 d = w_s[o * TG + u];
+            K[u] = fma(d.x, n0, fma(d.y, n1, K[u]));
+        }
     }
     T* out = static_cast<T*>(sg.out);
+    if ((b % nb) * kBlock + (int)threadIdx.x < n) {
 #pragma unroll
-    for (int u = 0; u < TG; ++u) out[(size_t)(t0 + u) * n + p] = (T)K[u];
+        for (int u = 0; u < TG; ++u) out[(size_t)(t0 + u) * n + p] = (T)K[u];
+    }
 }
 
-// Block 0: the Aff scalars.  The others: the stored kernels of the small
-// levels, segment by segment, so that all of them overlap.  KM: the matrix-core
-// form of the float segments of kind kGenMfma.
+// Blocks 0 .. L - 2: the Aff scalars of a level.  The others: the stored kernels,
+// segment by segment, so that all of them overlap.  KM: the matrix-core form of
+// the float segments of kind kGenMfma.
 template <class T, int KM>
-__global__ __launch_bounds__(kBlock) void k_setup_finish(FinishArgs a) {
-    int b = (int)blockIdx.x - 1;
+__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(4) void k_setup_finish(FinishArgs a) {
+    int b = (int)blockIdx.x - (a.L - 1);
     if (b < 0) {
-        aff_scalars(a);
+        aff_scalars(a, (int)blockIdx.x);
         return;
     }
+    __shared__ double2 w_s[kTaps * kGenTaps];
     int i = 0;
     while (i < a.nseg - 1 && b >= a.seg[i].blocks) b -= a.seg[i++].blocks;
     const KgenSeg sg = a.seg[i];
@@ -345,11 +368,11 @@ __global__ __launch_bounds__(kBlock) void k_setup_finish(FinishArgs a) {
             else kgen_mfma<KM, false>(sg.img, sg.g, sg.wm, static_cast<float*>(sg.out), b, sg.blocks);
         }
     } else if (sg.kind == kGenTap9) {
-        if (sg.l1) kgen_taps<T, true, 9>(sg, b);
-        else kgen_taps<T, false, 9>(sg, b);
+        if (sg.l1) kgen_taps<T, true, kGenTaps>(sg, b, w_s);
+        else kgen_taps<T, false, kGenTaps>(sg, b, w_s);
     } else {
-        if (sg.l1) kgen_taps<T, true, 1>(sg, b);
-        else kgen_taps<T, false, 1>(sg, b);
+        if (sg.l1) kgen_taps<T, true, 1>(sg, b, w_s);
+        else kgen_taps<T, false, 1>(sg, b, w_s);
     }
 }
 

@@ -735,14 +735,37 @@ __global__ __launch_bounds__(kBlock) void k_aff_grad(AffGradArgs a, double* __re
     __shared__ double sh[4][kBlock / 64], dc_s[2];
     __shared__ double n_s[2][kClasses];
     const int s = blockIdx.x, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    double v[4] = {0.0, 0.0, 0.0, 0.0};    // dL/dc1, dL/dc2, fluid and air cells of the grid
-    for (int b = threadIdx.x; b < a.nparts[s]; b += kBlock) {
-        v[0] += a.dc[s][b];
-        v[1] += a.dc[s][a.nparts[s] + b];
+    // every load that needs no sum goes out first
+    const int o = min((int)threadIdx.x, kTaps - 1);
+    const uint32_t cl = (uint32_t)lane;
+    const uint32_t k0 = cl ? a.cls->n[s][cl][0] : 0u, k1 = cl ? a.cls->n[s][cl][1] : 0u;
+    double* g1 = grad + a.ga[s];
+    double* g2 = g1 + 3 * kTaps + 1;
+    double old1[4], old2[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        old1[c] = g1[c < 3 ? c * kTaps + o : 3 * kTaps];
+        old2[c] = g2[c < 3 ? c * kTaps + o : 3 * kTaps];
     }
-    for (int b = threadIdx.x; b < a.pyr; b += kBlock) {
-        v[2] += (double)a.tot[b].x;
-        v[3] += (double)a.tot[b].y;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};    // dL/dc1, dL/dc2, fluid and air cells of the grid
+    const int np = a.nparts[s];
+    for (int b0 = 0; b0 < max(np, a.pyr); b0 += 2 * kBlock) {
+        double d0[2], d1[2];
+        uint2 t[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int b = b0 + u * kBlock + (int)threadIdx.x;
+            d0[u] = b < np ? a.dc[s][b] : 0.0;
+            d1[u] = b < np ? a.dc[s][np + b] : 0.0;
+            t[u] = b < a.pyr ? a.tot[b] : uint2{0u, 0u};
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            v[0] += d0[u];
+            v[1] += d1[u];
+            v[2] += (double)t[u].x;
+            v[3] += (double)t[u].y;
+        }
     }
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
@@ -751,7 +774,6 @@ __global__ __launch_bounds__(kBlock) void k_aff_grad(AffGradArgs a, double* __re
     }
     __syncthreads();
     if (threadIdx.x < kClasses) {          // wave 0: the class sums, class 0 the rest of the grid
-        const uint32_t c = threadIdx.x;
         double t[4];
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
@@ -759,18 +781,18 @@ __global__ __launch_bounds__(kBlock) void k_aff_grad(AffGradArgs a, double* __re
 #pragma unroll
             for (int i = 0; i < kBlock / 64; ++i) t[w] += sh[w][i];
         }
-        const double n0 = c ? (double)a.cls->n[s][c][0] : 0.0, n1 = c ? (double)a.cls->n[s][c][1] : 0.0;
+        const double n0 = (double)k0, n1 = (double)k1;
         const double b0 = wave_sum(n0), b1 = wave_sum(n1);
-        n_s[0][c] = c ? n0 : t[2] - b0;
-        n_s[1][c] = c ? n1 : t[3] - b1;
-        if (c < 2) dc_s[c] = t[c];
+        n_s[0][cl] = cl ? n0 : t[2] - b0;
+        n_s[1][cl] = cl ? n1 : t[3] - b1;
+        if (cl < 2) dc_s[cl] = t[cl];
     }
     __syncthreads();
+    if (threadIdx.x >= kTaps) return;
     const Grid g{a.g.nz >> s, a.g.ny >> s, a.g.nx >> s};
     const double n = (double)ncells(g), inv = 1.0 / (double)(1u << (3 * s)), n27 = 27.0 * n;
-    const int o = threadIdx.x;
-    if (o >= kTaps) return;
     double S[3] = {0.0, 0.0, 0.0};
+#pragma unroll 16
     for (uint32_t c = 0; c < kClasses; ++c) {
         const bool in = class_sees(c, o);
         S[0] += in ? n_s[0][c] : 0.0;
@@ -780,53 +802,109 @@ __global__ __launch_bounds__(kBlock) void k_aff_grad(AffGradArgs a, double* __re
     S[1] *= inv;
     S[2] = n - S[0] - S[1];
     const double d0 = dc_s[0], d1 = dc_s[1];
-    double* g1 = grad + a.ga[s];
-    double* g2 = g1 + 3 * kTaps + 1;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        g1[c * kTaps + o] += d0 * S[c] / n27;
-        g2[c * kTaps + o] += d1 * S[c] / n27;
+        g1[c * kTaps + o] = old1[c] + d0 * S[c] / n27;
+        g2[c * kTaps + o] = old2[c] + d1 * S[c] / n27;
     }
     if (o == 0) {   // Bbar
-        g1[3 * kTaps] += d0;
-        g2[3 * kTaps] += d1;
+        g1[3 * kTaps] = old1[3] + d0;
+        g2[3 * kTaps] = old2[3] + d1;
     }
 }
 
 // ---------------------------------------------------------------------------
 // the loss
 // ---------------------------------------------------------------------------
-// Training loss of one system: res = b - A y on fluid cells; partial ||res||^2,
-// and A res (whose scaled negative is dL/dy) written to ares.
+// The mixed-BC 7-point rows (Sec. "Spatial Discretization") of kZRun cells of one
+// column each: row(z, v, A v) for z = z0 .. z0 + kZRun - 1 inside the grid, v
+// the cell's value and label l.  A thread reads a cell and its four x/y
+// neighbours straight from memory (the neighbours' lines are in the caches; the
+// z neighbours are the column's own cells), all loads in flight: staged tiles
+// with a full halo read 2.5 cells per cell behind two barriers (128^3: 22 and
+// 18.5 us for the two kernels below).
+constexpr int kZRun = 4;
+
+template <class T, class Row>
+__device__ __forceinline__ void seven_point_run(const uint8_t* __restrict__ lab, const T* __restrict__ v, Grid g, int x,
+                                                int y, int z0, Row row) {
+    constexpr int N = kZRun + 2;
+    T c[N], nb[kZRun][4];
+    uint8_t lc[N], ln[kZRun][4];
+    const bool col = x < g.nx && y < g.ny;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int z = z0 - 1 + i;
+        const bool in = col && z >= 0 && z < g.nz;
+        const size_t q = in ? cell_index(g, z, y, x) : 0;
+        c[i] = *at_or(v, q, in, pad_zero<T>());
+        lc[i] = *at_or(lab, q, in, g_pad_solid);
+    }
+#pragma unroll
+    for (int i = 0; i < kZRun; ++i)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int yy = y + (k == 0 ? -1 : k == 1 ? 1 : 0), xx = x + (k == 2 ? -1 : k == 3 ? 1 : 0);
+            const bool in = col && in_grid(g, z0 + i, yy, xx);
+            const size_t q = in ? cell_index(g, z0 + i, yy, xx) : 0;
+            nb[i][k] = *at_or(v, q, in, pad_zero<T>());
+            ln[i][k] = *at_or(lab, q, in, g_pad_solid);
+        }
+#pragma unroll
+    for (int i = 0; i < kZRun; ++i) {
+        if (!col || z0 + i >= g.nz) continue;
+        T a = T(0);
+        if (lc[i + 1] == kFluid) {   // neighbours in the order z-, z+, y-, y+, x-, x+
+            const uint8_t l[6] = {lc[i], lc[i + 2], ln[i][0], ln[i][1], ln[i][2], ln[i][3]};
+            const T n[6] = {c[i], c[i + 2], nb[i][0], nb[i][1], nb[i][2], nb[i][3]};
+            int cnt = 0;
+            T s = T(0);
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                cnt += l[k] != kSolid;
+                if (l[k] == kFluid) s += n[k];
+            }
+            a = (T)cnt * c[i + 1] - s;
+        }
+        row(z0 + i, lc[i + 1], a);
+    }
+}
+
+// Runs of a grid: 64 x 4 columns by kZRun planes per block.
+__host__ __device__ inline int seven_point_blocks(Grid g) {
+    return ((g.nx + PX - 1) / PX) * ((g.ny + PY - 1) / PY) * ((g.nz + kZRun - 1) / kZRun);
+}
+
+template <class F>
+__device__ __forceinline__ void seven_point_items(Grid g, F f) {
+    const int ncx = (g.nx + PX - 1) / PX, ncy = (g.ny + PY - 1) / PY, n = seven_point_blocks(g);
+    for (TileSpan sp = tile_span(n); sp.t0 < sp.t1; sp.t0 += sp.step)
+        f(sp.t0 % ncx * PX + (int)threadIdx.x % PX, sp.t0 / ncx % ncy * PY + (int)threadIdx.x / PX,
+          sp.t0 / (ncx * ncy) * kZRun);
+}
+
+// Training loss of one system: res = b - A y on fluid cells; partial ||res||^2.
 template <class T>
 __global__ __launch_bounds__(kBlock) void k_train_residual(const uint8_t* __restrict__ lab, Grid g,
                                                            const T* __restrict__ b, const T* __restrict__ y,
                                                            T* __restrict__ res, double* partials) {
-    __shared__ uint32_t lab_s[kHaloP];
-    __shared__ T y_s[kHaloP];
-    const Tiles tl = tiles_of(g);
-    const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
-    const int base = halo_base(lx, ly, lz);
     double v[kRedWidth] = {0.0, 0.0, 0.0, 0.0};
-    for (TileSpan sp = tile_span(tl.count()); sp.t0 < sp.t1; sp.t0 += sp.step) {
-        const TileOrigin o = tile_origin(sp.t0, tl);
-        __syncthreads();
-        stage_image<true>(lab_s, lab, g, o);
-        for (int i = threadIdx.x; i < kHalo; i += kBlock) {
-            const int hx = i % HX, hy = (i / HX) % HY, hz = i / (HX * HY);
-            const int xx = o.x0 + hx - 1, yy = o.y0 + hy - 1, zz = o.z0 + hz - 1;
-            y_s[i] = in_grid(g, zz, yy, xx) ? y[cell_index(g, zz, yy, xx)] : T(0);
+    seven_point_items(g, [&](int x, int yy, int z0) {
+        T bv[kZRun];
+#pragma unroll
+        for (int i = 0; i < kZRun; ++i) {
+            const bool in = x < g.nx && yy < g.ny && z0 + i < g.nz;
+            bv[i] = *at_or(b, in ? cell_index(g, z0 + i, yy, x) : 0, in, pad_zero<T>());
         }
-        __syncthreads();
-        const int xx = o.x0 + lx, yy = o.y0 + ly, zz = o.z0 + lz;
-        if (in_grid(g, zz, yy, xx)) {
-            const size_t idx = cell_index(g, zz, yy, xx);
-            T rv = T(0);
-            if (lab_s[base] == (uint32_t)kFluid) rv = b[idx] - apply_A<T, T, uint32_t>(lab_s, y_s, base, HX, HX * HY);
-            res[idx] = rv;
+        seven_point_run<T>(lab, y, g, x, yy, z0, [&](int z, uint8_t l, T a) {
+            T bz = bv[0];
+#pragma unroll
+            for (int i = 1; i < kZRun; ++i) bz = z == z0 + i ? bv[i] : bz;
+            const T rv = l == kFluid ? bz - a : T(0);
+            res[cell_index(g, z, yy, x)] = rv;
             v[0] += (double)rv * (double)rv;
-        }
-    }
+        });
+    });
     block_partials<kBlock>(v, partials);
 }
 
@@ -835,31 +913,11 @@ __global__ __launch_bounds__(kBlock) void k_train_residual(const uint8_t* __rest
 template <class T>
 __global__ __launch_bounds__(kBlock) void k_train_gy(const uint8_t* __restrict__ lab, Grid g, const T* __restrict__ res,
                                                      const State* st, T* __restrict__ gy, double w) {
-    __shared__ uint32_t lab_s[kHaloP];
-    __shared__ T r_s[kHaloP];
     const T inv = (T)(-w / sqrt(st->rr));
-    const Tiles tl = tiles_of(g);
-    const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
-    const int base = halo_base(lx, ly, lz);
-    for (TileSpan sp = tile_span(tl.count()); sp.t0 < sp.t1; sp.t0 += sp.step) {
-        const TileOrigin o = tile_origin(sp.t0, tl);
-        __syncthreads();
-        stage_image<true>(lab_s, lab, g, o);
-        for (int i = threadIdx.x; i < kHalo; i += kBlock) {
-            const int hx = i % HX, hy = (i / HX) % HY, hz = i / (HX * HY);
-            const int xx = o.x0 + hx - 1, yy = o.y0 + hy - 1, zz = o.z0 + hz - 1;
-            r_s[i] = in_grid(g, zz, yy, xx) ? res[cell_index(g, zz, yy, xx)] : T(0);
-        }
-        __syncthreads();
-        const int xx = o.x0 + lx, yy = o.y0 + ly, zz = o.z0 + lz;
-        if (in_grid(g, zz, yy, xx)) gy[cell_index(g, zz, yy, xx)] = inv * apply_A<T, T, uint32_t>(lab_s, r_s, base, HX, HX * HY);
-    }
-}
-
-// acc = 0 (set) or acc += w ||res|| of the system just evaluated (one thread).
-__global__ void k_loss_accumulate(const State* st, double* acc, double w, int set) {
-    const double v = w * sqrt(st->rr);
-    *acc = set ? 0.0 : *acc + v;
+    seven_point_items(g, [&](int x, int y, int z0) {
+        seven_point_run<T>(lab, res, g, x, y, z0,
+                           [&](int z, uint8_t, T a) { gy[cell_index(g, z, y, x)] = inv * a; });
+    });
 }
 
 }  // namespace nps

@@ -128,7 +128,8 @@ Plan make_plan(nps_dims d, int levels, int precision, bool all_stored = false, b
             continue;
         }
         if (n <= (size_t)kStoreMaxCells) p.km[l] = kStored;
-        else if (precision == NPS_FP64 || l > kMfmaMaxLevel) p.km[l] = kVector;
+        else if (precision == NPS_FP64) p.km[l] = kMfmaF64;
+        else if (l > kMfmaMaxLevel) p.km[l] = kVector;
         else if (precision == NPS_FP32) p.km[l] = kMfmaBf16x3;
         else if (precision == NPS_MIXED_BF16) p.km[l] = kMfmaBf16;
         else p.km[l] = kMfmaF16;
@@ -583,8 +584,8 @@ int run_setup(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
         const Grid g = level_grid(d, l);
         const int grid = tile_grid(g);
         int8_t* md = mptr<int8_t>(ws, lay.wmode[l][0]);
-        if (l == 1 && is_mfma(plan.km[1])) continue;   // the marching kernels use the group modes
-        if (l > 1 && plan.km[l] == kStored) continue;   // a stored kernel takes no shortcut
+        if (l == 1 && is_mfma(plan.km[1])) continue;   // the level-1 kernels use the group modes
+        if (plan.km[l] == kStored) continue;            // a stored kernel takes no shortcut
         if (l == 1)
             NPS_TRY(launch("setup_wave_modes", (double)ncells(g), s, [&] {
                 k_wave_modes<true><<<grid, kBlock, 0, s>>>(img(l), g, 1u, md, mptr<int8_t>(ws, lay.wmode[l][1]));
@@ -597,16 +598,15 @@ int run_setup(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
     return NPS_OK;
 }
 
-// Kernel dispatch over the per-level KMode (MFMA modes exist for float only).
+// Kernel dispatch over the per-level KMode.
 template <class T, class F>
 int with_kmode(int km, F&& f) {
-    switch (km) {
-        case kVector: return f(std::integral_constant<int, kVector>());
-        case kStored: return f(std::integral_constant<int, kStored>());
-        default: break;
-    }
-    if constexpr (std::is_same_v<T, float>) {
+    if (km == kStored) return f(std::integral_constant<int, kStored>());
+    if constexpr (std::is_same_v<T, double>) {
+        if (km == kMfmaF64) return f(std::integral_constant<int, kMfmaF64>());
+    } else {
         switch (km) {
+            case kVector: return f(std::integral_constant<int, kVector>());
             case kMfmaBf16x3: return f(std::integral_constant<int, kMfmaBf16x3>());
             case kMfmaBf16: return f(std::integral_constant<int, kMfmaBf16>());
             case kMfmaF16: return f(std::integral_constant<int, kMfmaF16>());
@@ -675,9 +675,22 @@ int run_coarse(const nps_net* net, nps_dims d, const Plan& plan, const Layout& l
             v.mx = div_magic(g.nx);
             v.mxy = div_magic(g.nx * g.ny);
             off += 2 * pc;
-            a.k1[l] = cptr<T>(ws, lay.k1[l]);
-            a.k2[l] = l < L ? cptr<T>(ws, lay.k2[l]) : nullptr;
             cells += ncells(g);
+        }
+        a.k1 = cptr<T>(ws, lay.k1[plan.lb]);
+        if (plan.lb < L) {
+            // the sections of the levels past lb follow each other in the workspace
+            const size_t base = lay.k1[plan.lb + 1];
+            a.k2 = cptr<T>(ws, lay.k2[plan.lb]);
+            a.ks = cptr<T>(ws, base);
+            size_t end = 0;
+            for (int l = plan.lb + 1; l <= L; ++l) {
+                a.ko1[l] = (int)((lay.k1[l] - base) / sizeof(T));
+                if (l < L) a.ko2[l] = (int)((lay.k2[l] - base) / sizeof(T));
+                end = lay.k1[l] + align256(sizeof(T) * kTaps * ncells(level_grid(d, l)));
+            }
+            a.ksmall = (int)((end - base) / 16);
+            if (end - base > sizeof(T) * (size_t)kBottomK<T>) return fail(NPS_EINVAL, "bottom kernels exceed their buffer");
         }
         a.used = off;
         a.rin = cptr<T>(ws, lay.rb[plan.lb]);

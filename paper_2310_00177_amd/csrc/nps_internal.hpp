@@ -30,7 +30,7 @@ constexpr int kPieces = 3;            // bf16 pieces of an fp32 weight (sum is e
 enum Label : uint8_t { kFluid = 0, kAir = 1, kSolid = 2 };
 
 // How a level generates its per-cell kernels.
-enum KMode : int { kVector = 0, kStored = 1, kMfmaBf16x3 = 2, kMfmaBf16 = 3, kMfmaF16 = 4 };
+enum KMode : int { kVector = 0, kStored = 1, kMfmaBf16x3 = 2, kMfmaBf16 = 3, kMfmaF16 = 4, kMfmaF64 = 5 };
 
 struct Grid {
     int nz, ny, nx;

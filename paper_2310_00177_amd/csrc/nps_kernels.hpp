@@ -35,9 +35,10 @@ namespace nps {
 // 512 / n so that n waves of it fit per SIMD.
 #define NPS_WAVES_PER_EU(n) __attribute__((amdgpu_waves_per_eu(n)))
 
-// The three-piece bf16 weights of the FP32 MFMA path need more registers.
-// (Higher floors make the CConv kernels spill and run slower.)
-constexpr int waves_floor(int km) { return km == kMfmaBf16x3 ? 3 : 4; }
+// The three-piece bf16 weights of the FP32 MFMA path need more registers, and
+// so do the double weights of the FP64 one and 27 preloaded doubles (higher
+// floors make the CConv kernels spill and run slower).
+constexpr int waves_floor(int km, size_t word) { return km == kMfmaBf16x3 ? 3 : word == 8 ? 2 : 4; }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
@@ -364,12 +365,11 @@ __device__ __forceinline__ T cconv_stored(const T* r_s, int base, const T (&kv)[
 }
 
 // The stored kernel of the thread's cell, loaded at the start of a tile so
-// that its latency overlaps the staging instead of following it.  Done by
-// the float kernels of levels >= 2 only: 27 doubles do not stay in
-// registers beside the staging, nor 27 floats beside the level-1 staging
-// (the others load it where the CConv needs it).
-template <class T, int KM, bool COARSE>
-constexpr bool kpre_on = KM == kStored && COARSE && sizeof(T) == 4;
+// that its latency overlaps the staging instead of following it (the levels
+// that store their kernels in a solve have at most one tile per compute unit,
+// so the registers cost nothing).
+template <int KM>
+constexpr bool kpre_on = KM == kStored;
 
 template <class T, bool ON>
 struct KPre {};
@@ -512,27 +512,113 @@ __device__ __forceinline__ float cconv_mfma(const uint32_t* feat_s, const float*
     return mine;
 }
 
+// FP64: the same on v_mfma_f64_16x16x4_f64: K^T[tap][cell] over 14 steps of 4
+// features (54 counts, the constant 1, a zero).  Lane (k, n) supplies feature
+// 4 ks + k of tap 16 mb + n (A, straight from the count form) and of cell n (B:
+// window position 2 ks + k / 2, channel k % 2), and holds taps 16 mb + 4 i + k of
+// cell n.  On the vector ALU the 1458 multiply-adds of a cell and their weights,
+// read as scalars, took three to four times as long (40 x 56 x 72: 37 us down, 30
+// us up at level 1).
+template <>
+struct MfmaCtx<kMfmaF64> {
+    static constexpr int kSteps = 14;
+    double a[2][kSteps];
+    int base0;
+    int toff[8];    // LDS offsets of the lane's taps
+    bool air, hi;   // the lane's channel; the second window position of a step
+    bool one, none; // lane group 2, 3: the constant and the zero of the last step
+};
+
+__device__ __forceinline__ MfmaCtx<kMfmaF64> mfma64_ctx(const CConvW<double>* __restrict__ w, int lz) {
+    MfmaCtx<kMfmaF64> c;
+    const int lane = threadIdx.x & 63, k = lane >> 4, n = lane & 15;
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int ks = 0; ks < MfmaCtx<kMfmaF64>::kSteps; ++ks) {
+            const int t = 16 * mb + n, f = 4 * ks + k, tc = min(t, kTaps - 1), fc = min(f, 2 * kTaps - 1);
+            const double v = f == 2 * kTaps ? w->C[tc] : w->D[fc >> 1][tc][fc & 1];
+            c.a[mb][ks] = t < kTaps && f <= 2 * kTaps ? v : 0.0;
+        }
+    c.base0 = halo_base(n, 0, lz);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) c.toff[j] = halo_off_rt(min(16 * (j >> 2) + 4 * (j & 3) + k, kTaps - 1));
+    c.air = k & 1;
+    c.hi = k & 2;
+    c.one = k == 2;
+    c.none = k == 3;
+    return c;
+}
+
+// The sum over the four lane groups of four groups' values (lane (k, n) receives group k's), as doubles.
+__device__ __forceinline__ double reduce_scatter4(const double (&p)[4]) {
+    auto swap32 = [](double a, double b) {
+        const uint64_t x = __double_as_longlong(a), y = __double_as_longlong(b);
+        const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+        return __longlong_as_double((long long)((uint64_t)hi[0] << 32 | lo[0])) +
+               __longlong_as_double((long long)((uint64_t)hi[1] << 32 | lo[1]));
+    };
+    const double a0 = swap32(p[0], p[2]), a1 = swap32(p[1], p[3]);
+    const uint64_t x = __double_as_longlong(a0), y = __double_as_longlong(a1);
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+    return __longlong_as_double((long long)((uint64_t)hi[0] << 32 | lo[0])) +
+           __longlong_as_double((long long)((uint64_t)hi[1] << 32 | lo[1]));
+}
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+// All 64 lanes must call it; returns the output of the lane's own cell.
+template <bool L1>
+__device__ __forceinline__ double cconv_mfma64(const uint32_t* img_s, const double* r_s, const MfmaCtx<kMfmaF64>& c) {
+    double part[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int bq = c.base0 + q * HX;
+        f64x4 acc[2] = {f64x4{0.0, 0.0, 0.0, 0.0}, f64x4{0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+        for (int ks = 0; ks < MfmaCtx<kMfmaF64>::kSteps; ++ks) {
+            const int o0 = halo_off(2 * ks), o1 = halo_off(2 * ks + 1 < kTaps ? 2 * ks + 1 : kTaps - 1);
+            uint32_t c0, c1;
+            counts_of<L1>(img_s[bq + (c.hi ? o1 : o0)], c0, c1);
+            double b = (double)(c.air ? c1 : c0);
+            if (ks == MfmaCtx<kMfmaF64>::kSteps - 1) b = c.one ? 1.0 : c.none ? 0.0 : b;
+#pragma unroll
+            for (int mb = 0; mb < 2; ++mb) acc[mb] = __builtin_amdgcn_mfma_f64_16x16x4f64(c.a[mb][ks], b, acc[mb], 0, 0, 0);
+        }
+        double s = 0.0;
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)   // taps past 26: their K is zero
+                s = fma(acc[mb][i], r_s[bq + c.toff[4 * mb + i]], s);
+        part[q] = s;
+    }
+    return reduce_scatter4(part);
+}
+
+// The MFMA context of a kernel mode (nothing for the others).
+template <class T, int KM>
+__device__ __forceinline__ MfmaCtx<KM> cconv_ctx(const CConvW<T>* __restrict__ w, const MfmaW* __restrict__ wm, int lz) {
+    if constexpr (KM == kMfmaF64) return mfma64_ctx(w, lz);
+    else return mfma_ctx<KM>(wm, lz);
+}
+
 // One CConv output of the thread's cell (lx, ly, lz) for a wave-uniform mode.
-// kp: the preloaded stored kernel (PRE), else loaded here from kst.
+// kp: the preloaded stored kernel (PRE).
 template <class T, int KM, bool L1, bool PRE>
 __device__ __forceinline__ T cconv_any(int mode, bool active, const uint32_t* img_s, const uint32_t* feat_s,
                                        const T* r_s, int base, const CConvW<T>* __restrict__ w,
-                                       const MfmaCtx<KM>& mc, const T* __restrict__ kst, size_t n, size_t idx,
-                                       const KPre<T, PRE>& kp) {
+                                       const MfmaCtx<KM>& mc, const KPre<T, PRE>& kp) {
     if (mode == -3) return T(0);
     if (mode >= 0) return active ? cconv_pure<T>(r_s, base, w, mode) : T(0);
     if constexpr (KM == kStored) {
-        if (!active) return T(0);
-        if constexpr (PRE) {
-            return cconv_stored<T>(r_s, base, kp.kv);
-        } else {
-            T kv[kTaps];
-#pragma unroll
-            for (int t = 0; t < kTaps; ++t) kv[t] = kst[(size_t)t * n + idx];
-            return cconv_stored<T>(r_s, base, kv);
-        }
+        return active ? cconv_stored<T>(r_s, base, kp.kv) : T(0);
     } else if constexpr (KM == kVector) {
         return active ? cconv_vector<T, L1>(img_s, r_s, base, w) : T(0);
+    } else if constexpr (KM == kMfmaF64) {
+        return cconv_mfma64<L1>(img_s, r_s, mc);
     } else {
         static_assert(sizeof(T) == 4, "MFMA paths are float");
         return cconv_mfma<KM>(feat_s, reinterpret_cast<const float*>(r_s), mc);
@@ -953,7 +1039,7 @@ struct RL {    // network input and label of one haloed cell
 };
 
 template <class T, int KM>
-__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(3) void k_down_l1(
+__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM, sizeof(T))) void k_down_l1(
     const uint8_t* __restrict__ lab, Grid g, const T* __restrict__ r, T* __restrict__ x1, T* __restrict__ rnext,
     const CConvW<T>* __restrict__ w, const MfmaW* __restrict__ wm, const T* __restrict__ kst, const State* st,
     const int8_t* __restrict__ wmode) {
@@ -965,7 +1051,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(3) void k_down_l1(
     const size_t n = ncells(g);
     const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
     const int base = halo_base(lx, ly, lz);
-    const MfmaCtx<KM> mc = mfma_ctx<KM>(wm, lz);
+    const MfmaCtx<KM> mc = cconv_ctx<T, KM>(w, wm, lz);
     auto load = [&](int tile) {
         const TileOrigin o = tile_origin(tile, tl);
         return load_batch<kHalo, RL<T>>([&](int i) {
@@ -975,10 +1061,11 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(3) void k_down_l1(
     };
     tile_pipeline(tl.count(), load, [&](int tile, const auto& pre, auto prefetch) {
         const TileOrigin o = tile_origin(tile, tl);
-        const int wm_e = wave_mode_entry(wmode, tile, lz);
+        const int wm_e = KM == kStored ? 0 : wave_mode_entry(wmode, tile, lz);
         const int xx = o.x0 + lx, yy = o.y0 + ly, zz = o.z0 + lz;
         const bool active = in_grid(g, zz, yy, xx);
         const size_t idx = active ? cell_index(g, zz, yy, xx) : 0;
+        const auto kp = k_preload<T, kpre_on<KM>>(kst, n, idx);
         __syncthreads();
         put_batch(pre, [&](int i, RL<T> e) {
             r_s[i] = e.l == kFluid ? e.r : T(0);
@@ -987,9 +1074,8 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(3) void k_down_l1(
         });
         prefetch();
         __syncthreads();
-        const int mode = wave_mode<true>(wmode, wm_e, active, img_s, base, 1u, true, false);
-        const T out = cconv_any<T, KM, true>(mode, active, img_s, feat_s, r_s, base, w, mc, kst, n, idx,
-                                             KPre<T, false>{});
+        const int mode = KM == kStored ? -1 : wave_mode<true>(wmode, wm_e, active, img_s, base, 1u, true, false);
+        const T out = cconv_any<T, KM, true>(mode, active, img_s, feat_s, r_s, base, w, mc, kp);
         if (active) x1[idx] = out;
         out_s[threadIdx.x] = active ? out : T(0);
         __syncthreads();
@@ -1005,7 +1091,7 @@ struct CR {    // packed counts and network input of one haloed cell
 };
 
 template <class T, int KM, bool POOL>
-__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM)) void k_down(
+__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM, sizeof(T))) void k_down(
     const uint32_t* __restrict__ cnt, Grid g, uint32_t full, const T* __restrict__ rin, T* __restrict__ x1,
     T* __restrict__ rnext, const CConvW<T>* __restrict__ w, const MfmaW* __restrict__ wm, const T* __restrict__ kst,
     const State* st, const int8_t* __restrict__ wmode) {
@@ -1017,7 +1103,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM)) void k_do
     const size_t n = ncells(g);
     const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
     const int base = halo_base(lx, ly, lz);
-    const MfmaCtx<KM> mc = mfma_ctx<KM>(wm, lz);
+    const MfmaCtx<KM> mc = cconv_ctx<T, KM>(w, wm, lz);
     auto load = [&](int tile) {
         const TileOrigin o = tile_origin(tile, tl);
         return load_batch<kHalo, CR<T>>([&](int i) {
@@ -1027,11 +1113,11 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM)) void k_do
     };
     tile_pipeline(tl.count(), load, [&](int tile, const auto& pre, auto prefetch) {
         const TileOrigin o = tile_origin(tile, tl);
-        const int wm_e = wave_mode_entry(wmode, tile, lz);
+        const int wm_e = KM == kStored ? 0 : wave_mode_entry(wmode, tile, lz);
         const int xx = o.x0 + lx, yy = o.y0 + ly, zz = o.z0 + lz;
         const bool active = in_grid(g, zz, yy, xx);
         const size_t idx = active ? cell_index(g, zz, yy, xx) : 0;
-        const auto kp = k_preload<T, kpre_on<T, KM, true>>(kst, n, idx);
+        const auto kp = k_preload<T, kpre_on<KM>>(kst, n, idx);
         __syncthreads();
         put_batch(pre, [&](int i, CR<T> e) {
             img_s[i] = e.c;
@@ -1041,7 +1127,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM)) void k_do
         prefetch();
         __syncthreads();
         const int mode = KM == kStored ? -1 : wave_mode<false>(wmode, wm_e, active, img_s, base, full, false, false);
-        const T out = cconv_any<T, KM, false>(mode, active, img_s, feat_s, r_s, base, w, mc, kst, n, idx, kp);
+        const T out = cconv_any<T, KM, false>(mode, active, img_s, feat_s, r_s, base, w, mc, kp);
         if (active) x1[idx] = out;
         if (POOL) {
             out_s[threadIdx.x] = active ? out : T(0);
@@ -1198,7 +1284,7 @@ __device__ __forceinline__ void stage_image_interp(uint32_t* img_s, uint32_t* fe
 
 // x = c1 x1 + c2 CConv_2(Interp(xc), I) on one level l >= 2.
 template <class T, int KM>
-__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM)) void k_up(const uint32_t* __restrict__ cnt, Grid g, uint32_t full,
+__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM, sizeof(T))) void k_up(const uint32_t* __restrict__ cnt, Grid g, uint32_t full,
                                                const T* __restrict__ xc, const T* __restrict__ x1,
                                                T* __restrict__ xout, const CConvW<T>* __restrict__ w,
                                                const MfmaW* __restrict__ wm, const T* __restrict__ kst, int lvl,
@@ -1213,16 +1299,16 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM)) void k_up
     const size_t n = ncells(g);
     const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
     const int base = halo_base(lx, ly, lz);
-    const MfmaCtx<KM> mc = mfma_ctx<KM>(wm, lz);
+    const MfmaCtx<KM> mc = cconv_ctx<T, KM>(w, wm, lz);
     const InterpSlots isl = interp_slots();
     auto load = [&](int tile) { return load_image_interp<false, T>(cnt, xc, g, tile_origin(tile, tl)); };
     tile_pipeline(tl.count(), load, [&](int tile, const auto& pre, auto prefetch) {
         const TileOrigin o = tile_origin(tile, tl);
-        const int wm_e = wave_mode_entry(wmode, tile, lz);
+        const int wm_e = KM == kStored ? 0 : wave_mode_entry(wmode, tile, lz);
         const int xx = o.x0 + lx, yy = o.y0 + ly, zz = o.z0 + lz;
         const bool active = in_grid(g, zz, yy, xx);
         const size_t idx = active ? cell_index(g, zz, yy, xx) : 0;
-        const auto kp = k_preload<T, kpre_on<T, KM, true>>(kst, n, idx);
+        const auto kp = k_preload<T, kpre_on<KM>>(kst, n, idx);
         __syncthreads();
         put_image_interp<false, KM, T>(pre, img_s, feat_s, c_s);
         const T x1v = x1[idx];
@@ -1231,7 +1317,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM)) void k_up
         interp_tile<T>(r_s, c_s, g, o, isl);
         __syncthreads();
         const int mode = KM == kStored ? -1 : wave_mode<false>(wmode, wm_e, active, img_s, base, full, false, false);
-        const T x2 = cconv_any<T, KM, false>(mode, active, img_s, feat_s, r_s, base, w, mc, kst, n, idx, kp);
+        const T x2 = cconv_any<T, KM, false>(mode, active, img_s, feat_s, r_s, base, w, mc, kp);
         if (active) xout[idx] = c1 * x1v + c2 * x2;
         if (active && x2out) x2out[idx] = x2;
     }, st);
@@ -1242,7 +1328,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM)) void k_up
 // ad0.. (NPSDO: the stored A d_i of the previous directions; PCG: r; flexible
 // PCG: r and the previous residual).
 template <class T, int KM, bool HOOK>
-__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM)) void k_up_l1(
+__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM, sizeof(T))) void k_up_l1(
     const uint8_t* __restrict__ lab, Grid g, const T* __restrict__ xc, const T* __restrict__ x1,
     T* __restrict__ dhat, const CConvW<T>* __restrict__ w, const MfmaW* __restrict__ wm,
     const T* __restrict__ kst, const State* st, double* partials, const T* __restrict__ ad0,
@@ -1259,17 +1345,18 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM)) void k_up
     const size_t n = ncells(g);
     const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
     const int base = halo_base(lx, ly, lz);
-    const MfmaCtx<KM> mc = mfma_ctx<KM>(wm, lz);
+    const MfmaCtx<KM> mc = cconv_ctx<T, KM>(w, wm, lz);
     double v[kRedWidth] = {0.0, 0.0, 0.0, 0.0};
     const T* adp[kMaxOrtho] = {ad0, ad1, ad2, ad3};
     const InterpSlots isl = interp_slots();
     auto load = [&](int tile) { return load_image_interp<true, T>(lab, xc, g, tile_origin(tile, tl)); };
     const bool ran = tile_pipeline(tl.count(), load, [&](int tile, const auto& pre, auto prefetch) {
         const TileOrigin o = tile_origin(tile, tl);
-        const int wm_e = wave_mode_entry(wmode, tile, lz);
+        const int wm_e = KM == kStored ? 0 : wave_mode_entry(wmode, tile, lz);
         const int xx = o.x0 + lx, yy = o.y0 + ly, zz = o.z0 + lz;
         const bool active = in_grid(g, zz, yy, xx);
         const size_t idx = active ? cell_index(g, zz, yy, xx) : 0;
+        const auto kp = k_preload<T, kpre_on<KM>>(kst, n, idx);
         __syncthreads();
         put_image_interp<true, KM, T>(pre, img_s, feat_s, c_s);
         // per-cell operands, issued before the next tile's loads (an unused
@@ -1282,9 +1369,8 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM)) void k_up
         __syncthreads();
         interp_tile<T>(r_s, c_s, g, o, isl);
         __syncthreads();
-        const int mode = wave_mode<true>(wmode, wm_e, active, img_s, base, 1u, false, true);
-        const T x2 = cconv_any<T, KM, true>(mode, active, img_s, feat_s, r_s, base, w, mc, kst, n, idx,
-                                            KPre<T, false>{});
+        const int mode = KM == kStored ? -1 : wave_mode<true>(wmode, wm_e, active, img_s, base, 1u, false, true);
+        const T x2 = cconv_any<T, KM, true>(mode, active, img_s, feat_s, r_s, base, w, mc, kp);
         if (active) {
             T out = T(0);
             if (img_s[base] == (uint32_t)kFluid) out = (c1 * x1v + c2 * x2) * scale;
@@ -1332,8 +1418,11 @@ struct BottomArgs {
     int lb, L;
     int used;   // LDS elements the levels occupy
     BottomLevel lv[kMaxLevels + 1];
-    const T* k1[kMaxLevels + 1];
-    const T* k2[kMaxLevels + 1];
+    const T *k1, *k2;   // stored kernels of level lb
+    // those of the levels past lb: one region of the workspace, ksmall 16-byte
+    // words from ks on; CConv_1^l and CConv_2^l start at elements ko1[l], ko2[l]
+    const T* ks;
+    int ksmall, ko1[kMaxLevels + 1], ko2[kMaxLevels + 1];
     const T* rin;
     T* xout;
     // when set, the iteration's Residual stage runs here (sum of res_nparts
@@ -1345,6 +1434,11 @@ struct BottomArgs {
 
 constexpr int kBottomThreads = 512;
 constexpr int kBottomLds = 3072;   // elements: >= 2 * sum of the bottom levels' padded cells
+// Elements of the kernels past level lb: levels of at most 64, 8 and 1 cells, two
+// blocks each, in sections padded to 256 bytes; a whole number of loads per thread.
+template <class T>
+constexpr int kBottomK = (int)((27 * 2 * (64 + 8 + 1) * sizeof(T) + 6 * 256 + 16 * kBottomThreads - 1) /
+                               (16 * kBottomThreads) * 16 * kBottomThreads / sizeof(T));
 static_assert(kBottomMaxCells <= kBottomThreads, "one cell of each bottom level per thread");
 static_assert(kBottomThreads <= 512 && kBottomMaxCells <= 512, "cell splitting by div_magic");
 
@@ -1384,23 +1478,25 @@ __device__ __forceinline__ T bottom_interp(const T* xc, const BottomLevel& vc, i
     return a * (a * p00 + b * p01) + b * (a * p10 + b * p11);
 }
 
-// Levels lb and lb + 1 hold at most one cell per thread (lb has at most
-// kBottomThreads cells): every global load they need (r^lb and their stored
-// kernels) is issued at the start, so the sweep waits for one memory
-// latency instead of one per level.  Levels past lb + 1 (a handful of
-// cells) load their kernels where they are used.  The result of level l
-// (x1^l, then x^l once the up sweep has combined it in place) stays in the
-// level's x1 slot; the r slot holds r^l on the way down and Interp(x^(l+1))
-// on the way up.
+// Levels lb.. hold at most one cell per thread (lb has at most kBottomThreads
+// cells).  Every global load the sweep needs is issued at the start: r^lb and
+// level lb's stored kernels, a register each, and the kernels of the levels past
+// lb (at most 73 cells), which are copied to LDS as they lie in the workspace.
+// So the sweep waits for one memory latency, where the deeper levels had waited
+// for theirs in turn (32^3, four levels in the workgroup: 13.9 us in FP64).  The
+// result of level l (x1^l, then x^l once the up sweep has combined it in place)
+// stays in the level's x1 slot; the r slot holds r^l on the way down and
+// Interp(x^(l+1)) on the way up.
 template <class T>
 __global__ __launch_bounds__(kBottomThreads) void k_bottom(BottomArgs<T> a, State* st) {
     const int done = st->done;   // tested once the network is formed
     const ResidualIn rin = residual_in(st);   // read by the Residual stage below
     __shared__ T buf[kBottomLds];
+    __shared__ __attribute__((aligned(16))) T ksm[kBottomK<T>];
     const int lb = a.lb, L = a.L, p = threadIdx.x;
     const BottomLevel v0 = a.lv[lb];
-    const int n0 = v0.n, n1 = lb < L ? a.lv[lb + 1].n : 1;
-    const int q0 = min(p, n0 - 1), q1 = min(p, n1 - 1);   // clamped: every load is in bounds
+    const int n0 = v0.n;
+    const int q0 = min(p, n0 - 1);   // clamped: every load is in bounds
     // All loads go out at once: the Residual stage's partials (its sums are
     // only needed at the end), the input and the stored kernels.
     double rpart[1][kSumU];
@@ -1408,19 +1504,18 @@ __global__ __launch_bounds__(kBottomThreads) void k_bottom(BottomArgs<T> a, Stat
     T r0 = ld_global(a.rin + q0);
     // the combination weights of level lb (set up before the solve)
     const T c1_0 = (T)st->c1[lb - 1], c2_0 = (T)st->c2[lb - 1];
-    T k1_0[kTaps], k2_0[kTaps], k1_1[kTaps];
+    T k1_0[kTaps], k2_0[kTaps];
 #pragma unroll
-    for (int t = 0; t < kTaps; ++t) k1_0[t] = ld_global(a.k1[lb] + (size_t)t * n0 + q0);
-    if (lb < L) {   // in the order of use; level lb + 1's kernel only for its cells (whole waves skip it)
-        if (p < n1) {
+    for (int t = 0; t < kTaps; ++t) k1_0[t] = ld_global(a.k1 + (size_t)t * n0 + q0);
+    constexpr int KS = kBottomK<T> * (int)sizeof(T) / 16 / kBottomThreads;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 kw[KS];
+    if (lb < L) {   // in the order of use
 #pragma unroll
-            for (int t = 0; t < kTaps; ++t) k1_1[t] = ld_global(a.k1[lb + 1] + (size_t)t * n1 + q1);
-        } else {
+        for (int j = 0; j < KS; ++j)
+            kw[j] = ld_global(reinterpret_cast<const u32x4*>(a.ks) + min(p + j * kBottomThreads, a.ksmall - 1));
 #pragma unroll
-            for (int t = 0; t < kTaps; ++t) k1_1[t] = T(0);
-        }
-#pragma unroll
-        for (int t = 0; t < kTaps; ++t) k2_0[t] = ld_global(a.k2[lb] + (size_t)t * n0 + q0);
+        for (int t = 0; t < kTaps; ++t) k2_0[t] = ld_global(a.k2 + (size_t)t * n0 + q0);
     }
     // zero borders: clear the whole buffer, then fill the interiors
     for (int i = p; i < a.used; i += kBottomThreads) buf[i] = T(0);
@@ -1439,7 +1534,18 @@ __global__ __launch_bounds__(kBottomThreads) void k_bottom(BottomArgs<T> a, Stat
     __syncthreads();
     // down sweep and coarsest level
     if (p < n0) buf[v0.x1 + c0] = bottom_cconv(k1_0, buf + v0.r, v0.sy, v0.sz, c0);
+    if (lb < L) {
+#pragma unroll
+        for (int j = 0; j < KS; ++j) reinterpret_cast<u32x4*>(ksm)[p + j * kBottomThreads] = kw[j];
+    }
     __syncthreads();
+    // a stored kernel of a level past lb
+    auto small = [&](int at, int n) {
+        KPre<T, true> k;
+#pragma unroll
+        for (int t = 0; t < kTaps; ++t) k.kv[t] = ksm[at + t * n + p];
+        return k;
+    };
     for (int l = lb; l < L; ++l) {
         const BottomLevel f = a.lv[l], v = a.lv[l + 1];
         int z, y, x;
@@ -1453,16 +1559,7 @@ __global__ __launch_bounds__(kBottomThreads) void k_bottom(BottomArgs<T> a, Stat
         }
         __syncthreads();
         if (p < v.n) {
-            T acc;
-            if (l == lb) {
-                acc = bottom_cconv(k1_1, buf + v.r, v.sy, v.sz, c);
-            } else {
-                T kv[kTaps];
-#pragma unroll
-                for (int t = 0; t < kTaps; ++t) kv[t] = ld_global(a.k1[l + 1] + (size_t)t * v.n + p);
-                acc = bottom_cconv(kv, buf + v.r, v.sy, v.sz, c);
-            }
-            buf[v.x1 + c] = acc;
+            buf[v.x1 + c] = bottom_cconv(small(a.ko1[l + 1], v.n).kv, buf + v.r, v.sy, v.sz, c);
         }
         __syncthreads();
     }
@@ -1478,15 +1575,8 @@ __global__ __launch_bounds__(kBottomThreads) void k_bottom(BottomArgs<T> a, Stat
         if (p < v.n) buf[v.r + c] = bottom_interp<T>(buf + vc.x1, vc, z, y, x);
         __syncthreads();
         if (p < v.n) {
-            T acc;
-            if (l == lb) {
-                acc = bottom_cconv(k2_0, buf + v.r, v.sy, v.sz, c);
-            } else {
-                T kv[kTaps];
-#pragma unroll
-                for (int t = 0; t < kTaps; ++t) kv[t] = ld_global(a.k2[l] + (size_t)t * v.n + p);
-                acc = bottom_cconv(kv, buf + v.r, v.sy, v.sz, c);
-            }
+            const T acc = l == lb ? bottom_cconv(k2_0, buf + v.r, v.sy, v.sz, c)
+                                  : bottom_cconv(small(a.ko2[l], v.n).kv, buf + v.r, v.sy, v.sz, c);
             T* xo = buf + v.x1 + c;
             *xo = c1 * *xo + c2 * acc;
         }

@@ -418,7 +418,6 @@ struct WgradArgs {
 };
 
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // bf16 of a pair, rounded to nearest even, as one word; and its values.
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));

@@ -1439,7 +1439,7 @@ constexpr int kBottomLds = 3072;   // elements: >= 2 * sum of the bottom levels'
 template <class T>
 constexpr int kBottomK = (int)((27 * 2 * (64 + 8 + 1) * sizeof(T) + 6 * 256 + 16 * kBottomThreads - 1) /
                                (16 * kBottomThreads) * 16 * kBottomThreads / sizeof(T));
-static_assert(kBottomMaxCells <= kBottomThreads, "one cell of each bottom level per thread");
+static_assert(kBottomMaxCells <= kBottomThreads && kBottomMaxCells <= 8 * 64, "one cell per thread, the next level in one wave");
 static_assert(kBottomThreads <= 512 && kBottomMaxCells <= 512, "cell splitting by div_magic");
 
 // A load through a pointer that is known to address device memory: pointers
@@ -1478,45 +1478,58 @@ __device__ __forceinline__ T bottom_interp(const T* xc, const BottomLevel& vc, i
     return a * (a * p00 + b * p01) + b * (a * p10 + b * p11);
 }
 
-// Levels lb.. hold at most one cell per thread (lb has at most kBottomThreads
-// cells).  Every global load the sweep needs is issued at the start: r^lb and
-// level lb's stored kernels, a register each, and the kernels of the levels past
-// lb (at most 73 cells), which are copied to LDS as they lie in the workspace.
-// So the sweep waits for one memory latency, where the deeper levels had waited
-// for theirs in turn (32^3, four levels in the workgroup: 13.9 us in FP64).  The
-// result of level l (x1^l, then x^l once the up sweep has combined it in place)
-// stays in the level's x1 slot; the r slot holds r^l on the way down and
-// Interp(x^(l+1)) on the way up.
+// Level lb holds at most one cell per thread, the levels past it at most 64, 8
+// and 1 cells: one wave.  Every global load the sweep needs is issued at the
+// start: r^lb and level lb's stored kernels, a register each, the kernels of the
+// levels past lb, which are copied to LDS as they lie in the workspace, and the
+// combination weights.  So the sweep waits for one memory latency, where the
+// deeper levels had waited for theirs in turn.  Wave 0 then runs the levels past
+// lb by itself, in LDS order and without block barriers, while wave 1 sums the
+// partials of ||r||^2 and runs the Residual stage (the network is linear in r, so
+// nothing here needs its result; on the way of all waves it took 1.6 of the 7.8 us
+// after the network).  The result of level l (x1^l, then x^l once the up sweep has
+// combined it in place) stays in the level's x1 slot; the r slot holds r^l on the
+// way down and Interp(x^(l+1)) on the way up.
+
+// Orders a wave's LDS accesses (the hardware keeps them in order; the compiler
+// must too).
+__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
 template <class T>
 __global__ __launch_bounds__(kBottomThreads) void k_bottom(BottomArgs<T> a, State* st) {
     const int done = st->done;   // tested once the network is formed
     const ResidualIn rin = residual_in(st);   // read by the Residual stage below
     __shared__ T buf[kBottomLds];
     __shared__ __attribute__((aligned(16))) T ksm[kBottomK<T>];
+    __shared__ T c_s[2][kMaxLevels];
+    __shared__ int done_s;
     const int lb = a.lb, L = a.L, p = threadIdx.x;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const BottomLevel v0 = a.lv[lb];
     const int n0 = v0.n;
     const int q0 = min(p, n0 - 1);   // clamped: every load is in bounds
-    // All loads go out at once: the Residual stage's partials (its sums are
-    // only needed at the end), the input and the stored kernels.
-    double rpart[1][kSumU];
-    head_partials<1, kBottomThreads>(a.res_partials, a.res_partials ? a.res_nparts : 0, rpart);
+    // all loads go out at once
     T r0 = ld_global(a.rin + q0);
-    // the combination weights of level lb (set up before the solve)
-    const T c1_0 = (T)st->c1[lb - 1], c2_0 = (T)st->c2[lb - 1];
+    double cw = 0.0;
+    if (wv == 2 && lane < 2 * kMaxLevels) cw = (lane < kMaxLevels ? st->c1 : st->c2 - kMaxLevels)[lane];
     T k1_0[kTaps], k2_0[kTaps];
 #pragma unroll
     for (int t = 0; t < kTaps; ++t) k1_0[t] = ld_global(a.k1 + (size_t)t * n0 + q0);
     constexpr int KS = kBottomK<T> * (int)sizeof(T) / 16 / kBottomThreads;
     typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
     u32x4 kw[KS];
-    if (lb < L) {   // in the order of use
+    if (lb < L) {
 #pragma unroll
         for (int j = 0; j < KS; ++j)
             kw[j] = ld_global(reinterpret_cast<const u32x4*>(a.ks) + min(p + j * kBottomThreads, a.ksmall - 1));
-#pragma unroll
-        for (int t = 0; t < kTaps; ++t) k2_0[t] = ld_global(a.k2 + (size_t)t * n0 + q0);
     }
+    // The levels' descriptors lie in several cache lines of the kernel arguments,
+    // each a miss where a level is first reached: all are touched here, behind the
+    // loads.
+    int touch = 0;
+#pragma unroll
+    for (int l = 1; l <= kMaxLevels; ++l) touch ^= a.lv[l].n ^ a.ko1[l] ^ a.ko2[l];
+    __asm__ volatile("" ::"s"(touch));
     // zero borders: clear the whole buffer, then fill the interiors
     for (int i = p; i < a.used; i += kBottomThreads) buf[i] = T(0);
     // cell p of a level (at most one per thread) and its padded index
@@ -1532,69 +1545,85 @@ __global__ __launch_bounds__(kBottomThreads) void k_bottom(BottomArgs<T> a, Stat
     __syncthreads();
     if (p < n0) buf[v0.r + c0] = r0;
     __syncthreads();
-    // down sweep and coarsest level
+    // level lb down (x1^L itself when the workgroup holds only the coarsest level)
     if (p < n0) buf[v0.x1 + c0] = bottom_cconv(k1_0, buf + v0.r, v0.sy, v0.sz, c0);
     if (lb < L) {
 #pragma unroll
         for (int j = 0; j < KS; ++j) reinterpret_cast<u32x4*>(ksm)[p + j * kBottomThreads] = kw[j];
+        // needed last: behind the others (27 loads of every wave take the CU 0.5 us to issue)
+#pragma unroll
+        for (int t = 0; t < kTaps; ++t) k2_0[t] = ld_global(a.k2 + (size_t)t * n0 + q0);
+    }
+    if (wv == 2 && lane < 2 * kMaxLevels) (&c_s[0][0])[lane] = (T)cw;
+    __syncthreads();
+    if (wv == 0) {
+        // a stored kernel of a level past lb
+        auto small = [&](int at, int n) {
+            KPre<T, true> k;
+#pragma unroll
+            for (int t = 0; t < kTaps; ++t) k.kv[t] = ksm[at + t * n + p];
+            return k;
+        };
+        for (int l = lb; l < L; ++l) {   // down: Pool(x1^l), CConv_1^(l+1)
+            const BottomLevel f = a.lv[l], v = a.lv[l + 1];
+            int z, y, x;
+            const int c = cell(v, z, y, x);
+            if (p < v.n) {
+                const auto k = small(a.ko1[l + 1], v.n);
+                const T* s = buf + f.x1 + (2 * z + 1) * f.sz + (2 * y + 1) * f.sy + 2 * x + 1;
+                T sum = T(0);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) sum += s[(i >> 2) * f.sz + ((i >> 1) & 1) * f.sy + (i & 1)];
+                buf[v.r + c] = sum * T(0.125);
+                wave_lds_fence();
+                buf[v.x1 + c] = bottom_cconv(k.kv, buf + v.r, v.sy, v.sz, c);
+            }
+            wave_lds_fence();
+        }
+        // up: Interp(x^(l+1)) into the level's r slot (its down input is no longer
+        // needed; the border stays zero), then CConv_2 gathers from it and the
+        // combination overwrites x1^l, which only this lane reads, with x^l
+        for (int l = L - 1; l > lb; --l) {
+            const BottomLevel v = a.lv[l], vc = a.lv[l + 1];
+            int z, y, x;
+            const int c = cell(v, z, y, x);
+            if (p < v.n) {
+                const auto k = small(a.ko2[l], v.n);
+                buf[v.r + c] = bottom_interp<T>(buf + vc.x1, vc, z, y, x);
+                wave_lds_fence();
+                T* xo = buf + v.x1 + c;
+                *xo = c_s[0][l - 1] * *xo + c_s[1][l - 1] * bottom_cconv(k.kv, buf + v.r, v.sy, v.sz, c);
+            }
+            wave_lds_fence();
+        }
+    } else if (wv == 1 && a.res_partials && !done) {
+        constexpr int U = 16;
+        double sum = 0.0;
+        for (int b0 = 0; b0 < a.res_nparts; b0 += 64 * U) {
+            double t[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int b = b0 + u * 64 + lane;
+                t[u] = b < a.res_nparts ? ld_global(a.res_partials + b) : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) sum += t[u];
+        }
+        sum = wave_sum(sum);
+        if (lane == 0) done_s = residual_stage(st, rin, sum, a.hf);
     }
     __syncthreads();
-    // a stored kernel of a level past lb
-    auto small = [&](int at, int n) {
-        KPre<T, true> k;
-#pragma unroll
-        for (int t = 0; t < kTaps; ++t) k.kv[t] = ksm[at + t * n + p];
-        return k;
-    };
-    for (int l = lb; l < L; ++l) {
-        const BottomLevel f = a.lv[l], v = a.lv[l + 1];
-        int z, y, x;
-        const int c = cell(v, z, y, x);
-        if (p < v.n) {   // Pool(x1^l)
-            const T* s = buf + f.x1 + (2 * z + 1) * f.sz + (2 * y + 1) * f.sy + 2 * x + 1;
-            T sum = T(0);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) sum += s[(k >> 2) * f.sz + ((k >> 1) & 1) * f.sy + (k & 1)];
-            buf[v.r + c] = sum * T(0.125);
-        }
-        __syncthreads();
-        if (p < v.n) {
-            buf[v.x1 + c] = bottom_cconv(small(a.ko1[l + 1], v.n).kv, buf + v.r, v.sy, v.sz, c);
-        }
+    // level lb up
+    if (lb < L) {
+        const BottomLevel vc = a.lv[lb + 1];
+        if (p < n0) buf[v0.r + c0] = bottom_interp<T>(buf + vc.x1, vc, z0, y0, x0);
         __syncthreads();
     }
-    // up sweep: x^L = x1^L.  Interp(x^(l+1)) is formed once per level into the
-    // level's r slot (its down input is no longer needed; the border stays
-    // zero), then CConv_2 gathers from it and the combination overwrites
-    // x1^l, which only this thread reads, with x^l.
-    for (int l = L - 1; l >= lb; --l) {
-        const BottomLevel v = a.lv[l], vc = a.lv[l + 1];
-        const T c1 = l == lb ? c1_0 : (T)st->c1[l - 1], c2 = l == lb ? c2_0 : (T)st->c2[l - 1];
-        int z, y, x;
-        const int c = cell(v, z, y, x);
-        if (p < v.n) buf[v.r + c] = bottom_interp<T>(buf + vc.x1, vc, z, y, x);
-        __syncthreads();
-        if (p < v.n) {
-            const T acc = l == lb ? bottom_cconv(k2_0, buf + v.r, v.sy, v.sz, c)
-                                  : bottom_cconv(small(a.ko2[l], v.n).kv, buf + v.r, v.sy, v.sz, c);
-            T* xo = buf + v.x1 + c;
-            *xo = c1 * *xo + c2 * acc;
-        }
-        if (l > lb) __syncthreads();   // level lb's cells are read back only by the thread that wrote them
-    }
-    // The network is linear in r, so the stop test and the Residual stage
-    // (convergence, 1/||r||, read from the next kernel on) come last: a block
-    // of a stopped solve writes nothing.
-    if (done) return;
-    if (a.res_partials) {
-        __shared__ int done_s;
-        double v[1];
-        finish_partials<1, kBottomThreads>(rpart, a.res_partials, a.res_nparts, 1, v);
-        if (p == 0) done_s = residual_stage(st, rin, v[0], a.hf);
-        __syncthreads();
-        if (done_s) return;
-    }
-    if (p < n0) a.xout[p] = buf[v0.x1 + c0];   // x^lb (x1^L itself when the bottom holds only the coarsest level)
+    // a block of a stopped solve writes nothing
+    if (done || (a.res_partials && done_s) || p >= n0) return;
+    T x = buf[v0.x1 + c0];
+    if (lb < L) x = c_s[0][lb - 1] * x + c_s[1][lb - 1] * bottom_cconv(k2_0, buf + v0.r, v0.sy, v0.sz, c0);
+    a.xout[p] = x;
 }
 
 // ---------------------------------------------------------------------------

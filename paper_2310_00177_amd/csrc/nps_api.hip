@@ -152,6 +152,7 @@ struct Layout {
     size_t wmode[kMaxLevels + 1][2];   // per-wave CConv modes: [level][down, up (level 1)]
     size_t gmode[2];                   // level 1 on matrix cores: per-group modes [down, up]
     size_t izero[2];                   // and per-item zero flags [down, up]
+    size_t cmode[kMaxLevels + 1];      // levels 2 and 3 on matrix cores (float): per-group modes
     size_t live, items;                // 7-point work items: fluid flags, the list of those with fluid
     size_t cls, tot;                   // set-up: boundary class sums, totals per pyramid block
     size_t total;
@@ -191,6 +192,8 @@ Layout make_layout(nps_dims d, int levels, int precision, int n_ortho, bool solv
         L.izero[0] = put((size_t)march_columns(level_grid(d, 1)).count());
         L.izero[1] = put((size_t)march_columns(level_grid(d, 1)).count());
     }
+    for (int l = 2; l <= levels; ++l)
+        if (is_mfma(p.km[l])) L.cmode[l] = put(group_mode_bytes(level_grid(d, l)));
     // Set-up tables.  A network evaluation writes its output to the caller's
     // buffer, so there they share the bytes of the solve's d^.
     L.dhat = off;
@@ -584,8 +587,17 @@ int run_setup(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
         const Grid g = level_grid(d, l);
         const int grid = tile_grid(g);
         int8_t* md = mptr<int8_t>(ws, lay.wmode[l][0]);
-        if (l == 1 && is_mfma(plan.km[1])) continue;   // the level-1 kernels use the group modes
-        if (plan.km[l] == kStored) continue;            // a stored kernel takes no shortcut
+        if (plan.km[l] == kStored) continue;   // a stored kernel takes no shortcut
+        if (is_mfma(plan.km[l])) {              // group modes (level 1: above)
+            if (l == 1) continue;
+            NPS_TRY(with_chunk(g, [&](auto ch) {
+                return launch("setup_coarse_modes", (double)ncells(g), s, [&] {
+                    k_coarse_modes<decltype(ch)::value><<<march_columns(g).count(), kBlock, 0, s>>>(
+                        cptr<uint32_t>(ws, lay.counts[l]), g, full_count(l), mptr<uint8_t>(ws, lay.cmode[l]));
+                });
+            }));
+            continue;
+        }
         if (l == 1)
             NPS_TRY(launch("setup_wave_modes", (double)ncells(g), s, [&] {
                 k_wave_modes<true><<<grid, kBlock, 0, s>>>(img(l), g, 1u, md, mptr<int8_t>(ws, lay.wmode[l][1]));
@@ -642,16 +654,28 @@ int run_coarse(const nps_net* net, nps_dims d, const Plan& plan, const Layout& l
         const double cells = (double)ncells(g);
         NPS_TRY(with_kmode<T>(plan.km[l], [&](auto km) {
             constexpr int KM = decltype(km)::value;
-            const int grid = persist_grid(l < L ? &k_down<T, KM, true> : &k_down<T, KM, false>, g);
-            if (l < L)
-                return launch(kDownName[l], cells, s, [&] {
-                    k_down<T, KM, true><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), rin, x1, rnext, w, wm, kst, st,
-                                                                 cptr<int8_t>(ws, lay.wmode[l][0]));
+            if constexpr (is_mfma(KM)) {
+                return with_chunk(g, [&](auto ch) {
+                    constexpr int CH = decltype(ch)::value;
+                    const int grid = persist_grid_n(&k_down_m<KM, CH, false>, march_columns(g).count());
+                    return launch(l < L ? kDownName[l] : "net_coarsest", cells, s, [&] {
+                        k_down_m<KM, CH, false><<<grid, kBlock, 0, s>>>(cnt, g, rin, x1, rnext, w, wm, st,
+                                                                        cptr<uint32_t>(ws, lay.cmode[l]), nullptr,
+                                                                        g.nx % 4 == 0 ? 1 : 0);
+                    });
                 });
-            return launch("net_coarsest", cells, s, [&] {
-                k_down<T, KM, false><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), rin, x1, nullptr, w, wm, kst, st,
-                                                              cptr<int8_t>(ws, lay.wmode[l][0]));
-            });
+            } else {
+                const int grid = persist_grid(l < L ? &k_down<T, KM, true> : &k_down<T, KM, false>, g);
+                if (l < L)
+                    return launch(kDownName[l], cells, s, [&] {
+                        k_down<T, KM, true><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), rin, x1, rnext, w, kst, st,
+                                                                     cptr<int8_t>(ws, lay.wmode[l][0]));
+                    });
+                return launch("net_coarsest", cells, s, [&] {
+                    k_down<T, KM, false><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), rin, x1, nullptr, w, kst, st,
+                                                                  cptr<int8_t>(ws, lay.wmode[l][0]));
+                });
+            }
         }));
     }
     if (plan.lb <= L) {
@@ -715,11 +739,23 @@ int run_coarse(const nps_net* net, nps_dims d, const Plan& plan, const Layout& l
         const T* kst = plan.km[l] == kStored ? cptr<T>(ws, lay.k2[l]) : nullptr;
         NPS_TRY(with_kmode<T>(plan.km[l], [&](auto km) {
             constexpr int KM = decltype(km)::value;
-            const int grid = persist_grid(&k_up<T, KM>, g);
-            return launch(kUpName[l], (double)ncells(g), s, [&] {
-                k_up<T, KM><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), xc, x1, xo, w, wm, kst, l - 1, st, nullptr,
-                                                    cptr<int8_t>(ws, lay.wmode[l][0]));
-            });
+            if constexpr (is_mfma(KM)) {
+                return with_chunk(g, [&](auto ch) {
+                    constexpr int CH = decltype(ch)::value;
+                    const int grid = persist_grid_n(&k_up_m<KM, true, 0, CH, false>, march_columns(g).count());
+                    return launch(kUpName[l], (double)ncells(g), s, [&] {
+                        k_up_m<KM, true, 0, CH, false><<<grid, kBlock, 0, s>>>(
+                            cnt, g, xc, x1, xo, w, wm, st, nullptr, nullptr, nullptr, nullptr, nullptr,
+                            cptr<uint32_t>(ws, lay.cmode[l]), nullptr, g.nx % 4 == 0 ? 1 : 0, nullptr, l - 1);
+                    });
+                });
+            } else {
+                const int grid = persist_grid(&k_up<T, KM>, g);
+                return launch(kUpName[l], (double)ncells(g), s, [&] {
+                    k_up<T, KM><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), xc, x1, xo, w, kst, l - 1, st, nullptr,
+                                                        cptr<int8_t>(ws, lay.wmode[l][0]));
+                });
+            }
         }));
     }
     *x2 = x_of(2);
@@ -743,9 +779,9 @@ int run_down_l1(const nps_net* net, const uint8_t* labels, nps_dims d, const Pla
             // as many blocks as fit
             return with_chunk(g, [&](auto ch) {
                 constexpr int CH = decltype(ch)::value;
-                const int grid = persist_grid_n(&k_down_l1m<KM, CH>, march_columns(g).count());
+                const int grid = persist_grid_n(&k_down_m<KM, CH, true>, march_columns(g).count());
                 return launch("net_down_l1", (double)ncells(g), s, [&] {
-                    k_down_l1m<KM, CH><<<grid, kBlock, 0, s>>>(labels, g, r, x1, rnext, w, wm, st,
+                    k_down_m<KM, CH, true><<<grid, kBlock, 0, s>>>(labels, g, r, x1, rnext, w, wm, st,
                                                                cptr<uint32_t>(ws, lay.gmode[0]),
                                                                cptr<uint8_t>(ws, lay.izero[0]),
                                                                wide_quads(labels, r, g) ? 1 : 0);
@@ -754,7 +790,7 @@ int run_down_l1(const nps_net* net, const uint8_t* labels, nps_dims d, const Pla
         } else {
             const int grid = persist_grid(&k_down_l1<T, KM>, g);
             return launch("net_down_l1", (double)ncells(g), s, [&] {
-                k_down_l1<T, KM><<<grid, kBlock, 0, s>>>(labels, g, r, x1, rnext, w, wm, kst, st,
+                k_down_l1<T, KM><<<grid, kBlock, 0, s>>>(labels, g, r, x1, rnext, w, kst, st,
                                                          cptr<int8_t>(ws, lay.wmode[1][0]));
             });
         }
@@ -783,13 +819,13 @@ int run_up_l1(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
                 constexpr bool H = HOOK;
                 return with_chunk(g, [&](auto ch) {
                     constexpr int CH = decltype(ch)::value;
-                    const int grid = persist_grid_n(&k_up_l1m<KM, H, H ? 0 : ND, CH>, march_columns(g).count());
+                    const int grid = persist_grid_n(&k_up_m<KM, H, H ? 0 : ND, CH, true>, march_columns(g).count());
                     if (nparts) *nparts = grid;
                     return launch("net_up_l1", (double)ncells(g), s, [&] {
-                        k_up_l1m<KM, H, H ? 0 : ND, CH><<<grid, kBlock, 0, s>>>(
+                        k_up_m<KM, H, H ? 0 : ND, CH, true><<<grid, kBlock, 0, s>>>(
                             labels, g, x2, x1, dhat, w, wm, st, partials, ad[0], ad[1], ad[2], ad[3],
                             cptr<uint32_t>(ws, lay.gmode[1]), cptr<uint8_t>(ws, lay.izero[1]),
-                            wide_quads(labels, nullptr, g) ? 1 : 0, x2out);
+                            wide_quads(labels, nullptr, g) ? 1 : 0, x2out, 0);
                     });
                 });
             };
@@ -802,7 +838,7 @@ int run_up_l1(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
             const int grid = persist_grid(&k_up_l1<T, KM, HOOK>, g);
             if (nparts) *nparts = grid;
             return launch("net_up_l1", (double)ncells(g), s, [&] {
-                k_up_l1<T, KM, HOOK><<<grid, kBlock, 0, s>>>(labels, g, x2, x1, dhat, w, wm, kst, st, partials, ad[0], ad[1],
+                k_up_l1<T, KM, HOOK><<<grid, kBlock, 0, s>>>(labels, g, x2, x1, dhat, w, kst, st, partials, ad[0], ad[1],
                                                             ad[2], ad[3], x2out, cptr<int8_t>(ws, lay.wmode[1][1]));
             });
         }
@@ -1532,12 +1568,12 @@ int train_forward(const nps_net* net, const uint8_t* labels, nps_dims d, const T
         const CConvW<T>* w = wblock(block_down(l));
         if (l < L)
             NPS_TRY(launch("net_down", (double)ncells(g), s, [&] {
-                k_down<T, kStored, true><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), rin, x1, rnext, w, nullptr, kst, st,
+                k_down<T, kStored, true><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), rin, x1, rnext, w, kst, st,
                                                                   nullptr);
             }));
         else
             NPS_TRY(launch("net_coarsest", (double)ncells(g), s, [&] {
-                k_down<T, kStored, false><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), rin, x1, nullptr, w, nullptr, kst,
+                k_down<T, kStored, false><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), rin, x1, nullptr, w, kst,
                                                                    st, nullptr);
             }));
     }
@@ -1553,7 +1589,7 @@ int train_forward(const nps_net* net, const uint8_t* labels, nps_dims d, const T
         const T* kst = cptr<T>(ws, lay.k2[l]);
         const CConvW<T>* w = wblock(block_up(net, l));
         NPS_TRY(launch("net_up", (double)ncells(g), s, [&] {
-            k_up<T, kStored><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), xc, x1, xo, w, nullptr, kst, l - 1, st, x2o,
+            k_up<T, kStored><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), xc, x1, xo, w, kst, l - 1, st, x2o,
                                                          nullptr);
         }));
     }

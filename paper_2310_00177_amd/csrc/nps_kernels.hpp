@@ -35,10 +35,9 @@ namespace nps {
 // 512 / n so that n waves of it fit per SIMD.
 #define NPS_WAVES_PER_EU(n) __attribute__((amdgpu_waves_per_eu(n)))
 
-// The three-piece bf16 weights of the FP32 MFMA path need more registers, and
-// so do the double weights of the FP64 one and 27 preloaded doubles (higher
-// floors make the CConv kernels spill and run slower).
-constexpr int waves_floor(int km, size_t word) { return km == kMfmaBf16x3 ? 3 : word == 8 ? 2 : 4; }
+// The FP64 matrix-core weights and 27 preloaded doubles need more registers
+// (higher floors make the CConv kernels spill and run slower).
+constexpr int waves_floor(size_t word) { return word == 8 ? 2 : 4; }
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
@@ -417,108 +416,19 @@ __device__ __forceinline__ uint32_t feat_one() {
     return KM == kMfmaF16 ? 0x3c00u : 0x3f80u;
 }
 
-// What a wave keeps for all its MFMA CConvs: the weight fragments (A
-// operand), the haloed-tile index of its lane's cell in row 0, and the
-// offsets of the lane's window positions 16 s + 4 g + j (s = feature step or
-// tap block, g = lane / 16, j < 4; positions past 26 clamped, their A rows
-// and columns are zero).  The same offsets address the features (window
-// offset o) and the taps (tap t) because both run over the 27 positions in
-// the same order.
-template <int KM>
-struct MfmaCtx {
-    static constexpr int P = KM == kMfmaBf16x3 ? kPieces : 1;
-    u16x8 a[P][2][2];
-    int base0;
-    int off[2][4];
-    bool one;   // lane group 2: word 3 of step 1 is feature pair 54/55
-};
-
-template <int KM>
-__device__ __forceinline__ MfmaCtx<KM> mfma_ctx(const MfmaW* __restrict__ wm, int lz) {
-    MfmaCtx<KM> c;
-    if constexpr (is_mfma(KM)) {
-        const int lane = threadIdx.x & 63, g = lane >> 4, n = lane & 15;
-#pragma unroll
-        for (int p = 0; p < MfmaCtx<KM>::P; ++p)
-#pragma unroll
-            for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    const uint16_t* src = KM == kMfmaF16 ? &wm->f16[mb][ks][lane][0] : &wm->bf16[p][mb][ks][lane][0];
-                    c.a[p][mb][ks] = *reinterpret_cast<const u16x8*>(src);
-                }
-        c.base0 = halo_base(n, 0, lz);
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) c.off[s2][j] = halo_off_rt(min(16 * s2 + 4 * g + j, kTaps - 1));
-        c.one = g == 2;
-    }
-    return c;
-}
-
-// MFMA: one wave evaluates the CConv of its 64 cells (one z-plane of the
-// tile, x = lane % 16, y = lane / 16) as four 16-cell groups.  For group q
-// (y = q) the kernels of the 16 cells are K^T[tap][cell] = A[tap][feature] x
-// B[feature][cell] on v_mfma_f32_16x16x32 (2 tap blocks x 2 feature steps,
-// times the bf16 pieces); each lane then applies its 8 taps of one cell and
-// the four lane groups are summed with two butterflies.  Returns the output
-// of the lane's own cell.  All 64 lanes must call it.
-template <int KM>
-__device__ __forceinline__ float cconv_mfma(const uint32_t* feat_s, const float* r_s, const MfmaCtx<KM>& c) {
-    constexpr int P = MfmaCtx<KM>::P;
-    const int g = (threadIdx.x & 63) >> 4;
-    float mine = 0.0f;
-#pragma unroll 1
-    for (int q = 0; q < 4; ++q) {
-        const int bq = c.base0 + q * HX;
-        uint32_t wv[2][4];
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) wv[ks][j] = feat_s[bq + c.off[ks][j]];
-        wv[1][3] = c.one ? feat_one<KM>() : wv[1][3];
-        u16x8 B[2];
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-            B[ks] = __builtin_bit_cast(u16x8, (u32x4){wv[ks][0], wv[ks][1], wv[ks][2], wv[ks][3]});
-        }
-        f32x4 acc[2];
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb) {
-            acc[mb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-            for (int p = 0; p < P; ++p)
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    if (KM == kMfmaF16)
-                        acc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, c.a[p][mb][ks]),
-                                                                         __builtin_bit_cast(f16x8, B[ks]), acc[mb], 0, 0, 0);
-                    else
-                        acc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, c.a[p][mb][ks]),
-                                                                          __builtin_bit_cast(bf16x8, B[ks]), acc[mb], 0, 0, 0);
-                }
-        }
-        float part = 0.0f;
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) part = fmaf(acc[mb][i], r_s[bq + c.off[mb][i]], part);
-        part += __shfl_xor(part, 16, 64);
-        part += __shfl_xor(part, 32, 64);
-        if (q == g) mine = part;
-    }
-    return mine;
-}
-
-// FP64: the same on v_mfma_f64_16x16x4_f64: K^T[tap][cell] over 14 steps of 4
-// features (54 counts, the constant 1, a zero).  Lane (k, n) supplies feature
+// FP64 on the matrix cores: one wave evaluates the CConv of its 64 cells (one
+// z-plane of the tile, x = lane % 16, y = lane / 16) as four 16-cell groups.  For
+// group q (y = q) the kernels of the 16 cells are K^T[tap][cell] = A[tap][feature]
+// B[feature][cell] on v_mfma_f64_16x16x4_f64, over 14 steps of 4 features (54
+// counts, the constant 1, a zero).  Lane (k, n) supplies feature
 // 4 ks + k of tap 16 mb + n (A, straight from the count form) and of cell n (B:
 // window position 2 ks + k / 2, channel k % 2), and holds taps 16 mb + 4 i + k of
 // cell n.  On the vector ALU the 1458 multiply-adds of a cell and their weights,
 // read as scalars, took three to four times as long (40 x 56 x 72: 37 us down, 30
 // us up at level 1).
+template <int KM>
+struct MfmaCtx {};
+
 template <>
 struct MfmaCtx<kMfmaF64> {
     static constexpr int kSteps = 14;
@@ -600,16 +510,15 @@ __device__ __forceinline__ double cconv_mfma64(const uint32_t* img_s, const doub
 
 // The MFMA context of a kernel mode (nothing for the others).
 template <class T, int KM>
-__device__ __forceinline__ MfmaCtx<KM> cconv_ctx(const CConvW<T>* __restrict__ w, const MfmaW* __restrict__ wm, int lz) {
+__device__ __forceinline__ MfmaCtx<KM> cconv_ctx(const CConvW<T>* __restrict__ w, int lz) {
     if constexpr (KM == kMfmaF64) return mfma64_ctx(w, lz);
-    else return mfma_ctx<KM>(wm, lz);
+    else return MfmaCtx<KM>{};
 }
 
 // One CConv output of the thread's cell (lx, ly, lz) for a wave-uniform mode.
 // kp: the preloaded stored kernel (PRE).
 template <class T, int KM, bool L1, bool PRE>
-__device__ __forceinline__ T cconv_any(int mode, bool active, const uint32_t* img_s, const uint32_t* feat_s,
-                                       const T* r_s, int base, const CConvW<T>* __restrict__ w,
+__device__ __forceinline__ T cconv_any(int mode, bool active, const uint32_t* img_s, const T* r_s, int base, const CConvW<T>* __restrict__ w,
                                        const MfmaCtx<KM>& mc, const KPre<T, PRE>& kp) {
     if (mode == -3) return T(0);
     if (mode >= 0) return active ? cconv_pure<T>(r_s, base, w, mode) : T(0);
@@ -617,11 +526,9 @@ __device__ __forceinline__ T cconv_any(int mode, bool active, const uint32_t* im
         return active ? cconv_stored<T>(r_s, base, kp.kv) : T(0);
     } else if constexpr (KM == kVector) {
         return active ? cconv_vector<T, L1>(img_s, r_s, base, w) : T(0);
-    } else if constexpr (KM == kMfmaF64) {
-        return cconv_mfma64<L1>(img_s, r_s, mc);
     } else {
-        static_assert(sizeof(T) == 4, "MFMA paths are float");
-        return cconv_mfma<KM>(feat_s, reinterpret_cast<const float*>(r_s), mc);
+        static_assert(KM == kMfmaF64, "the float matrix-core levels have kernels of their own");
+        return cconv_mfma64<L1>(img_s, r_s, mc);
     }
 }
 
@@ -1039,19 +946,18 @@ struct RL {    // network input and label of one haloed cell
 };
 
 template <class T, int KM>
-__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM, sizeof(T))) void k_down_l1(
+__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) void k_down_l1(
     const uint8_t* __restrict__ lab, Grid g, const T* __restrict__ r, T* __restrict__ x1, T* __restrict__ rnext,
-    const CConvW<T>* __restrict__ w, const MfmaW* __restrict__ wm, const T* __restrict__ kst, const State* st,
+    const CConvW<T>* __restrict__ w, const T* __restrict__ kst, const State* st,
     const int8_t* __restrict__ wmode) {
     __shared__ uint32_t img_s[kHaloP];
-    __shared__ uint32_t feat_s[is_mfma(KM) ? kHaloP : 1];
     __shared__ T r_s[kHaloP];
     __shared__ T out_s[kBlock];
     const Tiles tl = tiles_of(g);
     const size_t n = ncells(g);
     const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
     const int base = halo_base(lx, ly, lz);
-    const MfmaCtx<KM> mc = cconv_ctx<T, KM>(w, wm, lz);
+    const MfmaCtx<KM> mc = cconv_ctx<T, KM>(w, lz);
     auto load = [&](int tile) {
         const TileOrigin o = tile_origin(tile, tl);
         return load_batch<kHalo, RL<T>>([&](int i) {
@@ -1070,12 +976,11 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM, sizeof(T))
         put_batch(pre, [&](int i, RL<T> e) {
             r_s[i] = e.l == kFluid ? e.r : T(0);
             img_s[i] = e.l;
-            if constexpr (is_mfma(KM)) feat_s[i] = feat_word<KM, true>(e.l);
         });
         prefetch();
         __syncthreads();
         const int mode = KM == kStored ? -1 : wave_mode<true>(wmode, wm_e, active, img_s, base, 1u, true, false);
-        const T out = cconv_any<T, KM, true>(mode, active, img_s, feat_s, r_s, base, w, mc, kp);
+        const T out = cconv_any<T, KM, true>(mode, active, img_s, r_s, base, w, mc, kp);
         if (active) x1[idx] = out;
         out_s[threadIdx.x] = active ? out : T(0);
         __syncthreads();
@@ -1091,19 +996,18 @@ struct CR {    // packed counts and network input of one haloed cell
 };
 
 template <class T, int KM, bool POOL>
-__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM, sizeof(T))) void k_down(
+__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) void k_down(
     const uint32_t* __restrict__ cnt, Grid g, uint32_t full, const T* __restrict__ rin, T* __restrict__ x1,
-    T* __restrict__ rnext, const CConvW<T>* __restrict__ w, const MfmaW* __restrict__ wm, const T* __restrict__ kst,
+    T* __restrict__ rnext, const CConvW<T>* __restrict__ w, const T* __restrict__ kst,
     const State* st, const int8_t* __restrict__ wmode) {
     __shared__ uint32_t img_s[kHaloP];
-    __shared__ uint32_t feat_s[is_mfma(KM) ? kHaloP : 1];
     __shared__ T r_s[kHaloP];
     __shared__ T out_s[kBlock];
     const Tiles tl = tiles_of(g);
     const size_t n = ncells(g);
     const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
     const int base = halo_base(lx, ly, lz);
-    const MfmaCtx<KM> mc = cconv_ctx<T, KM>(w, wm, lz);
+    const MfmaCtx<KM> mc = cconv_ctx<T, KM>(w, lz);
     auto load = [&](int tile) {
         const TileOrigin o = tile_origin(tile, tl);
         return load_batch<kHalo, CR<T>>([&](int i) {
@@ -1121,13 +1025,12 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM, sizeof(T))
         __syncthreads();
         put_batch(pre, [&](int i, CR<T> e) {
             img_s[i] = e.c;
-            if constexpr (is_mfma(KM)) feat_s[i] = feat_word<KM, false>(e.c);
             r_s[i] = e.r;
         });
         prefetch();
         __syncthreads();
         const int mode = KM == kStored ? -1 : wave_mode<false>(wmode, wm_e, active, img_s, base, full, false, false);
-        const T out = cconv_any<T, KM, false>(mode, active, img_s, feat_s, r_s, base, w, mc, kp);
+        const T out = cconv_any<T, KM, false>(mode, active, img_s, r_s, base, w, mc, kp);
         if (active) x1[idx] = out;
         if (POOL) {
             out_s[threadIdx.x] = active ? out : T(0);
@@ -1190,12 +1093,9 @@ __device__ __forceinline__ UpLoads<T> load_image_interp(const void* img, const T
     return u;
 }
 
-template <bool L1, int KM, class T>
-__device__ __forceinline__ void put_image_interp(const UpLoads<T>& u, uint32_t* img_s, uint32_t* feat_s, T* c_s) {
-    put_batch(u.img, [&](int i, uint32_t v) {
-        img_s[i] = v;
-        if constexpr (is_mfma(KM)) feat_s[i] = feat_word<KM, L1>(v);
-    });
+template <class T>
+__device__ __forceinline__ void put_image_interp(const UpLoads<T>& u, uint32_t* img_s, T* c_s) {
+    put_batch(u.img, [&](int i, uint32_t v) { img_s[i] = v; });
     put_batch(u.c, [&](int i, T v) { c_s[i] = v; });
 }
 
@@ -1272,26 +1172,14 @@ __device__ __forceinline__ void interp_tile(T* r_s, const T* c_s, Grid g, TileOr
     }
 }
 
-// Image and Interp(xc) of one tile in one go (for kernels that do not
-// pipeline their tiles).
-template <bool L1, int KM, class T>
-__device__ __forceinline__ void stage_image_interp(uint32_t* img_s, uint32_t* feat_s, const void* img, T* r_s, T* c_s,
-                                                   const T* __restrict__ xc, Grid g, TileOrigin o) {
-    put_image_interp<L1, KM, T>(load_image_interp<L1, T>(img, xc, g, o), img_s, feat_s, c_s);
-    __syncthreads();
-    interp_tile<T>(r_s, c_s, g, o, interp_slots());
-}
-
 // x = c1 x1 + c2 CConv_2(Interp(xc), I) on one level l >= 2.
 template <class T, int KM>
-__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM, sizeof(T))) void k_up(const uint32_t* __restrict__ cnt, Grid g, uint32_t full,
+__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) void k_up(const uint32_t* __restrict__ cnt, Grid g, uint32_t full,
                                                const T* __restrict__ xc, const T* __restrict__ x1,
-                                               T* __restrict__ xout, const CConvW<T>* __restrict__ w,
-                                               const MfmaW* __restrict__ wm, const T* __restrict__ kst, int lvl,
+                                               T* __restrict__ xout, const CConvW<T>* __restrict__ w, const T* __restrict__ kst, int lvl,
                                                const State* st, T* __restrict__ x2out,
                                                const int8_t* __restrict__ wmode) {
     __shared__ uint32_t img_s[kHaloP];
-    __shared__ uint32_t feat_s[is_mfma(KM) ? kHaloP : 1];
     __shared__ T r_s[kHaloP];
     __shared__ T c_s[kCoarseTileP];
     const T c1 = (T)st->c1[lvl], c2 = (T)st->c2[lvl];
@@ -1299,7 +1187,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM, sizeof(T))
     const size_t n = ncells(g);
     const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
     const int base = halo_base(lx, ly, lz);
-    const MfmaCtx<KM> mc = cconv_ctx<T, KM>(w, wm, lz);
+    const MfmaCtx<KM> mc = cconv_ctx<T, KM>(w, lz);
     const InterpSlots isl = interp_slots();
     auto load = [&](int tile) { return load_image_interp<false, T>(cnt, xc, g, tile_origin(tile, tl)); };
     tile_pipeline(tl.count(), load, [&](int tile, const auto& pre, auto prefetch) {
@@ -1310,14 +1198,14 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM, sizeof(T))
         const size_t idx = active ? cell_index(g, zz, yy, xx) : 0;
         const auto kp = k_preload<T, kpre_on<KM>>(kst, n, idx);
         __syncthreads();
-        put_image_interp<false, KM, T>(pre, img_s, feat_s, c_s);
+        put_image_interp<T>(pre, img_s, c_s);
         const T x1v = x1[idx];
         prefetch();
         __syncthreads();
         interp_tile<T>(r_s, c_s, g, o, isl);
         __syncthreads();
         const int mode = KM == kStored ? -1 : wave_mode<false>(wmode, wm_e, active, img_s, base, full, false, false);
-        const T x2 = cconv_any<T, KM, false>(mode, active, img_s, feat_s, r_s, base, w, mc, kp);
+        const T x2 = cconv_any<T, KM, false>(mode, active, img_s, r_s, base, w, mc, kp);
         if (active) xout[idx] = c1 * x1v + c2 * x2;
         if (active && x2out) x2out[idx] = x2;
     }, st);
@@ -1328,14 +1216,13 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM, sizeof(T))
 // ad0.. (NPSDO: the stored A d_i of the previous directions; PCG: r; flexible
 // PCG: r and the previous residual).
 template <class T, int KM, bool HOOK>
-__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM, sizeof(T))) void k_up_l1(
+__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) void k_up_l1(
     const uint8_t* __restrict__ lab, Grid g, const T* __restrict__ xc, const T* __restrict__ x1,
-    T* __restrict__ dhat, const CConvW<T>* __restrict__ w, const MfmaW* __restrict__ wm,
+    T* __restrict__ dhat, const CConvW<T>* __restrict__ w,
     const T* __restrict__ kst, const State* st, double* partials, const T* __restrict__ ad0,
     const T* __restrict__ ad1, const T* __restrict__ ad2, const T* __restrict__ ad3, T* __restrict__ x2out,
     const int8_t* __restrict__ wmode) {
     __shared__ uint32_t img_s[kHaloP];
-    __shared__ uint32_t feat_s[is_mfma(KM) ? kHaloP : 1];
     __shared__ T r_s[kHaloP];
     __shared__ T c_s[kCoarseTileP];
     const T c1 = (T)st->c1[0], c2 = (T)st->c2[0];
@@ -1345,7 +1232,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM, sizeof(T))
     const size_t n = ncells(g);
     const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
     const int base = halo_base(lx, ly, lz);
-    const MfmaCtx<KM> mc = cconv_ctx<T, KM>(w, wm, lz);
+    const MfmaCtx<KM> mc = cconv_ctx<T, KM>(w, lz);
     double v[kRedWidth] = {0.0, 0.0, 0.0, 0.0};
     const T* adp[kMaxOrtho] = {ad0, ad1, ad2, ad3};
     const InterpSlots isl = interp_slots();
@@ -1358,7 +1245,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM, sizeof(T))
         const size_t idx = active ? cell_index(g, zz, yy, xx) : 0;
         const auto kp = k_preload<T, kpre_on<KM>>(kst, n, idx);
         __syncthreads();
-        put_image_interp<true, KM, T>(pre, img_s, feat_s, c_s);
+        put_image_interp<T>(pre, img_s, c_s);
         // per-cell operands, issued before the next tile's loads (an unused
         // A d_i slot reads x1 instead: always a valid address)
         const T x1v = x1[idx];
@@ -1370,7 +1257,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(KM, sizeof(T))
         interp_tile<T>(r_s, c_s, g, o, isl);
         __syncthreads();
         const int mode = KM == kStored ? -1 : wave_mode<true>(wmode, wm_e, active, img_s, base, 1u, false, true);
-        const T x2 = cconv_any<T, KM, true>(mode, active, img_s, feat_s, r_s, base, w, mc, kp);
+        const T x2 = cconv_any<T, KM, true>(mode, active, img_s, r_s, base, w, mc, kp);
         if (active) {
             T out = T(0);
             if (img_s[base] == (uint32_t)kFluid) out = (c1 * x1v + c2 * x2) * scale;
@@ -1597,19 +1484,24 @@ __global__ __launch_bounds__(kBottomThreads) void k_bottom(BottomArgs<T> a, Stat
             wave_lds_fence();
         }
     } else if (wv == 1 && a.res_partials && !done) {
-        constexpr int U = 16;
-        double sum = 0.0;
-        for (int b0 = 0; b0 < a.res_nparts; b0 += 64 * U) {
-            double t[U];
+        // in the order of finish_partials for kBottomThreads threads: one value a
+        // virtual thread, a butterfly per virtual wave, then the waves in order
+        constexpr int W = kBottomThreads / 64;
+        double vs[W], sum = 0.0;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int b = b0 + u * 64 + lane;
-                t[u] = b < a.res_nparts ? ld_global(a.res_partials + b) : 0.0;
+        for (int w = 0; w < W; ++w) vs[w] = 0.0;
+        for (int b0 = 0; b0 < a.res_nparts; b0 += kBottomThreads) {
+            double t[W];
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                const int b = b0 + w * 64 + lane;
+                t[w] = b < a.res_nparts ? ld_global(a.res_partials + b) : 0.0;
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) sum += t[u];
+            for (int w = 0; w < W; ++w) vs[w] += t[w];
         }
-        sum = wave_sum(sum);
+#pragma unroll
+        for (int w = 0; w < W; ++w) sum += wave_sum(vs[w]);
         if (lane == 0) done_s = residual_stage(st, rin, sum, a.hf);
     }
     __syncthreads();

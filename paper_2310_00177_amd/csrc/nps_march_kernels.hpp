@@ -1,6 +1,7 @@
-// Level-1 network kernels on matrix cores, one work item (a 64 x 4 column
-// footprint over 4 or 2 z-planes) at a time (Alg. 2, first level: CConv_1^1 +
-// pool down, interpolation + CConv_2^1 + combine up).
+// Network kernels of the large levels on matrix cores in float (levels 1 to 3
+// above 32768 cells), one work item (a 64 x 4 column footprint over 4 or 2
+// z-planes) at a time (Alg. 2: CConv_1 + pool down, interpolation + CConv_2 +
+// combine up; at level 1 also the mask, the scaling and the dots).
 //
 // These kernels are bound by instruction issue (their traffic is 1 TB/s), so
 // the item is staged and evaluated with as few instructions per cell as
@@ -16,7 +17,8 @@
 // per solve (k_march_modes; the labels do not change during a solve):
 //   zero     every output is zero;
 //   pure     every cell that matters has an all-fluid window, i.e. the constant
-//            fluid kernel.  A wave with any pure group applies that kernel to
+//            fluid kernel (on coarser levels also all-air and all-solid windows,
+//            each with its own).  A wave with any pure group applies that kernel to
 //            all its cells: the 9 inputs of a plane around the lane's column
 //            are read once and enter the sums of the three output planes that
 //            see them (27 multiply-adds and 13 reads per cell of a 4-plane
@@ -35,8 +37,8 @@
 
 namespace nps {
 
-enum GroupMode : uint32_t { kGZero = 0, kGPure = 1, kGGeneral = 2 };
-constexpr uint32_t kAnyPure = 0x01010101u, kAnyGeneral = 0x02020202u;   // over a wave's four modes
+enum GroupMode : uint32_t { kGZero = 0, kGPure = 1, kGGeneral = 2, kGPureAir = 4, kGPureSolid = 8 };
+constexpr uint32_t kAnyGeneral = 0x02020202u;   // over a wave's four modes
 
 // Work items of the level-1 network kernels: a 64 x 4 column footprint
 // over a chunk of 4 z-planes (2 on grids with fewer than 1024 such items).
@@ -172,6 +174,73 @@ __global__ __launch_bounds__(kBlock) void k_march_modes(const uint8_t* __restric
     }
 }
 
+// Group modes of a coarser level: pure when all windows of a wave's four whole
+// groups in a plane are pure cells of one label, general otherwise (zero only
+// where the row lies outside the grid; no output is masked there).  Four groups at
+// once, as every precision has it: in the mixed modes the constant kernel is the
+// float one and the others are rounded, so the choice is part of the results.
+template <int CH>
+__global__ __launch_bounds__(kBlock) void k_coarse_modes(const uint32_t* __restrict__ cnt, Grid g, uint32_t full,
+                                                         uint8_t* __restrict__ mode) {
+    constexpr int R = (CH + 2) * PHY;
+    __shared__ uint64_t own_s[R][3];   // a row's pure cells of each label
+    __shared__ uint32_t edge_s[R][3];  // and the cells beside it (bits 0, 1)
+    const Columns cl = march_columns(g);
+    const int per = cl.ncx * cl.ncy, rest = (int)blockIdx.x % per, zc = (int)blockIdx.x / per;
+    const int cx = rest % cl.ncx, cy = rest / cl.ncx, x0 = cx * PX, y0 = cy * PY, z0 = zc * CH;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t own[R / 4], edge[R / 4];
+#pragma unroll
+    for (int k = 0; k < R / 4; ++k) {
+        const int r = wv + 4 * k, z = z0 + r / PHY - 1, y = y0 + r % PHY - 1;
+        const bool row = z >= 0 && z < g.nz && y >= 0 && y < g.ny;
+        const int x = x0 + lane, xe = lane == 0 ? x0 - 1 : x0 + PX;
+        const bool in = row && x < g.nx, ine = row && lane < 2 && xe >= 0 && xe < g.nx;
+        own[k] = *at_or(cnt, in ? cell_index(g, z, y, x) : 0, in, pad_zero<uint32_t>());
+        edge[k] = *at_or(cnt, ine ? cell_index(g, z, y, xe) : 0, ine, pad_zero<uint32_t>());
+    }
+    const uint32_t pure[3] = {full, full << 16, 0u};   // packed counts of a pure cell
+#pragma unroll
+    for (int k = 0; k < R / 4; ++k)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const uint64_t f = __ballot(own[k] == pure[c]), e = __ballot(edge[k] == pure[c]);
+            if (lane == 0) {
+                own_s[wv + 4 * k][c] = f;
+                edge_s[wv + 4 * k][c] = (uint32_t)e;
+            }
+        }
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    const int w = threadIdx.x & 3, q = (threadIdx.x >> 2) & 3, i = threadIdx.x >> 4;   // thread (i, q, w)
+    const bool on = i < CH && z0 + i < g.nz;
+    const int left = g.nx - x0;
+    uint64_t valid = left >= 64 ? ~(uint64_t)0 : (((uint64_t)1 << left) - 1u);
+    if (!on || y0 + q >= g.ny) valid = 0u;
+    const uint32_t need = (uint32_t)(valid >> (16 * w)) & 0xffffu;
+    int m = need ? (int)kGGeneral : (int)kGZero;
+    if (on) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            uint64_t all = ~(uint64_t)0;
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+#pragma unroll
+                for (int b = 0; b < 3; ++b) {
+                    const uint64_t f = own_s[(i + a) * PHY + q + b][c];
+                    const uint32_t e = edge_s[(i + a) * PHY + q + b][c];
+                    all &= f & ((f << 1) | (e & 1u)) & ((f >> 1) | ((uint64_t)(e >> 1) << 63));
+                }
+            if (((uint32_t)(all >> (16 * w)) & need) == 0xffffu)
+                m = c == 0 ? kGPure : c == 1 ? kGPureAir : kGPureSolid;
+        }
+    }
+    // the wave's four rows: one kernel for all 64 cells, or the matrix cores
+    const bool same = m == __shfl_xor(m, 4, 64) && m == __shfl_xor(m, 8, 64) && m == __shfl_xor(m, 12, 64);
+    if (!same && need) m = kGGeneral;
+    if (on) mode[(((size_t)(z0 + i) * cl.ncy + cy) * cl.ncx + cx) * 16 + 4 * w + q] = (uint8_t)m;
+}
+
 // The staged item: (CH + 2) planes of PHY rows of kRS records.  The cell at x
 // offset ix (-1 .. 64) from the footprint is record ix + XO of its row: XO = 2
 // for the down kernel, whose staging writes four cells from ix = 4k at once,
@@ -269,7 +338,7 @@ __device__ __forceinline__ float reduce_scatter4(const float (&p)[4]) {
 
 // The CConv of the lane's cell in every plane of the item.  modes[i]: the
 // wave's four group modes in plane i (one byte each, uniform).
-template <int KM, int XO, int CH>
+template <int KM, int XO, int CH, bool L1>
 __device__ __forceinline__ void march_cconv(const uint2* rec, const uint32_t (&modes)[CH], const MarchCtx<KM>& mc,
                                             const CConvW<float>* __restrict__ w, float (&out)[CH]) {
     const int lane = threadIdx.x & 63, gq = lane >> 4;
@@ -279,13 +348,19 @@ __device__ __forceinline__ void march_cconv(const uint2* rec, const uint32_t (&m
         out[i] = 0.0f;
         any |= modes[i];
     }
-    if (any & kAnyPure) {
-        // the fluid kernel in scalar registers, loaded per item: kept across the
-        // item loop, its 27 registers spilled
-        __asm__ volatile("" : "+s"(w));
-        float kp[kTaps];
+    // the constant kernels of the wave's pure groups (level 1: fluid only)
+#pragma unroll 1
+    for (int c = 0; c < (L1 ? 1 : 3); ++c) {
+        const uint32_t bit = c == 0 ? kGPure : c == 1 ? kGPureAir : kGPureSolid;
+        if (!(any & (0x01010101u * bit))) continue;
+        // in scalar registers, loaded per item: kept across the item loop, the 27 of them spilled
+        const float* kc = w->Kpure[c];
+        __asm__ volatile("" : "+s"(kc));
+        float kp[kTaps], acc[CH];
 #pragma unroll
-        for (int t = 0; t < kTaps; ++t) kp[t] = w->Kpure[kFluid][t];
+        for (int t = 0; t < kTaps; ++t) kp[t] = kc[t];
+#pragma unroll
+        for (int i = 0; i < CH; ++i) acc[i] = 0.0f;
         const uint2* corner = rec + gq * kRS + 16 * (int)(threadIdx.x >> 6) + (lane & 15) + XO - 1;
 #pragma unroll
         for (int k = 0; k < CH + 2; ++k) {
@@ -301,8 +376,10 @@ __device__ __forceinline__ void march_cconv(const uint2* rec, const uint32_t (&m
             }
 #pragma unroll
             for (int a = 0; a < 3; ++a)
-                if (k - a >= 0 && k - a < CH) out[k - a] += s[a][0] + s[a][1];
+                if (k - a >= 0 && k - a < CH) acc[k - a] += s[a][0] + s[a][1];
         }
+#pragma unroll
+        for (int i = 0; i < CH; ++i) out[i] = L1 || ((modes[i] >> (8 * gq)) & bit) ? acc[i] : out[i];
     }
     if (any & kAnyGeneral) {
 #pragma unroll
@@ -399,6 +476,39 @@ __device__ __forceinline__ float4 stage_values(const float* __restrict__ r, cons
     return float4{v[0], v[1], v[2], v[3]};
 }
 
+// The image of a staging task: four labels in a word (level 1), or four counts.
+template <bool L1>
+struct ImgQuad {
+    uint32_t v[L1 ? 1 : 4];
+    __device__ __forceinline__ uint32_t cell(int j) const {
+        if constexpr (L1) return (v[0] >> (8 * j)) & 255u;
+        else return v[j];
+    }
+};
+
+template <bool L1, bool QUAD>
+__device__ __forceinline__ ImgQuad<L1> stage_image_quad(const void* __restrict__ img, const StagePos& s, int wide) {
+    ImgQuad<L1> q{};
+    if constexpr (L1) {
+        q.v[0] = stage_labels<QUAD>(static_cast<const uint8_t*>(img), s, wide);
+    } else {
+        const uint32_t* cnt = static_cast<const uint32_t*>(img);
+        if constexpr (!QUAD) {
+            q.v[0] = *at_or(cnt, s.base, s.cells > 0, pad_zero<uint32_t>());
+        } else if (wide) {
+            const uint4 u = *reinterpret_cast<const uint4*>(at_or(cnt, s.base, s.cells > 0, pad_zero<uint32_t>()));
+            q.v[0] = u.x;
+            q.v[1] = u.y;
+            q.v[2] = u.z;
+            q.v[3] = u.w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) q.v[j] = *at_or(cnt, s.base + j, j < s.cells, pad_zero<uint32_t>());
+        }
+    }
+    return q;
+}
+
 // Waves per SIMD of the level-1 kernels: one more hides more of the staging's
 // latency (128^3 mixed: up 21.1 -> 18.8 us, down 16.1 -> 14.8 us; 256^3: up 98
 // -> 86 us, down 78 -> 67 us), yet another one spills (up 26.0 us).  The
@@ -406,12 +516,15 @@ __device__ __forceinline__ float4 stage_values(const float* __restrict__ r, cons
 // registers of one wave each.
 constexpr int march_waves(int km, int nd) { return 5 - (km == kMfmaBf16x3 ? 1 : 0) - (nd > 2 ? 1 : 0); }
 
-// x1 = CConv_1^1(r) and r^2 = Pool(x1) (the input masked to fluid).  The 2x2x2
+// x1 = CConv_1(r) and, below the coarsest level (rnext), r_next = Pool(x1); at
+// level 1 (L1) the input is masked to fluid and izero names the items that only
+// write zeros.  Levels 2 and 3 ran tile kernels with a full 3-D halo before (16 x
+// 4 x 4 cells a block; 128^3 level of a 256^3 grid: 32 us down, 40 us up).  The 2x2x2
 // pool sums x pairs with a DPP quad permutation, y pairs with a permlane swap
 // and z pairs in a register (items start on even planes).
-template <int KM, int CH>
-__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, 0)) void k_down_l1m(
-    const uint8_t* __restrict__ lab, Grid g, const float* __restrict__ r, float* __restrict__ x1,
+template <int KM, int CH, bool L1>
+__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, 0)) void k_down_m(
+    const void* __restrict__ img, Grid g, const float* __restrict__ r, float* __restrict__ x1,
     float* __restrict__ rnext, const CConvW<float>* __restrict__ w, const MfmaW* __restrict__ wm, const State* st,
     const uint32_t* __restrict__ gmode, const uint8_t* __restrict__ izero, int wide) {
     constexpr int XO = 2;
@@ -431,7 +544,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, 0)) void k
         const int x0 = it.cx * PX, y0 = it.cy * PY, z0 = it.zc * CH;
         const int xx = x0 + 16 * wv + n, yy = y0 + gq;
         const bool col = xx < g.nx && yy < g.ny;
-        if (izero[it.zc * mi.per + it.rest]) {   // no window holds fluid: x1 is zero (read nowhere), and so is the pool
+        if (L1 && izero[it.zc * mi.per + it.rest]) {   // no window holds fluid: x1 is zero (read nowhere), and so is the pool
             if (done) return;
 #pragma unroll
             for (int i = 1; i < CH; i += 2)
@@ -442,18 +555,18 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, 0)) void k
         const int tid = item_thread();
         uint32_t modes[CH];
         load_modes<CH>(gmode, cl, it, g.nz, modes);
-        uint32_t lw[S::K];
+        ImgQuad<L1> lw[S::K];
         float4 rw[S::K];
 #pragma unroll
         for (int k = 0; k < S::K; ++k) {
             if (S::quads(wv, k)) {
                 const StagePos s = stage_pos<CH, XO, true>(g, x0, y0, z0, tid + k * kBlock);
                 rw[k] = stage_values<true>(r, s, wide);
-                lw[k] = stage_labels<true>(lab, s, wide);
+                lw[k] = stage_image_quad<L1, true>(img, s, wide);
             } else if (S::edges(wv, k)) {
                 const StagePos s = stage_pos<CH, XO, false>(g, x0, y0, z0, tid + k * kBlock);
                 rw[k] = stage_values<false>(r, s, wide);
-                lw[k] = stage_labels<false>(lab, s, wide);
+                lw[k] = stage_image_quad<L1, false>(img, s, wide);
             }
         }
         if (first) {
@@ -467,8 +580,8 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, 0)) void k
         for (int k = 0; k < S::K; ++k) {
             const float v[4] = {rw[k].x, rw[k].y, rw[k].z, rw[k].w};
             auto record = [&](int j) {
-                const uint32_t l = (lw[k] >> (8 * j)) & 255u;
-                return uint2{bits(l == kFluid ? v[j] : 0.0f), feat_word<KM, true>(l)};
+                const uint32_t l = lw[k].cell(j);
+                return uint2{bits(!L1 || l == kFluid ? v[j] : 0.0f), feat_word<KM, L1>(l)};
             };
             if (S::quads(wv, k)) {
                 const uint2 e0 = record(0), e1 = record(1), e2 = record(2), e3 = record(3);
@@ -481,7 +594,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, 0)) void k
         }
         __syncthreads();   // the item is staged
         float out[CH];
-        march_cconv<KM, XO, CH>(rec, modes, mc, w, out);
+        march_cconv<KM, XO, CH, L1>(rec, modes, mc, w, out);
         const uint32_t own = col ? (uint32_t)z0 * pstride + (uint32_t)yy * g.nx + xx : 0u;
         float pool = 0.0f;
 #pragma unroll
@@ -489,11 +602,20 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, 0)) void k
             const bool zin = z0 + i < g.nz;
             if (col && zin) x1[(size_t)own + (size_t)i * pstride] = out[i];
             // 2x2x2 pool: x pair (DPP quad_perm [1,0,3,2]), y pair (rows 2k, 2k+1)
-            const float px = out[i] + fbits(__builtin_amdgcn_update_dpp(0u, bits(out[i]), 0xB1, 0xF, 0xF, false));
-            const auto t = __builtin_amdgcn_permlane16_swap(bits(px), bits(px), false, false);
-            pool += fbits(t[0]) + fbits(t[1]);
+            auto right = [](float v) {
+                return fbits(__builtin_amdgcn_update_dpp(0u, bits(v), 0xB1, 0xF, 0xF, false));
+            };
+            if constexpr (L1) {
+                const float px = out[i] + right(out[i]);
+                const auto t = __builtin_amdgcn_permlane16_swap(bits(px), bits(px), false, false);
+                pool += fbits(t[0]) + fbits(t[1]);
+            } else {   // in the order of the other levels' pool: x, then y, then z (valid on the storing lanes)
+                const auto t = __builtin_amdgcn_permlane16_swap(bits(out[i]), bits(out[i]), false, false);
+                const float below = fbits(t[1]);
+                pool = (((pool + out[i]) + right(out[i])) + below) + right(below);
+            }
             if (i & 1) {
-                if (((n | gq) & 1) == 0 && col && zin)
+                if (((n | gq) & 1) == 0 && col && zin && rnext)
                     rnext[cell_index(gc, (z0 + i) >> 1, yy >> 1, xx >> 1)] = pool * 0.125f;
                 pool = 0.0f;
             }
@@ -516,32 +638,36 @@ constexpr int kCoarseCells = (CH / 2 + 2) * kCPlane;
 template <int CH>
 constexpr int kOctets = (CH / 2 + 1) * (PY / 2 + 1) * (PX / 2 + 1);
 
-// The pair of fine values between coarse values lo and hi: 3/4 lo + 1/4 hi, 1/4 lo + 3/4 hi.
+// The pair of fine values between coarse values lo and hi: 3/4 lo + 1/4 hi, 1/4 lo
+// + 3/4 hi (rounded as the tile kernels of the other levels do off level 1).
+template <bool L1>
 __device__ __forceinline__ void interp_pair(float lo, float hi, float& a, float& b) {
     const float d = hi - lo;
     a = fmaf(0.25f, d, lo);
-    b = fmaf(-0.25f, d, hi);
+    b = L1 ? fmaf(-0.25f, d, hi) : fmaf(0.75f, d, lo);
 }
 
 // ND: the most dots the state can ask for (NPSDO: n_ortho; PCG 1; flexible
 // PCG 2; 0 for the hook and the symmetric variant); HOOK: the parity hook and
 // training's forward (no scaling, no dots; x2out, when given, receives the
 // CConv's output on the live items, for the backward).
-template <int KM, bool HOOK, int ND, int CH>
-__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, ND)) void k_up_l1m(
-    const uint8_t* __restrict__ lab, Grid g, const float* __restrict__ xc, const float* __restrict__ x1,
+// L1 false: a coarser level, x = c1 x1 + c2 CConv_2(Interp(xc)) on all cells
+// (written to dhat), lvl the index of its c1, c2.
+template <int KM, bool HOOK, int ND, int CH, bool L1>
+__global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, ND)) void k_up_m(
+    const void* __restrict__ img, Grid g, const float* __restrict__ xc, const float* __restrict__ x1,
     float* __restrict__ dhat, const CConvW<float>* __restrict__ w, const MfmaW* __restrict__ wm, const State* st,
     double* __restrict__ partials, const float* __restrict__ ad0, const float* __restrict__ ad1,
     const float* __restrict__ ad2, const float* __restrict__ ad3, const uint32_t* __restrict__ gmode,
-    const uint8_t* __restrict__ izero, int wide, float* __restrict__ x2out) {
-    static_assert(!HOOK || ND == 0, "the hook forms no dots");
+    const uint8_t* __restrict__ izero, int wide, float* __restrict__ x2out, int lvl) {
+    static_assert((!HOOK || ND == 0) && (L1 || HOOK), "the hook and the coarser levels form no dots");
     constexpr int XO = 1;
     using S = StageTasks<CH>;
     constexpr int KC = (kCoarseCells<CH> + kBlock - 1) / kBlock, KO = (kOctets<CH> + kBlock - 1) / kBlock;
     __shared__ __attribute__((aligned(16))) uint2 rec[kRecords<CH>];
     __shared__ float csh[KC * kBlock];
     const int done = st->done;
-    const float c1 = (float)st->c1[0], c2 = (float)st->c2[0];
+    const float c1 = (float)st->c1[L1 ? 0 : lvl], c2 = (float)st->c2[L1 ? 0 : lvl];
     const float scale = HOOK ? 1.0f : (float)st->scale;
     const int ndots = HOOK || st->sym ? 0 : min(st->ndots, ND);   // the symmetric variant dots after P^T
     const MarchCtx<KM> mc = march_ctx<KM, XO>(wm);
@@ -561,7 +687,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, ND)) void 
         const int xx = x0 + 16 * wv + n, yy = y0 + gq;
         const bool col = xx < g.nx && yy < g.ny;
         const uint32_t own = col ? (uint32_t)z0 * pstride + (uint32_t)yy * g.nx + xx : 0u;
-        if (izero[it.zc * mi.per + it.rest]) {   // no fluid cell: the output is zero, the dots get nothing
+        if (L1 && izero[it.zc * mi.per + it.rest]) {   // no fluid cell: the output is zero, the dots get nothing
             if (done) return;
 #pragma unroll
             for (int i = 0; i < CH; ++i)
@@ -580,13 +706,13 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, ND)) void 
                       jx = min(max(x0 / 2 - 1 + i % kCX, 0), gc.nx - 1);
             cw[k] = xc[cell_index(gc, jz, jy, jx)];
         }
-        uint32_t lw[S::K];
+        ImgQuad<L1> lw[S::K];
 #pragma unroll
         for (int k = 0; k < S::K; ++k) {
             if (S::quads(wv, k))
-                lw[k] = stage_labels<true>(lab, stage_pos<CH, XO, true>(g, x0, y0, z0, tid + k * kBlock), wide);
+                lw[k] = stage_image_quad<L1, true>(img, stage_pos<CH, XO, true>(g, x0, y0, z0, tid + k * kBlock), wide);
             else if (S::edges(wv, k))
-                lw[k] = stage_labels<false>(lab, stage_pos<CH, XO, false>(g, x0, y0, z0, tid + k * kBlock), wide);
+                lw[k] = stage_image_quad<L1, false>(img, stage_pos<CH, XO, false>(g, x0, y0, z0, tid + k * kBlock), wide);
         }
         if (first) {
             __asm__ volatile("" ::: "memory");
@@ -602,9 +728,9 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, ND)) void 
             if (S::quads(wv, k)) {
                 uint2* dst = rec + stage_pos<CH, XO, true>(g, x0, y0, z0, tid + k * kBlock).rec;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) dst[j].y = feat_word<KM, true>((lw[k] >> (8 * j)) & 255u);
+                for (int j = 0; j < 4; ++j) dst[j].y = feat_word<KM, L1>(lw[k].cell(j));
             } else if (S::edges(wv, k)) {   // lanes past the last task repeat it
-                rec[stage_pos<CH, XO, false>(g, x0, y0, z0, tid + k * kBlock).rec].y = feat_word<KM, true>(lw[k]);
+                rec[stage_pos<CH, XO, false>(g, x0, y0, z0, tid + k * kBlock).rec].y = feat_word<KM, L1>(lw[k].cell(0));
             }
         }
         __syncthreads();   // coarse cells and features staged
@@ -620,15 +746,15 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, ND)) void 
                 for (int a = 0; a < 2; ++a)
 #pragma unroll
                     for (int b = 0; b < 2; ++b)
-                        interp_pair(c[(a * kCY + b) * kCX], c[(a * kCY + b) * kCX + 1], f[a][b][0], f[a][b][1]);
+                        interp_pair<L1>(c[(a * kCY + b) * kCX], c[(a * kCY + b) * kCX + 1], f[a][b][0], f[a][b][1]);
 #pragma unroll
                 for (int a = 0; a < 2; ++a)
 #pragma unroll
-                    for (int x = 0; x < 2; ++x) interp_pair(f[a][0][x], f[a][1][x], fy[a][0][x], fy[a][1][x]);
+                    for (int x = 0; x < 2; ++x) interp_pair<L1>(f[a][0][x], f[a][1][x], fy[a][0][x], fy[a][1][x]);
 #pragma unroll
                 for (int b = 0; b < 2; ++b)
 #pragma unroll
-                    for (int x = 0; x < 2; ++x) interp_pair(fy[0][b][x], fy[1][b][x], f[0][b][x], f[1][b][x]);
+                    for (int x = 0; x < 2; ++x) interp_pair<L1>(fy[0][b][x], fy[1][b][x], f[0][b][x], f[1][b][x]);
                 // the CConv_2 input is zero outside the grid and not masked inside (only the level's output is)
                 const int fz = z0 + 2 * oz - 1, fyy = y0 + 2 * oy - 1, fx = x0 + 2 * ox - 1;
                 const bool xin[2] = {fx >= 0 && fx < g.nx, fx + 1 < g.nx};
@@ -655,10 +781,10 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, ND)) void 
         }
         __syncthreads();   // the item is staged
         float x2[CH];
-        march_cconv<KM, XO, CH>(rec, modes, mc, w, x2);
+        march_cconv<KM, XO, CH, L1>(rec, modes, mc, w, x2);
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
-            const bool fl = rec[((i + 1) * PHY + gq + 1) * kRS + 16 * wv + n + XO].y == fluid_word;
+            const bool fl = !L1 || rec[((i + 1) * PHY + gq + 1) * kRS + 16 * wv + n + XO].y == fluid_word;
             const float out = fl ? (c1 * x1v[i] + c2 * x2[i]) * scale : 0.0f;
             if (col && z0 + i < g.nz) {
                 dhat[(size_t)own + (size_t)i * pstride] = out;

@@ -1,4 +1,4 @@
-"""Level-1 network kernels of the float modes (GPU): one work item of 64 x 4
+"""Network kernels of the large levels in the float modes (GPU): one work item of 64 x 4
 columns over 4 or 2 z-planes at a time, staged four cells at once where rows of
 four are aligned, cell by cell elsewhere.
 
@@ -72,6 +72,23 @@ def test_items_match_fp64(shape, precision, bar):
         again = nps.apply_precond(net, offset_copy(lab, lo), offset_copy(r.float(), ro),
                                   precision=getattr(nps, precision))
         assert torch.equal(again, got), (lo, ro)
+
+
+# Coarser levels on the same kernels: 4-plane items with a last chunk of 2 planes and
+# rows not of four cells at level 2, a coarsest level 3 with an odd plane count; 2-plane
+# items of whole words at level 2, both sweeps at level 3.
+@pytest.mark.parametrize("shape,levels", [((132, 256, 260), 3), ((128, 136, 264), 4)])
+@pytest.mark.parametrize("precision,bar", [("FP32", 1e-5), ("MIXED_BF16", 8e-3), ("MIXED_FP16", 8e-4)])
+def test_coarse_levels_match_fp64(shape, levels, precision, bar):
+    lab = torch.from_numpy(box_labels(shape, levels, boxes=30)).cuda()
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    r = torch.randn(shape, generator=gen, device="cuda", dtype=torch.float64)
+    net = nps.Net(blob(levels, 8), levels)
+    ref = nps.apply_precond(net, lab, r)
+    got = nps.apply_precond(net, lab, r.float(), precision=getattr(nps, precision))
+    err = (got.double() - ref).abs()
+    assert float(torch.linalg.norm(err) / torch.linalg.norm(ref)) < bar
+    assert float(err.max()) < bar * float(ref.abs().max())
 
 
 @pytest.mark.parametrize("n_ortho", [0, 1, 2, 3, 4])

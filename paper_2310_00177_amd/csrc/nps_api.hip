@@ -1358,11 +1358,12 @@ struct Request {
     int slot = -1;
     size_t off = 0, bytes = 0;  // arena region
     int k = 0;                  // last body enqueued
+    unsigned waits = 0;         // polls since then
 };
 
 struct Slot {
     hipStream_t s = nullptr;
-    hipEvent_t ev[2] = {nullptr, nullptr};
+    hipEvent_t ev = nullptr;
     State* hs = nullptr;
     HostFlags* hf = nullptr;
     HostFlags* hf_d = nullptr;
@@ -1460,8 +1461,8 @@ int admit(nps_server* srv, Slot& sl, Request* r) {
     NPS_HIP(hipMemcpyAsync(base + rl.lab, r->lab_h, r->n, hipMemcpyHostToDevice, sl.s));
     NPS_HIP(hipMemcpyAsync(base + rl.b, r->b_h, 8 * r->n, hipMemcpyHostToDevice, sl.s));
     NPS_TRY(sv->enqueue_validate());
-    NPS_TRY(sv->enqueue_setup());   // behind the validation: nothing of the request is in flight once ev[0] is done
-    NPS_HIP(hipEventRecord(sl.ev[0], sl.s));
+    NPS_TRY(sv->enqueue_setup());   // behind the validation: nothing of the request is in flight once ev is done
+    NPS_HIP(hipEventRecord(sl.ev, sl.s));
     r->phase = Request::kValidating;
     return NPS_OK;
 }
@@ -1478,7 +1479,7 @@ int enqueue_finish(nps_server* srv, Slot& sl) {
     }
     NPS_TRY(sl.sv->enqueue_finalize(x_d));
     NPS_HIP(hipMemcpyAsync(r->x_h, x_d, 8 * r->n, hipMemcpyDeviceToHost, sl.s));
-    NPS_HIP(hipEventRecord(sl.ev[0], sl.s));
+    NPS_HIP(hipEventRecord(sl.ev, sl.s));
     r->x_ready = true;
     r->phase = Request::kFinishing;
     return NPS_OK;
@@ -1491,7 +1492,7 @@ int advance(nps_server* srv, Slot& sl) {
     Request* r = sl.req;
     switch (r->phase) {
         case Request::kValidating: {
-            if (!event_done(sl.ev[0])) return NPS_OK;
+            if (!event_done(sl.ev)) return NPS_OK;
             release_inputs(srv, r);
             const int v = validation_status(sl.hs);
             if (v != NPS_OK) {
@@ -1503,26 +1504,29 @@ int advance(nps_server* srv, Slot& sl) {
             const int last = std::max(r->o.max_iter, 0) + 1;
             for (int k = 1; k <= std::min(2, last); ++k) {
                 NPS_TRY(sl.sv->enqueue_body(k));
-                NPS_HIP(hipEventRecord(sl.ev[k & 1], sl.s));
                 r->k = k;
             }
+            r->waits = 0;
             r->phase = Request::kRunning;
             return NPS_OK;
         }
         case Request::kRunning: {
             const int last = std::max(r->o.max_iter, 0) + 1;
-            const int watch = r->k < last ? r->k - 1 : r->k;   // one behind, or the final body
-            if (watch >= 1 && !event_done(sl.ev[watch & 1])) return NPS_OK;
-            if (watch < 1 && !event_done(sl.ev[r->k & 1])) return NPS_OK;
             volatile HostFlags* hf = sl.hf;
-            if (hf->done || r->k >= last) return enqueue_finish(srv, sl);
+            // The next body goes out once body k - 1 has passed its residual test, which
+            // the flags it writes to pinned memory tell (as in run_solve; an event per
+            // body cost the host 4 us of the 45 it takes to enqueue one).  An idle stream
+            // ends the wait too: the flags have then been written for good.
+            if (!hf->done && r->k < last) {
+                if (hf->iter < r->k - 2 && ((++r->waits & 1023) != 0 || hipStreamQuery(sl.s) != hipSuccess)) return NPS_OK;
+                r->waits = 0;
+            }
+            if (hf->done || r->k >= last) return enqueue_finish(srv, sl);   // in stream order behind the bodies
             r->k += 1;
-            NPS_TRY(sl.sv->enqueue_body(r->k));
-            NPS_HIP(hipEventRecord(sl.ev[r->k & 1], sl.s));
-            return NPS_OK;
+            return sl.sv->enqueue_body(r->k);
         }
         case Request::kFinishing: {
-            if (!event_done(sl.ev[0])) return NPS_OK;
+            if (!event_done(sl.ev)) return NPS_OK;
             nps_info info{};
             const int st = fill_info(sl.hs, &info);
             r->info = info;
@@ -2378,8 +2382,7 @@ int nps_server_create(const nps_net* net, size_t hbm_budget, int max_slots, nps_
         bool ok = hipHostGetDevicePointer(&d, sl.hf, 0) == hipSuccess;
         sl.hf_d = static_cast<HostFlags*>(d);
         ok = ok && hipStreamCreateWithFlags(&sl.s, hipStreamNonBlocking) == hipSuccess;
-        ok = ok && hipEventCreateWithFlags(&sl.ev[0], hipEventDisableTiming) == hipSuccess;
-        ok = ok && hipEventCreateWithFlags(&sl.ev[1], hipEventDisableTiming) == hipSuccess;
+        ok = ok && hipEventCreateWithFlags(&sl.ev, hipEventDisableTiming) == hipSuccess;
         if (!ok) {
             nps_server_destroy(srv);
             return fail(NPS_EDEVICE, "stream/event creation failed");
@@ -2394,8 +2397,7 @@ void nps_server_destroy(nps_server* srv) {
     for (Slot& sl : srv->slots) {
         if (sl.s) (void)hipStreamSynchronize(sl.s);
         delete sl.sv;
-        if (sl.ev[0]) (void)hipEventDestroy(sl.ev[0]);
-        if (sl.ev[1]) (void)hipEventDestroy(sl.ev[1]);
+        if (sl.ev) (void)hipEventDestroy(sl.ev);
         if (sl.s) (void)hipStreamDestroy(sl.s);
     }
     for (auto& kv : srv->live) {

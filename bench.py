@@ -300,7 +300,7 @@ def train_bench(args):
            "dtype": "f32", "data": "synthetic",
            "config": {"workload": f"{batch} systems of the {n}^3 scene recipe (seeds {args.seed}..{args.seed + batch - 1}), "
                                   f"unit-norm N(0,1) right-hand sides, L=6, {gi.param_count(6)} parameters, "
-                                  "stored kernels at every level", "systems_per_s": head["systems_per_s"],
+                                  "stored kernels at every level but the first in float", "systems_per_s": head["systems_per_s"],
                       "bf16_leg": legs["bf16"]},
            "cpu_baseline": cpu}
     print(json.dumps(out))

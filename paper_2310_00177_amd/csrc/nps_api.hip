@@ -181,7 +181,8 @@ Layout make_layout(nps_dims d, int levels, int precision, int n_ortho, bool solv
         L.k1[l] = put(s * kTaps * nl);
         if (l < levels) L.k2[l] = put(s * kTaps * nl);
     }
-    for (int l = 1; l <= levels; ++l) {
+    for (int l = 1; l <= levels; ++l) {   // tile kernels that form their kernels
+        if (p.km[l] != kVector && p.km[l] != kMfmaF64) continue;
         const size_t waves = (size_t)tiles_of(level_grid(d, l)).count() * TZ;
         L.wmode[l][0] = put(waves);
         if (l == 1) L.wmode[l][1] = put(waves);
@@ -1602,8 +1603,9 @@ int train_forward(const nps_net* net, const uint8_t* labels, nps_dims d, const T
 }
 
 // The CConv blocks of a system for k_wgrad: the blocks (rows of partial sums)
-// are shared out by the work of a block's tiles, where an up block interpolates
-// its input and a count beyond level 3 has two pieces.
+// are shared out by tiles, twice as many where a count has two pieces.  An up
+// block's tile interpolates its input but skips the waves off fluid: weighing it
+// 1.4, 0.8 or 0.5 times a down block's ran slower (128^3: 93, 91, 108 us against 88.5).
 template <class T>
 WgradArgs wgrad_args(const nps_net* net, const uint8_t* labels, nps_dims d, const TrainLayout& tl, void* ws, const T* r,
                      const T* gy, int add) {
@@ -1627,7 +1629,7 @@ WgradArgs wgrad_args(const nps_net* net, const uint8_t* labels, nps_dims d, cons
             sg.pieces = l <= kMfmaMaxLevel ? 1 : 2;
             sg.scale = std::ldexp(1.0, -3 * (l - 1));
             sg.gw = up ? off_c2(L, l) : off_c1(l);
-            work[a.nseg] = (double)tiles_of(sg.g).count() * (up ? 1.4 : 1.0) * sg.pieces;
+            work[a.nseg] = (double)tiles_of(sg.g).count() * sg.pieces;
             total += work[a.nseg++];
         }
     int row = 0;

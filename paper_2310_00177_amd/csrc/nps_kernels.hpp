@@ -15,8 +15,9 @@
 //   ortho       Dots stage (beta_i = dhat . A d_i / d_i . A d_i), d = dhat -
 //               sum beta_i d_i, A d; partial d . A d, r . d
 // The per-cell kernels K_t(p) of a level are either regenerated from the
-// labels on chip every application (MFMA for the large levels, vector ALU in
-// FP64) or, for levels of at most 32768 cells, formed once per solve.
+// labels on chip every application (matrix cores for the large levels; vector
+// ALU in float beyond level 3) or, for levels of at most 32768 cells, formed once
+// per solve.
 //
 // No kernel synchronises across workgroups: each reduction writes one
 // partial per block, and the kernel that consumes the sum adds the partials
@@ -1374,7 +1375,7 @@ __device__ __forceinline__ T bottom_interp(const T* xc, const BottomLevel& vc, i
 // lb by itself, in LDS order and without block barriers, while wave 1 sums the
 // partials of ||r||^2 and runs the Residual stage (the network is linear in r, so
 // nothing here needs its result; on the way of all waves it took 1.6 of the 7.8 us
-// after the network).  The result of level l (x1^l, then x^l once the up sweep has
+// of a 64^3 launch: 8.7 -> 6.8 us).  The result of level l (x1^l, then x^l once the up sweep has
 // combined it in place) stays in the level's x1 slot; the r slot holds r^l on the
 // way down and Interp(x^(l+1)) on the way up.
 
@@ -1722,7 +1723,7 @@ __global__ __launch_bounds__(kBlock) void k_ortho(const uint8_t* __restrict__ la
 // network input, and the partial ||r||^2.  Plane-marching: step s stages
 // plane s (x + alpha d and the labels, outside the grid x = 0 and solid)
 // and forms plane s - 1.  Only the live items are visited (items[0 .. nlive),
-// k_item_list); the others hold r = 0 and x = 0 from set-up.
+// k_live_list); the others hold r = 0 and x = 0 from set-up.
 // With snp > 0 the kernel first runs the previous iteration's Step stage:
 // every block sums the snp partials of d . A d and r . d (the same sums in
 // each, a fixed order), forms alpha and applies the update; block 0 records

@@ -137,7 +137,8 @@ __global__ __launch_bounds__(kBlock) void k_adj(const uint8_t* __restrict__ lab,
 // groups whose fluid cells have all-fluid windows (g is zero on the others) take
 // the constant fluid kernel, by the modes of the forward's up kernel; an item
 // that no group reaches is zero.  The table bounds the occupancy (two blocks a
-// CU); per plane a wave writes 8 values a lane and group and reads 27 a cell.
+// CU); per plane a wave writes 8 values a lane and group and reads 27 a cell.  128^3:
+// 65 us, against 107 us to form and store K and 70 us to gather it.
 constexpr int kAF = 72, kAFRows = PHY + 2;      // feature rows: x offsets -4 .. 67, y offsets -2 .. 5
 constexpr int kAG = 72;                         // g rows: x offsets -4 .. 67 (-1 .. 64 used)
 constexpr int kAVRow = 68, kAV = 420;           // V rows: x offsets -1 .. 64; 4 kAV = 16 mod 64 banks between lane groups
@@ -448,9 +449,10 @@ struct WgradLds {
 //   double  v_mfma_f64_16x16x4_f64.
 // What bounds it is forming U (16 products and their pieces per lane and 32
 // cells) beside 24 matrix instructions.  A wave whose g is all zero skips its
-// cells, a level-1 down tile without fluid in reach the tile.  Partial sums in
-// float, and per-thread sums on the vector ALU in double, as before: level 1
-// of a 128^3 system 230 us (up, with the transposed apply) and 140 us (down).
+// cells, a level-1 down tile without fluid in reach the tile.  All blocks of a
+// 128^3 system: 88.5 us in float.  (On fp32 matrix cores, and per thread on the vector
+// ALU in double, inside the transposed applies: 230 us for level 1 up, 140 us down, 25
+// us and more for every other block.)
 template <class T, int PU, int NF, bool L1, bool UP>
 __device__ __forceinline__ void wgrad_block(const WgradSeg& sg, const State* st, int add, char* lds,
                                             double* __restrict__ row) {

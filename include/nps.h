@@ -249,7 +249,7 @@ size_t nps_train_workspace_bytes(nps_dims dims, int levels, int precision);
  * replaced by its adjoint -- the second half of the symmetric variant
  * P^T o P of the appendix on symmetry.  g_d, y_d: vectors of the precision's
  * type (NPS_FP64 double, NPS_FP32 float), device, caller-owned; y is 0 off
- * fluid.  Workspace: nps_train_workspace_bytes.  Not synchronised. */
+ * fluid and may be g_d itself or overlap it.  Workspace: nps_train_workspace_bytes.  Not synchronised. */
 int nps_apply_precond_transpose(const nps_net* net, const uint8_t* labels_d, nps_dims dims, const void* g_d,
                                 void* y_d, int precision, void* ws_d, size_t ws_bytes, void* stream);
 

@@ -936,10 +936,17 @@ int adjoint_sweep(const nps_net* net, const uint8_t* labels, nps_dims d, const T
     return NPS_OK;
 }
 
-// y = P^T g.
+// y = P^T g.  y may overlap g.
 template <class T>
 int adjoint_apply(const nps_net* net, const uint8_t* labels, nps_dims d, const TrainLayout& tl, void* ws,
                   const T* g_in, T* y, hipStream_t s) {
+    const size_t n = ncells(level_grid(d, 1));
+    const uintptr_t ga = reinterpret_cast<uintptr_t>(g_in), ya = reinterpret_cast<uintptr_t>(y);
+    if (ga < ya + n * sizeof(T) && ya < ga + n * sizeof(T)) {
+        T* keep = mptr<T>(ws, tl.gy);   // training's loss gradient, not used here
+        NPS_TRY(launch("adj_copy", (double)n, s, [&] { k_copy<T><<<elem_grid(n), kBlock, 0, s>>>(n, g_in, keep); }));
+        g_in = keep;
+    }
     return adjoint_sweep<T>(net, labels, d, tl, ws, g_in, y, nullptr, s);
 }
 

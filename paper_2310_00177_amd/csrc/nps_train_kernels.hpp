@@ -352,6 +352,14 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(2) void k_adj_l1m(
     if (UP && x1) dc_partials(v, part);
 }
 
+// A copy of the adjoint's input, for a caller whose output overlaps it: level 1
+// reads g in the up sweep's first step and again, a window at a time, in the last
+// step, which writes y.
+template <class T>
+__global__ __launch_bounds__(kBlock) void k_copy(size_t n, const T* __restrict__ src, T* __restrict__ dst) {
+    for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += (size_t)gridDim.x * kBlock) dst[i] = src[i];
+}
+
 // Adjoint of the 2x trilinear upsampling: gc(j) = sum over fine cells f of
 // w(f -> j) gf(f).  Along one axis a fine cell f feeds f/2 with 3/4 and its
 // neighbour on f's side (clamped) with 1/4, so coarse j collects f = 2j, 2j+1

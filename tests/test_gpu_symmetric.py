@@ -124,3 +124,26 @@ def test_symmetric_solve_reaches_tolerance(precision):
     # iterations (measured: 363 in FP32); the FP64 path matches the oracle
     # iterate by iterate above.
     assert 150 <= info.iterations <= 2 * 227, info.iterations
+
+
+@pytest.mark.parametrize("shape,L", [((16, 16, 16), 5), ((32, 40, 48), 3)])   # stored kernels at level 1; not in float
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("shift", [0, 5, -5])
+def test_transpose_output_may_overlap_its_input(shape, L, dtype, shift):
+    """y on top of g, and starting 5 elements past or before it: the bits of separate buffers."""
+    rng = np.random.default_rng(8)
+    labels = dev(rng.choice(3, size=shape, p=(0.6, 0.2, 0.2)).astype(np.uint8))
+    net, n = nps.Net(params_with_biases(L, 12), L), int(np.prod(shape))
+    g = dev(rng.standard_normal(shape), dtype)
+    prec = nps.FP64 if dtype == torch.float64 else nps.FP32
+    ws = nps.train_workspace(shape, L, prec)
+    ref = nps.apply_precond_transpose(net, labels, g, ws=ws)
+    for _ in range(3):
+        buf = torch.zeros(n + 16, dtype=dtype, device="cuda")
+        src, out = buf[8:8 + n], buf[8 + shift:8 + shift + n]
+        src.copy_(g.view(-1))
+        wp, wb = nps._ws_args(ws)
+        rc = nps._lib.nps_apply_precond_transpose(net.handle, labels.data_ptr(), nps._dims(shape), src.data_ptr(),
+                                                  out.data_ptr(), prec, wp, wb, nps._stream())
+        torch.cuda.synchronize()
+        assert rc == 0 and torch.equal(out.view(shape), ref)

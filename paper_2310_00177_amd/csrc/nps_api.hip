@@ -1493,14 +1493,22 @@ int enqueue_finish(nps_server* srv, Slot& sl) {
     return NPS_OK;
 }
 
-bool event_done(hipEvent_t e) { return hipEventQuery(e) == hipSuccess; }
+// Whether a stream or event that was queried is done: 1, or 0 while work is
+// pending.  Anything else is a failure of the device: a hard error, which the
+// server has no other place to notice.
+int query_done(hipError_t q) {
+    if (q == hipSuccess) return 1;
+    if (q == hipErrorNotReady) return 0;
+    return fail(NPS_EDEVICE, "stream failed: %s", hipGetErrorString(q));
+}
 
 // Advance one slot without blocking; returns a hard error only for device failures.
 int advance(nps_server* srv, Slot& sl) {
     Request* r = sl.req;
     switch (r->phase) {
         case Request::kValidating: {
-            if (!event_done(sl.ev)) return NPS_OK;
+            const int ready = query_done(hipEventQuery(sl.ev));
+            if (ready <= 0) return ready;   // pending (NPS_OK), or failed
             release_inputs(srv, r);
             const int v = validation_status(sl.hs);
             if (v != NPS_OK) {
@@ -1526,7 +1534,11 @@ int advance(nps_server* srv, Slot& sl) {
             // body cost the host 4 us of the 45 it takes to enqueue one).  An idle stream
             // ends the wait too: the flags have then been written for good.
             if (!hf->done && r->k < last) {
-                if (hf->iter < r->k - 2 && ((++r->waits & 1023) != 0 || hipStreamQuery(sl.s) != hipSuccess)) return NPS_OK;
+                if (hf->iter < r->k - 2) {
+                    if ((++r->waits & 1023) != 0) return NPS_OK;
+                    const int idle = query_done(hipStreamQuery(sl.s));
+                    if (idle <= 0) return idle;
+                }
                 r->waits = 0;
             }
             if (hf->done || r->k >= last) return enqueue_finish(srv, sl);   // in stream order behind the bodies
@@ -1534,7 +1546,8 @@ int advance(nps_server* srv, Slot& sl) {
             return sl.sv->enqueue_body(r->k);
         }
         case Request::kFinishing: {
-            if (!event_done(sl.ev)) return NPS_OK;
+            const int ready = query_done(hipEventQuery(sl.ev));
+            if (ready <= 0) return ready;   // pending (NPS_OK), or failed
             nps_info info{};
             const int st = fill_info(sl.hs, &info);
             r->info = info;

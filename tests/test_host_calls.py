@@ -1,0 +1,94 @@
+"""What the library's host code does, on the CPU: the calls run against a stand-in for
+the HIP runtime (fake_hip.cpp), whose kernels do not run and whose queries return what
+the test says.  Each test is a child process, so that the stand-in never meets torch."""
+import json
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+PRELUDE = r"""
+import ctypes, importlib.util, json, sys
+import numpy as np
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)   # ahead of the library: its calls bind to it
+fake.fake_launched.restype = ctypes.c_char_p
+fake.fake_state.argtypes = [ctypes.c_double] + [ctypes.c_int] * 3
+spec = importlib.util.spec_from_file_location("_lib", sys.argv[2])
+lib = importlib.util.module_from_spec(spec)
+spec.loader.exec_module(lib)
+SUCCESS, NOT_READY, FAILED = 0, 600, 719   # hipSuccess, hipErrorNotReady, hipErrorLaunchFailure
+keep = []
+
+def device(nbytes):
+    b = np.zeros(nbytes + 256, dtype=np.uint8)
+    keep.append(b)
+    return (b.ctypes.data + 255) & ~255
+
+def network(levels):
+    p = np.zeros(lib.nps_param_count(levels))
+    rc, net = lib.nps_net_create(p.ctypes.data, p.size, levels, device(lib.nps_net_bytes(levels)),
+                                 lib.nps_net_bytes(levels), 0)
+    assert rc == 0
+    return net
+
+def launched():
+    out = [line.rsplit(" ", 2) for line in fake.fake_launched().decode().splitlines()]
+    fake.fake_forget()
+    return [(n, int(x), int(y)) for n, x, y in out]
+"""
+
+
+@pytest.fixture(scope="module")
+def call(repo_root, tmp_path_factory):
+    lib = os.path.join(repo_root, "paper_2310_00177_amd", "libnps.so")
+    if not os.path.exists(lib):
+        pytest.skip("libnps.so not built")
+    if not shutil.which("g++"):
+        pytest.skip("no host compiler")
+    so = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
+                    "-I", os.path.join(repo_root, "paper_2310_00177_amd", "csrc"),
+                    os.path.join(repo_root, "tests", "fake_hip.cpp"), "-o", so], check=True)
+
+    def run(body, **args):
+        script = PRELUDE + "args = json.loads(sys.argv[3])\n" + body
+        res = subprocess.run([sys.executable, "-c", script, so, os.path.join(repo_root, "paper_2310_00177_amd", "_lib.py"),
+                              json.dumps(args)], capture_output=True, text=True, timeout=110)
+        assert res.returncode == 0, res.stderr[-2000:]
+        return json.loads(res.stdout.splitlines()[-1])
+
+    return run
+
+
+@pytest.mark.parametrize("phase", ["validating", "running", "finishing"])
+def test_server_reports_a_failed_stream(call, phase):
+    """Pending work keeps a step at NPS_OK; a failed stream ends it with NPS_EDEVICE in every phase."""
+    rcs = call(r"""
+phase = args["phase"]
+rc, srv = lib.nps_server_create(network(2), 64 << 20, 1)
+assert rc == 0
+fake.fake_state(1.0, 8, 0, 0)
+lab, b = np.zeros((4, 4, 4), dtype=np.uint8), np.ones((4, 4, 4))
+o = lib.nps_opts(1e-6, 0 if phase == "finishing" else 100, 2, lib.NPS_FP32, 0, 0, 0)
+rc, rid = lib.nps_server_submit(srv, lab.ctypes.data, lib.nps_dims(4, 4, 4), b.ctypes.data, o)
+assert rc == 0
+step = lambda n: [lib.nps_server_step(srv)[0] for _ in range(n)]
+seen = []
+fake.fake_query(0, NOT_READY if phase == "validating" else SUCCESS)
+seen += step(2)          # admitted (and validated)
+if phase != "validating":
+    seen += step(1)      # bodies are out (finishing: the result's copy)
+fake.fake_query(0, NOT_READY)
+fake.fake_query(1, NOT_READY)
+seen += step(4096)
+fake.fake_query(0, FAILED)
+fake.fake_query(1, FAILED)
+failed = step(4096)      # the running phase looks at its stream once in 1024 steps
+print(json.dumps([sorted(set(seen)), sorted(set(failed)), lib.nps_server_poll(srv, rid, 0, lib.nps_info())[0]]))
+""", phase=phase)
+    seen, failed, poll = rcs
+    assert seen == [0]
+    assert -8 in failed and set(failed) <= {0, -8}
+    assert poll == 2

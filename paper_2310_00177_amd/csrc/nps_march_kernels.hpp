@@ -236,8 +236,9 @@ __global__ __launch_bounds__(kBlock) void k_coarse_modes(const uint32_t* __restr
         }
     }
     // the wave's four rows: one kernel for all 64 cells, or the matrix cores
-    const bool same = m == __shfl_xor(m, 4, 64) && m == __shfl_xor(m, 8, 64) && m == __shfl_xor(m, 12, 64);
-    if (!same && need) m = kGGeneral;
+    // (all three exchanges before any test: every lane takes part in each)
+    const int m1 = __shfl_xor(m, 4, 64), m2 = __shfl_xor(m, 8, 64), m3 = __shfl_xor(m, 12, 64);
+    if (need && (m != m1 || m != m2 || m != m3)) m = kGGeneral;
     if (on) mode[(((size_t)(z0 + i) * cl.ncy + cy) * cl.ncx + cx) * 16 + 4 * w + q] = (uint8_t)m;
 }
 

@@ -195,13 +195,20 @@ Layout make_layout(nps_dims d, int levels, int precision, int n_ortho, bool solv
     }
     for (int l = 2; l <= levels; ++l)
         if (is_mfma(p.km[l])) L.cmode[l] = put(group_mode_bytes(level_grid(d, l)));
-    // Set-up tables.  A network evaluation writes its output to the caller's
-    // buffer, so there they share the bytes of the solve's d^.
+    // Set-up tables, in bytes that are free during set-up: a solve's class sums in
+    // its dots, which the first body writes, its totals in d^; a network evaluation
+    // writes its output to the caller's buffer, and training reads the tables
+    // again in its backward pass, so there both have the bytes of d^.
     L.dhat = off;
-    L.cls = put(sizeof(ClassSums));
-    L.tot = put(sizeof(uint2) * (size_t)pyramid_blocks(level_grid(d, 1)));
-    if (!solve) off = std::max(off, L.dhat + align256(s * n));
-    else L.dhat = put(s * n);
+    if (solve) {
+        static_assert(sizeof(ClassSums) <= sizeof(double) * kRedWidth * kMaxRedBlocks, "class sums fit the dots");
+        L.cls = L.dots;
+        L.tot = put(sizeof(uint2) * (size_t)pyramid_blocks(level_grid(d, 1)));
+    } else {
+        L.cls = put(sizeof(ClassSums));
+        L.tot = put(sizeof(uint2) * (size_t)pyramid_blocks(level_grid(d, 1)));
+    }
+    off = std::max(off, L.dhat + align256(s * n));
     if (solve) {
         for (int i = 0; i <= n_ortho; ++i) {
             L.dring[i] = put(s * n);

@@ -86,11 +86,13 @@ __device__ __forceinline__ MarchItem march_item(const MarchItems& m, int li, Col
     return it;
 }
 
-// One mode byte per (footprint, z, wave, row): index ((z ncy + cy) ncx + cx)
-// * 16 + 4 w + q, so a wave's four modes are one aligned word.
+// One mode byte per 16-cell group, the four rows of a wave in one aligned word: word
+// (z ncy + cy) nwx + (16-cell column).  nwx counts the columns that hold cells (words
+// for whole footprints took up to four times as much: with them the coarser levels'
+// modes were 86 MB of the workspace of a grid 4 cells wide and 375936 long).
+__host__ __device__ inline int wave_columns(Grid g) { return (g.nx + 15) / 16; }
 __host__ __device__ inline size_t group_mode_bytes(Grid g) {
-    const Columns cl = columns_of(g);
-    return (size_t)cl.ncx * cl.ncy * g.nz * 16;
+    return (size_t)wave_columns(g) * ((g.ny + PY - 1) / PY) * g.nz * 4;
 }
 
 // Group modes of the level-1 down (CConv_1, input zero off fluid) and up
@@ -163,9 +165,12 @@ __global__ __launch_bounds__(kBlock) void k_march_modes(const uint8_t* __restric
         };
         md = mode(any);
         mu = mode(own_f);
-        const size_t at = (((size_t)(z0 + i) * cl.ncy + cy) * cl.ncx + cx) * 16 + 4 * w + q;
-        mdown[at] = (uint8_t)md;
-        mup[at] = (uint8_t)mu;
+        const int nwx = wave_columns(g), wx = 4 * cx + w;
+        if (wx < nwx) {   // the others hold no cell
+            const size_t at = (((size_t)(z0 + i) * cl.ncy + cy) * nwx + wx) * 4 + q;
+            mdown[at] = (uint8_t)md;
+            mup[at] = (uint8_t)mu;
+        }
     }
     const uint64_t nd = __ballot(md != kGZero), nu = __ballot(mu != kGZero);
     if (threadIdx.x == 0) {
@@ -239,7 +244,8 @@ __global__ __launch_bounds__(kBlock) void k_coarse_modes(const uint32_t* __restr
     // (all three exchanges before any test: every lane takes part in each)
     const int m1 = __shfl_xor(m, 4, 64), m2 = __shfl_xor(m, 8, 64), m3 = __shfl_xor(m, 12, 64);
     if (need && (m != m1 || m != m2 || m != m3)) m = kGGeneral;
-    if (on) mode[(((size_t)(z0 + i) * cl.ncy + cy) * cl.ncx + cx) * 16 + 4 * w + q] = (uint8_t)m;
+    const int nwx = wave_columns(g), wx = 4 * cx + w;
+    if (on && wx < nwx) mode[(((size_t)(z0 + i) * cl.ncy + cy) * nwx + wx) * 4 + q] = (uint8_t)m;
 }
 
 // The staged item: (CH + 2) planes of PHY rows of kRS records.  The cell at x
@@ -399,15 +405,15 @@ __device__ __forceinline__ void march_cconv(const uint2* rec, const uint32_t (&m
 
 // The wave's modes of the item's planes (zero past the grid).
 template <int CH>
-__device__ __forceinline__ void load_modes(const uint32_t* __restrict__ gmode, Columns cl, const MarchItem& it, int nz,
+__device__ __forceinline__ void load_modes(const uint32_t* __restrict__ gmode, Columns cl, const MarchItem& it, Grid g,
                                            uint32_t (&modes)[CH]) {
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wx = 4 * it.cx + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwx = wave_columns(g);
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
         const int z = it.zc * CH + i;
-        modes[i] = z < nz ? __builtin_amdgcn_readfirstlane(
-                                gmode[(((size_t)z * cl.ncy + it.cy) * cl.ncx + it.cx) * 4 + wv])
-                          : 0u;
+        modes[i] = z < g.nz && wx < nwx
+                       ? __builtin_amdgcn_readfirstlane(gmode[((size_t)z * cl.ncy + it.cy) * nwx + wx])
+                       : 0u;
     }
 }
 
@@ -555,7 +561,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, 0)) void k
         }
         const int tid = item_thread();
         uint32_t modes[CH];
-        load_modes<CH>(gmode, cl, it, g.nz, modes);
+        load_modes<CH>(gmode, cl, it, g, modes);
         ImgQuad<L1> lw[S::K];
         float4 rw[S::K];
 #pragma unroll
@@ -697,7 +703,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, ND)) void 
         }
         const int tid = item_thread();
         uint32_t modes[CH];
-        load_modes<CH>(gmode, cl, it, g.nz, modes);
+        load_modes<CH>(gmode, cl, it, g, modes);
         float cw[KC];
 #pragma unroll
         for (int k = 0; k < KC; ++k) {

@@ -158,6 +158,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(2) void k_adj_l1m(
     const float coef = UP ? (float)st->c2[0] : (float)st->c1[0];
     const Columns cl = march_columns(g);
     const Grid gc = coarser(g);
+    const int nwx = wave_columns(g);
     const int lane = threadIdx.x & 63, lg = lane >> 4, n = lane & 15;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t fluid_word = feat_word<KM, true>(kFluid), pstride = (uint32_t)g.ny * (uint32_t)g.nx;
@@ -231,9 +232,9 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(2) void k_adj_l1m(
         // modes of the planes' groups: the footprint's rows and its y neighbours' (four waves each)
         uint32_t mw = 0u;
         if (tid < NPL * 12) {
-            const int z = z0 - 1 + tid / 12, cy = it.cy - 1 + tid / 4 % 3;
-            const bool in = z >= 0 && z < g.nz && cy >= 0 && cy < cl.ncy;
-            if (in) mw = UP ? gmode[(((size_t)z * cl.ncy + cy) * cl.ncx + it.cx) * 4 + tid % 4] : kAnyGeneral;
+            const int z = z0 - 1 + tid / 12, cy = it.cy - 1 + tid / 4 % 3, wx = 4 * it.cx + tid % 4;
+            const bool in = z >= 0 && z < g.nz && cy >= 0 && cy < cl.ncy && wx < nwx;
+            if (in) mw = UP ? gmode[((size_t)z * cl.ncy + cy) * nwx + wx] : kAnyGeneral;
         }
         float4 gw[S::K];
         uint32_t lw[S::K];

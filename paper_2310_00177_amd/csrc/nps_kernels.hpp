@@ -1531,15 +1531,9 @@ __global__ __launch_bounds__(kBottomThreads) void k_bottom(BottomArgs<T> a, Stat
 // cell come from the planes staged before and after its own.  Against a
 // tile with a full 3-D halo this stages about 0.6x the elements, in rows
 // 3.7x longer.
-constexpr int PX = 64, PY = kBlock / PX;
 constexpr int PHX = PX + 2, PHY = PY + 2;
 constexpr int kPlane = PHX * PHY;
 constexpr int kPlaneP = pad_block(kPlane);
-struct Columns {   // column footprints x z-chunks of a grid
-    int ncx, ncy, ncz, chunk;
-    __host__ __device__ int count() const { return ncx * ncy * ncz; }
-};
-
 // Chunks of 8 planes (the plane below a chunk is read once more per chunk);
 // 4 or 2 on grids that would otherwise give fewer than 512 chunks, so that
 // small grids still spread over the compute units.  A function of the grid

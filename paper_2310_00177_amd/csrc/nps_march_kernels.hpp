@@ -40,52 +40,6 @@ namespace nps {
 enum GroupMode : uint32_t { kGZero = 0, kGPure = 1, kGGeneral = 2, kGPureAir = 4, kGPureSolid = 8 };
 constexpr uint32_t kAnyGeneral = 0x02020202u;   // over a wave's four modes
 
-// Work items of the level-1 network kernels: a 64 x 4 column footprint
-// over a chunk of 4 z-planes (2 on grids with fewer than 1024 such items).
-// Shorter items than the 7-point kernels' keep the per-block work even: an
-// item's cost depends on its group modes and the cost field is smooth in
-// space.  When the grid of blocks is a multiple of the XCD count, XCD x
-// (blocks b with b % 8 == x) takes the z-chunks zc with zc % 8 == x, every
-// footprint of each, so its blocks share the y halos of a slab in their L2
-// while every XCD gets slabs from the whole height; its blocks take the XCD's
-// items round-robin.  A function of the grid alone: launches and kernels agree
-// on it.
-__host__ __device__ inline Columns march_columns(Grid g) {
-    const int ncx = (g.nx + PX - 1) / PX, ncy = (g.ny + PY - 1) / PY;
-    const int chunk = ncx * ncy * ((g.nz + 3) / 4) >= 1024 ? 4 : 2;
-    return Columns{ncx, ncy, (g.nz + chunk - 1) / chunk, chunk};
-}
-
-// The items of a block, in the order above.
-struct MarchItems {
-    int per, count, xcd, zmul, li, step;
-};
-
-__device__ __forceinline__ MarchItems march_items(Columns cl) {
-    const bool xs = gridDim.x % kXcds == 0;
-    MarchItems m;
-    m.xcd = xs ? (int)(blockIdx.x % kXcds) : 0;
-    m.zmul = xs ? kXcds : 1;
-    m.per = cl.ncx * cl.ncy;
-    m.count = m.per * (xs ? (cl.ncz - m.xcd + kXcds - 1) / kXcds : cl.ncz);
-    m.li = xs ? (int)blockIdx.x / kXcds : (int)blockIdx.x;
-    m.step = xs ? (int)gridDim.x / kXcds : (int)gridDim.x;
-    return m;
-}
-
-struct MarchItem {
-    int cx, cy, zc, rest;
-};
-
-__device__ __forceinline__ MarchItem march_item(const MarchItems& m, int li, Columns cl) {
-    MarchItem it;
-    it.zc = m.xcd + m.zmul * (li / m.per);
-    it.rest = li % m.per;
-    it.cx = it.rest % cl.ncx;
-    it.cy = it.rest / cl.ncx;
-    return it;
-}
-
 // One mode byte per 16-cell group, the four rows of a wave in one aligned word: word
 // (z ncy + cy) nwx + (16-cell column).  nwx counts the columns that hold cells (words
 // for whole footprints took up to four times as much: with them the coarser levels'
@@ -544,7 +498,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, 0)) void k
     const int lane = threadIdx.x & 63, gq = lane >> 4, n = lane & 15;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t pstride = (uint32_t)g.ny * (uint32_t)g.nx;
-    const MarchItems mi = march_items(cl);
+    const MarchItems mi = march_items(cl, (int)gridDim.x, (int)blockIdx.x);
     bool first = true;
     for (int li = mi.li; li < mi.count; li += mi.step) {
         const MarchItem it = march_item(mi, li, cl);
@@ -686,7 +640,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, ND)) void 
     const uint32_t fluid_word = feat_word<KM, true>(kFluid);
     double v[kRedWidth] = {0.0, 0.0, 0.0, 0.0};
     const uint32_t pstride = (uint32_t)g.ny * (uint32_t)g.nx;
-    const MarchItems mi = march_items(cl);
+    const MarchItems mi = march_items(cl, (int)gridDim.x, (int)blockIdx.x);
     bool first = true;
     for (int li = mi.li; li < mi.count; li += mi.step) {
         const MarchItem it = march_item(mi, li, cl);

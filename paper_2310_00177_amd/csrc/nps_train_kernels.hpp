@@ -221,7 +221,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(2) void k_adj_l1m(
     const int evi = n < 2 * PHY ? erow * kAVRow + eix + 1 : PHY * kAVRow + n - 2 * PHY;
     static_assert(PHY * kAVRow + 16 - 2 * PHY <= kAV, "spare columns");
     double v[2] = {0.0, 0.0};
-    const MarchItems mi = march_items(cl);
+    const MarchItems mi = march_items(cl, (int)gridDim.x, (int)blockIdx.x);
     for (int li = mi.li; li < mi.count; li += mi.step) {
         const MarchItem it = march_item(mi, li, cl);
         const int x0 = it.cx * PX, y0 = it.cy * PY, z0 = it.zc * CH;

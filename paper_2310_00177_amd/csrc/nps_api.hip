@@ -111,20 +111,37 @@ size_t bottom_footprint(nps_dims d, int lb, int levels) {
     return e;
 }
 
-Plan make_plan(nps_dims d, int levels, int precision, bool all_stored = false, bool bf16w = false) {
+// What a plan is for.  All but the solve's own network gather from the kernels of
+// every level (the adjoint), so they store them and have no one-workgroup bottom.
+enum Use { kUseSolve, kUseSymmetric, kUseTranspose, kUseTrain };
+
+// Whether a large level 1 in float keeps its kernels too, where the network kernels and
+// the adjoint can form them on matrix cores: their cost goes with the work items, so it
+// depends on the share of an item's cells that the grid fills (64 columns; 8 cells of x
+// fill an eighth).  Stored against formed, in us:
+//   symmetric iterations (ten)  512 x 512 x 32 (1/2) 16330 and 17910, 66^3 (1/2) 958 and 1520,
+//                               200 x 200 x 40 (5/8) 3724 and 3753, 128^3 (1) 5000 and 3800
+//   P^T                         1024 x 512 x 8 (1/8) 1312 and 2323, 300 x 300 x 24 (3/8) 447 and 485,
+//                               512 x 512 x 32 (1/2) 1514 and 1320, 128^3 (1) 417 and 260
+//   training (bf16)             1024 x 512 x 8 (1/8) 2060 and 2114, 300 x 300 x 24 (3/8) 737 and 545
+bool store_level1(Grid g, Use use) {
+    const Columns cl = march_columns(g);
+    const double fill = (double)ncells(g) / ((double)cl.count() * kBlock * cl.chunk);
+    return fill < (use == kUseSymmetric ? 0.6 : use == kUseTranspose ? 0.4 : 0.0);
+}
+
+Plan make_plan(nps_dims d, int levels, int precision, Use use = kUseSolve, bool bf16w = false) {
     Plan p = {};
     p.L = levels;
     p.lb = levels + 1;
     for (int l = 1; l <= levels; ++l) {
-        const size_t n = ncells(level_grid(d, l));
-        if (all_stored) {
-            // training and the symmetric variant: no one-workgroup bottom, and every
-            // level keeps its kernels but a large level 1 in float, whose adjoint forms
-            // them on matrix cores like the forward (in three pieces also where the
-            // solve's own network is mixed; one in the bf16 training leg)
-            p.km[l] = l == 1 && precision != NPS_FP64 && n > (size_t)kStoreMaxCells
-                          ? (bf16w ? kMfmaBf16 : kMfmaBf16x3)
-                          : kStored;
+        const Grid g = level_grid(d, l);
+        const size_t n = ncells(g);
+        if (use != kUseSolve) {
+            // formed on matrix cores in three pieces also where the solve's own network
+            // is mixed, in one in the bf16 training leg
+            const bool formed = l == 1 && precision != NPS_FP64 && n > (size_t)kStoreMaxCells && !store_level1(g, use);
+            p.km[l] = !formed ? kStored : bf16w ? kMfmaBf16 : kMfmaBf16x3;
             continue;
         }
         if (n <= (size_t)kStoreMaxCells) p.km[l] = kStored;
@@ -158,9 +175,12 @@ struct Layout {
     size_t total;
 };
 
-Layout make_layout(nps_dims d, int levels, int precision, int n_ortho, bool solve, bool all_stored = false) {
+// use: kUseSolve (also a network evaluation), kUseSymmetric, or kUseTrain, whose
+// workspace serves P^T as well and so has room for what either keeps.
+Layout make_layout(nps_dims d, int levels, int precision, int n_ortho, bool solve, Use use = kUseSolve) {
     Layout L = {};
-    const Plan p = make_plan(d, levels, precision, all_stored);
+    const Plan p = make_plan(d, levels, precision, use);
+    const Plan adj = use == kUseTrain ? make_plan(d, levels, precision, kUseTranspose) : p;
     size_t off = 0;
     auto put = [&](size_t bytes) {
         const size_t at = off;
@@ -176,7 +196,7 @@ Layout make_layout(nps_dims d, int levels, int precision, int n_ortho, bool solv
     for (int l = 1; l <= levels; ++l) L.x1[l] = put(s * ncells(level_grid(d, l)));
     for (int l = 2; l <= levels; ++l) L.rb[l] = put(s * ncells(level_grid(d, l)));
     for (int l = 1; l <= levels; ++l) {
-        if (p.km[l] != kStored) continue;
+        if (p.km[l] != kStored && adj.km[l] != kStored) continue;
         const size_t nl = ncells(level_grid(d, l));
         L.k1[l] = put(s * kTaps * nl);
         if (l < levels) L.k2[l] = put(s * kTaps * nl);
@@ -240,7 +260,7 @@ struct TrainLayout {
 
 TrainLayout make_train_layout(nps_dims d, int levels, int precision, bool solve = false, int n_ortho = 0) {
     TrainLayout t = {};
-    t.base = make_layout(d, levels, precision, n_ortho, solve, true);
+    t.base = make_layout(d, levels, precision, n_ortho, solve, solve ? kUseSymmetric : kUseTrain);
     size_t off = t.base.total;
     auto put = [&](size_t bytes) {
         const size_t at = off;
@@ -879,14 +899,13 @@ int adjoint_l1m(const nps_net* net, const uint8_t* labels, nps_dims d, const Tra
 }
 
 // The adjoint sweep: Alg. 2 backwards with each linear step replaced by its
-// adjoint (the setup of the layout tl must have run).  g_in: gradient of the network's output (level 1).  With y,
+// adjoint (the setup of the plan in the layout tl must have run).  g_in: gradient of the network's output (level 1).  With y,
 // y = P^T g_in (P is linear in its input vector); in training (dcparts: the
 // partials per level of dL/dc1, dL/dc2, left in tl.dc) the sweep ends at level 2.
 template <class T>
-int adjoint_sweep(const nps_net* net, const uint8_t* labels, nps_dims d, const TrainLayout& tl, void* ws,
+int adjoint_sweep(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan& plan, const TrainLayout& tl, void* ws,
                   const T* g_in, T* y, int* dcparts, hipStream_t s, bool bf16w = false) {
     const int L = net->levels;
-    const Plan plan = make_plan(d, L, sizeof(T) == 4 ? NPS_FP32 : NPS_FP64, true, bf16w);
     const Layout& lay = tl.base;
     const State* st = cptr<State>(ws, lay.state);
     for (int l = 1; l < L; ++l) {   // up sweep, reversed
@@ -945,7 +964,7 @@ int adjoint_sweep(const nps_net* net, const uint8_t* labels, nps_dims d, const T
 
 // y = P^T g.  y may overlap g.
 template <class T>
-int adjoint_apply(const nps_net* net, const uint8_t* labels, nps_dims d, const TrainLayout& tl, void* ws,
+int adjoint_apply(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan& plan, const TrainLayout& tl, void* ws,
                   const T* g_in, T* y, hipStream_t s) {
     const size_t n = ncells(level_grid(d, 1));
     const uintptr_t ga = reinterpret_cast<uintptr_t>(g_in), ya = reinterpret_cast<uintptr_t>(y);
@@ -954,7 +973,7 @@ int adjoint_apply(const nps_net* net, const uint8_t* labels, nps_dims d, const T
         NPS_TRY(launch("adj_copy", (double)n, s, [&] { k_copy<T><<<elem_grid(n), kBlock, 0, s>>>(n, g_in, keep); }));
         g_in = keep;
     }
-    return adjoint_sweep<T>(net, labels, d, tl, ws, g_in, y, nullptr, s);
+    return adjoint_sweep<T>(net, labels, d, plan, tl, ws, g_in, y, nullptr, s);
 }
 
 int check_opts(const nps_opts& o) {
@@ -981,7 +1000,7 @@ struct SolveLayout {
 SolveLayout solve_layout(nps_dims d, int levels, const nps_opts& o) {
     SolveLayout r{};
     if (o.symmetric) {
-        r.plan = make_plan(d, levels, o.precision, true);
+        r.plan = make_plan(d, levels, o.precision, kUseSymmetric);
         r.tl = make_train_layout(d, levels, o.precision, true, o.n_ortho);
         r.lay = r.tl.base;
         r.total = r.tl.total;
@@ -1165,7 +1184,7 @@ struct SolverT : Solver {
                                      o.symmetric ? 0 : (o.method == NPS_NPSDO ? o.n_ortho : o.method == NPS_PCG ? 1 : 2))));
         if (o.symmetric) {   // d^ = P^T P(r)/||r||, then the dots the up kernel left out
             T* dsym = mptr<T>(ws, tl.dsym);
-            NPS_TRY(adjoint_apply<T>(net, labels, d, tl, ws, dhat, dsym, s));
+            NPS_TRY(adjoint_apply<T>(net, labels, d, plan, tl, ws, dhat, dsym, s));
             const size_t n = ncells(g);
             np = red_elem_grid(n);
             NPS_TRY(launch("sym_dots", cells, s, [&] {
@@ -1579,7 +1598,7 @@ int train_forward(const nps_net* net, const uint8_t* labels, nps_dims d, const T
                   const T* r, T* y, hipStream_t s, bool bf16w = false) {
     const int L = net->levels;
     const Layout& lay = tl.base;
-    const Plan plan = make_plan(d, L, vec_bytes(NPS_FP32) == sizeof(T) ? NPS_FP32 : NPS_FP64, true, bf16w);
+    const Plan plan = make_plan(d, L, vec_bytes(NPS_FP32) == sizeof(T) ? NPS_FP32 : NPS_FP64, kUseTrain, bf16w);
     State* st = mptr<State>(ws, lay.state);
     auto wblock = [&](int b) { return bf16w ? cconv_block_bf16<T>(net, b) : cconv_block<T>(net, b); };
     ClassSums* cls = mptr<ClassSums>(ws, lay.cls);
@@ -1682,7 +1701,8 @@ int train_backward(const nps_net* net, const uint8_t* labels, nps_dims d, const 
     const State* st = cptr<State>(ws, lay.state);
     double* wpart = mptr<double>(ws, tl.wpart);
     int dcparts[kMaxLevels + 1] = {};
-    NPS_TRY(adjoint_sweep<T>(net, labels, d, tl, ws, gy, nullptr, dcparts, s, bf16w));
+    const Plan plan = make_plan(d, L, sizeof(T) == 4 ? NPS_FP32 : NPS_FP64, kUseTrain, bf16w);
+    NPS_TRY(adjoint_sweep<T>(net, labels, d, plan, tl, ws, gy, nullptr, dcparts, s, bf16w));
     *args = wgrad_args<T>(net, labels, d, tl, ws, r, gy, add);
     const WgradArgs a = *args;
     NPS_TRY(launch("train_wgrad", (double)ncells(level_grid(d, 1)), s, [&] {
@@ -2112,17 +2132,17 @@ int nps_apply_precond_transpose(const nps_net* net, const uint8_t* labels_d, nps
     if (ws_bytes < tl.total) return fail(NPS_ENOMEM, "workspace has %zu bytes, needs %zu", ws_bytes, tl.total);
     if (reinterpret_cast<uintptr_t>(ws_d) % 256) return fail(NPS_EINVAL, "workspace not 256-byte aligned");
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const Plan plan = make_plan(dims, net->levels, precision, true);
+    const Plan plan = make_plan(dims, net->levels, precision, kUseTranspose);
     State* st = mptr<State>(ws_d, tl.base.state);
     ClassSums* cls = mptr<ClassSums>(ws_d, tl.base.cls);
     NPS_TRY(launch("state_init", 0, s, [&] { k_state_init<<<1, kBlock, 0, s>>>(st, cls); }));
     if (precision == NPS_FP64) {
         NPS_TRY(run_setup<double>(net, labels_d, dims, plan, tl.base, ws_d, s));
-        return adjoint_apply<double>(net, labels_d, dims, tl, ws_d, static_cast<const double*>(g_d),
+        return adjoint_apply<double>(net, labels_d, dims, plan, tl, ws_d, static_cast<const double*>(g_d),
                                      static_cast<double*>(y_d), s);
     }
     NPS_TRY(run_setup<float>(net, labels_d, dims, plan, tl.base, ws_d, s));
-    return adjoint_apply<float>(net, labels_d, dims, tl, ws_d, static_cast<const float*>(g_d), static_cast<float*>(y_d),
+    return adjoint_apply<float>(net, labels_d, dims, plan, tl, ws_d, static_cast<const float*>(g_d), static_cast<float*>(y_d),
                                 s);
 }
 

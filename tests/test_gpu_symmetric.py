@@ -147,3 +147,36 @@ def test_transpose_output_may_overlap_its_input(shape, L, dtype, shift):
                                                   out.data_ptr(), prec, wp, wb, nps._stream())
         torch.cuda.synchronize()
         assert rc == 0 and torch.equal(out.view(shape), ref)
+
+
+# thin grids whose level 1 keeps its kernels in float (work items an eighth and a sixteenth
+# full), and a half-full one (P^T forms them, the symmetric variant keeps them)
+THIN = [((128, 66, 8), 2), ((132, 128, 4), 3), ((34, 70, 66), 2)]
+
+
+@pytest.mark.parametrize("shape,L", THIN)
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_transpose_on_thin_grids(shape, L, dtype):
+    rng = np.random.default_rng(sum(shape))
+    lab = rng.choice(3, size=shape, p=(0.6, 0.2, 0.2)).astype(np.uint8)
+    g, params = rng.standard_normal(shape), params_with_biases(L, 13)
+    y = nps.apply_precond_transpose(nps.Net(params, L), dev(lab), dev(g, dtype)).cpu().double().numpy()
+    ref = og.transpose_apply(onet.Network(params, L, lab), g)
+    assert rel(y, ref) <= (1e-12 if dtype == torch.float64 else 1e-5), rel(y, ref)
+    assert np.all(y[lab != gi.FLUID] == 0)
+
+
+@pytest.mark.parametrize("shape,L", THIN)
+def test_symmetric_iterates_on_thin_grids(shape, L):
+    """Float iterates of the symmetric variant against FP64's (1e-4, the bar of the other ragged-grid iterates)."""
+    lab = np.zeros(shape, dtype=np.uint8)
+    lab[3 * shape[0] // 4:] = gi.AIR
+    lab[5:9, 3:7] = gi.SOLID
+    b = gi.gen_rhs(lab, seed=4)
+    net = nps.Net(gi.multilevel_params(L), L)
+    kw = dict(max_iter=4, fixed_iters=True, symmetric=True)
+    ref, _ = nps.solve(net, dev(lab), dev(b), precision=nps.FP64, **kw)
+    for p in (nps.FP32, nps.MIXED_BF16):
+        x, info = nps.solve(net, dev(lab), dev(b), precision=p, **kw)
+        assert info.iterations == 4
+        assert rel(x.cpu().numpy(), ref.cpu().numpy()) < 1e-4

@@ -92,3 +92,32 @@ print(json.dumps([sorted(set(seen)), sorted(set(failed)), lib.nps_server_poll(sr
     assert seen == [0]
     assert -8 in failed and set(failed) <= {0, -8}
     assert poll == 2
+
+
+ADJOINT = r"""
+def adjoint(kind, dims):
+    '''Whether the call forms level 1's kernels in its adjoint (k_adj_l1m) instead of storing them.'''
+    d, net = lib.nps_dims(*dims), network(2)
+    ws, n = device(1 << 16), 1 << 62      # no kernel runs: nothing touches the workspace
+    fake.fake_forget()
+    if kind == "transpose":
+        rc = lib.nps_apply_precond_transpose(net, 1 << 40, d, 2 << 40, 3 << 40, lib.NPS_FP32, ws, n, 0)
+    elif kind == "train":
+        rc, _ = lib.nps_train_step(net, 1 << 40, d, 1, 2 << 40, 3 << 40, lib.NPS_FP32, ws, n, 0)
+    else:
+        fake.fake_state(1.0, 8, 0, 0)
+        o = lib.nps_opts(1e-6, 1, 2, lib.NPS_FP32, 0, 0, 1)
+        rc = lib.nps_solve(net, 1 << 40, d, 2 << 40, 3 << 40, o, lib.nps_info(), ws, n, 0)
+    assert rc >= 0, (kind, dims, rc, lib.nps_last_error())
+    return any("k_adj_l1m" in name for name, _, _ in launched())
+"""
+
+
+def test_adjoint_stores_level_1_where_work_items_are_mostly_empty(call):
+    """Thin grids and footprints that are half empty: the symmetric variant and P^T ran up to four times
+    slower there than with stored kernels."""
+    got = call(ADJOINT + r"""
+print(json.dumps([[adjoint(k, d) for k in ("symmetric", "transpose", "train")] for d in args["dims"]]))
+""", dims=[(512, 512, 4), (1024, 512, 8), (66, 66, 66), (512, 512, 32), (128, 128, 128), (256, 256, 256)])
+    assert got == [[False, False, True], [False, False, True], [False, True, True], [False, True, True],
+                   [True, True, True], [True, True, True]]

@@ -123,11 +123,14 @@ enum Use { kUseSolve, kUseSymmetric, kUseTranspose, kUseTrain };
 //                               200 x 200 x 40 (5/8) 3724 and 3753, 128^3 (1) 5000 and 3800
 //   P^T                         1024 x 512 x 8 (1/8) 1312 and 2323, 300 x 300 x 24 (3/8) 447 and 485,
 //                               512 x 512 x 32 (1/2) 1514 and 1320, 128^3 (1) 417 and 260
-//   training (bf16)             1024 x 512 x 8 (1/8) 2060 and 2114, 300 x 300 x 24 (3/8) 737 and 545
+//   training                    512 x 512 x 4 (1/16) 1029 and 1245, 1024 x 512 x 8 (1/8) 2188 and 2371 (bf16
+//                               2060 and 2114), 300 x 300 x 24 (3/8) 778 and 615
+// (At a tenth the items of the largest grids are also few enough for one launch of
+// k_march_modes, a block each.)
 bool store_level1(Grid g, Use use) {
     const Columns cl = march_columns(g);
     const double fill = (double)ncells(g) / ((double)cl.count() * kBlock * cl.chunk);
-    return fill < (use == kUseSymmetric ? 0.6 : use == kUseTranspose ? 0.4 : 0.0);
+    return fill < (use == kUseSymmetric ? 0.6 : use == kUseTranspose ? 0.4 : 0.1);
 }
 
 Plan make_plan(nps_dims d, int levels, int precision, Use use = kUseSolve, bool bf16w = false) {
@@ -547,7 +550,7 @@ int run_setup(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
     PyramidOut po{};
     for (int l = 2; l <= L; ++l) po.cnt[l] = mptr<uint32_t>(ws, lay.counts[l]);
     NPS_TRY(launch("setup_pyramid", (double)ncells(g1), s, [&] {
-        k_pyramid<<<pyr, kPyrThreads, 0, s>>>(labels, g1, L, po, cls, tot, wide_labels(labels, g1) ? 1 : 0);
+        k_pyramid<<<unit_grid(pyr, kPyrThreads), kPyrThreads, 0, s>>>(labels, g1, L, po, cls, tot, wide_labels(labels, g1) ? 1 : 0);
     }));
     FinishArgs fa{};
     fa.g = g1;
@@ -572,10 +575,10 @@ int run_setup(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
             const int blk = which == 0 ? block_down(l) : block_up(net, l);
             const CConvW<double>* w = bf16w ? cconv_block_bf16<double>(net, blk) : cconv_block<double>(net, blk);
             const MfmaW* wm = mfma_block(net, blk);
-// 16-cell groups, a wave each; several per wave once they fill the chip (a
+            // 16-cell groups, a wave each; several per wave once they fill the chip (a
             // wave's weight fragments are 12 KB)
             const int groups = g.nz * g.ny * ((g.nx + 15) / 16);
-            const int mg = std::min((groups + 3) / 4, std::max(256, (groups + 31) / 32));
+            const int mg = std::min({(groups + 3) / 4, std::max(256, (groups + 31) / 32), 65536});
             if (mfma || n <= (size_t)kStoreMaxCells) {   // beside the other levels
                 KgenSeg& sg = fa.seg[fa.nseg++];
                 sg.img = img(l);

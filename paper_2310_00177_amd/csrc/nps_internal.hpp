@@ -188,6 +188,15 @@ __host__ __device__ inline MarchItem march_item(const MarchItems& m, int li, Col
     return it;
 }
 
+// A grid of one block per work unit without a cap: a launch's threads along an axis
+// stay below 2^32, so counts past that (grids a few cells wide and 10^8 long) go on in
+// y.  The kernel takes its unit from block_unit and leaves when there are fewer.
+constexpr unsigned units_per_axis(int threads) { return 0xffffffffu / (unsigned)threads; }
+inline dim3 unit_grid(int units, int threads) {
+    const unsigned per = units_per_axis(threads), n = (unsigned)(units < 1 ? 1 : units);
+    return dim3(n < per ? n : per, (n + per - 1) / per);
+}
+
 inline int red_blocks(int work_blocks) {
     return work_blocks < kMaxRedBlocks ? (work_blocks > 0 ? work_blocks : 1) : kMaxRedBlocks;
 }

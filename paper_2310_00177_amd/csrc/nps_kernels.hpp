@@ -106,6 +106,12 @@ __device__ __forceinline__ TileOrigin tile_origin(int tile, Tiles tl) {
     return o;
 }
 
+// The work unit of a block of unit_grid.
+template <int NT>
+__device__ __forceinline__ int block_unit() {
+    return (int)(blockIdx.y * units_per_axis(NT) + blockIdx.x);
+}
+
 // Grids hold at most 1e9 cells (the entry points check), so the index of an
 // in-grid cell is formed in 32 bits.
 __device__ __forceinline__ size_t cell_index(Grid g, int z, int y, int x) {

@@ -60,11 +60,11 @@ __global__ __launch_bounds__(kPyrThreads) void k_pyramid(const uint8_t* __restri
     constexpr int H = kPyrSide / 2;
     __shared__ uint32_t sum[2][H * H * H];
     __shared__ uint32_t cs[kMaxLevels][kClasses][2];
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, cube = block_unit<kPyrThreads>();
+    if (cube >= pyramid_blocks(g)) return;
     for (int i = t; i < kMaxLevels * kClasses * 2; i += kPyrThreads) (&cs[0][0][0])[i] = 0u;
     const int bx = (g.nx + kPyrSide - 1) / kPyrSide, by = (g.ny + kPyrSide - 1) / kPyrSide;
-    const int x0 = (int)(blockIdx.x % bx) * kPyrSide, y0 = (int)(blockIdx.x / bx % by) * kPyrSide,
-              z0 = (int)(blockIdx.x / (bx * by)) * kPyrSide;
+    const int x0 = cube % bx * kPyrSide, y0 = cube / bx % by * kPyrSide, z0 = cube / (bx * by) * kPyrSide;
     // a wave holds two z-planes of 32 rows: lane bit 0 = y & 1, lane bit 5 = z & 1
     const int y = y0 + (t & 31), z = z0 + (t >> 5);
     const bool row = y < g.ny && z < g.nz;
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(kPyrThreads) void k_pyramid(const uint8_t* __restri
         cur ^= 1;
         __syncthreads();
     }
-    if (t == 0) tot[blockIdx.x] = uint2{sum[cur][0] & 0xffffu, sum[cur][0] >> 16};
+    if (t == 0) tot[cube] = uint2{sum[cur][0] & 0xffffu, sum[cur][0] >> 16};
     for (int i = t; i < kMaxLevels * kClasses * 2; i += kPyrThreads) {
         const uint32_t v = (&cs[0][0][0])[i];
         if (v) atomicAdd(&(&cls->n[0][0][0])[i], v);

@@ -62,3 +62,23 @@ def test_invalid_solve_leaves_no_work_behind():
     assert bool((x == 7.0).all())
     _, info = nps.solve(net, labels, torch.from_numpy(b).cuda(), x=x)
     assert info.status == 0 and info.n_fluid == int((lab == gi.FLUID).sum())
+
+
+def test_grid_past_a_launch_axis():
+    """A grid of 2 x 2 cells so long that its pyramid blocks pass one axis of a launch (2^32 threads): the first
+    planes, those around the last block of the axis and the last ones against short grids of the same cells (the
+    Aff weights are zero, so the network is local; 16 planes at a cut are left out)."""
+    nz, w = 134_217_728 + 4096, 256
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    lab = torch.randint(0, 3, (nz, 2, 2), generator=gen, device="cuda", dtype=torch.uint8)
+    r = torch.randn((nz, 2, 2), generator=gen, device="cuda", dtype=torch.float64)
+    blob = random_blob(2, 5)
+    for name, _, off, size in gi.blob_layout(2):
+        if name in ("a1W", "a2W"):
+            blob[off:off + size] = 0.0
+    net = nps.Net(blob, 2)
+    y = nps.apply_precond(net, lab, r)
+    for at in (0, 134_217_696 - w // 2, nz - w):
+        ref = nps.apply_precond(net, lab[at:at + w].contiguous(), r[at:at + w].contiguous())
+        lo, hi = (0 if at == 0 else 16), (w if at + w == nz else w - 16)
+        assert float((y[at + lo:at + hi] - ref[lo:hi]).abs().max()) < 1e-12 * float(ref.abs().max())

@@ -131,3 +131,19 @@ def test_symmetric_iterates_on_a_large_level_1(precision):
     ref, _ = nps.solve(net, labels, bt, precision=nps.FP64, **kw)
     got, _ = nps.solve(net, labels, bt, precision=getattr(nps, precision), **kw)
     assert float(torch.linalg.norm(got - ref) / torch.linalg.norm(ref)) < 1e-4
+
+
+@pytest.mark.parametrize("precision", list(BARS))
+def test_gradient_on_a_thin_grid_matches_oracle(precision):
+    """A large level 1 whose work items are a sixteenth full keeps its kernels in float too."""
+    shape, levels = (132, 128, 4), 3
+    params, p = blob(levels, 6), getattr(nps, precision)
+    lab, b = scene(shape, 5)
+    ref_loss, ref = og.batch_loss_and_grad(params, levels, [lab], [b])
+    ws = nps.train_workspace(shape, levels, p)
+    ws.fill_(255)
+    grad = torch.zeros(gi.param_count(levels), dtype=torch.float64, device="cuda")
+    loss = nps.train_step(nps.Net(params, levels), torch.from_numpy(lab[None]).cuda(),
+                          torch.from_numpy(b[None]).to(nps.vector_dtype(p)).cuda(), grad, ws, precision=p)
+    assert loss == pytest.approx(ref_loss, rel=10 * BARS[precision])
+    assert rel(grad.cpu().numpy(), ref) <= BARS[precision]

@@ -119,5 +119,30 @@ def test_adjoint_stores_level_1_where_work_items_are_mostly_empty(call):
     got = call(ADJOINT + r"""
 print(json.dumps([[adjoint(k, d) for k in ("symmetric", "transpose", "train")] for d in args["dims"]]))
 """, dims=[(512, 512, 4), (1024, 512, 8), (66, 66, 66), (512, 512, 32), (128, 128, 128), (256, 256, 256)])
-    assert got == [[False, False, True], [False, False, True], [False, True, True], [False, True, True],
+    assert got == [[False, False, False], [False, False, True], [False, True, True], [False, True, True],
                    [True, True, True], [True, True, True]]
+
+
+def test_launches_stay_within_the_axis_limit(call):
+    """Grids a few cells wide and up to 10^8 long, which the calls accept, launch fewer than 2^32 threads along an axis."""
+    got = call(r"""
+most = {}
+for dims in args["dims"]:
+    d, net = lib.nps_dims(*dims), network(2)
+    ws, n = device(1 << 16), 1 << 62
+    fake.fake_state(1.0, 8, 0, 0)
+    for p in (lib.NPS_FP64, lib.NPS_FP32):
+        rcs = [lib.nps_apply_precond_transpose(net, 1 << 40, d, 2 << 40, 3 << 40, p, ws, n, 0),
+               lib.nps_train_step(net, 1 << 40, d, 1, 2 << 40, 3 << 40, p, ws, n, 0)[0],
+               lib.nps_solve(net, 1 << 40, d, 2 << 40, 3 << 40, lib.nps_opts(1e-6, 1, 2, p, 0, 0, 1), lib.nps_info(), ws, n, 0)]
+        if p == lib.NPS_FP64 or min(dims) == 24:   # in float the item kernels take fewer than 2^24 work items
+            rcs += [lib.nps_apply_precond(net, 1 << 40, d, 2 << 40, 3 << 40, p, ws, n, 0),
+                    lib.nps_solve(net, 1 << 40, d, 2 << 40, 3 << 40, lib.nps_opts(1e-6, 1, 2, p, 0, 0, 0), lib.nps_info(), ws, n, 0)]
+        assert min(rcs) >= 0, (dims, p, rcs, lib.nps_last_error())
+        for name, x, y in launched():
+            most[name] = max(most.get(name, 0), x, 256 * y)
+print(json.dumps(most))
+""", dims=[(140000000, 2, 2), (2, 140000000, 2), (2, 2, 140000000), (60000000, 4, 4), (24, 24, 1600000),
+         (1600000, 24, 24)])
+    assert any("k_pyramid" in name for name in got) and any("k_march_modes" in name for name in got)
+    assert {name: t for name, t in got.items() if t >= 2 ** 32} == {}

@@ -1033,7 +1033,7 @@ struct Solver {
     HostFlags* hf_d = nullptr;    // device address of hf
     virtual ~Solver() {}
     virtual int enqueue_validate() = 0;            // scan, then copy the state to hs
-    virtual int enqueue_setup() = 0;               // pyramid, Aff, stored kernels (needs no verdict)
+    virtual int enqueue_setup() = 0;               // pyramid, Aff, stored kernels (after the verdict)
     virtual void begin() = 0;                      // after the verdict, before the first body
     virtual int enqueue_body(int k) = 0;           // iteration k (see below)
     virtual int enqueue_finalize(double* x_out) = 0;   // x_out, then copy the state to hs
@@ -1240,7 +1240,7 @@ Solver* make_solver(int precision) {
 // nps_solve: validate, set up, iterate with a one-body-behind poll, finalize.
 // Events bracketing a solve's phases on its stream (created once per thread).
 struct SolveEvents {
-    hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};   // start, setup done, end, validated
+    hipEvent_t ev[3] = {nullptr, nullptr, nullptr};   // start, setup done, end
     bool ok = false;
     SolveEvents() {
         ok = true;
@@ -1252,19 +1252,12 @@ int run_solve(Solver& sv, double* x_out, nps_info* info) {
     thread_local SolveEvents tev;
     if (!tev.ok) return fail(NPS_EDEVICE, "hipEventCreate failed");
     NPS_HIP(hipEventRecord(tev.ev[0], sv.s));
-    // The set-up kernels read the labels and the weights only: they follow the
-    // validation at once, so the host's wait for its verdict costs the GPU nothing.
     NPS_TRY(sv.enqueue_validate());
-    NPS_HIP(hipEventRecord(tev.ev[3], sv.s));
-    NPS_TRY(sv.enqueue_setup());
-    NPS_HIP(hipEventRecord(tev.ev[1], sv.s));
-    NPS_HIP(hipEventSynchronize(tev.ev[3]));
-    const int verdict = validation_status(sv.hs);
-    if (verdict != NPS_OK) {
-        NPS_HIP(hipStreamSynchronize(sv.s));
-        return verdict;
-    }
+    NPS_HIP(hipStreamSynchronize(sv.s));
+    NPS_TRY(validation_status(sv.hs));
     if (sv.hs->bb != 0.0) {
+        NPS_TRY(sv.enqueue_setup());
+        NPS_HIP(hipEventRecord(tev.ev[1], sv.s));
         sv.begin();
         const int max_iter = std::max(sv.o.max_iter, 0);
         volatile HostFlags* hf = sv.hf;
@@ -1285,6 +1278,8 @@ int run_solve(Solver& sv, double* x_out, nps_info* info) {
             }
             if (hf->done) break;
         }
+    } else {
+        NPS_HIP(hipEventRecord(tev.ev[1], sv.s));   // b = 0: no set-up, no iteration
     }
     NPS_TRY(sv.enqueue_finalize(x_out));
     NPS_HIP(hipEventRecord(tev.ev[2], sv.s));
@@ -1498,7 +1493,6 @@ int admit(nps_server* srv, Slot& sl, Request* r) {
     NPS_HIP(hipMemcpyAsync(base + rl.lab, r->lab_h, r->n, hipMemcpyHostToDevice, sl.s));
     NPS_HIP(hipMemcpyAsync(base + rl.b, r->b_h, 8 * r->n, hipMemcpyHostToDevice, sl.s));
     NPS_TRY(sv->enqueue_validate());
-    NPS_TRY(sv->enqueue_setup());   // behind the validation: nothing of the request is in flight once ev is done
     NPS_HIP(hipEventRecord(sl.ev, sl.s));
     r->phase = Request::kValidating;
     return NPS_OK;
@@ -1545,6 +1539,7 @@ int advance(nps_server* srv, Slot& sl) {
                 return NPS_OK;
             }
             if (sl.hs->bb == 0.0) return enqueue_finish(srv, sl);
+            NPS_TRY(sl.sv->enqueue_setup());
             sl.sv->begin();
             const int last = std::max(r->o.max_iter, 0) + 1;
             for (int k = 1; k <= std::min(2, last); ++k) {

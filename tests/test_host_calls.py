@@ -146,3 +146,29 @@ print(json.dumps(most))
          (1600000, 24, 24)])
     assert any("k_pyramid" in name for name in got) and any("k_march_modes" in name for name in got)
     assert {name: t for name, t in got.items() if t >= 2 ** 32} == {}
+
+
+@pytest.mark.parametrize("what", ["b = 0", "bad label", "no fluid", "not finite"])
+@pytest.mark.parametrize("entry", ["solve", "server"])
+def test_no_set_up_without_a_solve(call, what, entry):
+    """A solve that ends at its validation launches the validation, and the result's copy where there is one."""
+    got = call(r"""
+state = {"b = 0": (0.0, 8, 0, 0), "bad label": (1.0, 8, 1, 0), "no fluid": (1.0, 0, 0, 0), "not finite": (1.0, 8, 0, 1)}[args["what"]]
+fake.fake_state(*state)
+net, d, o = network(2), lib.nps_dims(64, 64, 64), lib.nps_opts(1e-6, 100, 2, lib.NPS_MIXED_BF16, 0, 0, 0)
+fake.fake_forget()
+if args["entry"] == "solve":
+    rc = lib.nps_solve(net, 1 << 40, d, 2 << 40, 3 << 40, o, lib.nps_info(), device(1 << 16), 1 << 62, 0)
+else:
+    rc, srv = lib.nps_server_create(net, 64 << 20, 1)
+    lab, b = np.zeros((64, 64, 64), dtype=np.uint8), np.ones((64, 64, 64))
+    _, rid = lib.nps_server_submit(srv, lab.ctypes.data, d, b.ctypes.data, o)
+    for _ in range(8):
+        assert lib.nps_server_step(srv)[0] == 0
+    rc = lib.nps_server_poll(srv, rid, b.ctypes.data, lib.nps_info())[0]
+print(json.dumps([rc, [name for name, _, _ in launched()]]))
+""", what=what, entry=entry)
+    rc, names = got
+    assert rc == {"b = 0": 0, "bad label": -3, "no fluid": -4, "not finite": -5}[what]
+    kept = ["k_validate", "k_live_list"] + (["k_finalize"] if what == "b = 0" else [])
+    assert len(names) == len(kept) and all(k in n for k, n in zip(kept, names)), names

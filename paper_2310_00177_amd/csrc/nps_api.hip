@@ -659,6 +659,16 @@ int with_kmode(int km, F&& f) {
     return fail(NPS_EINVAL, "kernel mode %d not available for this precision", km);
 }
 
+// f(groups a wave evaluates) of a tile kernel as a constant (see MfmaCtx).
+template <int KM, class F>
+int with_groups(Grid g, F&& f) {
+    if constexpr (KM == kMfmaF64) {
+        if (g.nz == 1) return f(std::integral_constant<int, 1>());
+        if (g.nz == 2) return f(std::integral_constant<int, 2>());
+    }
+    return f(std::integral_constant<int, 4>());
+}
+
 // Alg. 2 below level 1: coarse down levels, bottom workgroup, coarse up
 // levels.  On return *x2 points at x^2, the input of level 1's up block.
 // res_partials (with res_np and hf): the iteration's Residual stage, run by
@@ -696,15 +706,18 @@ int run_coarse(const nps_net* net, nps_dims d, const Plan& plan, const Layout& l
                     });
                 });
             } else {
-                const int grid = persist_grid(l < L ? &k_down<T, KM, true> : &k_down<T, KM, false>, g);
-                if (l < L)
-                    return launch(kDownName[l], cells, s, [&] {
-                        k_down<T, KM, true><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), rin, x1, rnext, w, kst, st,
-                                                                     cptr<int8_t>(ws, lay.wmode[l][0]));
+                return with_groups<KM>(g, [&](auto ng) {
+                    constexpr int NG = decltype(ng)::value;
+                    const int grid = persist_grid(l < L ? &k_down<T, KM, true, NG> : &k_down<T, KM, false, NG>, g);
+                    if (l < L)
+                        return launch(kDownName[l], cells, s, [&] {
+                            k_down<T, KM, true, NG><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), rin, x1, rnext, w, kst,
+                                                                            st, cptr<int8_t>(ws, lay.wmode[l][0]));
+                        });
+                    return launch("net_coarsest", cells, s, [&] {
+                        k_down<T, KM, false, NG><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), rin, x1, nullptr, w, kst,
+                                                                         st, cptr<int8_t>(ws, lay.wmode[l][0]));
                     });
-                return launch("net_coarsest", cells, s, [&] {
-                    k_down<T, KM, false><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), rin, x1, nullptr, w, kst, st,
-                                                                  cptr<int8_t>(ws, lay.wmode[l][0]));
                 });
             }
         }));
@@ -781,10 +794,13 @@ int run_coarse(const nps_net* net, nps_dims d, const Plan& plan, const Layout& l
                     });
                 });
             } else {
-                const int grid = persist_grid(&k_up<T, KM>, g);
-                return launch(kUpName[l], (double)ncells(g), s, [&] {
-                    k_up<T, KM><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), xc, x1, xo, w, kst, l - 1, st, nullptr,
-                                                        cptr<int8_t>(ws, lay.wmode[l][0]));
+                return with_groups<KM>(g, [&](auto ng) {
+                    constexpr int NG = decltype(ng)::value;
+                    const int grid = persist_grid(&k_up<T, KM, NG>, g);
+                    return launch(kUpName[l], (double)ncells(g), s, [&] {
+                        k_up<T, KM, NG><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), xc, x1, xo, w, kst, l - 1, st,
+                                                                nullptr, cptr<int8_t>(ws, lay.wmode[l][0]));
+                    });
                 });
             }
         }));
@@ -819,10 +835,13 @@ int run_down_l1(const nps_net* net, const uint8_t* labels, nps_dims d, const Pla
                 });
             });
         } else {
-            const int grid = persist_grid(&k_down_l1<T, KM>, g);
-            return launch("net_down_l1", (double)ncells(g), s, [&] {
-                k_down_l1<T, KM><<<grid, kBlock, 0, s>>>(labels, g, r, x1, rnext, w, kst, st,
-                                                         cptr<int8_t>(ws, lay.wmode[1][0]));
+            return with_groups<KM>(g, [&](auto ng) {
+                constexpr int NG = decltype(ng)::value;
+                const int grid = persist_grid(&k_down_l1<T, KM, NG>, g);
+                return launch("net_down_l1", (double)ncells(g), s, [&] {
+                    k_down_l1<T, KM, NG><<<grid, kBlock, 0, s>>>(labels, g, r, x1, rnext, w, kst, st,
+                                                                 cptr<int8_t>(ws, lay.wmode[1][0]));
+                });
             });
         }
     });
@@ -866,11 +885,15 @@ int run_up_l1(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
             if (max_dots == 3) return go(std::integral_constant<int, 3>());
             return go(std::integral_constant<int, 4>());
         } else {
-            const int grid = persist_grid(&k_up_l1<T, KM, HOOK>, g);
-            if (nparts) *nparts = grid;
-            return launch("net_up_l1", (double)ncells(g), s, [&] {
-                k_up_l1<T, KM, HOOK><<<grid, kBlock, 0, s>>>(labels, g, x2, x1, dhat, w, kst, st, partials, ad[0], ad[1],
-                                                            ad[2], ad[3], x2out, cptr<int8_t>(ws, lay.wmode[1][1]));
+            return with_groups<KM>(g, [&](auto ng) {
+                constexpr int NG = decltype(ng)::value;
+                const int grid = persist_grid(&k_up_l1<T, KM, HOOK, NG>, g);
+                if (nparts) *nparts = grid;
+                return launch("net_up_l1", (double)ncells(g), s, [&] {
+                    k_up_l1<T, KM, HOOK, NG><<<grid, kBlock, 0, s>>>(labels, g, x2, x1, dhat, w, kst, st, partials, ad[0],
+                                                                    ad[1], ad[2], ad[3], x2out,
+                                                                    cptr<int8_t>(ws, lay.wmode[1][1]));
+                });
             });
         }
     });
@@ -1617,12 +1640,12 @@ int train_forward(const nps_net* net, const uint8_t* labels, nps_dims d, const T
         const CConvW<T>* w = wblock(block_down(l));
         if (l < L)
             NPS_TRY(launch("net_down", (double)ncells(g), s, [&] {
-                k_down<T, kStored, true><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), rin, x1, rnext, w, kst, st,
+                k_down<T, kStored, true, 4><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), rin, x1, rnext, w, kst, st,
                                                                   nullptr);
             }));
         else
             NPS_TRY(launch("net_coarsest", (double)ncells(g), s, [&] {
-                k_down<T, kStored, false><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), rin, x1, nullptr, w, kst,
+                k_down<T, kStored, false, 4><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), rin, x1, nullptr, w, kst,
                                                                    st, nullptr);
             }));
     }
@@ -1638,7 +1661,7 @@ int train_forward(const nps_net* net, const uint8_t* labels, nps_dims d, const T
         const T* kst = cptr<T>(ws, lay.k2[l]);
         const CConvW<T>* w = wblock(block_up(net, l));
         NPS_TRY(launch("net_up", (double)ncells(g), s, [&] {
-            k_up<T, kStored><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), xc, x1, xo, w, kst, l - 1, st, x2o,
+            k_up<T, kStored, 4><<<grid, kBlock, 0, s>>>(cnt, g, full_count(l), xc, x1, xo, w, kst, l - 1, st, x2o,
                                                          nullptr);
         }));
     }

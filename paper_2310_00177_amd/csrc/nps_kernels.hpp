@@ -433,11 +433,15 @@ __device__ __forceinline__ uint32_t feat_one() {
 // cell n.  On the vector ALU the 1458 multiply-adds of a cell and their weights,
 // read as scalars, took three to four times as long (40 x 56 x 72: 37 us down, 30
 // us up at level 1).
-template <int KM>
+// NG: the groups a wave evaluates.  On levels of two planes or one, four a wave would
+// leave half or three quarters of the waves without a plane: they share the planes'
+// rows instead, two (one) a wave (an evaluation at 2 x 1024 x 1024: 626 us with four
+// groups a wave, 398 us so, 559 us on the vector ALU).
+template <int KM, int NG>
 struct MfmaCtx {};
 
-template <>
-struct MfmaCtx<kMfmaF64> {
+template <int NG>
+struct MfmaCtx<kMfmaF64, NG> {
     static constexpr int kSteps = 14;
     double a[2][kSteps];
     int base0;
@@ -446,18 +450,35 @@ struct MfmaCtx<kMfmaF64> {
     bool one, none; // lane group 2, 3: the constant and the zero of the last step
 };
 
-__device__ __forceinline__ MfmaCtx<kMfmaF64> mfma64_ctx(const CConvW<double>* __restrict__ w, int lz) {
-    MfmaCtx<kMfmaF64> c;
+// The cell of a tile that a thread owns; own: whether one does (NG < 4: a wave owns NG
+// rows of its plane, its other lanes nothing).
+struct TileCell {
+    int lx, ly, lz;
+    bool own;
+};
+
+template <int NG>
+__device__ __forceinline__ TileCell tile_cell() {
+    static_assert(TZ == 4 && TY == 4, "a wave per plane, a group per row");
+    const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, wv = threadIdx.x / (TX * TY);
+    if constexpr (NG == 4) return TileCell{lx, ly, wv, true};
+    return TileCell{lx, ly, NG == 2 ? wv & 1 : 0, ly / NG == (NG == 2 ? wv >> 1 : wv)};
+}
+
+template <int NG>
+__device__ __forceinline__ MfmaCtx<kMfmaF64, NG> mfma64_ctx(const CConvW<double>* __restrict__ w, int lz) {
+    MfmaCtx<kMfmaF64, NG> c;
     const int lane = threadIdx.x & 63, k = lane >> 4, n = lane & 15;
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-        for (int ks = 0; ks < MfmaCtx<kMfmaF64>::kSteps; ++ks) {
+        for (int ks = 0; ks < MfmaCtx<kMfmaF64, NG>::kSteps; ++ks) {
             const int t = 16 * mb + n, f = 4 * ks + k, tc = min(t, kTaps - 1), fc = min(f, 2 * kTaps - 1);
             const double v = f == 2 * kTaps ? w->C[tc] : w->D[fc >> 1][tc][fc & 1];
             c.a[mb][ks] = t < kTaps && f <= 2 * kTaps ? v : 0.0;
         }
-    c.base0 = halo_base(n, 0, lz);
+    const int wv = threadIdx.x >> 6;
+    c.base0 = halo_base(n, NG == 4 ? 0 : NG == 2 ? 2 * (wv >> 1) : wv, lz);   // the wave's first row
 #pragma unroll
     for (int j = 0; j < 8; ++j) c.toff[j] = halo_off_rt(min(16 * (j >> 2) + 4 * (j & 3) + k, kTaps - 1));
     c.air = k & 1;
@@ -487,20 +508,21 @@ __device__ __forceinline__ double reduce_scatter4(const double (&p)[4]) {
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // All 64 lanes must call it; returns the output of the lane's own cell.
-template <bool L1>
-__device__ __forceinline__ double cconv_mfma64(const uint32_t* img_s, const double* r_s, const MfmaCtx<kMfmaF64>& c) {
-    double part[4];
+template <bool L1, int NG>
+__device__ __forceinline__ double cconv_mfma64(const uint32_t* img_s, const double* r_s,
+                                               const MfmaCtx<kMfmaF64, NG>& c) {
+    double part[NG];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < NG; ++q) {
         const int bq = c.base0 + q * HX;
         f64x4 acc[2] = {f64x4{0.0, 0.0, 0.0, 0.0}, f64x4{0.0, 0.0, 0.0, 0.0}};
 #pragma unroll
-        for (int ks = 0; ks < MfmaCtx<kMfmaF64>::kSteps; ++ks) {
+        for (int ks = 0; ks < MfmaCtx<kMfmaF64, NG>::kSteps; ++ks) {
             const int o0 = halo_off(2 * ks), o1 = halo_off(2 * ks + 1 < kTaps ? 2 * ks + 1 : kTaps - 1);
             uint32_t c0, c1;
             counts_of<L1>(img_s[bq + (c.hi ? o1 : o0)], c0, c1);
             double b = (double)(c.air ? c1 : c0);
-            if (ks == MfmaCtx<kMfmaF64>::kSteps - 1) b = c.one ? 1.0 : c.none ? 0.0 : b;
+            if (ks == MfmaCtx<kMfmaF64, NG>::kSteps - 1) b = c.one ? 1.0 : c.none ? 0.0 : b;
 #pragma unroll
             for (int mb = 0; mb < 2; ++mb) acc[mb] = __builtin_amdgcn_mfma_f64_16x16x4f64(c.a[mb][ks], b, acc[mb], 0, 0, 0);
         }
@@ -512,21 +534,24 @@ __device__ __forceinline__ double cconv_mfma64(const uint32_t* img_s, const doub
                 s = fma(acc[mb][i], r_s[bq + c.toff[4 * mb + i]], s);
         part[q] = s;
     }
-    return reduce_scatter4(part);
+    // lane group k owns row k of the plane: group k less the wave's first row
+    if constexpr (NG == 4) return reduce_scatter4(part);
+    else if constexpr (NG == 2) return reduce_scatter4({part[0], part[1], part[0], part[1]});
+    else return reduce_scatter4({part[0], part[0], part[0], part[0]});
 }
 
 // The MFMA context of a kernel mode (nothing for the others).
-template <class T, int KM>
-__device__ __forceinline__ MfmaCtx<KM> cconv_ctx(const CConvW<T>* __restrict__ w, int lz) {
-    if constexpr (KM == kMfmaF64) return mfma64_ctx(w, lz);
-    else return MfmaCtx<KM>{};
+template <class T, int KM, int NG>
+__device__ __forceinline__ MfmaCtx<KM, NG> cconv_ctx(const CConvW<T>* __restrict__ w, int lz) {
+    if constexpr (KM == kMfmaF64) return mfma64_ctx<NG>(w, lz);
+    else return MfmaCtx<KM, NG>{};
 }
 
 // One CConv output of the thread's cell (lx, ly, lz) for a wave-uniform mode.
 // kp: the preloaded stored kernel (PRE).
-template <class T, int KM, bool L1, bool PRE>
+template <class T, int KM, bool L1, int NG, bool PRE>
 __device__ __forceinline__ T cconv_any(int mode, bool active, const uint32_t* img_s, const T* r_s, int base, const CConvW<T>* __restrict__ w,
-                                       const MfmaCtx<KM>& mc, const KPre<T, PRE>& kp) {
+                                       const MfmaCtx<KM, NG>& mc, const KPre<T, PRE>& kp) {
     if (mode == -3) return T(0);
     if (mode >= 0) return active ? cconv_pure<T>(r_s, base, w, mode) : T(0);
     if constexpr (KM == kStored) {
@@ -535,7 +560,7 @@ __device__ __forceinline__ T cconv_any(int mode, bool active, const uint32_t* im
         return active ? cconv_vector<T, L1>(img_s, r_s, base, w) : T(0);
     } else {
         static_assert(KM == kMfmaF64, "the float matrix-core levels have kernels of their own");
-        return cconv_mfma64<L1>(img_s, r_s, mc);
+        return cconv_mfma64<L1, NG>(img_s, r_s, mc);
     }
 }
 
@@ -952,7 +977,7 @@ struct RL {    // network input and label of one haloed cell
     uint8_t l;
 };
 
-template <class T, int KM>
+template <class T, int KM, int NG>
 __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) void k_down_l1(
     const uint8_t* __restrict__ lab, Grid g, const T* __restrict__ r, T* __restrict__ x1, T* __restrict__ rnext,
     const CConvW<T>* __restrict__ w, const T* __restrict__ kst, const State* st,
@@ -962,9 +987,10 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) vo
     __shared__ T out_s[kBlock];
     const Tiles tl = tiles_of(g);
     const size_t n = ncells(g);
-    const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
+    const TileCell tc = tile_cell<NG>();
+    const int lx = tc.lx, ly = tc.ly, lz = tc.lz;
     const int base = halo_base(lx, ly, lz);
-    const MfmaCtx<KM> mc = cconv_ctx<T, KM>(w, lz);
+    const MfmaCtx<KM, NG> mc = cconv_ctx<T, KM, NG>(w, lz);
     auto load = [&](int tile) {
         const TileOrigin o = tile_origin(tile, tl);
         return load_batch<kHalo, RL<T>>([&](int i) {
@@ -976,7 +1002,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) vo
         const TileOrigin o = tile_origin(tile, tl);
         const int wm_e = KM == kStored ? 0 : wave_mode_entry(wmode, tile, lz);
         const int xx = o.x0 + lx, yy = o.y0 + ly, zz = o.z0 + lz;
-        const bool active = in_grid(g, zz, yy, xx);
+        const bool active = tc.own && in_grid(g, zz, yy, xx);
         const size_t idx = active ? cell_index(g, zz, yy, xx) : 0;
         const auto kp = k_preload<T, kpre_on<KM>>(kst, n, idx);
         __syncthreads();
@@ -987,9 +1013,9 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) vo
         prefetch();
         __syncthreads();
         const int mode = KM == kStored ? -1 : wave_mode<true>(wmode, wm_e, active, img_s, base, 1u, true, false);
-        const T out = cconv_any<T, KM, true>(mode, active, img_s, r_s, base, w, mc, kp);
+        const T out = cconv_any<T, KM, true, NG>(mode, active, img_s, r_s, base, w, mc, kp);
         if (active) x1[idx] = out;
-        out_s[threadIdx.x] = active ? out : T(0);
+        if (tc.own) out_s[(lz * TY + ly) * TX + lx] = active ? out : T(0);
         __syncthreads();
         pool_tile_to<T>(out_s, o, g, rnext);
     }, st);
@@ -1002,7 +1028,7 @@ struct CR {    // packed counts and network input of one haloed cell
     T r;
 };
 
-template <class T, int KM, bool POOL>
+template <class T, int KM, bool POOL, int NG>
 __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) void k_down(
     const uint32_t* __restrict__ cnt, Grid g, uint32_t full, const T* __restrict__ rin, T* __restrict__ x1,
     T* __restrict__ rnext, const CConvW<T>* __restrict__ w, const T* __restrict__ kst,
@@ -1012,9 +1038,10 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) vo
     __shared__ T out_s[kBlock];
     const Tiles tl = tiles_of(g);
     const size_t n = ncells(g);
-    const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
+    const TileCell tc = tile_cell<NG>();
+    const int lx = tc.lx, ly = tc.ly, lz = tc.lz;
     const int base = halo_base(lx, ly, lz);
-    const MfmaCtx<KM> mc = cconv_ctx<T, KM>(w, lz);
+    const MfmaCtx<KM, NG> mc = cconv_ctx<T, KM, NG>(w, lz);
     auto load = [&](int tile) {
         const TileOrigin o = tile_origin(tile, tl);
         return load_batch<kHalo, CR<T>>([&](int i) {
@@ -1026,7 +1053,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) vo
         const TileOrigin o = tile_origin(tile, tl);
         const int wm_e = KM == kStored ? 0 : wave_mode_entry(wmode, tile, lz);
         const int xx = o.x0 + lx, yy = o.y0 + ly, zz = o.z0 + lz;
-        const bool active = in_grid(g, zz, yy, xx);
+        const bool active = tc.own && in_grid(g, zz, yy, xx);
         const size_t idx = active ? cell_index(g, zz, yy, xx) : 0;
         const auto kp = k_preload<T, kpre_on<KM>>(kst, n, idx);
         __syncthreads();
@@ -1037,10 +1064,10 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) vo
         prefetch();
         __syncthreads();
         const int mode = KM == kStored ? -1 : wave_mode<false>(wmode, wm_e, active, img_s, base, full, false, false);
-        const T out = cconv_any<T, KM, false>(mode, active, img_s, r_s, base, w, mc, kp);
+        const T out = cconv_any<T, KM, false, NG>(mode, active, img_s, r_s, base, w, mc, kp);
         if (active) x1[idx] = out;
         if (POOL) {
-            out_s[threadIdx.x] = active ? out : T(0);
+            if (tc.own) out_s[(lz * TY + ly) * TX + lx] = active ? out : T(0);
             __syncthreads();
             pool_tile_to<T>(out_s, o, g, rnext);
         }
@@ -1180,7 +1207,7 @@ __device__ __forceinline__ void interp_tile(T* r_s, const T* c_s, Grid g, TileOr
 }
 
 // x = c1 x1 + c2 CConv_2(Interp(xc), I) on one level l >= 2.
-template <class T, int KM>
+template <class T, int KM, int NG>
 __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) void k_up(const uint32_t* __restrict__ cnt, Grid g, uint32_t full,
                                                const T* __restrict__ xc, const T* __restrict__ x1,
                                                T* __restrict__ xout, const CConvW<T>* __restrict__ w, const T* __restrict__ kst, int lvl,
@@ -1192,16 +1219,17 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) vo
     const T c1 = (T)st->c1[lvl], c2 = (T)st->c2[lvl];
     const Tiles tl = tiles_of(g);
     const size_t n = ncells(g);
-    const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
+    const TileCell tc = tile_cell<NG>();
+    const int lx = tc.lx, ly = tc.ly, lz = tc.lz;
     const int base = halo_base(lx, ly, lz);
-    const MfmaCtx<KM> mc = cconv_ctx<T, KM>(w, lz);
+    const MfmaCtx<KM, NG> mc = cconv_ctx<T, KM, NG>(w, lz);
     const InterpSlots isl = interp_slots();
     auto load = [&](int tile) { return load_image_interp<false, T>(cnt, xc, g, tile_origin(tile, tl)); };
     tile_pipeline(tl.count(), load, [&](int tile, const auto& pre, auto prefetch) {
         const TileOrigin o = tile_origin(tile, tl);
         const int wm_e = KM == kStored ? 0 : wave_mode_entry(wmode, tile, lz);
         const int xx = o.x0 + lx, yy = o.y0 + ly, zz = o.z0 + lz;
-        const bool active = in_grid(g, zz, yy, xx);
+        const bool active = tc.own && in_grid(g, zz, yy, xx);
         const size_t idx = active ? cell_index(g, zz, yy, xx) : 0;
         const auto kp = k_preload<T, kpre_on<KM>>(kst, n, idx);
         __syncthreads();
@@ -1212,7 +1240,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) vo
         interp_tile<T>(r_s, c_s, g, o, isl);
         __syncthreads();
         const int mode = KM == kStored ? -1 : wave_mode<false>(wmode, wm_e, active, img_s, base, full, false, false);
-        const T x2 = cconv_any<T, KM, false>(mode, active, img_s, r_s, base, w, mc, kp);
+        const T x2 = cconv_any<T, KM, false, NG>(mode, active, img_s, r_s, base, w, mc, kp);
         if (active) xout[idx] = c1 * x1v + c2 * x2;
         if (active && x2out) x2out[idx] = x2;
     }, st);
@@ -1222,7 +1250,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) vo
 // fluid cells (0 elsewhere), and the state's ndots partial dots of dhat with
 // ad0.. (NPSDO: the stored A d_i of the previous directions; PCG: r; flexible
 // PCG: r and the previous residual).
-template <class T, int KM, bool HOOK>
+template <class T, int KM, bool HOOK, int NG>
 __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) void k_up_l1(
     const uint8_t* __restrict__ lab, Grid g, const T* __restrict__ xc, const T* __restrict__ x1,
     T* __restrict__ dhat, const CConvW<T>* __restrict__ w,
@@ -1237,9 +1265,10 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) vo
     const int ndots = HOOK || st->sym ? 0 : st->ndots;   // the symmetric variant dots after P^T
     const Tiles tl = tiles_of(g);
     const size_t n = ncells(g);
-    const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, lz = threadIdx.x / (TX * TY);
+    const TileCell tc = tile_cell<NG>();
+    const int lx = tc.lx, ly = tc.ly, lz = tc.lz;
     const int base = halo_base(lx, ly, lz);
-    const MfmaCtx<KM> mc = cconv_ctx<T, KM>(w, lz);
+    const MfmaCtx<KM, NG> mc = cconv_ctx<T, KM, NG>(w, lz);
     double v[kRedWidth] = {0.0, 0.0, 0.0, 0.0};
     const T* adp[kMaxOrtho] = {ad0, ad1, ad2, ad3};
     const InterpSlots isl = interp_slots();
@@ -1248,7 +1277,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) vo
         const TileOrigin o = tile_origin(tile, tl);
         const int wm_e = KM == kStored ? 0 : wave_mode_entry(wmode, tile, lz);
         const int xx = o.x0 + lx, yy = o.y0 + ly, zz = o.z0 + lz;
-        const bool active = in_grid(g, zz, yy, xx);
+        const bool active = tc.own && in_grid(g, zz, yy, xx);
         const size_t idx = active ? cell_index(g, zz, yy, xx) : 0;
         const auto kp = k_preload<T, kpre_on<KM>>(kst, n, idx);
         __syncthreads();
@@ -1264,7 +1293,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) vo
         interp_tile<T>(r_s, c_s, g, o, isl);
         __syncthreads();
         const int mode = KM == kStored ? -1 : wave_mode<true>(wmode, wm_e, active, img_s, base, 1u, false, true);
-        const T x2 = cconv_any<T, KM, true>(mode, active, img_s, r_s, base, w, mc, kp);
+        const T x2 = cconv_any<T, KM, true, NG>(mode, active, img_s, r_s, base, w, mc, kp);
         if (active) {
             T out = T(0);
             if (img_s[base] == (uint32_t)kFluid) out = (c1 * x1v + c2 * x2) * scale;

@@ -26,8 +26,10 @@ def blob(levels, seed):
 
 
 # level 2 of 34 x 36 x 52 cells, its tiles cut along every axis, as the coarsest level and
-# with a level below
-@pytest.mark.parametrize("shape,levels", [((68, 72, 104), 2), ((68, 72, 104), 3)])
+# with a level below; grids of two planes (waves share their rows: level 1 of two planes,
+# level 2 of one) and of four (level 2 of two planes, pooled), rows and columns cut
+@pytest.mark.parametrize("shape,levels", [((68, 72, 104), 2), ((68, 72, 104), 3), ((2, 518, 254), 2),
+                                          ((4, 292, 460), 3)])
 def test_coarse_levels_match_oracle(shape, levels):
     rng = np.random.default_rng(sum(shape) + levels)
     lab = rng.choice(3, size=shape, p=(0.5, 0.3, 0.2)).astype(np.uint8)
@@ -38,3 +40,19 @@ def test_coarse_levels_match_oracle(shape, levels):
     ref = onet.Network(params, levels, lab).apply(r)
     assert np.linalg.norm(got - ref) / np.linalg.norm(ref) < 1e-12
     assert np.abs(got - ref).max() < 1e-12 * np.abs(ref).max()
+
+
+def test_iterates_on_two_planes():
+    """The level-1 kernels of a solve on two planes (their dots, the masked output) against the oracle's iterates."""
+    from oracle import npsdo as onpsdo
+    shape = (2, 130, 132)
+    lab = np.zeros(shape, dtype=np.uint8)
+    lab[:, :20] = gi.AIR
+    lab[:, 60:70, 30:50] = gi.SOLID
+    b = gi.gen_rhs(lab, seed=3)
+    params = gi.multilevel_params(2)
+    ref = onpsdo.solve(lab, b, onet.Network(params, 2, lab).apply, max_iter=5, fixed_iters=True)
+    x, info = nps.solve(nps.Net(params, 2), torch.from_numpy(lab).cuda(), torch.from_numpy(b).cuda(), max_iter=5,
+                        fixed_iters=True, precision=nps.FP64)
+    assert info.iterations == 5
+    assert np.linalg.norm(x.cpu().numpy() - ref.x) <= 1e-9 * np.linalg.norm(ref.x)

@@ -595,8 +595,9 @@ int run_setup(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
             }
             const int grid = elem_grid(n);
             NPS_TRY(launch("setup_kgen", (double)n, s, [&] {
-                if (l == 1) k_kgen_store<T, true><<<grid, kBlock, 0, s>>>(img(l), g, w, out);
-                else k_kgen_store<T, false><<<grid, kBlock, 0, s>>>(img(l), g, w, out);
+                if constexpr (sizeof(T) == 8)   // in float a large level 1 goes by matrix cores, above
+                    if (l == 1) return k_kgen_store<T, true><<<grid, kBlock, 0, s>>>(img(l), g, w, out);
+                k_kgen_store<T, false><<<grid, kBlock, 0, s>>>(img(l), g, w, out);
             }));
         }
     }
@@ -1625,9 +1626,6 @@ int train_forward(const nps_net* net, const uint8_t* labels, nps_dims d, const T
     ClassSums* cls = mptr<ClassSums>(ws, lay.cls);
     NPS_TRY(launch("state_init", 0, s, [&] { k_state_init<<<1, kBlock, 0, s>>>(st, cls); }));
     NPS_TRY(run_setup<T>(net, labels, d, plan, lay, ws, s, bf16w));
-    auto img = [&](int l) -> const void* {
-        return l == 1 ? static_cast<const void*>(labels) : static_cast<const void*>(cptr<uint32_t>(ws, lay.counts[l]));
-    };
     NPS_TRY(run_down_l1<T>(net, labels, d, plan, lay, ws, r, s, bf16w));
     for (int l = 2; l <= L; ++l) {
         const Grid g = level_grid(d, l);

@@ -208,6 +208,6 @@ struct HostFlags {
 };
 
 // Control-kernel stages.
-enum Stage : int { kStageResidual = 0, kStageDots = 1, kStageStep = 2, kStageLoss = 3 };
+enum Stage : int { kStageResidual = 0, kStageLoss = 1 };
 
 }  // namespace nps

@@ -91,9 +91,10 @@ typedef struct {
     int fixed_iters;     /* 1: run exactly max_iter iterations, no convergence test    */
     int method;          /* enum nps_method (0 = NPSDO)                               */
     int symmetric;       /* 1: precondition with P^T o P, the symmetric variant of    *
-                          * the appendix on symmetry (kernels of every level are     *
-                          * kept in the workspace; size it with                      *
-                          * nps_solve_workspace_bytes)                               */
+                          * the appendix on symmetry (the workspace also keeps the   *
+                          * kernels of every level, but of a level 1 above 32768     *
+                          * cells in float whose work items are mostly full; size it *
+                          * with nps_solve_workspace_bytes)                          */
 } nps_opts;
 
 typedef struct {
@@ -225,13 +226,15 @@ int nps_server_poll(nps_server* srv, uint64_t req_id, double* x_h, nps_info* inf
 
 /* ------------------------------------------------------------------------
  * Training (loss of Sec. "Training": || b - A P(I, b) ||_2 per system).
- * precision NPS_FP64 (double vectors; parameter sums on the vector ALU),
- * NPS_FP32 (float vectors; the weight-gradient contraction over cells on
- * fp32 matrix cores) or NPS_MIXED_BF16 (float vectors; per-cell kernels
- * formed from the count-form weights rounded to bf16, as on the mixed solve's
- * matrix cores, and the weight-gradient contraction on bf16 matrix cores with
- * fp32 accumulation); every level keeps its per-cell kernels in the
- * workspace.
+ * precision NPS_FP64 (double vectors; parameter sums on fp64 matrix cores),
+ * NPS_FP32 (float vectors; the weight-gradient contraction over cells on bf16
+ * matrix cores, each float product in three bf16 pieces whose sum it is, with
+ * fp32 accumulation) or NPS_MIXED_BF16 (float vectors; per-cell kernels formed
+ * from the count-form weights rounded to bf16, as on the mixed solve's matrix
+ * cores, and the weight-gradient contraction in one bf16 piece with fp32
+ * accumulation).  The workspace keeps the per-cell kernels of every level but
+ * of a level 1 above 32768 cells in float, which forms them where they are
+ * applied (thin grids keep that level's too).
  *   nps_net_forward   y = P(I, r); keeps the per-level activations (the
  *                     down inputs, x1, the up outputs, the CConv_2 outputs)
  *                     in ws for the backward pass of the same system.

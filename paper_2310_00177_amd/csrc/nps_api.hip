@@ -249,8 +249,9 @@ Layout make_layout(nps_dims d, int levels, int precision, int n_ortho, bool solv
     return L;
 }
 
-// Training (and symmetric-variant) workspace: the base layout with stored
-// kernels at every level, plus the adjoint sweep's per-level gradients.
+// Workspace of training, P^T and the symmetric variant: the base layout with the
+// stored kernels of every level (level 1: see store_level1), plus the adjoint
+// sweep's per-level gradients.
 struct TrainLayout {
     Layout base;                 // state, partials, counts, x1, rb (= down inputs), stored K
     size_t xup[kMaxLevels + 1], x2[kMaxLevels + 1];
@@ -1014,9 +1015,9 @@ int check_opts(const nps_opts& o) {
     return NPS_OK;
 }
 
-// Plan and workspace layout of a solve: the symmetric variant keeps the
-// kernels of every level in HBM (its P^T sweep gathers them) and carries the
-// adjoint's buffers.
+// Plan and workspace layout of a solve: the symmetric variant keeps the kernels
+// of every level in HBM for its P^T sweep (level 1: see store_level1) and carries
+// the adjoint's buffers.
 struct SolveLayout {
     Plan plan;
     Layout lay;
@@ -1813,10 +1814,10 @@ int train_step(const nps_net* net, const uint8_t* labels, nps_dims d, int batch,
     return NPS_OK;
 }
 
-// Training precisions: NPS_FP64 (double vectors, vector-ALU parameter sums),
-// NPS_FP32 (float vectors, fp32 matrix-core sums), NPS_MIXED_BF16 (float
-// vectors, kernels from bf16-rounded weights, bf16 matrix-core sums with fp32
-// accumulation).
+// Training precisions: NPS_FP64 (double vectors, fp64 matrix-core sums),
+// NPS_FP32 (float vectors, matrix-core sums of products in three bf16 pieces),
+// NPS_MIXED_BF16 (float vectors, kernels from bf16-rounded weights, sums of
+// products in one bf16 piece); float sums accumulate in fp32.
 bool train_precision_ok(int p) { return p == NPS_FP64 || p == NPS_FP32 || p == NPS_MIXED_BF16; }
 
 }  // namespace

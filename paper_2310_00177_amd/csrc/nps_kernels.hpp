@@ -589,8 +589,9 @@ __device__ __forceinline__ Acc apply_A(const L* lab_s, const V* v_s, int base, i
 // ---------------------------------------------------------------------------
 // setup kernels
 // ---------------------------------------------------------------------------
-// K[t][cell] of one CConv block on one large level (training and the
-// symmetric variant), formed in double: one thread per cell, whose window is
+// K[t][cell] of one CConv block on one large level that is stored and not formed on
+// matrix cores (training, P^T and the symmetric variant: in double, and in float
+// past level 3), formed in double: one thread per cell, whose window is
 // read once for all 27 taps; the taps share uniform weight loads.
 template <class T, bool L1>
 __global__ __launch_bounds__(kBlock) void k_kgen_store(const void* __restrict__ img, Grid g,
@@ -621,8 +622,9 @@ __global__ __launch_bounds__(kBlock) void k_kgen_store(const void* __restrict__ 
     }
 }
 
-// K[t][cell] of one CConv block on a large level (training and the symmetric
-// variant store every level), formed on matrix cores: per 16-cell group along
+// K[t][cell] of one CConv block on a stored level above 4096 cells in float (a
+// solve's up to 32768 cells; training, P^T and the symmetric variant also larger
+// ones), formed on matrix cores: per 16-cell group along
 // x, K^T[tap][cell] = A[tap][feature] B[feature][cell] as in the solve's
 // kernels (KM = kMfmaBf16x3: three bf16 pieces, the FP32 bar; kMfmaBf16: one
 // piece, the bf16 training leg), B from the 27 window cells' counts (exact in

@@ -42,8 +42,8 @@ constexpr uint32_t kAnyGeneral = 0x02020202u;   // over a wave's four modes
 
 // One mode byte per 16-cell group, the four rows of a wave in one aligned word: word
 // (z ncy + cy) nwx + (16-cell column).  nwx counts the columns that hold cells (words
-// for whole footprints took up to four times as much: with them the coarser levels'
-// modes were 86 MB of the workspace of a grid 4 cells wide and 375936 long).
+// for whole footprints take up to four times as much: for the coarser levels of a grid
+// 4 cells wide and 375936 long, 118 MB more).
 __host__ __device__ inline int wave_columns(Grid g) { return (g.nx + 15) / 16; }
 __host__ __device__ inline size_t group_mode_bytes(Grid g) {
     return (size_t)wave_columns(g) * ((g.ny + PY - 1) / PY) * g.nz * 4;
@@ -471,8 +471,9 @@ __device__ __forceinline__ ImgQuad<L1> stage_image_quad(const void* __restrict__
 }
 
 // Waves per SIMD of the level-1 kernels: one more hides more of the staging's
-// latency (128^3 mixed: up 21.1 -> 18.8 us, down 16.1 -> 14.8 us; 256^3: up 98
-// -> 86 us, down 78 -> 67 us), yet another one spills (up 26.0 us).  The
+// latency (network evaluations in bf16 on scenes of spheres under a flat surface,
+// 128^3: up 21.1 -> 18.8 us, down 16.1 -> 14.8 us; 256^3: up 98 -> 86 us, down 78 -> 67
+// us), yet another one spills (up 26.0 us).  The
 // three-piece weights of FP32 and the operands of more than two dots take
 // registers of one wave each.
 constexpr int march_waves(int km, int nd) { return 5 - (km == kMfmaBf16x3 ? 1 : 0) - (nd > 2 ? 1 : 0); }

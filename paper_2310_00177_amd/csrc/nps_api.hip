@@ -529,7 +529,12 @@ bool wide_quads(const uint8_t* labels, const void* r, Grid g) {
     return g.nx % 4 == 0 && reinterpret_cast<uintptr_t>(labels) % 4 == 0 && reinterpret_cast<uintptr_t>(r) % 16 == 0;
 }
 
-// f(planes per work item of the level-1 network kernels) as a constant.
+// The flags of an item kernel launched on a grid of blocks.
+int item_flags(Grid g, int blocks, bool wide) {
+    return (wide ? kWideRows : 0) | (march_slabs(march_columns(g), blocks) ? kSlabs : 0);
+}
+
+// f(planes per work item of the network kernels) as a constant.
 template <class F>
 int with_chunk(Grid g, F&& f) {
     return march_columns(g).chunk == 4 ? f(std::integral_constant<int, 4>()) : f(std::integral_constant<int, 2>());
@@ -704,7 +709,7 @@ int run_coarse(const nps_net* net, nps_dims d, const Plan& plan, const Layout& l
                     return launch(l < L ? kDownName[l] : "net_coarsest", cells, s, [&] {
                         k_down_m<KM, CH, false><<<grid, kBlock, 0, s>>>(cnt, g, rin, x1, rnext, w, wm, st,
                                                                         cptr<uint32_t>(ws, lay.cmode[l]), nullptr,
-                                                                        g.nx % 4 == 0 ? 1 : 0);
+                                                                        item_flags(g, grid, g.nx % 4 == 0));
                     });
                 });
             } else {
@@ -792,7 +797,7 @@ int run_coarse(const nps_net* net, nps_dims d, const Plan& plan, const Layout& l
                     return launch(kUpName[l], (double)ncells(g), s, [&] {
                         k_up_m<KM, true, 0, CH, false><<<grid, kBlock, 0, s>>>(
                             cnt, g, xc, x1, xo, w, wm, st, nullptr, nullptr, nullptr, nullptr, nullptr,
-                            cptr<uint32_t>(ws, lay.cmode[l]), nullptr, g.nx % 4 == 0 ? 1 : 0, nullptr, l - 1);
+                            cptr<uint32_t>(ws, lay.cmode[l]), nullptr, item_flags(g, grid, g.nx % 4 == 0), nullptr, l - 1);
                     });
                 });
             } else {
@@ -833,7 +838,7 @@ int run_down_l1(const nps_net* net, const uint8_t* labels, nps_dims d, const Pla
                     k_down_m<KM, CH, true><<<grid, kBlock, 0, s>>>(labels, g, r, x1, rnext, w, wm, st,
                                                                cptr<uint32_t>(ws, lay.gmode[0]),
                                                                cptr<uint8_t>(ws, lay.izero[0]),
-                                                               wide_quads(labels, r, g) ? 1 : 0);
+                                                               item_flags(g, grid, wide_quads(labels, r, g)));
                 });
             });
         } else {
@@ -877,7 +882,7 @@ int run_up_l1(const nps_net* net, const uint8_t* labels, nps_dims d, const Plan&
                         k_up_m<KM, H, H ? 0 : ND, CH, true><<<grid, kBlock, 0, s>>>(
                             labels, g, x2, x1, dhat, w, wm, st, partials, ad[0], ad[1], ad[2], ad[3],
                             cptr<uint32_t>(ws, lay.gmode[1]), cptr<uint8_t>(ws, lay.izero[1]),
-                            wide_quads(labels, nullptr, g) ? 1 : 0, x2out, 0);
+                            item_flags(g, grid, wide_quads(labels, nullptr, g)), x2out, 0);
                     });
                 });
             };
@@ -910,7 +915,6 @@ int adjoint_l1m(const nps_net* net, const uint8_t* labels, nps_dims d, const Tra
     const State* st = cptr<State>(ws, lay.state);
     const int blk = UP ? block_up(net, 1) : block_down(1);
     const CConvW<float>* w = bf16w ? cconv_block_bf16<float>(net, blk) : cconv_block<float>(net, blk);
-    const int wide = wide_quads(labels, gx, g) ? 1 : 0;
     auto go = [&](auto km) {
         return with_chunk(g, [&](auto ch) {
             constexpr int KM = decltype(km)::value, CH = decltype(ch)::value;
@@ -919,7 +923,8 @@ int adjoint_l1m(const nps_net* net, const uint8_t* labels, nps_dims d, const Tra
             return launch(UP ? "adj_up_l1" : "adj_down_l1", (double)ncells(g), s, [&] {
                 k_adj_l1m<KM, UP, CH><<<grid, kBlock, 0, s>>>(labels, g, gx, gnext, w, mfma_block(net, blk), st, x1, x2,
                                                               out, mptr<double>(ws, tl.dc[1]),
-                                                              cptr<uint32_t>(ws, lay.gmode[1]), wide);
+                                                              cptr<uint32_t>(ws, lay.gmode[1]),
+                                                              item_flags(g, grid, wide_quads(labels, gx, g)));
             });
         });
     };

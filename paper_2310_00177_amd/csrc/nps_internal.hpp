@@ -157,14 +157,18 @@ __host__ __device__ inline Columns march_columns(Grid g) {
 // them empty), or any where every block has one item, since a second round for a few
 // doubles the time.  Level 1 down / up in bf16 by slabs and round-robin: 4 x 512 x 512
 // (1 chunk) 57.4 / 63.6 and 13.9 / 15.8 us, 140 x 256 x 256 (35 chunks) 41.2 / 57.9 and
-// 36.8 / 51.0 us; at 32 chunks slabs are 0.4 to 0.6 us faster.
+// 36.8 / 51.0 us; at 32 chunks slabs are 0.4 to 0.6 us faster.  The launch decides (in
+// the kernel the rule cost 0.4 us of a down kernel's 15).
+inline bool march_slabs(Columns cl, int grid) {
+    const int turns = (cl.ncz + kXcds - 1) / kXcds, empty = kXcds * turns - cl.ncz;
+    return grid % kXcds == 0 && (cl.count() <= grid ? empty == 0 : 9 * empty <= cl.ncz);
+}
+
 struct MarchItems {
     int per, count, xcd, zmul, li, step;
 };
 
-__host__ __device__ inline MarchItems march_items(Columns cl, int grid, int block) {
-    const int turns = (cl.ncz + kXcds - 1) / kXcds, empty = kXcds * turns - cl.ncz;
-    const bool slabs = grid % kXcds == 0 && (cl.count() <= grid ? empty == 0 : 9 * empty <= cl.ncz);
+__host__ __device__ inline MarchItems march_items(Columns cl, int grid, int block, bool slabs) {
     MarchItems m;
     m.xcd = slabs ? block % kXcds : 0;
     m.zmul = slabs ? kXcds : 1;
@@ -174,6 +178,9 @@ __host__ __device__ inline MarchItems march_items(Columns cl, int grid, int bloc
     m.step = slabs ? grid / kXcds : grid;
     return m;
 }
+
+// What a launch tells an item kernel: rows of four are aligned words; items go by slabs.
+constexpr int kWideRows = 1, kSlabs = 2;
 
 struct MarchItem {
     int cx, cy, zc, rest;

@@ -488,7 +488,8 @@ template <int KM, int CH, bool L1>
 __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, 0)) void k_down_m(
     const void* __restrict__ img, Grid g, const float* __restrict__ r, float* __restrict__ x1,
     float* __restrict__ rnext, const CConvW<float>* __restrict__ w, const MfmaW* __restrict__ wm, const State* st,
-    const uint32_t* __restrict__ gmode, const uint8_t* __restrict__ izero, int wide) {
+    const uint32_t* __restrict__ gmode, const uint8_t* __restrict__ izero, int flags) {
+    const int wide = flags & kWideRows;
     constexpr int XO = 2;
     using S = StageTasks<CH>;
     __shared__ __attribute__((aligned(16))) uint2 rec[kRecords<CH>];
@@ -499,7 +500,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, 0)) void k
     const int lane = threadIdx.x & 63, gq = lane >> 4, n = lane & 15;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t pstride = (uint32_t)g.ny * (uint32_t)g.nx;
-    const MarchItems mi = march_items(cl, (int)gridDim.x, (int)blockIdx.x);
+    const MarchItems mi = march_items(cl, (int)gridDim.x, (int)blockIdx.x, flags & kSlabs);
     bool first = true;
     for (int li = mi.li; li < mi.count; li += mi.step) {
         const MarchItem it = march_item(mi, li, cl);
@@ -621,7 +622,8 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, ND)) void 
     float* __restrict__ dhat, const CConvW<float>* __restrict__ w, const MfmaW* __restrict__ wm, const State* st,
     double* __restrict__ partials, const float* __restrict__ ad0, const float* __restrict__ ad1,
     const float* __restrict__ ad2, const float* __restrict__ ad3, const uint32_t* __restrict__ gmode,
-    const uint8_t* __restrict__ izero, int wide, float* __restrict__ x2out, int lvl) {
+    const uint8_t* __restrict__ izero, int flags, float* __restrict__ x2out, int lvl) {
+    const int wide = flags & kWideRows;
     static_assert((!HOOK || ND == 0) && (L1 || HOOK), "the hook and the coarser levels form no dots");
     constexpr int XO = 1;
     using S = StageTasks<CH>;
@@ -641,7 +643,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(march_waves(KM, ND)) void 
     const uint32_t fluid_word = feat_word<KM, true>(kFluid);
     double v[kRedWidth] = {0.0, 0.0, 0.0, 0.0};
     const uint32_t pstride = (uint32_t)g.ny * (uint32_t)g.nx;
-    const MarchItems mi = march_items(cl, (int)gridDim.x, (int)blockIdx.x);
+    const MarchItems mi = march_items(cl, (int)gridDim.x, (int)blockIdx.x, flags & kSlabs);
     bool first = true;
     for (int li = mi.li; li < mi.count; li += mi.step) {
         const MarchItem it = march_item(mi, li, cl);

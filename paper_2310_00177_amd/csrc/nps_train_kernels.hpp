@@ -148,7 +148,8 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(2) void k_adj_l1m(
     const uint8_t* __restrict__ lab, Grid g, const float* __restrict__ gx, const float* __restrict__ gnext,
     const CConvW<float>* __restrict__ w, const MfmaW* __restrict__ wm, const State* st, const float* __restrict__ x1,
     const float* __restrict__ x2, float* __restrict__ out, double* __restrict__ part,
-    const uint32_t* __restrict__ gmode, int wide) {
+    const uint32_t* __restrict__ gmode, int flags) {
+    const int wide = flags & kWideRows;
     constexpr int P = MarchCtx<KM>::P, NPL = CH + 2;
     using S = StageTasks<CH>;
     __shared__ __attribute__((aligned(16))) uint32_t f_s[(CH + 4) * kAFRows * kAF];
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(2) void k_adj_l1m(
     const int evi = n < 2 * PHY ? erow * kAVRow + eix + 1 : PHY * kAVRow + n - 2 * PHY;
     static_assert(PHY * kAVRow + 16 - 2 * PHY <= kAV, "spare columns");
     double v[2] = {0.0, 0.0};
-    const MarchItems mi = march_items(cl, (int)gridDim.x, (int)blockIdx.x);
+    const MarchItems mi = march_items(cl, (int)gridDim.x, (int)blockIdx.x, flags & kSlabs);
     for (int li = mi.li; li < mi.count; li += mi.step) {
         const MarchItem it = march_item(mi, li, cl);
         const int x0 = it.cx * PX, y0 = it.cy * PY, z0 = it.zc * CH;

@@ -17,7 +17,7 @@ static double share(Grid g, int grid) {
     std::vector<int> seen(cl.count(), 0);
     double die[kXcds] = {0}, most = 0.0;
     for (int b = 0; b < grid; ++b) {
-        const MarchItems m = march_items(cl, grid, b);
+        const MarchItems m = march_items(cl, grid, b, march_slabs(cl, grid));
         for (int li = m.li; li < m.count; li += m.step) {
             const MarchItem it = march_item(m, li, cl);
             if (it.cx < 0 || it.cx >= cl.ncx || it.cy < 0 || it.cy >= cl.ncy || it.zc < 0 || it.zc >= cl.ncz) return -1.0;

@@ -455,7 +455,7 @@ struct MfmaCtx<kMfmaF64, NG> {
 // The cell of a tile that a thread owns; own: whether one does (NG < 4: a wave owns NG
 // rows of its plane, its other lanes nothing).
 struct TileCell {
-    int lx, ly, lz;
+    int lx, ly, lz, slot;   // slot: the cell's place in the tile
     bool own;
 };
 
@@ -463,8 +463,9 @@ template <int NG>
 __device__ __forceinline__ TileCell tile_cell() {
     static_assert(TZ == 4 && TY == 4, "a wave per plane, a group per row");
     const int lx = threadIdx.x % TX, ly = (threadIdx.x / TX) % TY, wv = threadIdx.x / (TX * TY);
-    if constexpr (NG == 4) return TileCell{lx, ly, wv, true};
-    return TileCell{lx, ly, NG == 2 ? wv & 1 : 0, ly / NG == (NG == 2 ? wv >> 1 : wv)};
+    if constexpr (NG == 4) return TileCell{lx, ly, wv, (int)threadIdx.x, true};
+    const int lz = NG == 2 ? wv & 1 : 0;
+    return TileCell{lx, ly, lz, (lz * TY + ly) * TX + lx, ly / NG == (NG == 2 ? wv >> 1 : wv)};
 }
 
 template <int NG>
@@ -1019,7 +1020,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) vo
         const int mode = KM == kStored ? -1 : wave_mode<true>(wmode, wm_e, active, img_s, base, 1u, true, false);
         const T out = cconv_any<T, KM, true, NG>(mode, active, img_s, r_s, base, w, mc, kp);
         if (active) x1[idx] = out;
-        if (tc.own) out_s[(lz * TY + ly) * TX + lx] = active ? out : T(0);
+        if (tc.own) out_s[tc.slot] = active ? out : T(0);
         __syncthreads();
         pool_tile_to<T>(out_s, o, g, rnext);
     }, st);
@@ -1071,7 +1072,7 @@ __global__ __launch_bounds__(kBlock) NPS_WAVES_PER_EU(waves_floor(sizeof(T))) vo
         const T out = cconv_any<T, KM, false, NG>(mode, active, img_s, r_s, base, w, mc, kp);
         if (active) x1[idx] = out;
         if (POOL) {
-            if (tc.own) out_s[(lz * TY + ly) * TX + lx] = active ? out : T(0);
+            if (tc.own) out_s[tc.slot] = active ? out : T(0);
             __syncthreads();
             pool_tile_to<T>(out_s, o, g, rnext);
         }

@@ -44,7 +44,7 @@ constexpr uint32_t kAnyGeneral = 0x02020202u;   // over a wave's four modes
 // (z ncy + cy) nwx + (16-cell column).  nwx counts the columns that hold cells (words
 // for whole footprints take up to four times as much: for the coarser levels of a grid
 // 4 cells wide and 375936 long, 118 MB more).
-__host__ __device__ inline int wave_columns(Grid g) { return (g.nx + 15) / 16; }
+__host__ __device__ inline int wave_columns(Grid g) { return (int)((unsigned)(g.nx + 15) / 16u); }
 __host__ __device__ inline size_t group_mode_bytes(Grid g) {
     return (size_t)wave_columns(g) * ((g.ny + PY - 1) / PY) * g.nz * 4;
 }
@@ -362,12 +362,11 @@ template <int CH>
 __device__ __forceinline__ void load_modes(const uint32_t* __restrict__ gmode, Columns cl, const MarchItem& it, Grid g,
                                            uint32_t (&modes)[CH]) {
     const int wx = 4 * it.cx + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwx = wave_columns(g);
+    const int nz = wx < nwx ? g.nz : 0;   // a wave past the columns has no plane
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
         const int z = it.zc * CH + i;
-        modes[i] = z < g.nz && wx < nwx
-                       ? __builtin_amdgcn_readfirstlane(gmode[((size_t)z * cl.ncy + it.cy) * nwx + wx])
-                       : 0u;
+        modes[i] = z < nz ? __builtin_amdgcn_readfirstlane(gmode[((size_t)z * cl.ncy + it.cy) * nwx + wx]) : 0u;
     }
 }
 

@@ -3,9 +3,12 @@
 // z-planes) at a time (Alg. 2: CConv_1 + pool down, interpolation + CConv_2 +
 // combine up; at level 1 also the mask, the scaling and the dots).
 //
-// These kernels are bound by instruction issue (their traffic is 1 TB/s), so
-// the item is staged and evaluated with as few instructions per cell as
-// possible.  All planes of the item, with their one-cell border, are staged in
+// These kernels are bound by issue and by latency together, not by memory
+// (their traffic is 1 TB/s).  On the benchmark's 128^3 scene the waves of
+// level 1 issue in 28 % of their cycles, wait for a turn in 28 to 32 % and for
+// LDS, memory or a barrier in 39 to 44 %; the matrix cores are busy in 7 to
+// 11 %.  So the item is staged and evaluated with as few instructions per cell
+// as possible.  All planes of the item, with their one-cell border, are staged in
 // LDS in one go, as one 8-byte record per cell: the CConv input (float) and the
 // cell's two MFMA features (fluid and air counts as a bf16 / fp16 pair).  One
 // barrier separates staging from the CConv, and every LDS address of the CConv
@@ -60,8 +63,8 @@ __host__ __device__ inline size_t group_mode_bytes(Grid g) {
 //         cell's window is all fluid (other outputs are masked).
 // A row of 64 labels becomes a 64-bit mask (one ballot), so the windows are
 // shifts and a few ANDs and ORs of row masks: one label load per cell and halo
-// cell, where one thread per cell read its 27 window labels (128^3: 30.5 us,
-// and 4.5 us for the item flags in a launch of their own).
+// cell, where one thread per cell read its 27 window labels (128^3: 9.9 us;
+// before, 30.5 us and 4.5 us for the item flags in a launch of their own).
 template <int CH>
 __global__ __launch_bounds__(kBlock) void k_march_modes(const uint8_t* __restrict__ lab, Grid g,
                                                         uint8_t* __restrict__ mdown, uint8_t* __restrict__ mup,
